@@ -37,7 +37,8 @@ namespace {
 
 using namespace qsgd;
 
-// workspace: words appended by each team (u32) and their exclusive prefix sums (u64)
+// workspace: words appended by each team (u32), and 64 KB that earlier layouts used (the
+// sizes that the workspace calls report stay what they were)
 constexpr uint64_t kTotalsBytes = (uint64_t)kMaxTeams * 4 + (uint64_t)kMaxTeams * 8;
 constexpr uint64_t kStatusBytes = 256;                      // workspace: decode status word
 
@@ -667,12 +668,16 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
   if (g.code != QSGD_CODE_FIXED) {
     CompactArgs c;
     c.staging = a.staging; c.region_words = pl.region_words; c.totals = a.totals;
-    c.prefix = reinterpret_cast<unsigned long long*>(wsb + (uint64_t)kMaxTeams * 4);
     c.table = table; c.payload = payload; c.header = header; c.cap_words = cap_words;
     c.bper = pl.bper; c.nb = (uint32_t)g.nb; c.table_words = (uint32_t)g.table_words;
     c.raw_words = raw_words;
+    // a team per wavefront while that leaves at most four workgroups per compute unit (each
+    // of them reads all totals before its first team), several per wavefront beyond
+    c.teams = pl.teams;
+    const uint32_t wgs = 4 * (uint32_t)device_cus();
+    c.tpb = std::min<uint32_t>(kWave, std::max<uint32_t>(4, (pl.teams + wgs - 1) / wgs));
     ScopedTiming tm("encode_compact", st);
-    if (launch_encode_compact(c, pl.teams, st) != hipSuccess) return QSGD_ERR_HIP;
+    if (launch_encode_compact(c, st) != hipSuccess) return QSGD_ERR_HIP;
   }
   if (L && L->R) {
     ScopedTiming tm("encode_raw", st);

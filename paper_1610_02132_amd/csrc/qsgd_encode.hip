@@ -532,71 +532,67 @@ void k_encode_fixed_small(EncodeArgs a) {
   }
 }
 
-// Exclusive prefix sums of the teams' totals: one workgroup, up to kMaxTeams values.
-__global__ __launch_bounds__(1024) void k_encode_prefix(CompactArgs a, uint32_t teams) {
-  __shared__ unsigned long long wave_tot[16];
-  __shared__ unsigned long long carry;
-  constexpr uint32_t kPer = 8;   // totals per thread: kMaxTeams in one trip
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) carry = 0;
-  __syncthreads();
-  for (uint32_t c0 = 0; c0 < teams; c0 += 1024 * kPer) {
-    const uint32_t i0 = c0 + (uint32_t)tid * kPer;
-    uint32_t v[kPer];
-    unsigned long long sum = 0;
-#pragma unroll
-    for (uint32_t t = 0; t < kPer; ++t) {
-      v[t] = i0 + t < teams ? a.totals[i0 + t] : 0u;
-      sum += v[t];
-    }
-    unsigned long long incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long up = __shfl_up(incl, o, kWave);
-      if (lane >= o) incl += up;
-    }
-    if (lane == 63) wave_tot[wave] = incl;
-    __syncthreads();
-    unsigned long long before = carry;
-    for (int w = 0; w < wave; ++w) before += wave_tot[w];
-    unsigned long long run = before + incl - sum;
-#pragma unroll
-    for (uint32_t t = 0; t < kPer; ++t) {
-      if (i0 + t < teams) a.prefix[i0 + t] = run;
-      run += v[t];
-    }
-    __syncthreads();
-    if (tid == 1023) carry = before + incl;
-    __syncthreads();
-  }
-}
-
 // Moves each team's region to its place in the message: base_j = words of the teams
-// before j (k_encode_prefix).  One workgroup per team.
-__global__ __launch_bounds__(256) void k_encode_compact(CompactArgs a) {
-  const int tid = threadIdx.x;
-  const uint32_t j = blockIdx.x;
-  const uint64_t base = a.prefix[j];
-  const uint32_t mine = a.totals[j];
-  const uint32_t b_begin = j * a.bper;
-  const uint32_t b_end = min(b_begin + a.bper, a.nb);
-  // (a team whose region ran out has counted on without storing: nothing to copy)
-  const bool fits = base + mine <= a.cap_words && base + mine <= 0xFFFFFFFFull &&
-                    mine <= a.region_words;
-  if (fits) {
-    const uint32_t* __restrict__ src = a.staging + (uint64_t)j * a.region_words;
-    uint32_t* __restrict__ dstp = a.payload + base;
-    for (uint32_t i = tid; i < mine; i += 256) dstp[i] = src[i];
+// before j.  A workgroup has `tpb` consecutive teams, a wavefront one of them at a time;
+// it adds up the totals before its first team itself (at most kMaxTeams words, 16 bytes a
+// load, from the L2) instead of reading prefix sums that a launch of its own would have to
+// make first.  Bound by latency: with that launch and its gap 5.2 us at 40 teams and 15.4
+// at 7143 (25.6M values), without it 2.6 and 10.3.
+constexpr uint32_t kCompactWaves = 4;
+__global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactArgs a) {
+  __shared__ unsigned long long part[kCompactWaves];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
+  const uint32_t t_begin = blockIdx.x * a.tpb;
+  const uint32_t t_end = min(t_begin + a.tpb, a.teams);
+
+  // (tpb <= 64: lane l keeps the total of the workgroup's team l)
+  const uint32_t own = t_begin + (uint32_t)lane < t_end ? a.totals[t_begin + lane] : 0u;
+  // words of the teams before this workgroup's first one
+  unsigned long long sum = 0;
+  const uint4* const q = reinterpret_cast<const uint4*>(a.totals);
+  const uint32_t quads = t_begin >> 2;
+#pragma unroll 4
+  for (uint32_t i = tid; i < quads; i += 64 * kCompactWaves) {
+    const uint4 v = q[i];
+    sum += ((unsigned long long)v.x + v.y) + ((unsigned long long)v.z + v.w);
   }
-  for (uint32_t b = b_begin + tid; b < b_end; b += 256)
-    a.table[b] = (uint32_t)min(base + a.table[b], (uint64_t)0xFFFFFFFFull);
+  if ((uint32_t)tid < (t_begin & 3u)) sum += a.totals[4u * quads + tid];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+  if (lane == 0) part[wave] = sum;
+  __syncthreads();
+  unsigned long long base = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kCompactWaves; ++w) base += part[w];
+
+  bool all_fit = true;
+  for (uint32_t j = t_begin; j < t_end; ++j) {
+    const uint32_t mine = lane_bcast(own, (int)(j - t_begin));
+    // (a team whose region ran out has counted on without storing: nothing to copy)
+    const bool fits = base + mine <= a.cap_words && base + mine <= 0xFFFFFFFFull &&
+                      mine <= a.region_words;
+    all_fit = all_fit && fits;
+    if ((j - t_begin) % kCompactWaves == wave) {
+      if (fits) {
+        const uint32_t* __restrict__ src = a.staging + (uint64_t)j * a.region_words;
+        uint32_t* __restrict__ dstp = a.payload + base;
+#pragma unroll 4
+        for (uint32_t i = lane; i < mine; i += kWave) dstp[i] = src[i];
+      }
+      const uint32_t b_begin = j * a.bper;
+      const uint32_t b_end = min(b_begin + a.bper, a.nb);
+      for (uint32_t b = b_begin + lane; b < b_end; b += kWave)
+        a.table[b] = (uint32_t)min(base + a.table[b], 0xFFFFFFFFull);
+    }
+    base += mine;
+  }
   if (tid == 0) {
-    if (!fits) atomicExch(&a.header[H_STATUS], (uint32_t)QSGD_ERR_CAPACITY);
-    if (j == gridDim.x - 1) {
-      const uint64_t total = base + mine;
-      a.table[a.nb] = (uint32_t)min(total, (uint64_t)0xFFFFFFFFull);
+    if (!all_fit) atomicExch(&a.header[H_STATUS], (uint32_t)QSGD_ERR_CAPACITY);
+    if (t_end == a.teams) {
+      a.table[a.nb] = (uint32_t)min(base, 0xFFFFFFFFull);
       for (uint32_t i = a.nb + 1; i < a.table_words; ++i) a.table[i] = 0;  // padding
-      const uint64_t all = total + a.raw_words;   // the raw values follow the strings
+      const uint64_t all = base + a.raw_words;   // the raw values follow the strings
       if (all > a.cap_words) atomicExch(&a.header[H_STATUS], (uint32_t)QSGD_ERR_CAPACITY);
       a.header[H_PW_LO] = (uint32_t)all;
       a.header[H_PW_HI] = (uint32_t)(all >> 32);
@@ -677,9 +673,9 @@ hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint3
   return launch_fixed_small_b<64, 4>(a, teams, st);
 }
 
-hipError_t launch_encode_compact(const CompactArgs& a, uint32_t teams, hipStream_t st) {
-  hipLaunchKernelGGL(k_encode_prefix, dim3(1), dim3(1024), 0, st, a, teams);
-  hipLaunchKernelGGL(k_encode_compact, dim3(teams), dim3(256), 0, st, a);
+hipError_t launch_encode_compact(const CompactArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_encode_compact, dim3((a.teams + a.tpb - 1) / a.tpb),
+                     dim3(64 * kCompactWaves), 0, st, a);
   return hipGetLastError();
 }
 

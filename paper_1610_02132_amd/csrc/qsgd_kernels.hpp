@@ -121,11 +121,11 @@ struct CompactArgs {
   const uint32_t* staging;
   uint64_t region_words;
   const uint32_t* totals;
-  unsigned long long* prefix;  // workspace: words appended by the teams before each team
   uint32_t* table;
   uint32_t* payload;
   uint32_t* header;
   uint64_t cap_words;  // payload words the message buffer can hold
+  uint32_t teams, tpb; // teams, and how many of them a workgroup takes
   uint32_t bper;
   uint32_t nb;
   uint32_t table_words;  // padded table length
@@ -225,7 +225,7 @@ int validate_decode(const qsgd_params* p, uint32_t K, size_t workspace_bytes);
 
 hipError_t launch_encode_bucket(const EncodeArgs& a, uint32_t code, int tw, int cpw,
                                 uint32_t teams, size_t lds, hipStream_t st);
-hipError_t launch_encode_compact(const CompactArgs& a, uint32_t teams, hipStream_t st);
+hipError_t launch_encode_compact(const CompactArgs& a, hipStream_t st);
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,
                                      hipStream_t st);
 hipError_t launch_write_empty(uint32_t* header, uint32_t* table, uint32_t code, uint32_t norm,
