@@ -354,17 +354,19 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // Elias codes: one lane per string.
   if (a.kloop && g.s <= 127) {
     // dense strings whose levels fit a byte: the tile decoder
-    const uint32_t W = QSGD_TILE_WIN;
     uint32_t gw = 1;  // buckets per wavefront: a power of two, gw * K lanes
-    while (gw * 2 * K <= 64 && gw * 2 <= 16) gw *= 2;
-    while (gw > 1 && (g.nb + gw - 1) / gw < (uint64_t)cus * 8) gw /= 2;
-    a.tile_w = W; a.gw = gw;
-    a.win = (uint32_t)std::min<uint64_t>((g.d + 3) & ~(uint64_t)3, W);
-    a.winp = W;
-    const size_t lds = 64 * (size_t)W + 4 * 64 * ((size_t)kStrWin + 1) + 128;   // tile, string rings, Elias table
-    const uint32_t blocks = (uint32_t)((g.nb + gw - 1) / gw);
+    while (gw * 2 * K <= 64) gw *= 2;
+    while (gw > 1 && (g.nb + gw - 1) / gw < (uint64_t)cus * 4) gw /= 2;
+    a.gw = gw;
+    const uint32_t tasks = (uint32_t)((g.nb + gw - 1) / gw);
+    // as many wavefronts per compute unit as give every one of them the same number of
+    // groups; at least four, one per SIMD, share the work of loading the table
+    const uint32_t per_cu = (tasks + cus - 1) / cus, most = tile_max_waves(g.code);
+    const uint32_t rounds = (per_cu + most - 1) / most;
+    const uint32_t waves = std::max(4u, (per_cu + rounds - 1) / rounds);
+    const uint32_t blocks = std::min(cus, (tasks + waves - 1) / waves);
     ScopedTiming tm("decode_elias", st);
-    if (launch_decode_tile(a, blocks, lds, st) != hipSuccess) return QSGD_ERR_HIP;
+    if (launch_decode_tile(a, blocks, waves, st) != hipSuccess) return QSGD_ERR_HIP;
     return QSGD_OK;
   }
   const uint32_t win = (uint32_t)std::min<uint64_t>((g.d + 3) & ~(uint64_t)3, 256);
