@@ -157,6 +157,8 @@ int device_cus() {
 
 struct EncodePlan {
   int tw, cpw;
+  bool direct;     // every lane codes its own values (launch_encode_direct) ...
+  bool few;        // ... with as many lanes to a bucket as have work
   uint32_t teams, bper;
   uint64_t region_words;
   uint32_t dst_words, sub_words;
@@ -165,13 +167,32 @@ struct EncodePlan {
   uint64_t ws_bytes;
 };
 
-// `teams_target` <= kMaxTeams.  `ws_avail`: bytes of workspace behind the status block; a
-// workspace below the worst case gives every team an equal, smaller region.
-void plan_encode(const Geometry& g, uint32_t teams_target, uint64_t ws_avail, EncodePlan& pl) {
+// Dense strings: the share of nonzero levels grows like s / sqrt(d) (Lemma 3.1 (iii)); with the
+// largest value as scale it is larger still, and Code'_s codes every coordinate.
+bool dense_strings(const Geometry& g) {
+  return g.code == QSGD_CODE_DENSE || 64ull * g.s * g.s > g.d || g.norm == QSGD_NORM_MAX;
+}
+
+// `ws_avail`: bytes of workspace behind the status block; a workspace below the worst case
+// gives every team an equal, smaller region.
+void plan_encode(const Geometry& g, uint64_t ws_avail, EncodePlan& pl) {
   team_shape(g.d, pl.tw, pl.cpw);
-  const uint32_t nb = (uint32_t)g.nb;
-  const uint32_t t = std::max(1u, std::min(nb, teams_target));
-  pl.bper = (nb + t - 1) / t;
+  const uint32_t nb = (uint32_t)g.nb, cus = (uint32_t)device_cus();
+  // Every lane codes its own values wherever that was measured the faster way: dense strings
+  // (25.6M values, s = 16, d = 512: 70 us per encode through the survivor ring, 53 directly),
+  // and sparse ones except where the ring's chunks of 256 fit the bucket better than the
+  // direct coder's runs of 64 lanes x 4 or 8 values (20M values, s = 2: d = 512 43.7 and 41.1 us,
+  // d = 600 49 and 55, d = 1024 36 and 42, d = 1028 70 and 54, d = 2048 53 and 44).
+  pl.direct = g.code != QSGD_CODE_FIXED && g.d <= 2048 &&
+              (dense_strings(g) || g.d <= 512 || g.d > 1024);
+  // direct: the teams a compute unit holds at once, whole passes each; else persistent teams
+  // well above what is resident
+  pl.few = nb <= cus * 16;
+  const uint32_t pass = pl.direct ? direct_buckets_per_pass((uint32_t)g.d, pl.few) : 1u;
+  const uint32_t target = std::min(kMaxTeams, cus * (pl.direct ? QSGD_DIRECT_TEAMS : QSGD_ENC_TEAMS / pl.tw));
+  const uint32_t passes = (nb + pass - 1) / pass;
+  const uint32_t t = std::max(1u, std::min(passes, target));
+  pl.bper = std::min(nb, (passes + t - 1) / t * pass);
   pl.teams = (nb + pl.bper - 1) / pl.bper;
   if (g.code == QSGD_CODE_FIXED) {
     pl.region_words = 0; pl.dst_words = 2; pl.sub_words = 2;
@@ -410,10 +431,7 @@ int validate_encode(const qsgd_params* p, uint64_t index_base, size_t msg_capaci
   }
   if (workspace_bytes < kStatusBytes + kTotalsBytes) return QSGD_ERR_CAPACITY;
   EncodePlan pl;
-  int tw, cpw;
-  team_shape(g.d, tw, cpw);
-  const uint32_t target = std::min<uint32_t>(kMaxTeams, (uint32_t)device_cus() * (QSGD_ENC_TEAMS / tw));
-  plan_encode(g, target, workspace_bytes - kStatusBytes, pl);
+  plan_encode(g, workspace_bytes - kStatusBytes, pl);
   if (g.code != QSGD_CODE_FIXED && pl.region_words < std::min<uint64_t>(64, g.max_words(g.d)))
     return QSGD_ERR_CAPACITY;
   if (g.code == QSGD_CODE_FIXED && cap_words < g.max_payload_words()) return QSGD_ERR_CAPACITY;
@@ -602,11 +620,8 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
   }
 
   EncodePlan pl;
-  int tw, cpw;
-  team_shape(g.d, tw, cpw);
-  const uint32_t target = std::min<uint32_t>(kMaxTeams, (uint32_t)device_cus() * (QSGD_ENC_TEAMS / tw));
   if (workspace_bytes < kStatusBytes + kTotalsBytes) return QSGD_ERR_CAPACITY;
-  plan_encode(g, target, workspace_bytes - kStatusBytes, pl);
+  plan_encode(g, workspace_bytes - kStatusBytes, pl);
   // Elias codes: a region must at least hold one string of typical size; below the
   // worst case the device reports a region that ran out like a message that did
   if (g.code != QSGD_CODE_FIXED && pl.region_words < std::min<uint64_t>(64, g.max_words(g.d)))
@@ -664,8 +679,10 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
   }
   {
     ScopedTiming tm("encode_bucket", st);
-    if (launch_encode_bucket(a, g.code, pl.tw, pl.cpw, pl.teams, pl.lds, st) != hipSuccess)
-      return QSGD_ERR_HIP;
+    const hipError_t err =
+        pl.direct ? launch_encode_direct(a, g.code, pl.few, pl.teams, st)
+                  : launch_encode_bucket(a, g.code, pl.tw, pl.cpw, pl.teams, pl.lds, st);
+    if (err != hipSuccess) return QSGD_ERR_HIP;
   }
   if (g.code != QSGD_CODE_FIXED) {
     CompactArgs c;

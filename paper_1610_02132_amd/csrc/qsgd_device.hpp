@@ -202,6 +202,7 @@ __device__ __forceinline__ uint32_t dpp_fetch_or(uint32_t other, uint32_t v) {  
 }
 constexpr int kDppShl1 = 0x101, kDppShl2 = 0x102, kDppShl4 = 0x104;  // lane l reads lane l+k of its row
 constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+constexpr int kDppWaveShr1 = 0x138;   // lane l reads lane l-1 of the wavefront
 constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
 
 template <int CTRL, int ROW_MASK>

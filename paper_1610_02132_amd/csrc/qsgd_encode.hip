@@ -615,39 +615,35 @@ __global__ void k_write_empty(uint32_t* header, uint32_t* table, uint32_t code, 
 }
 
 // ---- launch table -------------------------------------------------------------
-template <int TW, int CPW>
-static hipError_t launch_tw_cpw(const EncodeArgs& a, uint32_t code, dim3 grid, size_t lds,
-                                hipStream_t st) {
+// (d <= 2048: Elias codes mostly take launch_encode_direct, fixed width up to 1024
+// launch_encode_fixed_small)
+template <int TW, int CPW, int CODE, uint32_t LIST = 0>
+static hipError_t launch_bucket(const EncodeArgs& a, uint32_t teams, size_t lds, hipStream_t st) {
+  hipLaunchKernelGGL((k_encode_bucket<TW, CPW, CODE, LIST>), dim3(teams), dim3(64 * TW), lds, st, a);
+  return hipGetLastError();
+}
+
+template <int TW>
+static hipError_t launch_team(const EncodeArgs& a, uint32_t code, uint32_t teams, size_t lds,
+                              hipStream_t st) {
   switch (code) {
     case QSGD_CODE_SPARSE:
-      if (TW >= 2 && a.ring == list_records(CPW))
-        hipLaunchKernelGGL((k_encode_bucket<TW, CPW, QSGD_CODE_SPARSE, TW >= 2 ? list_records(CPW) : 0u>),
-                           grid, dim3(64 * TW), lds, st, a);
-      else
-        hipLaunchKernelGGL((k_encode_bucket<TW, CPW, QSGD_CODE_SPARSE>), grid, dim3(64 * TW), lds,
-                           st, a);
-      break;
-    case QSGD_CODE_DENSE:
-      hipLaunchKernelGGL((k_encode_bucket<TW, CPW, QSGD_CODE_DENSE>), grid, dim3(64 * TW), lds,
-                         st, a);
-      break;
-    default:
-      hipLaunchKernelGGL((k_encode_bucket<TW, CPW, QSGD_CODE_FIXED>), grid, dim3(64 * TW), lds,
-                         st, a);
-      break;
+      return a.ring == list_records(8)
+                 ? launch_bucket<TW, 8, QSGD_CODE_SPARSE, list_records(8)>(a, teams, lds, st)
+                 : launch_bucket<TW, 8, QSGD_CODE_SPARSE>(a, teams, lds, st);
+    case QSGD_CODE_DENSE: return launch_bucket<TW, 8, QSGD_CODE_DENSE>(a, teams, lds, st);
+    default: return launch_bucket<TW, 8, QSGD_CODE_FIXED>(a, teams, lds, st);
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_encode_bucket(const EncodeArgs& a, uint32_t code, int tw, int cpw,
                                 uint32_t teams, size_t lds, hipStream_t st) {
-  const dim3 grid(teams);
-  if (tw == 1 && cpw == 1) return launch_tw_cpw<1, 1>(a, code, grid, lds, st);
-  if (tw == 1 && cpw == 2) return launch_tw_cpw<1, 2>(a, code, grid, lds, st);
-  if (tw == 1 && cpw == 4) return launch_tw_cpw<1, 4>(a, code, grid, lds, st);
-  if (tw == 1 && cpw == 8) return launch_tw_cpw<1, 8>(a, code, grid, lds, st);
-  if (tw == 2 && cpw == 8) return launch_tw_cpw<2, 8>(a, code, grid, lds, st);
-  if (tw == 4 && cpw == 8) return launch_tw_cpw<4, 8>(a, code, grid, lds, st);
+  if (tw == 1 && cpw == 4 && code == QSGD_CODE_SPARSE)
+    return launch_bucket<1, 4, QSGD_CODE_SPARSE>(a, teams, lds, st);
+  if (tw == 1 && cpw == 8 && code == QSGD_CODE_FIXED)
+    return launch_bucket<1, 8, QSGD_CODE_FIXED>(a, teams, lds, st);
+  if (tw == 2 && cpw == 8) return launch_team<2>(a, code, teams, lds, st);
+  if (tw == 4 && cpw == 8) return launch_team<4>(a, code, teams, lds, st);
   return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,405 @@
+// Encode of Elias strings, d <= 2048: every lane codes its own values.
+//
+// Compacting the nonzero levels before they are coded costs more than it saves unless they are
+// very rare.  Here a wavefront holds 64 / LPB buckets at once, LPB lanes each; a lane owns runs
+// of 4 Q consecutive values, coalesced across the lanes.  Per run: Q Philox blocks, levels by
+// Eq. (2), a prefix maximum over the bucket's lanes (where is the nonzero level before the
+// lane's first one?), one look-up per value in a table in LDS that holds the whole code word
+// of (gap, sign, level), the run's code words joined in a 64-bit register, a prefix sum of the
+// lengths, and two or three ORs into the bucket's string in LDS.  The gap in front of a run's
+// first nonzero level may be beyond the table and is then coded by arithmetic; a run with a
+// level beyond it (32 and more), or of more than 64 bits, sends its wavefront through a small
+// general coder.
+//
+// Bound by instruction issue: about 45 vector instructions per value and lane (of those Philox 10,
+// rounding 8, code word 10), 78% of the issue slots.  25.6M values, s = 16, d = 512: 60 us through
+// the survivor ring (about 100 instructions), 42 directly; Code'_s of the same data 62 -> 36 us.
+// A copy of the bytes would take 19 us.
+#include "qsgd_device.hpp"
+#include "qsgd_encode_wave.hpp"
+#include "qsgd_kernels.hpp"
+
+namespace qsgd {
+
+namespace {
+
+// Code word table: index gap * 64 + level * 2 + sign, entry (code << 8) | length; Code_s: gap 0
+// stands for sign and level alone, level 0 has length 0; Code'_s: gap 0 only.
+constexpr uint32_t kMaxGap = 64, kMaxLev = 32;
+
+struct CodeLen { uint32_t code, len; };
+constexpr CodeLen omega_word(uint32_t k) {
+  uint32_t code = 0, len = 1;
+  while (k > 1) {
+    uint32_t nb = 0;
+    for (uint32_t t = k; t; t >>= 1) ++nb;
+    code |= k << len;
+    len += nb;
+    k = nb - 1;
+  }
+  return {code, len};
+}
+
+template <bool SPARSE> constexpr uint32_t code_entries() { return 2u * kMaxLev * (SPARSE ? kMaxGap : 1u); }
+template <bool SPARSE>
+struct alignas(16) CodeTable {
+  uint32_t e[code_entries<SPARSE>()];
+  constexpr CodeTable() : e() {
+    for (uint32_t i = 0; i < code_entries<SPARSE>(); ++i) {
+      const uint32_t gap = i / (2 * kMaxLev), z = (i / 2) % kMaxLev, sign = i % 2;
+      if (SPARSE && z == 0) { e[i] = 0; continue; }
+      const CodeLen l = omega_word(SPARSE ? z : z + 1);
+      uint32_t code = sign << l.len | l.code, len = l.len + 1;
+      if (SPARSE && gap) {
+        const CodeLen g = omega_word(gap);
+        code |= g.code << len;
+        len += g.len;
+      }
+      e[i] = code << 8 | len;
+    }
+  }
+};
+__device__ const CodeTable<true> g_codes_sparse;
+__device__ const CodeTable<false> g_codes_dense;
+
+// Inclusive scans over groups of LPB lanes (16, 32 or 64), and the value of the lane below
+// (0 for the first lane of a group).
+template <int LPB>
+__device__ __forceinline__ uint32_t group_incl_sum(uint32_t v) {
+  v += dpp_fetch<kDppShr1, 0xf>(v);
+  v += dpp_fetch<kDppShr2, 0xf>(v);
+  v += dpp_fetch<kDppShr4, 0xf>(v);
+  v += dpp_fetch<kDppShr8, 0xf>(v);
+  if (LPB >= 32) v += dpp_fetch<kDppBcast15, 0xa>(v);
+  if (LPB >= 64) v += dpp_fetch<kDppBcast31, 0xc>(v);
+  return v;
+}
+template <int LPB>
+__device__ __forceinline__ uint32_t group_incl_max(uint32_t v) {
+  v = max(v, dpp_fetch<kDppShr1, 0xf>(v));
+  v = max(v, dpp_fetch<kDppShr2, 0xf>(v));
+  v = max(v, dpp_fetch<kDppShr4, 0xf>(v));
+  v = max(v, dpp_fetch<kDppShr8, 0xf>(v));
+  if (LPB >= 32) v = max(v, dpp_fetch<kDppBcast15, 0xa>(v));
+  if (LPB >= 64) v = max(v, dpp_fetch<kDppBcast31, 0xc>(v));
+  return v;
+}
+template <int LPB>
+__device__ __forceinline__ uint32_t group_lane_below(uint32_t v, uint32_t l) {
+  const uint32_t up = dpp_fetch<kDppWaveShr1, 0xf>(v);
+  return l == 0 ? 0u : up;
+}
+// Value of the group's last lane.
+template <int LPB>
+__device__ __forceinline__ uint32_t group_last(uint32_t v, int last_lane) {
+  if (LPB == 64) return lane_bcast(v, 63);
+  return (uint32_t)__shfl((int)v, last_lane, kWave);
+}
+
+}  // namespace
+
+template <int LPB, int CP, int Q, int CODE>
+__global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs a) {
+  constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
+  constexpr uint32_t NB = 64 / LPB;             // buckets per wavefront pass
+  constexpr int R = 4 * Q;                      // values of a run
+  constexpr uint32_t kStep = LPB * R;           // values one run of the bucket's lanes covers
+  constexpr uint32_t kTab = code_entries<kSparse>();
+  __shared__ uint32_t codes[kTab];
+  extern __shared__ uint32_t smem[];            // per wavefront: NB bucket strings of dst_words
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
+  const uint32_t sb = (uint32_t)lane / LPB, l = (uint32_t)lane % LPB;
+  const int last_lane = (int)(sb * LPB + LPB - 1);
+  uint32_t* const dst = smem + (wave * NB + sb) * a.dst_words;
+
+  {
+    const uint32_t* src;
+    if constexpr (kSparse) src = g_codes_sparse.e; else src = g_codes_dense.e;
+    for (uint32_t i = tid; i < kTab; i += blockDim.x) codes[i] = src[i];
+    for (uint32_t j = l; j < a.dst_words; j += LPB) dst[j] = 0;
+  }
+  if (blockIdx.x == 0 && tid == 0) {  // header; length and status are completed later
+    uint32_t* h = a.header;
+    h[H_MAGIC] = kMagic; h[H_VERSION] = a.version; h[H_CODE] = CODE; h[H_NORM] = a.norm_mode;
+    h[H_S] = a.s; h[H_STREAM] = a.stream_id;
+    h[H_D_LO] = (uint32_t)a.d; h[H_D_HI] = 0;
+    h[H_N_LO] = (uint32_t)a.n; h[H_N_HI] = (uint32_t)(a.n >> 32);
+    h[H_NB_LO] = a.nb; h[H_NB_HI] = 0;
+    h[H_PW_LO] = 0; h[H_PW_HI] = 0;
+    h[H_STATUS] = 0; h[H_ITER] = a.iteration;
+  }
+  __syncthreads();
+
+  const uint32_t team = blockIdx.x * kDirectWaves + wave;
+  const uint32_t b_begin = team * a.bper;
+  if (b_begin >= a.nb) return;
+  const uint32_t b_end = min(b_begin + a.bper, a.nb);
+  uint32_t* const region = a.staging + (uint64_t)team * a.region_words;
+  uint32_t run = 0;  // words this team has appended to its region
+  const uint32_t s = a.s;
+  const float s_f = (float)s;
+  const uint32_t zlim = min(s, kMaxLev - 1u);
+  QuantCtx qc;
+  qc.inv = 0.f; qc.s_f = s_f; qc.s = s; qc.key0 = a.key0; qc.key1 = a.key1;
+  qc.stream_id = a.stream_id; qc.iteration = a.iteration;
+
+  for (uint32_t b0 = b_begin; b0 < b_end; b0 += NB) {
+    const uint32_t b = b0 + sb;
+    const bool live = b < b_end;
+    uint64_t base = 0;
+    uint32_t m = 0;
+    if (live) bucket_extent(a, b, base, m);
+    const float* __restrict__ gb = a.g + base;
+    const bool all_full = __ballot(m == (uint32_t)CP * kStep) == ~0ull;
+
+    float v[CP][R];
+#pragma unroll
+    for (int c = 0; c < CP; ++c) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const uint32_t e0 = (uint32_t)c * kStep + l * R + 4 * q;
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (all_full || e0 + 3 < m) {
+          x = *reinterpret_cast<const float4*>(gb + e0);
+        } else {
+          if (e0 + 0 < m) x.x = gb[e0 + 0];
+          if (e0 + 1 < m) x.y = gb[e0 + 1];
+          if (e0 + 2 < m) x.z = gb[e0 + 2];
+        }
+        v[c][4 * q] = x.x; v[c][4 * q + 1] = x.y; v[c][4 * q + 2] = x.z; v[c][4 * q + 3] = x.w;
+      }
+    }
+
+    // ---- scale of each bucket: reduction over its LPB lanes ------------------------------
+    float scale;
+    if (a.norm_mode == 0) {
+      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;   // squares are exact in fp64
+#pragma unroll
+      for (int c = 0; c < CP; ++c) {
+#pragma unroll
+        for (int j = 0; j < R; j += 4) {
+          s0 = fma((double)v[c][j], (double)v[c][j], s0);
+          s1 = fma((double)v[c][j + 1], (double)v[c][j + 1], s1);
+          s2 = fma((double)v[c][j + 2], (double)v[c][j + 2], s2);
+          s3 = fma((double)v[c][j + 3], (double)v[c][j + 3], s3);
+        }
+      }
+      double ss = (s0 + s1) + (s2 + s3);
+      ss += dpp_fetch_f64<kDppShr1, 0xf>(ss);
+      ss += dpp_fetch_f64<kDppShr2, 0xf>(ss);
+      ss += dpp_fetch_f64<kDppShr4, 0xf>(ss);
+      ss += dpp_fetch_f64<kDppShr8, 0xf>(ss);
+      if (LPB >= 32) ss += dpp_fetch_f64<kDppBcast15, 0xa>(ss);
+      if (LPB >= 64) ss += dpp_fetch_f64<kDppBcast31, 0xc>(ss);
+      scale = (float)sqrt(ss);  // right in the last lane of each bucket
+    } else {
+      float mx = 0.f;
+#pragma unroll
+      for (int c = 0; c < CP; ++c)
+#pragma unroll
+        for (int j = 0; j < R; ++j) mx = fmaxf(mx, fabsf(v[c][j]));
+      mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr1, 0xf>(__float_as_uint(mx))));
+      mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr2, 0xf>(__float_as_uint(mx))));
+      mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr4, 0xf>(__float_as_uint(mx))));
+      mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr8, 0xf>(__float_as_uint(mx))));
+      if (LPB >= 32) mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppBcast15, 0xa>(__float_as_uint(mx))));
+      if (LPB >= 64) mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppBcast31, 0xc>(__float_as_uint(mx))));
+      scale = mx;
+    }
+    scale = __uint_as_float(group_last<LPB>(__float_as_uint(scale), last_lane));
+    const float inv = (scale > 0.f) ? s_f / scale : 0.f;
+
+    // ---- runs ---------------------------------------------------------------------------
+    const uint64_t g0 = a.index_base + base + l * R;
+    uint32_t hi;
+    const bool uhi = uniform_counter_hi(g0, g0 + (uint64_t)(CP - 1) * kStep + R - 4, hi);
+    uint32_t bits = 32;        // bits of the bucket's string so far (the same in all its lanes)
+    uint32_t last_pos = 0;     // 1-based position of the last nonzero level so far
+#pragma unroll
+    for (int c = 0; c < CP; ++c) {
+      // (one run after the other: side by side they cost the fifth wavefront per SIMD)
+      __builtin_amdgcn_sched_barrier(0);
+      uint32_t z[R], zmax = 0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        uint32_t r[4];
+        const uint64_t gi = g0 + (uint64_t)c * kStep + 4 * q;
+        if (uhi) draw4_uniform_hi(gi, hi, qc, r);
+        else draw4<true>(gi, qc, r);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          z[4 * q + j] = quantize_unclamped(v[c][4 * q + j], inv, r[j]);
+          zmax = max(zmax, z[4 * q + j]);
+        }
+      }
+      const uint32_t e0 = (uint32_t)c * kStep + l * R;     // bucket position of the run, 0-based
+      // where the nonzero level before the run is; inside a run gaps are at most R, so only its
+      // first one can be beyond the table
+      uint64_t acc = 0;
+      uint32_t len = 0, prev0 = 0, from = 0;
+      if constexpr (kSparse) {
+        uint32_t lastnz = 0;
+#pragma unroll
+        for (int j = 0; j < R; ++j) lastnz = z[j] ? (uint32_t)j + 1u : lastnz;
+        const uint32_t im = group_incl_max<LPB>(lastnz ? e0 + lastnz : 0u);
+        prev0 = max(group_lane_below<LPB>(im, l), last_pos);
+        last_pos = max(last_pos, group_last<LPB>(im, last_lane));
+        // (a run without a nonzero level looks up level 0 at gaps of the table all the same)
+        from = lastnz ? prev0 : e0;
+        const bool far = e0 + (uint32_t)R - from >= kMaxGap;
+        if (__builtin_amdgcn_ballot_w64(far)) {
+          // the gap's code word opens the run, its first level is looked up alone
+          uint32_t firstnz = 0;
+#pragma unroll
+          for (int j = R - 1; j >= 0; --j) firstnz = z[j] ? (uint32_t)j + 1u : firstnz;
+          if (far) {
+            omega_encode(e0 + firstnz - prev0, acc, len);
+            from = e0 + firstnz;
+          }
+        }
+      }
+      bool easy = __builtin_amdgcn_ballot_w64(zmax > zlim) == 0;
+      if (easy) {
+        // positions from the run's start on, in bytes of the table (2 kMaxLev words per gap); as
+        // constants: positions in the bucket would be kept in 2 R registers over all buckets
+        constexpr uint32_t kGapBytes = 8u * kMaxLev;
+        uint32_t prev = (from - e0) * kGapBytes;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          uint32_t e;
+          if constexpr (kSparse) {
+            const uint32_t pos = ((uint32_t)j + 1u) * kGapBytes;
+            const uint32_t zs = __builtin_amdgcn_alignbit(z[j], __float_as_uint(v[c][j]), 31);   // z * 2 + sign
+            e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(codes) +
+                                                   ((zs << 2) | (pos - prev)));
+            prev = z[j] ? pos : prev;
+          } else {
+            const uint32_t zs = z[j] * 2u + (v[c][j] < 0.f ? 1u : 0u);   // (-0.0 counts as positive)
+            e = codes[zs];
+            if (!all_full) e = e0 + (uint32_t)j < m ? e : 0u;
+          }
+          acc = (acc << (e & 63u)) | (e >> 8);
+          len += e & 0xFFu;
+        }
+        easy = __builtin_amdgcn_ballot_w64(len > 64u) == 0;
+      }
+      if (easy) {
+        const uint32_t incl = group_incl_sum<LPB>(len);
+        if (len) lds_emit(dst, bits + incl - len, acc, len);
+        bits += group_last<LPB>(incl, last_lane);
+      } else {
+        // the general coder, from memory (rare: kept small rather than fast, so that it costs
+        // the usual path no registers): lengths, prefix sum, then one code word at a time
+        uint32_t off = 0, incl = 0;
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {
+          uint32_t prev = prev0, tot = 0;
+#pragma unroll 1
+          for (uint32_t j = 0; j < (uint32_t)R; ++j) {
+            const uint32_t pos = e0 + j + 1u;
+            if (pos > m) break;
+            uint32_t r[4];
+            draw4<true>(g0 + (uint64_t)c * kStep + (j & ~3u), qc, r);
+            const uint32_t q = j & 3u;
+            const float x = gb[pos - 1u];
+            const uint32_t lev = quantize_one(x, inv, s_f, s, q == 0 ? r[0] : q == 1 ? r[1] : q == 2 ? r[2] : r[3]);
+            if (kSparse && lev == 0) continue;
+            uint64_t gc = 0, lc;
+            uint32_t gl = 0, ll;
+            if (kSparse) omega_encode(pos - prev, gc, gl);
+            omega_encode(kSparse ? lev : lev + 1u, lc, ll);
+            if (pass) {
+              if (gl) lds_emit(dst, off + tot, gc, gl);
+              lds_emit(dst, off + tot + gl, ((uint64_t)(x < 0.f ? 1u : 0u) << ll) | lc, ll + 1u);
+            }
+            tot += gl + ll + 1u;
+            prev = pos;
+          }
+          if (pass == 0) {
+            incl = group_incl_sum<LPB>(tot);
+            off = bits + incl - tot;
+          }
+        }
+        bits += group_last<LPB>(incl, last_lane);
+      }
+    }
+
+    // ---- close the strings and append them to the team's region ----------------------------
+    const uint32_t stop = kSparse ? 1u : 0u;
+    const uint32_t words = live ? (bits + stop + 31u) >> 5 : 0u;
+    if (l == 0 && live) {
+      dst[0] = __float_as_uint(scale);
+      if (kSparse) lds_emit(dst, bits, 1ull, 1u);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t before = 0, all = words;
+    if (NB > 1) {
+      before = 0; all = 0;
+#pragma unroll
+      for (uint32_t t = 0; t < NB; ++t) {
+        const uint32_t wt = lane_bcast(words, (int)(t * LPB));
+        if (t < sb) before += wt;
+        all += wt;
+      }
+    }
+    // (a region smaller than the worst case may run out: the string is then dropped, the
+    // count goes on, and the message ends up with the capacity status and the size needed)
+    const uint32_t at = run + before;
+    const bool room = (uint64_t)at + words <= a.region_words;
+    if (l == 0 && live) a.table[b] = at;  // relative to the region; rebased later
+    for (uint32_t j = l; j < words; j += LPB) {
+      if (room) region[at + j] = dst[j];
+      dst[j] = 0;
+    }
+    run += all;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (lane == 0) a.totals[team] = run;
+}
+
+namespace {
+
+template <int LPB, int CP, int Q>
+hipError_t launch_direct(const EncodeArgs& a, uint32_t code, uint32_t teams, hipStream_t st) {
+  const dim3 grid((teams + kDirectWaves - 1) / kDirectWaves), block(64 * kDirectWaves);
+  const size_t lds = 4 * (size_t)kDirectWaves * (64 / LPB) * a.dst_words;
+  if (code == QSGD_CODE_SPARSE)
+    hipLaunchKernelGGL((k_encode_direct<LPB, CP, Q, QSGD_CODE_SPARSE>), grid, block, lds, st, a);
+  else
+    hipLaunchKernelGGL((k_encode_direct<LPB, CP, Q, QSGD_CODE_DENSE>), grid, block, lds, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Lanes per bucket: one run of eight values (four up to d = 64) per lane up to d = 512, several
+// runs of all 64 lanes beyond.  (Two runs per lane and half the lanes per bucket at d = 512
+// share the work per bucket, but cost wavefronts: 53.7 us instead of 53.2 on 25.6M values,
+// 42.4 instead of 41.3 on 20M sparser ones.)  Few buckets: runs of four and twice the lanes
+// up to d = 256, for the shortest chain.
+static int lanes_per_bucket(uint32_t d, bool few) {
+  if (d <= 64) return 16;
+  if (d <= 128) return few ? 32 : 16;
+  if (d <= 256) return few ? 64 : 32;
+  return 64;
+}
+uint32_t direct_buckets_per_pass(uint32_t d, bool few) { return 64u / lanes_per_bucket(d, few); }
+
+hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, uint32_t teams,
+                                hipStream_t st) {
+  if (a.d <= 64) return launch_direct<16, 1, 1>(a, code, teams, st);
+  if (a.d <= 128) return few ? launch_direct<32, 1, 1>(a, code, teams, st)
+                             : launch_direct<16, 1, 2>(a, code, teams, st);
+  if (a.d <= 256) return few ? launch_direct<64, 1, 1>(a, code, teams, st)
+                             : launch_direct<32, 1, 2>(a, code, teams, st);
+  if (a.d <= 512) return launch_direct<64, 1, 2>(a, code, teams, st);
+  if (a.d <= 768) return launch_direct<64, 3, 1>(a, code, teams, st);
+  if (a.d <= 1024) return launch_direct<64, 2, 2>(a, code, teams, st);
+  if (a.d <= 1536) return launch_direct<64, 3, 2>(a, code, teams, st);
+  return launch_direct<64, 4, 2>(a, code, teams, st);
+}
+
+}  // namespace qsgd

@@ -30,6 +30,11 @@ constexpr uint32_t kMaxTeams = 8192;       // most teams (regions) one encode us
 #ifndef QSGD_ENC_TEAMS
 #define QSGD_ENC_TEAMS 128u
 #endif
+// Direct encoder (Elias codes, d <= 2048): teams per compute unit, about what its registers let
+// be resident at once (25.6M values: 20 -> 53.7 us, 32 -> 53.2; 20M of d = 1500: 24 -> 48.9, 32 -> 45.9).
+#ifndef QSGD_DIRECT_TEAMS
+#define QSGD_DIRECT_TEAMS 32u
+#endif
 // Small-bucket fixed-width encoder: wavefronts per compute unit the grid may have.  A
 // persistent grid (32 per CU) measured 0.19 ms on c3, one pass per wavefront 0.15 ms.
 #ifndef QSGD_FS_TEAMS
@@ -224,6 +229,9 @@ int validate_decode(const qsgd_params* p, uint32_t K, size_t workspace_bytes);
 
 hipError_t launch_encode_bucket(const EncodeArgs& a, uint32_t code, int tw, int cpw,
                                 uint32_t teams, size_t lds, hipStream_t st);
+constexpr uint32_t kDirectWaves = 4;   // wavefronts (teams) that share a code word table
+uint32_t direct_buckets_per_pass(uint32_t d, bool few);
+hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, uint32_t teams, hipStream_t st);
 hipError_t launch_encode_compact(const CompactArgs& a, hipStream_t st);
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,
                                      hipStream_t st);
