@@ -328,12 +328,27 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // word: more than 32 messages go the other way whatever the data.)
   a.kloop = (g.code == QSGD_CODE_DENSE || 64ull * g.s * g.s > g.d || K > 32) ? 1u : 0u;
 
+  const uint32_t cus = (uint32_t)device_cus();
+  if (g.n > 0 && g.code == QSGD_CODE_SPARSE && g.d > kEntryMinD && std::isfinite(c)) {
+    // Long buckets of Code_s: a message has at most q = s (s + sqrt(d)) nonzero levels in
+    // expectation (Lemma 3.1 (iii)), so about K^2 q^2 / (2 d) coordinates are hit by two
+    // messages.  Where that is a few hundred at most, only the touched coordinates are updated.
+    const double q = (double)g.s * ((double)g.s + std::sqrt((double)g.d));
+    if ((double)K * K * q * q <= 512.0 * (double)g.d) {
+      uint8_t* const area = static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes;
+      // wavefronts per string: a stretch is about 1024 bits, a record about Elias(d / q) + 3
+      const double bits = q * (omega_len_host((uint64_t)((double)g.d / q) + 1) + 3.0);
+      const uint32_t chunks = (uint32_t)std::min(64.0, bits / (64.0 * kEntryBits) + 1.0);
+      ScopedTiming tm("decode_general", st);
+      return launch_sparse_long(a, reinterpret_cast<uint32_t*>(area), area + align_up(4 * g.n, 256),
+                                cus, chunks, st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
+    }
+  }
   {
     ScopedTiming tm("decode_check", st);
     if (launch_decode_check(a, st) != hipSuccess) return QSGD_ERR_HIP;
   }
   if (g.n == 0) return QSGD_OK;
-  const uint32_t cus = (uint32_t)device_cus();
   if (L && L->R) {   // the small tensors: raw values behind the strings
     ScopedTiming tm("decode_raw", st);
     if (launch_raw_apply(a, raw_args(g, L), st) != hipSuccess) return QSGD_ERR_HIP;
@@ -347,22 +362,10 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
       return QSGD_OK;
     }
     float* acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes);
-    // Long buckets of Code_s: a message has at most q = s (s + sqrt(d)) nonzero levels in
-    // expectation (Lemma 3.1 (iii)), so about K^2 q^2 / (2 d) coordinates are hit by two
-    // messages.  Where that is a few hundred at most, the K messages are read at once.
-    {
-      const double q = (double)g.s * ((double)g.s + std::sqrt((double)g.d));
-      a.together = (g.code == QSGD_CODE_SPARSE && g.d > kEntryMinD &&
-                    (double)K * K * q * q <= 512.0 * (double)g.d) ? 1u : 0u;
-    }
-    if (launch_gen_zero(acc, g.n, blocks, st) != hipSuccess) return QSGD_ERR_HIP;
-    if (a.together) {
-      uint8_t* lists = reinterpret_cast<uint8_t*>(acc) + align_up(4 * g.n, 256);
-      if (launch_gen_parse_together(a, acc, lists, st) != hipSuccess) return QSGD_ERR_HIP;
-    } else if (launch_gen_parse(a, acc, g.d > kEntryMinD, st) != hipSuccess) {
+    if (launch_gen_zero(acc, g.n, blocks, st) != hipSuccess ||
+        launch_gen_parse(a, acc, g.d > kEntryMinD, st) != hipSuccess ||
+        launch_gen_apply(a, acc, blocks, st) != hipSuccess)
       return QSGD_ERR_HIP;
-    }
-    if (launch_gen_apply(a, acc, blocks, st) != hipSuccess) return QSGD_ERR_HIP;
     return QSGD_OK;
   }
 

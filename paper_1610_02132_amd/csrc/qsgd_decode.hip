@@ -48,46 +48,6 @@ __device__ __forceinline__ void ring_put_piece(uint32_t* ring, uint32_t idx,
   if (sl == 0) ring[kStrWin] = t[0];
 }
 
-// Recursive Elias code (App. A.2), decoder rule unrolled: N = 1; a 0 bit outputs N,
-// a 1 bit opens an (N+1)-bit group whose value is the new N.  `w` holds the next
-// 32 stream bits, first bit on top.  G = most groups accepted (G = 1: k <= 3,
-// 2: k <= 15, 3: k < 2^16, 4: every code word of at most 32 bits, k < 2^20).
-// Returns 0 (len 0) for anything longer or malformed.
-template <int G>
-__device__ __forceinline__ uint32_t omega_peek(uint32_t w, uint32_t& len) {
-  const uint32_t t0 = w >> 31;
-  const uint32_t g1 = w >> 30;            // first group, 2 bits: 2 or 3
-  const uint32_t w1 = w << 2;
-  const uint32_t t1 = w1 >> 31;
-  uint32_t v = 0, l = 0;
-  if constexpr (G >= 2) {
-    const uint32_t n1 = g1 + 1u;            // 3 or 4
-    const uint32_t g2 = w1 >> (32u - n1);   // 4..15
-    const uint32_t w2 = w1 << n1;
-    const uint32_t t2 = w2 >> 31;
-    if constexpr (G >= 3) {
-      const uint32_t n2 = g2 + 1u;            // 5..16
-      const uint32_t g3 = w2 >> (32u - n2);   // 16..65535
-      const uint32_t w3 = w2 << n2;
-      const uint32_t t3 = w3 >> 31;
-      const uint32_t l3 = 3u + n1 + n2;       // length when the third group is the value
-      if constexpr (G >= 4) {
-        const uint32_t n3 = min(g3 + 1u, 31u);  // only used when the whole word fits 32 bits
-        const uint32_t g4 = w3 >> (32u - n3);
-        // a fourth group only counts if it and its closing 0 lie inside the 32 bits
-        const bool fits4 = l3 + g3 + 1u <= 32u && ((w3 << n3) >> 31) == 0u;
-        if (t3 && fits4) { v = g4; l = l3 + n3; }
-      }
-      if (!t3) { v = g3; l = l3; }
-    }
-    if (!t2) { v = g2; l = 3u + n1; }
-  }
-  if (!t1) { v = g1; l = 3u; }
-  if (!t0) { v = 1u; l = 1u; }
-  len = l;
-  return v;
-}
-
 // Entry of the Elias table for the 7-bit pattern b7 (first stream bit on top): (after, more)
 // = where the bits of the LAST group after its leading 1 start, and how many they are.  The
 // value of the code word is then 2^more + those bits and its length after + more + 1:
@@ -115,29 +75,7 @@ __device__ __forceinline__ uint8_t omega_table_entry(uint32_t b7) {
 
 }  // namespace
 
-// One thread per message: the header must describe the same code as the call.
-__global__ void k_decode_check(DecodeArgs a) {
-  const uint32_t k = threadIdx.x;
-  if (k == 0) *a.status = 0;
-  __syncthreads();
-  if (k >= a.K) return;
-  bool ok = a.msg_words[k] >= (uint64_t)H_WORDS + a.table_words;
-  if (ok) {
-    const uint32_t* h = a.msgs[k];
-    const uint64_t pw = h[H_PW_LO] | ((uint64_t)h[H_PW_HI] << 32);
-    ok = h[H_MAGIC] == kMagic && h[H_VERSION] == a.version && h[H_CODE] == a.code &&
-         h[H_NORM] == a.norm_mode && h[H_S] == a.s && h[H_D_LO] == a.d && h[H_D_HI] == 0 &&
-         h[H_N_LO] == (uint32_t)a.n && h[H_N_HI] == (uint32_t)(a.n >> 32) &&
-         h[H_NB_LO] == a.nb && h[H_NB_HI] == 0 && h[H_STATUS] == 0 &&
-         (uint64_t)H_WORDS + a.table_words + pw <= a.msg_words[k];
-    if (ok && a.version == 2) {   // tensor-aware: the strings and the raw values fill the payload
-      const uint64_t strings = a.table_words ? (uint64_t)h[H_WORDS + a.nb]
-                                             : (uint64_t)a.nb * a.fixed_words_full;
-      ok = strings + a.raw_words == pw;
-    }
-  }
-  if (!ok) flag_corrupt(a.status);
-}
+__global__ void k_decode_check(DecodeArgs a) { check_headers(a); }
 
 // ---- fixed width: one wavefront per bucket ----------------------------------------
 // Lane k < K keeps message k's scale and escape index.  A wavefront takes CH chunks

@@ -147,6 +147,27 @@ __device__ __forceinline__ uint32_t omega_length(uint32_t k) {
   return len;
 }
 
+// Recursive Elias code (App. A.2), decoder rule unrolled for up to three groups (values
+// below 2^16): `w` holds the next 32 stream bits, first bit on top.  Returns 0 for anything
+// longer.
+__device__ __forceinline__ uint32_t omega_peek3(uint32_t w, uint32_t& len) {
+  const uint32_t g1 = w >> 30;            // first group, 2 bits: 2 or 3
+  const uint32_t w1 = w << 2;
+  const uint32_t n1 = g1 + 1u;            // 3 or 4
+  const uint32_t g2 = w1 >> (32u - n1);   // 4..15
+  const uint32_t w2 = w1 << n1;
+  const uint32_t n2 = g2 + 1u;            // 5..16
+  const uint32_t g3 = w2 >> (32u - n2);
+  const uint32_t w3 = w2 << n2;
+  uint32_t v = 0, l = 0;
+  if (!(w3 >> 31)) { v = g3; l = 3u + n1 + n2; }
+  if (!(w2 >> 31)) { v = g2; l = 3u + n1; }
+  if (!(w1 >> 31)) { v = g1; l = 3u; }
+  if (!(w >> 31)) { v = 1u; l = 1u; }
+  len = l;
+  return v;
+}
+
 // ---- bit strings: stream bit j is bit 31-(j%32) of word j/32 --------------------
 // ORs the `len` (1..64) low bits of `code` into zero-initialised LDS words so that
 // the code's first bit lands on stream bit `bitoff`.

@@ -17,6 +17,8 @@
 // the order k = 0, 1, ...); a last kernel applies the accumulator to x.  Buckets
 // above 8192 values carry a list of entry points behind their string and are read
 // by a workgroup, a thread per stretch; shorter ones by a thread per bucket.
+#include <cmath>
+
 #include "qsgd_device.hpp"
 #include "qsgd_encode_wave.hpp"
 #include "qsgd_kernels.hpp"
@@ -716,54 +718,29 @@ __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* 
   }
 }
 
-// Code_s records of one stretch, handed to f eight at a time: f(positions (0-based; ~0 for
-// an unused slot), values), so that f can have its memory accesses in flight together.
-constexpr int kWalkBatch = 8;
-template <class F>
-__device__ __forceinline__ bool walk_stretch(const StringRef& sr, uint64_t stop, uint64_t m,
-                                             uint32_t s, uint64_t& bitpos, uint64_t& pos, F&& f) {
-  WordWindow win;
-  win.open(sr.str, sr.nwords, bitpos);
-  for (;;) {
-    uint64_t where[kWalkBatch];
-    float what[kWalkBatch];
-    bool done = false;
-#pragma unroll
-    for (int t = 0; t < kWalkBatch; ++t) {
-      where[t] = ~0ull;
-      what[t] = 0.f;
-      if (done) continue;
-      if (bitpos >= stop) { done = true; continue; }
-      uint32_t gl, ll;
-      const uint32_t gap = omega_loop(win.peek(bitpos), gl);
-      if (gap == 0) return false;
-      const uint64_t w = win.peek(bitpos + gl);
-      const uint32_t lev = omega_loop(w << 1, ll);
-      bitpos += gl + 1u + ll;
-      pos += gap;
-      if (lev == 0 || lev > s || pos > m || bitpos > stop) return false;
-      const float mag = sr.scale * (float)lev;
-      where[t] = pos - 1;
-      what[t] = (w >> 63) ? -mag : mag;
-    }
-    f(where, what);
-    if (done) return true;
-  }
-}
+// ---- long buckets of sparse Code_s messages ------------------------------------------------
+// Where the host expects few coordinates that several messages hit, nearly all of x stays as it
+// is, so no dense accumulator is made: the records of all K messages are listed first (a
+// damaged message must leave x alone), then each updates its own coordinate.  Four launches:
+//   clear    checks the headers, clears the bucket's bitmaps and counters
+//   list     a wavefront per 64 stretches between entry points, a thread per stretch, string
+//            words staged in LDS: (position, value) into the message's list, the position's
+//            bit into `seen` and, if it was set already, into `multi`
+//   apply    a record whose position is not in `multi` updates x (0 + v = v is the sum in
+//            message order), the others go to the bucket's collision list
+//   resolve  a coordinate on that list is summed from 0 in message order by the thread that
+//            holds its record of the lowest message.  Lists that overflowed (the messages
+//            collide, or are longer, than expected) make the bucket's workgroup read the
+//            messages in turns into a dense accumulator.
+// Bound by latency: the stretch's chain of records (about 46, an LDS round trip and some 40
+// instructions each) and four launches.  13M values, s = 1, K = 16: 180 us with a dense
+// accumulator (zeroed, counted, stored, resolved, applied: 24 us of it for x alone), FIGURE.
+// Untouched coordinates: fma(-c, 0, x) is x for c >= 0; where it is not (accumulating, and
+// c < 0, turn -0 into +0) one more launch does that.
 
-// Long buckets of sparse Code_s messages (the host expects few coordinates that several
-// messages hit): all K messages are read at the same time, a workgroup per (bucket,
-// message) and a thread per stretch, in three kernels:
-//   count    every record adds 1 to its coordinate's word of the accumulator (an integer);
-//   store    the strings are read again: a record whose coordinate counts 1 stores its
-//            value (0 + v = v, the sum in message order); the others go to the bucket's
-//            list in the workspace;
-//   resolve  a coordinate on the list is summed from 0 in message order by the thread that
-//            holds its record of the lowest message.  A list that overflowed (the messages
-//            collide after all) makes the bucket's workgroup clear the bucket and read the
-//            messages in turns.
 struct CollideList {
   uint32_t* count;
+  uint32_t* overflow;   // the records did not fit: the messages are read in turns
   uint32_t* pos;
   float* val;
   uint32_t* msg;
@@ -772,115 +749,308 @@ __device__ __forceinline__ CollideList collide_list(uint8_t* lists, uint64_t b) 
   uint8_t* const base = lists + b * (uint64_t)kCollideBytes;
   CollideList l;
   l.count = reinterpret_cast<uint32_t*>(base);
+  l.overflow = l.count + 1;
   l.pos = reinterpret_cast<uint32_t*>(base + 256);
   l.val = reinterpret_cast<float*>(base + 256 + 4 * kCollide);
   l.msg = reinterpret_cast<uint32_t*>(base + 256 + 8 * kCollide);
   return l;
 }
 
-__global__ __launch_bounds__(256) void k_gen_zero_lists(uint8_t* lists, uint64_t nb) {
-  const uint64_t b = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b < nb) *collide_list(lists, b).count = 0;
+// A bucket's share of the accumulator area, m words: two bitmaps, a counter per message, and the
+// messages' lists of records.  cap 0: too small a bucket for that.
+struct SparseArea {
+  uint32_t *seen, *multi, *count;
+  uint32_t fixed;   // words in front of the lists
+  uint32_t cap;     // records per list
+  uint32_t* lists;
+  __device__ uint32_t* pos(uint32_t k) const { return lists + 2ull * k * cap; }
+  __device__ uint32_t* val(uint32_t k) const { return lists + (2ull * k + 1ull) * cap; }
+};
+__device__ __forceinline__ SparseArea sparse_area(uint32_t* area, uint64_t base, uint32_t m,
+                                                  uint32_t K) {
+  SparseArea s;
+  const uint32_t mw = (m + 31u) >> 5;
+  s.seen = area + base;
+  s.multi = s.seen + mw;
+  s.count = s.multi + mw;
+  s.fixed = 2u * mw + K;
+  s.lists = s.seen + s.fixed;
+  s.cap = m > s.fixed ? (m - s.fixed) / (2u * K) : 0u;
+  return s;
 }
 
-// STORE false: the counting pass; true: the storing pass.
-template <bool STORE>
-__global__ __launch_bounds__(256) void k_gen_walk(DecodeArgs a, float* acc, uint8_t* lists) {
+__global__ __launch_bounds__(256) void k_sparse_clear(DecodeArgs a, uint32_t* area, uint8_t* lists) {
+  if (blockIdx.x == 0) check_headers(a);
+  const uint32_t per = 2u * ((a.d + 31u) >> 5) + a.K;   // words of a full bucket
+  const uint64_t total = (uint64_t)a.nb * per;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
+       i += (uint64_t)gridDim.x * 256) {
+    const uint32_t b = (uint32_t)(i / per), w = (uint32_t)(i - (uint64_t)b * per);
+    const uint64_t base = (uint64_t)b * a.d;
+    const uint32_t m = (uint32_t)min((uint64_t)a.d, a.n - base);
+    const SparseArea s = sparse_area(area, base, m, a.K);
+    if (w == 0) {
+      const CollideList cl = collide_list(lists, b);
+      *cl.count = 0;
+      *cl.overflow = s.cap ? 0u : 1u;
+    }
+    if (s.cap && w < s.fixed) s.seen[w] = 0;
+  }
+}
+
+constexpr uint32_t kStage = 4096;   // words of a string a wavefront stages
+constexpr uint32_t kPad = 8;        // zeros behind them: a damaged record may reach past its stretch
+constexpr uint32_t kSlots = 32;     // records a thread reads between two deliveries
+__global__ __launch_bounds__(64) void k_sparse_list(DecodeArgs a, uint32_t* area, uint8_t* lists) {
   if (*a.status != 0) return;
-  __shared__ StringRef ref;
-  __shared__ uint32_t bad;
+  __shared__ uint32_t words[kStage];
+  __shared__ uint32_t rpos[64 * kSlots];
+  __shared__ float rval[64 * kSlots];
+  const int lane = threadIdx.x;
   const uint64_t b = blockIdx.x;
   const uint32_t k = blockIdx.y;
-  if (threadIdx.x == 0) {
-    StringRef mine;
-    bad = open_string(a, k, b, true, mine) ? 0u : 1u;
-    if (!bad) ref = mine;
-  }
-  __syncthreads();
-  if (bad) {
-    if (threadIdx.x == 0) flag_corrupt(a.status);
+  StringRef sr;
+  if (!open_string(a, k, b, true, sr)) {   // (the same in every lane)
+    if (lane == 0) flag_corrupt(a.status);
     return;
   }
-  const StringRef sr = ref;
   const uint64_t base = b * (uint64_t)a.d;
-  const uint64_t m = min((uint64_t)a.d, a.n - base);
-  float* const out = acc + base;
-  uint32_t* const outu = reinterpret_cast<uint32_t*>(out);
-  const CollideList cl = collide_list(lists, b);
-  for (uint64_t r = threadIdx.x; r <= sr.ents; r += blockDim.x) {
-    uint64_t bitpos = r ? sr.list[2 * (r - 1)] : 32;
-    uint64_t pos = r ? sr.list[2 * (r - 1) + 1] : 0;
-    const bool last_stretch = r == sr.ents;
-    const uint64_t stop = last_stretch ? sr.endbit : sr.list[2 * r];
-    bool ok = bitpos >= 32 && bitpos <= stop && stop <= sr.endbit && pos <= m;
-    ok = ok && walk_stretch(sr, stop, m, a.s, bitpos, pos,
-                            [&](const uint64_t (&p)[kWalkBatch], const float (&v)[kWalkBatch]) {
-      if (!STORE) {
-#pragma unroll
-        for (int t = 0; t < kWalkBatch; ++t)
-          if (p[t] != ~0ull) atomicAdd(&outu[p[t]], 1u);
+  const uint32_t m = (uint32_t)min((uint64_t)a.d, a.n - base);
+  const SparseArea s = sparse_area(area, base, m, a.K);
+  uint32_t* const lpos = s.pos(k);
+  uint32_t* const lval = s.val(k);
+  uint32_t* const overflow = collide_list(lists, b).overflow;
+
+  for (uint64_t r0 = (uint64_t)blockIdx.z * 64; r0 <= sr.ents; r0 += 64ull * gridDim.z) {
+    const uint64_t r = r0 + lane;
+    const bool mine = r <= sr.ents, last_stretch = r == sr.ents;
+    uint64_t bitpos = 0, stop = 0, pos = 0, pos_end = 0;
+    bool ok = true;
+    if (mine) {
+      bitpos = r ? sr.list[2 * (r - 1)] : 32;
+      pos = r ? sr.list[2 * (r - 1) + 1] : 0;
+      stop = last_stretch ? sr.endbit : sr.list[2 * r];
+      pos_end = last_stretch ? 0 : sr.list[2 * r + 1];
+      ok = bitpos >= 32 && bitpos <= stop && stop <= sr.endbit && pos <= m;
+      if (!ok) stop = bitpos = 0;
+    }
+    // the wavefront's stretches lie side by side: their words, read together
+    const uint32_t w_first = wave_min_u32(mine && ok ? (uint32_t)(bitpos >> 5) : 0xFFFFFFFFu);
+    const uint32_t w_end = wave_max_u32(mine && ok ? (uint32_t)((stop + 31) >> 5) : 0u);
+    const uint32_t span = w_end > w_first ? w_end - w_first : 0u;
+    const bool staged = span <= kStage - kPad;
+    if (staged) {
+#pragma unroll 8
+      for (uint32_t i = lane; i < span; i += 64) words[1 + i] = sr.str[w_first + i];
+      if (lane == 0) words[0] = 0;
+      if (lane < (int)kPad - 1) words[1 + span + lane] = 0;
+    }
+    __syncthreads();
+    // positions fit 32 bits, bit offsets are counted from the first staged word on
+    const uint64_t bit0 = staged ? (uint64_t)w_first * 32u : 0u;
+    uint32_t at_bit = (uint32_t)(bitpos - bit0), at_pos = (uint32_t)pos;
+    const uint32_t stop_bit = (uint32_t)(stop - bit0);
+    bool more = mine && ok && bitpos < stop;
+    while (__builtin_amdgcn_ballot_w64(more)) {
+      uint32_t cnt = 0;
+      if (staged) {
+        // 32 stream bits from bit `at` on: two words of LDS, aligned (p = at - 1: no shift by 32)
+        auto peek = [&](uint32_t at) -> uint32_t {
+          const uint32_t p = at - 1u + 32u;                  // (one word of padding in front)
+          return __builtin_amdgcn_alignbit(words[p >> 5], words[(p >> 5) + 1u], ~p);
+        };
+        while (more && cnt < kSlots) {
+          uint32_t gl, ll;
+          const uint32_t v = peek(at_bit);
+          uint32_t gap = omega_peek3(v, gl);
+          if (gap == 0)                                        // 2^16 and more, or malformed
+            gap = omega_loop((uint64_t)v << 32 | peek(at_bit + 32u), gl);
+          const uint32_t w = peek(at_bit + gl);
+          const uint32_t lev = omega_peek3(w << 1, ll);
+          at_bit += gl + 1u + ll;
+          at_pos += gap;
+          const bool good = (gap != 0) & (lev != 0) & (lev <= a.s) & (at_pos <= m) & (gap <= m) &
+                            (at_bit <= stop_bit);
+          const float mag = sr.scale * (float)lev;
+          rpos[cnt * 64 + lane] = at_pos - 1u;
+          rval[cnt * 64 + lane] = (w >> 31) ? -mag : mag;
+          cnt += good ? 1u : 0u;
+          ok = good;
+          more = good & (at_bit < stop_bit);
+        }
+      } else {                                                 // stretches too long to stage
+        while (more && cnt < kSlots) {
+          uint32_t gl, ll;
+          const uint32_t gap = omega_loop(peek64(sr.str, sr.nwords, bitpos), gl);
+          const uint32_t w = (uint32_t)(peek64(sr.str, sr.nwords, bitpos + gl) >> 32);
+          const uint32_t lev = omega_peek3(w << 1, ll);
+          bitpos += gl + 1u + ll;
+          at_pos += gap;
+          ok = gap != 0 && lev != 0 && lev <= a.s && gap <= m && at_pos <= m && bitpos <= stop;
+          if (ok) {
+            const float mag = sr.scale * (float)lev;
+            rpos[cnt * 64 + lane] = at_pos - 1u;
+            rval[cnt * 64 + lane] = (w >> 31) ? -mag : mag;
+            ++cnt;
+          }
+          more = ok && bitpos < stop;
+        }
+      }
+      // deliver: a place in the message's list for every record, and its bit
+      const uint32_t incl = wave_incl_scan_u32(cnt, lane);
+      const uint32_t total = lane_bcast(incl, 63);
+      uint32_t at = 0;
+      if (s.cap && lane == 0) at = atomicAdd(&s.count[k], total);
+      at = lane_bcast(at, 0);
+      if (at + total > s.cap) {
+        if (lane == 0) *overflow = 1;
       } else {
-        uint32_t c[kWalkBatch];
+        at += incl - cnt;
+        constexpr uint32_t kFly = 16;
+        for (uint32_t i0 = 0; i0 < cnt; i0 += kFly) {
+          uint32_t p[kFly], old[kFly];
 #pragma unroll
-        for (int t = 0; t < kWalkBatch; ++t) c[t] = p[t] != ~0ull ? outu[p[t]] : 0u;
-#pragma unroll
-        for (int t = 0; t < kWalkBatch; ++t) {
-          if (p[t] == ~0ull) continue;
-          if (c[t] == 1u) {   // (only this record names the coordinate: nobody else touches it)
-            out[p[t]] = v[t];
-          } else {
-            const uint32_t idx = atomicAdd(cl.count, 1u);
-            if (idx < kCollide) {
-              cl.pos[idx] = (uint32_t)p[t]; cl.val[idx] = v[t]; cl.msg[idx] = k;
+          for (uint32_t j = 0; j < kFly; ++j) {
+            old[j] = 0;
+            if (i0 + j < cnt) {
+              p[j] = rpos[(i0 + j) * 64 + lane];
+              old[j] = atomicOr(&s.seen[p[j] >> 5], 1u << (p[j] & 31u));
+              lpos[at + i0 + j] = p[j];
+              lval[at + i0 + j] = __float_as_uint(rval[(i0 + j) * 64 + lane]);
             }
+          }
+#pragma unroll
+          for (uint32_t j = 0; j < kFly; ++j) {
+            if (i0 + j < cnt && (old[j] >> (p[j] & 31u)) & 1u)
+              atomicOr(&s.multi[p[j] >> 5], 1u << (p[j] & 31u));
           }
         }
       }
-    });
+      __syncthreads();
+    }
     // the stretch ends where the next one starts, at the position the list names
-    if (ok && !last_stretch) ok = bitpos == stop && pos == sr.list[2 * r + 1];
+    if (staged) bitpos = bit0 + at_bit;
+    if (mine && ok && !last_stretch) ok = bitpos == stop && at_pos == pos_end;
     if (!ok) flag_corrupt(a.status);
+    __syncthreads();
   }
 }
 
-__global__ __launch_bounds__(1024) void k_gen_resolve(DecodeArgs a, float* acc, uint8_t* lists) {
+__device__ __forceinline__ float updated(const DecodeArgs& a, float x, float sum) {
+  return a.step ? fmaf(-a.c, sum, x) : x + sum;
+}
+
+__global__ __launch_bounds__(256) void k_sparse_apply(DecodeArgs a, uint32_t* area, uint8_t* lists) {
+  if (*a.status != 0) return;
+  const uint64_t b = blockIdx.x;
+  const uint32_t k = blockIdx.y;
+  const CollideList cl = collide_list(lists, b);
+  if (*cl.overflow) return;
+  const uint64_t base = b * (uint64_t)a.d;
+  const uint32_t m = (uint32_t)min((uint64_t)a.d, a.n - base);
+  const SparseArea s = sparse_area(area, base, m, a.K);
+  const uint32_t n = s.count[k];
+  const uint32_t* const lpos = s.pos(k);
+  const uint32_t* const lval = s.val(k);
+  float* const x = a.x + base;
+  constexpr uint32_t kU = 2;
+  const uint32_t step = 256u * gridDim.z;
+  for (uint32_t i0 = blockIdx.z * 256u + threadIdx.x; i0 < n; i0 += kU * step) {
+    uint32_t p[kU], bits[kU];
+    float v[kU], old[kU];
+#pragma unroll
+    for (uint32_t j = 0; j < kU; ++j) {
+      const uint32_t i = min(i0 + j * step, n - 1u);
+      p[j] = lpos[i];
+      v[j] = __uint_as_float(lval[i]);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kU; ++j) { bits[j] = s.multi[p[j] >> 5]; old[j] = x[p[j]]; }
+#pragma unroll
+    for (uint32_t j = 0; j < kU; ++j) {
+      if (i0 + j * step >= n) continue;
+      if (((bits[j] >> (p[j] & 31u)) & 1u) == 0) {   // (only this record names the coordinate)
+        x[p[j]] = updated(a, old[j], v[j]);
+      } else {
+        const uint32_t idx = atomicAdd(cl.count, 1u);
+        if (idx < kCollide) { cl.pos[idx] = p[j]; cl.val[idx] = v[j]; cl.msg[idx] = k; }
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_sparse_resolve(DecodeArgs a, uint32_t* area, uint8_t* lists) {
   if (*a.status != 0) return;
   __shared__ uint32_t bad;
   __shared__ StringRef refs[QSGD_MAX_PEERS];
   __shared__ uint32_t lpos[kCollide];
   __shared__ float lval[kCollide];
   __shared__ uint8_t lk[kCollide];
+  constexpr int kHashBits = 11;
+  __shared__ uint32_t head[1 << kHashBits], next[kCollide];
   const uint64_t b = blockIdx.x;
   const uint64_t base = b * (uint64_t)a.d;
-  const uint64_t m = min((uint64_t)a.d, a.n - base);
-  float* const out = acc + base;
+  const uint32_t m = (uint32_t)min((uint64_t)a.d, a.n - base);
+  float* const x = a.x + base;
+  for (uint32_t i = threadIdx.x; i < (1u << kHashBits); i += blockDim.x) head[i] = 0xFFFFFFFFu;
   const CollideList cl = collide_list(lists, b);
+  const bool overflow = *cl.overflow != 0;
   const uint32_t L = *cl.count;
-  if (threadIdx.x == 0) bad = 0;
-  __syncthreads();
-  if (L > kCollide) {
-    for (uint64_t p = threadIdx.x; p < m; p += blockDim.x) out[p] = 0.f;
+  if (overflow || L > kCollide) {
+    // (the messages parsed before; coordinates that `apply` has updated already are told by
+    // their bits, before the area becomes the accumulator)
+    const SparseArea s = sparse_area(area, base, m, a.K);
+    float* const acc = reinterpret_cast<float*>(area) + base;
+    if (threadIdx.x == 0) bad = 0;
     __syncthreads();
-    if (!open_strings(a, b, refs, &bad) || !parse_in_turns(a, refs, m, out, &bad)) {
-      if (threadIdx.x == 0) flag_corrupt(a.status);
+    if (!overflow) {
+      // the collision list alone was too short: the coordinates in `multi` remain
+      for (uint32_t p0 = 0; p0 < m; p0 += 32u * 1024u) {
+        const uint32_t w = p0 / 32u + threadIdx.x;
+        uint32_t bits = w < (m + 31u) / 32u ? s.multi[w] : 0u;
+        while (bits) {
+          const uint32_t p = w * 32u + (uint32_t)__ffs((int)bits) - 1u;
+          bits &= bits - 1u;
+          float sum = 0.f;
+          for (uint32_t k = 0; k < a.K; ++k) {
+            const uint32_t* const q = s.pos(k);
+            const uint32_t n = s.count[k];
+            for (uint32_t i = 0; i < n; ++i)
+              if (q[i] == p) { sum += __uint_as_float(s.val(k)[i]); break; }
+          }
+          x[p] = updated(a, x[p], sum);
+        }
+      }
+      return;
     }
+    for (uint32_t p = threadIdx.x; p < m; p += blockDim.x) acc[p] = 0.f;
+    __syncthreads();
+    if (!open_strings(a, b, refs, &bad) || !parse_in_turns(a, refs, m, acc, &bad)) {
+      if (threadIdx.x == 0) flag_corrupt(a.status);
+      return;
+    }
+    for (uint32_t p = threadIdx.x; p < m; p += blockDim.x) x[p] = updated(a, x[p], acc[p]);
     return;
   }
   for (uint32_t e = threadIdx.x; e < L; e += blockDim.x) {
     lpos[e] = cl.pos[e]; lval[e] = cl.val[e]; lk[e] = (uint8_t)cl.msg[e];
   }
   __syncthreads();
+  // entries of one coordinate hang on one chain
+  for (uint32_t e = threadIdx.x; e < L; e += blockDim.x)
+    next[e] = atomicExch(&head[(lpos[e] * 0x9E3779B9u) >> (32 - kHashBits)], e);
+  __syncthreads();
   // (a message names a coordinate at most once: the terms of p are found in message order
-  // by looking for the lowest message above the last one, terms + 1 scans of the list)
+  // by looking for the lowest message above the last one, terms + 1 walks along the chain)
   for (uint32_t e = threadIdx.x; e < L; e += blockDim.x) {
     const uint32_t p = lpos[e];
+    const uint32_t first = head[(p * 0x9E3779B9u) >> (32 - kHashBits)];
     float sum = 0.f;
     int last = -1;
     for (;;) {
       uint32_t best = 0xFFFFFFFFu;
       float bestv = 0.f;
-#pragma unroll 4
-      for (uint32_t j = 0; j < L; ++j) {
+      for (uint32_t j = first; j != 0xFFFFFFFFu; j = next[j]) {
         const uint32_t kj = lk[j];
         if (lpos[j] == p && (int)kj > last && kj < best) { best = kj; bestv = lval[j]; }
       }
@@ -889,8 +1059,15 @@ __global__ __launch_bounds__(1024) void k_gen_resolve(DecodeArgs a, float* acc, 
       sum += bestv;
       last = (int)best;
     }
-    if (last >= 0) out[p] = sum;
+    if (last >= 0) x[p] = updated(a, x[p], sum);
   }
+}
+
+// What adding a sum of +0 does to the coordinates that no message names: -0 becomes +0.
+__global__ __launch_bounds__(256) void k_plus_zero(DecodeArgs a) {
+  if (*a.status != 0) return;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < a.n; i += (uint64_t)gridDim.x * 256)
+    if (__float_as_uint(a.x[i]) == 0x80000000u) a.x[i] = 0.f;
 }
 
 __global__ __launch_bounds__(256) void k_gen_apply(DecodeArgs a, const float* acc) {
@@ -971,15 +1148,18 @@ hipError_t launch_gen_parse(const DecodeArgs& a, float* acc, bool entries, hipSt
   }
   return hipGetLastError();
 }
-// lists: a.nb x kCollideBytes of workspace behind the accumulator.
-hipError_t launch_gen_parse_together(const DecodeArgs& a, float* acc, uint8_t* lists,
-                                     hipStream_t st) {
-  hipLaunchKernelGGL(k_gen_zero_lists, dim3((a.nb + 255) / 256), dim3(256), 0, st, lists,
-                     (uint64_t)a.nb);
-  const dim3 grid(a.nb, a.K);
-  hipLaunchKernelGGL((k_gen_walk<false>), grid, dim3(256), 0, st, a, acc, lists);
-  hipLaunchKernelGGL((k_gen_walk<true>), grid, dim3(256), 0, st, a, acc, lists);
-  hipLaunchKernelGGL(k_gen_resolve, dim3(a.nb), dim3(1024), 0, st, a, acc, lists);
+// area: n words; lists: a.nb x kCollideBytes behind it; chunks: wavefronts per string.
+hipError_t launch_sparse_long(const DecodeArgs& a, uint32_t* area, uint8_t* lists, uint32_t cus,
+                              uint32_t chunks, hipStream_t st) {
+  const uint64_t clear = (uint64_t)a.nb * (2u * ((a.d + 31u) >> 5) + a.K);
+  const uint64_t most = (uint64_t)cus * 32;
+  const uint32_t blocks = (uint32_t)((clear + 255) / 256 < most ? (clear + 255) / 256 : most);
+  hipLaunchKernelGGL(k_sparse_clear, dim3(blocks), dim3(256), 0, st, a, area, lists);
+  hipLaunchKernelGGL(k_sparse_list, dim3(a.nb, a.K, chunks), dim3(64), 0, st, a, area, lists);
+  if (!a.step || std::signbit(a.c))
+    hipLaunchKernelGGL(k_plus_zero, dim3(cus * 32), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_sparse_apply, dim3(a.nb, a.K, 4 * chunks), dim3(256), 0, st, a, area, lists);
+  hipLaunchKernelGGL(k_sparse_resolve, dim3(a.nb), dim3(1024), 0, st, a, area, lists);
   return hipGetLastError();
 }
 hipError_t launch_gen_apply(const DecodeArgs& a, const float* acc, uint32_t blocks, hipStream_t st) {

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "qsgd.h"
+#include "qsgd_device.hpp"
 
 namespace qsgd {
 
@@ -162,11 +163,35 @@ struct DecodeArgs {
   uint32_t rec;          // record slots per string (message-by-message apply)
   uint32_t kloop;        // 1: records are applied message by message (dense messages)
   uint32_t q16;          // 1: 16-bit records (counting apply, s <= 4)
-  uint32_t together;     // 1: long buckets, all messages read at once (few shared coordinates)
   // fixed width
   uint32_t fixed_bits;
   uint32_t fixed_words_full;
 };
+
+// One thread per message (the first workgroup of a launch, at least K threads): resets the
+// status word; the header must describe the same code as the call.
+__device__ __forceinline__ void check_headers(const DecodeArgs& a) {
+  const uint32_t k = threadIdx.x;
+  if (k == 0) *a.status = 0;
+  __syncthreads();
+  if (k >= a.K) return;
+  bool ok = a.msg_words[k] >= (uint64_t)H_WORDS + a.table_words;
+  if (ok) {
+    const uint32_t* h = a.msgs[k];
+    const uint64_t pw = h[H_PW_LO] | ((uint64_t)h[H_PW_HI] << 32);
+    ok = h[H_MAGIC] == kMagic && h[H_VERSION] == a.version && h[H_CODE] == a.code &&
+         h[H_NORM] == a.norm_mode && h[H_S] == a.s && h[H_D_LO] == a.d && h[H_D_HI] == 0 &&
+         h[H_N_LO] == (uint32_t)a.n && h[H_N_HI] == (uint32_t)(a.n >> 32) &&
+         h[H_NB_LO] == a.nb && h[H_NB_HI] == 0 && h[H_STATUS] == 0 &&
+         (uint64_t)H_WORDS + a.table_words + pw <= a.msg_words[k];
+    if (ok && a.version == 2) {   // tensor-aware: the strings and the raw values fill the payload
+      const uint64_t strings = a.table_words ? (uint64_t)h[H_WORDS + a.nb]
+                                             : (uint64_t)a.nb * a.fixed_words_full;
+      ok = strings + a.raw_words == pw;
+    }
+  }
+  if (!ok) flag_corrupt(a.status);
+}
 
 // Raw section of tensor-aware messages: the small tensors in pieces of kRawPiece values.
 constexpr uint32_t kRawPiece = 1024;
@@ -260,12 +285,13 @@ hipError_t launch_gen_fill(const GenArgs& a, uint32_t blocks, hipStream_t st);
 hipError_t launch_gen_place(const GenArgs& a, hipStream_t st);
 hipError_t launch_gen_zero(float* p, uint64_t n, uint32_t blocks, hipStream_t st);
 hipError_t launch_gen_parse(const DecodeArgs& a, float* acc, bool entries, hipStream_t st);
-// Long buckets read with all messages at once: records at coordinates that several
-// messages hit go to a list per bucket (a count, then kCollide x (position, value, message)).
+// Long buckets of sparse messages, straight to the touched coordinates of x (a.c finite):
+// records at coordinates that several messages hit go to a list per bucket (counters, then
+// kCollide x (position, value, message)).  Includes the header check.
 constexpr uint32_t kCollide = 1024;
 constexpr uint32_t kCollideBytes = 256 + 12 * kCollide;
-hipError_t launch_gen_parse_together(const DecodeArgs& a, float* acc, uint8_t* lists,
-                                     hipStream_t st);
+hipError_t launch_sparse_long(const DecodeArgs& a, uint32_t* area, uint8_t* lists, uint32_t cus,
+                              uint32_t chunks, hipStream_t st);
 hipError_t launch_gen_apply(const DecodeArgs& a, const float* acc, uint32_t blocks, hipStream_t st);
 hipError_t launch_gen_decode_fixed(const DecodeArgs& a, uint32_t blocks, hipStream_t st);
 
