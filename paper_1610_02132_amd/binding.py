@@ -138,22 +138,37 @@ def _load():
     return L
 
 
+_raw_stream = None   # torch's current stream of the current device, as a raw handle
+
+
 def _stream(stream):
     """A torch.cuda.Stream, a raw handle (int) or None (torch's current stream)."""
+    global _raw_stream
     if stream is None:
-        import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _raw_stream is None:
+            # torch.cuda.current_stream() makes a Stream object for its handle: 2.7 us of a
+            # call's 12; torch's own code generators ask for the handle itself (0.1 us)
+            import torch
+            get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            dev = getattr(torch._C, "_cuda_getDevice", None)
+            if get is not None and dev is not None:
+                torch.cuda.init()
+                _raw_stream = lambda: get(dev())
+            else:
+                _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+        return _raw_stream()
     if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _dev(t, what: str):
+    """(address, bytes) of a device tensor; (None, 0) for None."""
     if t is None:
-        return C.c_void_p(0), 0
+        return None, 0
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{what} must be a contiguous device tensor")
-    return C.c_void_p(t.data_ptr()), t.numel() * t.element_size()
+    return t.data_ptr(), t.nbytes
 
 
 def qsgd_version() -> int:
@@ -191,12 +206,12 @@ def qsgd_encode(p: Params, g, msg, workspace, stream=None) -> None:
 
 def _msgs(msgs, msg_bytes):
     K = len(msgs)
-    ptrs = (C.c_void_p * K)()
-    sizes = (C.c_size_t * K)()
-    for k, m in enumerate(msgs):
-        p, nbytes = _dev(m, "message")
-        ptrs[k] = p.value
-        sizes[k] = nbytes if msg_bytes is None else min(nbytes, int(msg_bytes[k]))
+    each = [_dev(m, "message") for m in msgs]
+    ptrs = (C.c_void_p * K)(*[e[0] for e in each])
+    if msg_bytes is None:
+        sizes = (C.c_size_t * K)(*[e[1] for e in each])
+    else:
+        sizes = (C.c_size_t * K)(*[min(e[1], int(msg_bytes[k])) for k, e in enumerate(each)])
     return ptrs, sizes, K
 
 
@@ -447,12 +462,12 @@ def qsgd_pipeline_step(pipe: Pipeline, p: Params, chunk_elems: int, grads, eta: 
         raise ValueError("msgs must hold 2*K buffers")
     if x.numel() != p.n or any(g.numel() != p.n for g in grads):
         raise ValueError("x and the gradients must hold n float32")
-    gptr = (C.c_void_p * K)(*[_dev(g, "g")[0].value for g in grads])
+    gptr = (C.c_void_p * K)(*[_dev(g, "g")[0] for g in grads])
     mptr = (C.c_void_p * (2 * K))()
     cap = None
     for i, m in enumerate(msgs):
         mp, nbytes = _dev(m, "message")
-        mptr[i] = mp.value
+        mptr[i] = mp
         cap = nbytes if cap is None else min(cap, nbytes)
     xp, _ = _dev(x, "x")
     ep, ebytes = _dev(enc_workspace, "enc_workspace")
