@@ -537,9 +537,11 @@ size_t qsgd_encode_workspace_bytes(const qsgd_params* p, size_t msg_capacity) {
   return (size_t)std::min<uint64_t>(worst, (bytes + 255) & ~(uint64_t)255);
 }
 
+// `batch`, `K`: fixed width, d <= 1024: the first of K gradients whose pointers are in `batch`.
 static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t index_base,
                        const float* g_dev, void* msg_dev, size_t msg_capacity,
-                       void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
+                       void* workspace_dev, size_t workspace_bytes, void* hip_stream,
+                       const EncodeBatch* batch = nullptr, uint32_t K = 1) {
   Geometry g;
   int rc = layout_geometry(p, L, g);
   if (rc) return rc;
@@ -672,7 +674,9 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
     const uint32_t teams = (groups + a.bper - 1) / a.bper;
     {
       ScopedTiming tm("encode_bucket", st);
-      if (launch_encode_fixed_small(a, lpb, cp, teams, st) != hipSuccess) return QSGD_ERR_HIP;
+      const hipError_t err = batch ? launch_encode_fixed_small_batch(a, *batch, K, lpb, cp, teams, st)
+                                   : launch_encode_fixed_small(a, lpb, cp, teams, st);
+      if (err != hipSuccess) return QSGD_ERR_HIP;
     }
     if (L && L->R) {
       ScopedTiming tm("encode_raw", st);
@@ -707,6 +711,35 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
   }
   return QSGD_OK;
 }
+
+}  // extern "C"
+
+int qsgd::encode_slices(const qsgd_params* p, uint64_t index_base, const float* const* g_dev,
+                        uint32_t K, void* const* msg_dev, size_t msg_capacity,
+                        void* workspace_dev, size_t workspace_bytes, hipStream_t st) {
+  Geometry g;
+  int rc = make_geometry(p, g);
+  if (rc) return rc;
+  if (g.code == QSGD_CODE_FIXED && g.bucket_path() && g.d <= 1024 && K > 1) {
+    EncodeBatch batch;
+    for (uint32_t k = 0; k < K; ++k) {
+      batch.g[k] = g_dev[k];
+      batch.msg[k] = static_cast<uint32_t*>(msg_dev[k]);
+    }
+    return encode_impl(p, nullptr, index_base, g_dev[0], msg_dev[0], msg_capacity, workspace_dev,
+                       workspace_bytes, st, &batch, K);
+  }
+  qsgd_params pk = *p;
+  for (uint32_t k = 0; k < K; ++k) {
+    pk.stream_id = p->stream_id + k;
+    rc = encode_impl(&pk, nullptr, index_base, g_dev[k], msg_dev[k], msg_capacity, workspace_dev,
+                     workspace_bytes, st);
+    if (rc) return rc;
+  }
+  return QSGD_OK;
+}
+
+extern "C" {
 
 // ---- scratch that is part of the library image, for callers that cannot allocate --------
 // One array per GPU the library runs on, held until the process ends.  Host code never

@@ -12,6 +12,8 @@
 // (exclusive sum over at most a few thousand team totals): no team ever waits
 // for another one.  Fixed-width strings have closed-form offsets and go straight
 // to the message.
+#include <type_traits>
+
 #include "qsgd_device.hpp"
 #include "qsgd_encode_wave.hpp"
 #include "qsgd_kernels.hpp"
@@ -356,8 +358,7 @@ __global__ __launch_bounds__(64 * TW)
 // the per-bucket work (scale reduction, square root, divide) is shared by the
 // buckets that ride in one wavefront.
 template <int LPB, int CP, int B>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(QSGD_FS_WAVES)))
-void k_encode_fixed_small(EncodeArgs a) {
+__device__ __forceinline__ void encode_fixed_small(const EncodeArgs& a) {
   constexpr int NB = 64 / LPB;             // buckets per wavefront pass
   constexpr uint32_t kStep = LPB * 4;      // values one pass of the bucket's lanes covers
   constexpr uint32_t fmax = (1u << B) - 1u;
@@ -532,6 +533,25 @@ void k_encode_fixed_small(EncodeArgs a) {
   }
 }
 
+template <int LPB, int CP, int B>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(QSGD_FS_WAVES)))
+void k_encode_fixed_small(EncodeArgs a) {
+  encode_fixed_small<LPB, CP, B>(a);
+}
+
+// The K gradients of a double-buffered pass's chunk in one launch: a chunk of 16M values alone is
+// 16 thousand wavefronts, four rounds of what the machine holds, and ran at 3.7 TB/s; FIGURE.
+template <int LPB, int CP, int B>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(QSGD_FS_WAVES)))
+void k_encode_fixed_small_batch(EncodeArgs a, EncodeBatch batch) {
+  const uint32_t k = blockIdx.y;
+  a.g = batch.g[k];
+  a.header = batch.msg[k];
+  a.payload = batch.msg[k] + H_WORDS;
+  a.stream_id += k;
+  encode_fixed_small<LPB, CP, B>(a);
+}
+
 // Moves each team's region to its place in the message: base_j = words of the teams
 // before j.  A workgroup has `tpb` consecutive teams, a wavefront one of them at a time;
 // it adds up the totals before its first team itself (at most kMaxTeams words, 16 bytes a
@@ -647,26 +667,42 @@ hipError_t launch_encode_bucket(const EncodeArgs& a, uint32_t code, int tw, int 
   return hipErrorInvalidValue;
 }
 
-template <int LPB, int CP>
-static hipError_t launch_fixed_small_b(const EncodeArgs& a, uint32_t teams, hipStream_t st) {
-  const dim3 grid(teams), block(64);
-  switch (a.fixed_bits) {
-    case 2: hipLaunchKernelGGL((k_encode_fixed_small<LPB, CP, 2>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_encode_fixed_small<LPB, CP, 4>), grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL((k_encode_fixed_small<LPB, CP, 8>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_encode_fixed_small<LPB, CP, 16>), grid, block, 0, st, a); break;
-  }
-  return hipGetLastError();
+// f(lanes per bucket, float4 per lane, field bits), all as compile-time constants
+template <class F>
+static void fixed_small_shape(int lpb, int cp, uint32_t bits, F&& f) {
+  auto field = [&](auto l, auto c) {
+    switch (bits) {
+      case 2: f(l, c, std::integral_constant<int, 2>()); break;
+      case 4: f(l, c, std::integral_constant<int, 4>()); break;
+      case 8: f(l, c, std::integral_constant<int, 8>()); break;
+      default: f(l, c, std::integral_constant<int, 16>()); break;
+    }
+  };
+  using std::integral_constant;
+  if (lpb == 16 && cp <= 1) field(integral_constant<int, 16>(), integral_constant<int, 1>());
+  else if (lpb == 16 && cp <= 2) field(integral_constant<int, 16>(), integral_constant<int, 2>());
+  else if (lpb == 16) field(integral_constant<int, 16>(), integral_constant<int, 4>());
+  else if (lpb == 32) field(integral_constant<int, 32>(), integral_constant<int, 4>());
+  else field(integral_constant<int, 64>(), integral_constant<int, 4>());
 }
 
 // d <= 1024, d % 4 == 0; a.bper counts groups of 64/lpb buckets per team.
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,
                                      hipStream_t st) {
-  if (lpb == 16 && cp <= 1) return launch_fixed_small_b<16, 1>(a, teams, st);
-  if (lpb == 16 && cp <= 2) return launch_fixed_small_b<16, 2>(a, teams, st);
-  if (lpb == 16) return launch_fixed_small_b<16, 4>(a, teams, st);
-  if (lpb == 32) return launch_fixed_small_b<32, 4>(a, teams, st);
-  return launch_fixed_small_b<64, 4>(a, teams, st);
+  fixed_small_shape(lpb, cp, a.fixed_bits, [&](auto l, auto c, auto b) {
+    hipLaunchKernelGGL((k_encode_fixed_small<decltype(l)::value, decltype(c)::value, decltype(b)::value>),
+                       dim3(teams), dim3(64), 0, st, a);
+  });
+  return hipGetLastError();
+}
+
+hipError_t launch_encode_fixed_small_batch(const EncodeArgs& a, const EncodeBatch& batch, uint32_t K,
+                                           int lpb, int cp, uint32_t teams, hipStream_t st) {
+  fixed_small_shape(lpb, cp, a.fixed_bits, [&](auto l, auto c, auto b) {
+    hipLaunchKernelGGL((k_encode_fixed_small_batch<decltype(l)::value, decltype(c)::value, decltype(b)::value>),
+                       dim3(teams, K), dim3(64), 0, st, a, batch);
+  });
+  return hipGetLastError();
 }
 
 hipError_t launch_encode_compact(const CompactArgs& a, hipStream_t st) {

@@ -123,6 +123,13 @@ struct EncodeArgs {
   uint64_t fixed_payload_words;
 };
 
+// Several peers' gradients of one geometry in one launch (blockIdx.y = peer): what differs from
+// the EncodeArgs they share; peer k draws with stream_id + k.
+struct EncodeBatch {
+  const float* g[QSGD_MAX_PEERS];
+  uint32_t* msg[QSGD_MAX_PEERS];
+};
+
 struct CompactArgs {
   const uint32_t* staging;
   uint64_t region_words;
@@ -251,6 +258,11 @@ struct GenArgs {
 int validate_encode(const qsgd_params* p, uint64_t index_base, size_t msg_capacity,
                     size_t workspace_bytes);
 int validate_decode(const qsgd_params* p, uint32_t K, size_t workspace_bytes);
+// qsgd_encode_slice for K gradients of one geometry, peer k with stream_id + k; one launch where
+// the encoder keeps nothing in the workspace, else one after the other.
+int encode_slices(const qsgd_params* p, uint64_t index_base, const float* const* g_dev, uint32_t K,
+                  void* const* msg_dev, size_t msg_capacity, void* workspace_dev,
+                  size_t workspace_bytes, hipStream_t st);
 
 hipError_t launch_encode_bucket(const EncodeArgs& a, uint32_t code, int tw, int cpw,
                                 uint32_t teams, size_t lds, hipStream_t st);
@@ -260,6 +272,8 @@ hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, ui
 hipError_t launch_encode_compact(const CompactArgs& a, hipStream_t st);
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,
                                      hipStream_t st);
+hipError_t launch_encode_fixed_small_batch(const EncodeArgs& a, const EncodeBatch& batch, uint32_t K,
+                                           int lpb, int cp, uint32_t teams, hipStream_t st);
 hipError_t launch_write_empty(uint32_t* header, uint32_t* table, uint32_t code, uint32_t norm,
                               uint32_t s, uint64_t d, uint32_t stream_id, uint32_t iteration,
                               hipStream_t st);

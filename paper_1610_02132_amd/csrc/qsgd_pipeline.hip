@@ -95,6 +95,7 @@ int qsgd_pipeline_step(qsgd_pipeline* pl, const qsgd_params* p, uint64_t chunk_e
   const float c_eta = eta;   // every chunk applies eta / K to its own slice
   size_t sizes[QSGD_MAX_PEERS];
   const void* set[QSGD_MAX_PEERS];
+  const float* slice[QSGD_MAX_PEERS];
   for (uint32_t k = 0; k < K; ++k) sizes[k] = msg_capacity;
   uint64_t chunk = 0;
   for (uint64_t off = 0; off < p->n; off += chunk_elems, ++chunk) {
@@ -105,17 +106,16 @@ int qsgd_pipeline_step(qsgd_pipeline* pl, const qsgd_params* p, uint64_t chunk_e
     if (chunk >= 2 && hipStreamWaitEvent(pl->enc, pl->decoded[sb], 0) != hipSuccess)
       return QSGD_ERR_HIP;
     for (uint32_t k = 0; k < K; ++k) {
-      pc.stream_id = p->stream_id + k;
-      const int rc = qsgd_encode_slice(&pc, off, g_dev[k] + off, msg_dev[sb * K + k], msg_capacity,
-                                       enc_workspace_dev, workspace_bytes, pl->enc);
-      if (rc) return rc;
+      slice[k] = g_dev[k] + off;
       set[k] = msg_dev[sb * K + k];
     }
+    int rc = qsgd::encode_slices(&pc, off, slice, K, msg_dev + sb * K, msg_capacity,
+                                 enc_workspace_dev, workspace_bytes, pl->enc);
+    if (rc) return rc;
     if (hipEventRecord(pl->encoded[sb], pl->enc) != hipSuccess ||
         hipStreamWaitEvent(pl->dec, pl->encoded[sb], 0) != hipSuccess)
       return QSGD_ERR_HIP;
-    pc.stream_id = p->stream_id;
-    const int rc = qsgd_sgd_step(&pc, set, sizes, K, c_eta, x_dev + off, dec_workspace_dev,
+    rc = qsgd_sgd_step(&pc, set, sizes, K, c_eta, x_dev + off, dec_workspace_dev,
                                  workspace_bytes, pl->dec);
     if (rc) return rc;
     if (hipEventRecord(pl->decoded[sb], pl->dec) != hipSuccess) return QSGD_ERR_HIP;
