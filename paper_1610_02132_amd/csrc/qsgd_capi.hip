@@ -167,6 +167,32 @@ struct EncodePlan {
   uint64_t ws_bytes;
 };
 
+// About how many words a full bucket's string has: the levels of normal values, mean
+// magnitude 0.8 of their rms (Elias codes).
+uint32_t string_words(const Geometry& g) {
+  const double d = (double)g.d;
+  const double t = 0.8 * g.s / (g.norm == QSGD_NORM_MAX ? std::sqrt(2.0 * std::log(d + 2.0)) : std::sqrt(d));
+  const double level = omega_len_host((uint64_t)t + 1), share = 1.0 - std::exp(-t);
+  const double bits = g.code == QSGD_CODE_DENSE
+                          ? d * (1.0 + level)
+                          : d * share * (1.0 + level + omega_len_host((uint64_t)(1.0 / share)));
+  return 1 + (uint32_t)(bits / 32.0);
+}
+
+// Whether a lane for every word of the strings (split decoder) beats a lane for every string.
+// With few strings the latter takes as long as its longest string, 0.64 us per word (tile decoder) or
+// 1.7 us (ring decoder, sparse strings), measured from 5 to 470 words; the former takes some
+// 12 us more than a launch does and works off about 10 thousand words per us (6 thousand of
+// sparse strings, whose records need the general reader).  Step, us, lane per string / split:
+//   d = 512, s = 16 (37 words): 78 strings 33 / 18, 4096 strings 32 / 24, 16384 strings 34 / 62
+//   d = 8192, s = 40 (466 words): 4 strings 294 / 42, 4096 strings 347 / 192, 8192 strings 342 / 382
+//   d = 8192, s = 4 (102 words, ring): 4 strings 170 / 30, 8192 strings 347 / 170
+bool split_pays(const Geometry& g, uint32_t K, bool tile) {
+  const double words = string_words(g), strings = (double)g.nb * K;
+  if (tile) return 12.0 + strings * words / 10000.0 < 5.0 + 0.64 * words;
+  return 17.0 + strings * words / 6000.0 < 3.0 + 1.7 * words;
+}
+
 // Dense strings: the share of nonzero levels grows like s / sqrt(d) (Lemma 3.1 (iii)); with the
 // largest value as scale it is larger still, and Code'_s codes every coordinate.
 bool dense_strings(const Geometry& g) {
@@ -354,6 +380,29 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     if (launch_raw_apply(a, raw_args(g, L), st) != hipSuccess) return QSGD_ERR_HIP;
   }
   if (g.nb == 0) return QSGD_OK;
+  const bool bytes = g.code != QSGD_CODE_FIXED && g.d <= kMaxBucketFast && g.s <= 127;   // levels fit a byte
+  if (bytes && split_pays(g, K, a.kloop || g.d % 4)) {
+    ScopedTiming tm("decode_elias", st);
+    return launch_decode_split(a, cus, string_words(g), st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
+  }
+  if (bytes && (a.kloop || g.d % 4)) {
+    // dense strings, and bucket sizes that the ring decoder's loads do not fit: the tile
+    // decoder, one lane per string
+    uint32_t gw = 1;  // buckets per wavefront: a power of two, gw * K lanes
+    while (gw * 2 * K <= 64) gw *= 2;
+    while (gw > 1 && (g.nb + gw - 1) / gw < (uint64_t)cus * 4) gw /= 2;
+    a.gw = gw;
+    const uint32_t tasks = (uint32_t)((g.nb + gw - 1) / gw);
+    // as many wavefronts per compute unit as give every one of them the same number of
+    // groups; at least four, one per SIMD, share the work of loading the table
+    const uint32_t per_cu = (tasks + cus - 1) / cus, most = tile_max_waves(g.code);
+    const uint32_t rounds = (per_cu + most - 1) / most;
+    const uint32_t waves = std::max(4u, (per_cu + rounds - 1) / rounds);
+    const uint32_t blocks = std::min(cus, (tasks + waves - 1) / waves);
+    ScopedTiming tm("decode_elias", st);
+    if (launch_decode_tile(a, blocks, waves, st) != hipSuccess) return QSGD_ERR_HIP;
+    return QSGD_OK;
+  }
   if (!g.bucket_path()) {
     const uint32_t blocks = (uint32_t)std::min<uint64_t>((g.n + 255) / 256, (uint64_t)cus * 32);
     ScopedTiming tm("decode_general", st);
@@ -376,23 +425,6 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     return QSGD_OK;
   }
   // Elias codes: one lane per string.
-  if (a.kloop && g.s <= 127) {
-    // dense strings whose levels fit a byte: the tile decoder
-    uint32_t gw = 1;  // buckets per wavefront: a power of two, gw * K lanes
-    while (gw * 2 * K <= 64) gw *= 2;
-    while (gw > 1 && (g.nb + gw - 1) / gw < (uint64_t)cus * 4) gw /= 2;
-    a.gw = gw;
-    const uint32_t tasks = (uint32_t)((g.nb + gw - 1) / gw);
-    // as many wavefronts per compute unit as give every one of them the same number of
-    // groups; at least four, one per SIMD, share the work of loading the table
-    const uint32_t per_cu = (tasks + cus - 1) / cus, most = tile_max_waves(g.code);
-    const uint32_t rounds = (per_cu + most - 1) / most;
-    const uint32_t waves = std::max(4u, (per_cu + rounds - 1) / rounds);
-    const uint32_t blocks = std::min(cus, (tasks + waves - 1) / waves);
-    ScopedTiming tm("decode_elias", st);
-    if (launch_decode_tile(a, blocks, waves, st) != hipSuccess) return QSGD_ERR_HIP;
-    return QSGD_OK;
-  }
   const uint32_t win = (uint32_t)std::min<uint64_t>((g.d + 3) & ~(uint64_t)3, 256);
   const uint32_t winp = (win + kChunk - 1) / kChunk * kChunk;
   uint32_t gw = 1;  // buckets per wavefront: a power of two, gw * K lanes, gw * winp floats

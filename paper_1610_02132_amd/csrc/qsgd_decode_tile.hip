@@ -275,6 +275,10 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
     if (!open || (kSparse && np == np_end)) cur += kDoneFlag;
     const float my_scale = open ? __uint_as_float(first) / (float)s : 0.f;
     if (g < gw) *lds_at<float>(scales + 4u * (g * K4 + k)) = my_scale;
+    // Where a scale is not finite, a coordinate without a record must not get 0 * scale (with
+    // d % 4 != 0 in either code, as in the general path's sum of records).
+    const bool records_only = (kSparse || a.d % 4u != 0) &&
+        __builtin_amdgcn_ballot_w64(!(fabsf(my_scale) <= 3.402823466e+38f)) != 0;
     // windows that lie inside every one of gw buckets need no bounds
     const uint32_t m_min = gcount == gw ? wave_min_u32(g < gw ? m : 0xFFFFFFFFu) : 0u;
 
@@ -428,6 +432,18 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
             };
             auto word = [&](uint32_t j) { return *lds_at<uint32_t>(p + j * kRowBytes); };
             uint32_t kk = 0;
+            if (records_only) {
+              for (; kk < K; ++kk) {
+                const uint32_t w = word(0);
+                const float sc = *lds_at<float>(sp);
+                if ((int8_t)w) sum.x += sc * (float)(int)(int8_t)w;
+                if ((int8_t)(w >> 8)) sum.y += sc * (float)(int)(int8_t)(w >> 8);
+                if ((int8_t)(w >> 16)) sum.z += sc * (float)(int)(int8_t)(w >> 16);
+                if ((int8_t)(w >> 24)) sum.w += sc * (float)(int)(int8_t)(w >> 24);
+                p += kRowBytes;
+                sp += 4u;
+              }
+            }
             for (; kk + 4u <= K; kk += 4u) {
               const v4f s4 = *lds_at<v4f>(sp);
               const uint32_t w0 = word(0), w1 = word(1), w2 = word(2), w3 = word(3);

@@ -16,7 +16,8 @@
 // bucket and inside a bucket message after message (so every coordinate's sum has
 // the order k = 0, 1, ...); a last kernel applies the accumulator to x.  Buckets
 // above 8192 values carry a list of entry points behind their string and are read
-// by a workgroup, a thread per stretch; shorter ones by a thread per bucket.
+// by a workgroup, a thread per stretch; shorter ones by a thread per bucket (levels
+// above 127 only: the tile and split decoders take any bucket size up to 8192).
 #include <cmath>
 
 #include "qsgd_device.hpp"
@@ -634,7 +635,7 @@ __device__ __forceinline__ bool open_string(const DecodeArgs& a, uint32_t k, uin
   return true;
 }
 
-// Short buckets of the general path (d <= kEntryMinD, d not a multiple of 4): one thread
+// Short buckets of the general path (d <= kEntryMinD, d not a multiple of 4, s > 127): one thread
 // per bucket reads the K strings one after the other, so every coordinate receives its
 // terms in message order.
 __global__ __launch_bounds__(256) void k_gen_parse(DecodeArgs a, float* acc) {
