@@ -78,6 +78,9 @@ struct Geometry {
     return (nb - 1) * max_words(d) + max_words(bucket_len(nb - 1));
   }
   bool bucket_path() const { return n > 0 && d % 4 == 0 && d <= kMaxBucketFast; }
+  // Elias buckets of a size that no vector load fits: coded like those of the bucket path, in a
+  // workspace as large as the general path asks for
+  bool odd_bucket() const { return n > 0 && d % 4 != 0 && d <= kMaxBucketFast && code != QSGD_CODE_FIXED; }
 };
 
 // General path (any d): segments of kSeg values, workspace layout.
@@ -209,8 +212,17 @@ void plan_encode(const Geometry& g, uint64_t ws_avail, EncodePlan& pl) {
   // and sparse ones except where the ring's chunks of 256 fit the bucket better than the
   // direct coder's runs of 64 lanes x 4 or 8 values (20M values, s = 2: d = 512 43.7 and 41.1 us,
   // d = 600 49 and 55, d = 1024 36 and 42, d = 1028 70 and 54, d = 2048 53 and 44).
-  pl.direct = g.code != QSGD_CODE_FIXED && g.d <= 2048 &&
-              (dense_strings(g) || g.d <= 512 || g.d > 1024);
+  // Above 2048 values a wavefront reads its bucket's runs twice, and one wavefront to a bucket
+  // has to fill the machine; the other encoder has a team of wavefronts per bucket (30M values,
+  // d = 8192, s = 40: 117 and 89 us, 1M 20 and 36; Code'_s, s = 80: 74 and 84; 4M of d = 3000: 35 and
+  // 22; 9M of d = 3232, Code'_s: 46 and 36).  Buckets that no vector load fits have no other
+  // encoder but the general path (20M values, d = 443: 261 and 80 us, d = 41: 2250 and 113).
+  const bool sparse = g.code == QSGD_CODE_SPARSE;
+  if (g.code == QSGD_CODE_FIXED) pl.direct = false;
+  else if (g.d % 4 != 0) pl.direct = true;
+  else if (g.d <= 2048) pl.direct = dense_strings(g) || g.d <= 512 || g.d > 1024;
+  else pl.direct = dense_strings(g) && g.max_words(g.d) <= 4096 &&   // (LDS: eight wavefronts at least)
+                   nb >= cus * (g.d <= 4096 ? (sparse ? 2u : 8u) : (sparse ? 4u : 24u));
   // direct: the teams a compute unit holds at once, whole passes each; else persistent teams
   // well above what is resident
   pl.few = nb <= cus * 16;
@@ -598,7 +610,12 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
       return QSGD_ERR_HIP;
     return QSGD_OK;
   }
-  if (!g.bucket_path()) {
+  if (g.odd_bucket()) {
+    GenPlan gp;
+    plan_general(g, gp);
+    if (gp.nseg > 0x7FFFFFFFull) return QSGD_ERR_UNSUPPORTED;
+    if (workspace_bytes < kStatusBytes + kTotalsBytes + gp.enc_bytes) return QSGD_ERR_CAPACITY;
+  } else if (!g.bucket_path()) {
     GenPlan gp;
     plan_general(g, gp);
     if (gp.nseg > 0x7FFFFFFFull) return QSGD_ERR_UNSUPPORTED;

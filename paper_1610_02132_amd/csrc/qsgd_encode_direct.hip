@@ -1,4 +1,4 @@
-// Encode of Elias strings, d <= 2048: every lane codes its own values.
+// Encode of Elias strings (d <= 8192): every lane codes its own values.
 //
 // Compacting the nonzero levels before they are coded costs more than it saves unless they are
 // very rare.  Here a wavefront holds 64 / LPB buckets at once, LPB lanes each; a lane owns runs
@@ -7,14 +7,21 @@
 // lane's first one?), one look-up per value in a table in LDS that holds the whole code word
 // of (gap, sign, level), the run's code words joined in a 64-bit register, a prefix sum of the
 // lengths, and two or three ORs into the bucket's string in LDS.  The gap in front of a run's
-// first nonzero level may be beyond the table and is then coded by arithmetic; a run with a
-// level beyond it (32 and more), or of more than 64 bits, sends its wavefront through a small
-// general coder.
+// first nonzero level may be beyond the table and is then coded by arithmetic.  Levels of 32 to 63
+// and runs of more than 64 bits look up gap and level one by one and go out four values at a
+// time (where levels are expected to be high: LONG); a level beyond that sends its wavefront
+// through a small general coder.  Above d = 2048
+// a bucket's runs do not fit the registers: they are read twice, the second time from the caches.
 //
 // Bound by instruction issue: about 45 vector instructions per value and lane (of those Philox 10,
 // rounding 8, code word 10), 78% of the issue slots.  25.6M values, s = 16, d = 512: 60 us through
 // the survivor ring (about 100 instructions), 42 directly; Code'_s of the same data 62 -> 36 us.
-// A copy of the bytes would take 19 us.
+// A copy of the bytes would take 19 us.  Per encode, before and after: 57M values, d = 2124,
+// s = 23 (max scale) 351 -> 187 us; 35M values, d = 4996, s = 11 153 -> 79 us.  (Kept in
+// registers, 4 to 16 runs: 57M of d = 2124 689 us, of which most was the general coder, but also
+// 30M of d = 8192, s = 40 177 instead of 89.)  Bucket sizes that are no multiple of 4 pay a Philox
+// block per run and two selects per value: 20M values, d = 443, s = 11, 80 us, 261 on the general
+// path.
 #include "qsgd_device.hpp"
 #include "qsgd_encode_wave.hpp"
 #include "qsgd_kernels.hpp"
@@ -23,9 +30,14 @@ namespace qsgd {
 
 namespace {
 
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // Code word table: index gap * 64 + level * 2 + sign, entry (code << 8) | length; Code_s: gap 0
-// stands for sign and level alone, level 0 has length 0; Code'_s: gap 0 only.
-constexpr uint32_t kMaxGap = 64, kMaxLev = 32;
+// stands for sign and level alone, level 0 has length 0 (also at the kGuard gaps below 0, which
+// the zeros before a run's first nonzero level look up); Code'_s: gap 0 only.
+constexpr uint32_t kGuard = 7, kMaxGap = 57, kMaxLev = 32;
+// Elias code words of 1 .. kOmegas - 1, for longer runs of bits
+constexpr uint32_t kOmegas = 128;
 
 struct CodeLen { uint32_t code, len; };
 constexpr CodeLen omega_word(uint32_t k) {
@@ -40,14 +52,16 @@ constexpr CodeLen omega_word(uint32_t k) {
   return {code, len};
 }
 
-template <bool SPARSE> constexpr uint32_t code_entries() { return 2u * kMaxLev * (SPARSE ? kMaxGap : 1u); }
+template <bool SPARSE> constexpr uint32_t code_entries() { return 2u * kMaxLev * (SPARSE ? kGuard + kMaxGap : 1u); }
 template <bool SPARSE>
 struct alignas(16) CodeTable {
-  uint32_t e[code_entries<SPARSE>()];
-  constexpr CodeTable() : e() {
+  uint32_t e[code_entries<SPARSE>()], omega[kOmegas];
+  constexpr CodeTable() : e(), omega() {
+    for (uint32_t k = 1; k < kOmegas; ++k) omega[k] = omega_word(k).code << 8 | omega_word(k).len;
     for (uint32_t i = 0; i < code_entries<SPARSE>(); ++i) {
-      const uint32_t gap = i / (2 * kMaxLev), z = (i / 2) % kMaxLev, sign = i % 2;
-      if (SPARSE && z == 0) { e[i] = 0; continue; }
+      const uint32_t row = i / (2 * kMaxLev), z = (i / 2) % kMaxLev, sign = i % 2;
+      if (SPARSE && (z == 0 || row < kGuard)) { e[i] = 0; continue; }
+      const uint32_t gap = SPARSE ? row - kGuard : 0;
       const CodeLen l = omega_word(SPARSE ? z : z + 1);
       uint32_t code = sign << l.len | l.code, len = l.len + 1;
       if (SPARSE && gap) {
@@ -98,14 +112,17 @@ __device__ __forceinline__ uint32_t group_last(uint32_t v, int last_lane) {
 
 }  // namespace
 
-template <int LPB, int CP, int Q, int CODE>
+// ODD: bucket sizes that are no multiple of 4, whose buckets start anywhere in a Philox block.
+// LONG: with the coder of long code words, which costs 12 registers (and 25.6M values, s = 16,
+// d = 512 52.7 -> 58.7 us); without it they go through the general coder.
+template <int LPB, int CP, int Q, int CODE, bool ODD, bool LONG>
 __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs a) {
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
   constexpr uint32_t NB = 64 / LPB;             // buckets per wavefront pass
   constexpr int R = 4 * Q;                      // values of a run
   constexpr uint32_t kStep = LPB * R;           // values one run of the bucket's lanes covers
   constexpr uint32_t kTab = code_entries<kSparse>();
-  __shared__ uint32_t codes[kTab];
+  __shared__ uint32_t codes[kTab], omegas[LONG ? kOmegas : 1];
   extern __shared__ uint32_t smem[];            // per wavefront: NB bucket strings of dst_words
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
@@ -114,9 +131,11 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
   uint32_t* const dst = smem + (wave * NB + sb) * a.dst_words;
 
   {
-    const uint32_t* src;
-    if constexpr (kSparse) src = g_codes_sparse.e; else src = g_codes_dense.e;
+    const uint32_t *src, *om;
+    if constexpr (kSparse) { src = g_codes_sparse.e; om = g_codes_sparse.omega; }
+    else { src = g_codes_dense.e; om = g_codes_dense.omega; }
     for (uint32_t i = tid; i < kTab; i += blockDim.x) codes[i] = src[i];
+    if (LONG && tid < (int)kOmegas) omegas[tid] = om[tid];
     for (uint32_t j = l; j < a.dst_words; j += LPB) dst[j] = 0;
   }
   if (blockIdx.x == 0 && tid == 0) {  // header; length and status are completed later
@@ -140,6 +159,7 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
   const uint32_t s = a.s;
   const float s_f = (float)s;
   const uint32_t zlim = min(s, kMaxLev - 1u);
+  const uint32_t zlong = min(s, kSparse ? 63u : kOmegas - 2u);   // four values then fit 64 bits
   QuantCtx qc;
   qc.inv = 0.f; qc.s_f = s_f; qc.s = s; qc.key0 = a.key0; qc.key1 = a.key1;
   qc.stream_id = a.stream_id; qc.iteration = a.iteration;
@@ -151,38 +171,57 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
     uint32_t m = 0;
     if (live) bucket_extent(a, b, base, m);
     const float* __restrict__ gb = a.g + base;
-    const bool all_full = __ballot(m == (uint32_t)CP * kStep) == ~0ull;
+    const bool all_full = CP > 0 && __ballot(m == (uint32_t)CP * kStep) == ~0ull;
+    // (CP = 0: one bucket at a time, its runs are read twice instead of kept in registers)
+    const uint32_t runs = CP > 0 ? (uint32_t)CP : __builtin_amdgcn_readfirstlane((m + kStep - 1u) / kStep);
 
-    float v[CP][R];
-#pragma unroll
-    for (int c = 0; c < CP; ++c) {
+    auto load_run = [&](uint32_t at, bool full, float (&x8)[R]) {
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const uint32_t e0 = (uint32_t)c * kStep + l * R + 4 * q;
+        const uint32_t e0 = at + l * R + 4 * q;
         float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (all_full || e0 + 3 < m) {
-          x = *reinterpret_cast<const float4*>(gb + e0);
+        if (full || e0 + 3 < m) {
+          if constexpr (ODD) {
+            const v4f_any t = *reinterpret_cast<const v4f_any*>(gb + e0);
+            x = make_float4(t.x, t.y, t.z, t.w);
+          } else {
+            x = *reinterpret_cast<const float4*>(gb + e0);
+          }
         } else {
           if (e0 + 0 < m) x.x = gb[e0 + 0];
           if (e0 + 1 < m) x.y = gb[e0 + 1];
           if (e0 + 2 < m) x.z = gb[e0 + 2];
         }
-        v[c][4 * q] = x.x; v[c][4 * q + 1] = x.y; v[c][4 * q + 2] = x.z; v[c][4 * q + 3] = x.w;
+        x8[4 * q] = x.x; x8[4 * q + 1] = x.y; x8[4 * q + 2] = x.z; x8[4 * q + 3] = x.w;
       }
-    }
+    };
+    auto run_full = [&](uint32_t c) { return CP > 0 ? all_full : (c + 1u) * kStep <= m; };
+    float v[CP > 0 ? CP : 1][R];
+#pragma unroll
+    for (int c = 0; c < CP; ++c) load_run((uint32_t)c * kStep, all_full, v[c]);
 
     // ---- scale of each bucket: reduction over its LPB lanes ------------------------------
     float scale;
     if (a.norm_mode == 0) {
       double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;   // squares are exact in fp64
-#pragma unroll
-      for (int c = 0; c < CP; ++c) {
+      auto add_run = [&](const float (&x8)[R]) {
 #pragma unroll
         for (int j = 0; j < R; j += 4) {
-          s0 = fma((double)v[c][j], (double)v[c][j], s0);
-          s1 = fma((double)v[c][j + 1], (double)v[c][j + 1], s1);
-          s2 = fma((double)v[c][j + 2], (double)v[c][j + 2], s2);
-          s3 = fma((double)v[c][j + 3], (double)v[c][j + 3], s3);
+          s0 = fma((double)x8[j], (double)x8[j], s0);
+          s1 = fma((double)x8[j + 1], (double)x8[j + 1], s1);
+          s2 = fma((double)x8[j + 2], (double)x8[j + 2], s2);
+          s3 = fma((double)x8[j + 3], (double)x8[j + 3], s3);
+        }
+      };
+      if constexpr (CP > 0) {
+#pragma unroll
+        for (int c = 0; c < CP; ++c) add_run(v[c]);
+      } else {
+#pragma unroll 2
+        for (uint32_t c = 0; c < runs; ++c) {
+          float x8[R];
+          load_run(c * kStep, run_full(c), x8);
+          add_run(x8);
         }
       }
       double ss = (s0 + s1) + (s2 + s3);
@@ -195,10 +234,21 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
       scale = (float)sqrt(ss);  // right in the last lane of each bucket
     } else {
       float mx = 0.f;
+      auto max_run = [&](const float (&x8)[R]) {
 #pragma unroll
-      for (int c = 0; c < CP; ++c)
+        for (int j = 0; j < R; ++j) mx = fmaxf(mx, fabsf(x8[j]));
+      };
+      if constexpr (CP > 0) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) mx = fmaxf(mx, fabsf(v[c][j]));
+        for (int c = 0; c < CP; ++c) max_run(v[c]);
+      } else {
+#pragma unroll 2
+        for (uint32_t c = 0; c < runs; ++c) {
+          float x8[R];
+          load_run(c * kStep, run_full(c), x8);
+          max_run(x8);
+        }
+      }
       mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr1, 0xf>(__float_as_uint(mx))));
       mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr2, 0xf>(__float_as_uint(mx))));
       mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr4, 0xf>(__float_as_uint(mx))));
@@ -213,27 +263,36 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
     // ---- runs ---------------------------------------------------------------------------
     const uint64_t g0 = a.index_base + base + l * R;
     uint32_t hi;
-    const bool uhi = uniform_counter_hi(g0, g0 + (uint64_t)(CP - 1) * kStep + R - 4, hi);
+    const bool uhi = uniform_counter_hi(g0, g0 + (uint64_t)(runs ? runs - 1u : 0u) * kStep + R - (ODD ? 0 : 4), hi);
     uint32_t bits = 32;        // bits of the bucket's string so far (the same in all its lanes)
     uint32_t last_pos = 0;     // 1-based position of the last nonzero level so far
-#pragma unroll
-    for (int c = 0; c < CP; ++c) {
+    auto code_run = [&](const uint32_t c, const float (&x8)[R], const bool full) {
       // (one run after the other: side by side they cost the fifth wavefront per SIMD)
       __builtin_amdgcn_sched_barrier(0);
       uint32_t z[R], zmax = 0;
+      uint32_t r[4 * (Q + ODD)];
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        uint32_t r[4];
-        const uint64_t gi = g0 + (uint64_t)c * kStep + 4 * q;
-        if (uhi) draw4_uniform_hi(gi, hi, qc, r);
-        else draw4<true>(gi, qc, r);
+      for (int q = 0; q < Q + ODD; ++q) {
+        uint32_t r4[4];
+        const uint64_t gi = g0 + (uint64_t)(c * kStep) + 4 * q;
+        if (uhi) draw4_uniform_hi(gi, hi, qc, r4);
+        else draw4<true>(gi, qc, r4);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          z[4 * q + j] = quantize_unclamped(v[c][4 * q + j], inv, r[j]);
-          zmax = max(zmax, z[4 * q + j]);
-        }
+        for (int j = 0; j < 4; ++j) r[4 * q + j] = r4[j];
       }
-      const uint32_t e0 = (uint32_t)c * kStep + l * R;     // bucket position of the run, 0-based
+      if constexpr (ODD) {   // the run's first value has word g0 % 4 of the first block
+        const bool one = (g0 & 1u) != 0, two = (g0 & 2u) != 0;
+#pragma unroll
+        for (int j = 0; j < R + 2; ++j) r[j] = one ? r[j + 1] : r[j];
+#pragma unroll
+        for (int j = 0; j < R; ++j) r[j] = two ? r[j + 2] : r[j];
+      }
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        z[j] = quantize_unclamped(x8[j], inv, r[j]);
+        zmax = max(zmax, z[j]);
+      }
+      const uint32_t e0 = c * kStep + l * R;     // bucket position of the run, 0-based
       // where the nonzero level before the run is; inside a run gaps are at most R, so only its
       // first one can be beyond the table
       uint64_t acc = 0;
@@ -264,20 +323,20 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
         // positions from the run's start on, in bytes of the table (2 kMaxLev words per gap); as
         // constants: positions in the bucket would be kept in 2 R registers over all buckets
         constexpr uint32_t kGapBytes = 8u * kMaxLev;
-        uint32_t prev = (from - e0) * kGapBytes;
+        uint32_t prev = (from - e0 - kGuard) * kGapBytes;
 #pragma unroll
         for (int j = 0; j < R; ++j) {
           uint32_t e;
           if constexpr (kSparse) {
             const uint32_t pos = ((uint32_t)j + 1u) * kGapBytes;
-            const uint32_t zs = __builtin_amdgcn_alignbit(z[j], __float_as_uint(v[c][j]), 31);   // z * 2 + sign
+            const uint32_t zs = __builtin_amdgcn_alignbit(z[j], __float_as_uint(x8[j]), 31);   // z * 2 + sign
             e = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(codes) +
                                                    ((zs << 2) | (pos - prev)));
-            prev = z[j] ? pos : prev;
+            prev = z[j] ? pos - kGuard * kGapBytes : prev;
           } else {
-            const uint32_t zs = z[j] * 2u + (v[c][j] < 0.f ? 1u : 0u);   // (-0.0 counts as positive)
+            const uint32_t zs = z[j] * 2u + (x8[j] < 0.f ? 1u : 0u);   // (-0.0 counts as positive)
             e = codes[zs];
-            if (!all_full) e = e0 + (uint32_t)j < m ? e : 0u;
+            if (!full) e = e0 + (uint32_t)j < m ? e : 0u;
           }
           acc = (acc << (e & 63u)) | (e >> 8);
           len += e & 0xFFu;
@@ -287,6 +346,46 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
       if (easy) {
         const uint32_t incl = group_incl_sum<LPB>(len);
         if (len) lds_emit(dst, bits + incl - len, acc, len);
+        bits += group_last<LPB>(incl, last_lane);
+      } else if (LONG && __builtin_amdgcn_ballot_w64(zmax > zlong) == 0) {
+        // long code words: gap and level looked up one by one, the first gap and every four
+        // values go out by themselves (at most 61 bits)
+        uint64_t gc = 0, part[Q];
+        uint32_t gl = 0, plen[Q], first = 0, tot = 0, prev = 0;
+        if constexpr (kSparse) {
+#pragma unroll
+          for (int j = R - 1; j >= 0; --j) first = z[j] ? (uint32_t)j + 1u : first;
+          if (first) omega_encode(e0 + first - prev0, gc, gl);
+          tot = gl;
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          part[q] = 0; plen[q] = 0;
+#pragma unroll
+          for (int j = 4 * q; j < 4 * q + 4; ++j) {
+            if (kSparse ? z[j] != 0 : full || e0 + (uint32_t)j < m) {
+              const uint32_t lw = omegas[kSparse ? z[j] : z[j] + 1u], ll = lw & 0xFFu;
+              if (kSparse && prev) {
+                const uint32_t gw = omegas[(uint32_t)j + 1u - prev];
+                part[q] = part[q] << (gw & 63u) | gw >> 8;
+                plen[q] += gw & 0xFFu;
+              }
+              part[q] = part[q] << (ll + 1u) | ((x8[j] < 0.f ? 1u : 0u) << ll | lw >> 8);
+              plen[q] += ll + 1u;
+              prev = (uint32_t)j + 1u;
+            }
+          }
+          tot += plen[q];
+        }
+        const uint32_t incl = group_incl_sum<LPB>(tot);
+        uint32_t at = bits + incl - tot;
+        if (gl) lds_emit(dst, at, gc, gl);
+        at += gl;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          if (plen[q]) lds_emit(dst, at, part[q], plen[q]);
+          at += plen[q];
+        }
         bits += group_last<LPB>(incl, last_lane);
       } else {
         // the general coder, from memory (rare: kept small rather than fast, so that it costs
@@ -300,8 +399,9 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
             const uint32_t pos = e0 + j + 1u;
             if (pos > m) break;
             uint32_t r[4];
-            draw4<true>(g0 + (uint64_t)c * kStep + (j & ~3u), qc, r);
-            const uint32_t q = j & 3u;
+            const uint64_t gi = g0 + (uint64_t)(c * kStep) + j;
+            draw4<true>(gi, qc, r);
+            const uint32_t q = (uint32_t)gi & 3u;
             const float x = gb[pos - 1u];
             const uint32_t lev = quantize_one(x, inv, s_f, s, q == 0 ? r[0] : q == 1 ? r[1] : q == 2 ? r[2] : r[3]);
             if (kSparse && lev == 0) continue;
@@ -322,6 +422,21 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
           }
         }
         bits += group_last<LPB>(incl, last_lane);
+      }
+    };
+    if constexpr (CP > 0) {
+#pragma unroll
+      for (int c = 0; c < CP; ++c) code_run((uint32_t)c, v[c], all_full);
+    } else {
+      float next[R];
+      if (runs) load_run(0, run_full(0), next);
+#pragma unroll 1
+      for (uint32_t c = 0; c < runs; ++c) {
+        float x8[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) x8[j] = next[j];
+        if (c + 1u < runs) load_run((c + 1u) * kStep, run_full(c + 1u), next);
+        code_run(c, x8, run_full(c));
       }
     }
 
@@ -362,15 +477,30 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
 
 namespace {
 
-template <int LPB, int CP, int Q>
-hipError_t launch_direct(const EncodeArgs& a, uint32_t code, uint32_t teams, hipStream_t st) {
+template <int LPB, int CP, int Q, bool ODD, bool LONG>
+hipError_t launch_code(const EncodeArgs& a, uint32_t code, uint32_t teams, hipStream_t st) {
   const dim3 grid((teams + kDirectWaves - 1) / kDirectWaves), block(64 * kDirectWaves);
   const size_t lds = 4 * (size_t)kDirectWaves * (64 / LPB) * a.dst_words;
   if (code == QSGD_CODE_SPARSE)
-    hipLaunchKernelGGL((k_encode_direct<LPB, CP, Q, QSGD_CODE_SPARSE>), grid, block, lds, st, a);
+    hipLaunchKernelGGL((k_encode_direct<LPB, CP, Q, QSGD_CODE_SPARSE, ODD, LONG>), grid, block, lds, st, a);
   else
-    hipLaunchKernelGGL((k_encode_direct<LPB, CP, Q, QSGD_CODE_DENSE>), grid, block, lds, st, a);
+    hipLaunchKernelGGL((k_encode_direct<LPB, CP, Q, QSGD_CODE_DENSE, ODD, LONG>), grid, block, lds, st, a);
   return hipGetLastError();
+}
+
+// Mean level of normal values above one: with one or two bits of gap and sign, eight values are
+// then close to 64 bits.
+bool long_words(const EncodeArgs& a) {
+  const float scale = a.norm_mode ? sqrtf(2.f * logf((float)a.d + 2.f)) : sqrtf((float)a.d);
+  return 0.8f * (float)a.s > 1.2f * scale;
+}
+
+template <int LPB, int CP, int Q, bool ODD = false>
+hipError_t launch_direct(const EncodeArgs& a, uint32_t code, uint32_t teams, hipStream_t st) {
+  // (runs read twice have the registers, and bucket sizes off the usual ones don't need two kernels)
+  if constexpr (ODD || CP == 0) return launch_code<LPB, CP, Q, ODD, true>(a, code, teams, st);
+  else if (long_words(a)) return launch_code<LPB, CP, Q, ODD, true>(a, code, teams, st);
+  else return launch_code<LPB, CP, Q, ODD, false>(a, code, teams, st);
 }
 
 }  // namespace
@@ -386,10 +516,21 @@ static int lanes_per_bucket(uint32_t d, bool few) {
   if (d <= 256) return few ? 64 : 32;
   return 64;
 }
-uint32_t direct_buckets_per_pass(uint32_t d, bool few) { return 64u / lanes_per_bucket(d, few); }
+uint32_t direct_buckets_per_pass(uint32_t d, bool few) {
+  return 64u / lanes_per_bucket(d, few && d % 4 == 0);
+}
 
 hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, uint32_t teams,
                                 hipStream_t st) {
+  if (a.d % 4) {
+    if (a.d <= 64) return launch_direct<16, 1, 1, true>(a, code, teams, st);
+    if (a.d <= 128) return launch_direct<16, 1, 2, true>(a, code, teams, st);
+    if (a.d <= 256) return launch_direct<32, 1, 2, true>(a, code, teams, st);
+    if (a.d <= 512) return launch_direct<64, 1, 2, true>(a, code, teams, st);
+    if (a.d <= 1024) return launch_direct<64, 2, 2, true>(a, code, teams, st);
+    if (a.d <= 2048) return launch_direct<64, 4, 2, true>(a, code, teams, st);
+    return launch_direct<64, 0, 2, true>(a, code, teams, st);
+  }
   if (a.d <= 64) return launch_direct<16, 1, 1>(a, code, teams, st);
   if (a.d <= 128) return few ? launch_direct<32, 1, 1>(a, code, teams, st)
                              : launch_direct<16, 1, 2>(a, code, teams, st);
@@ -399,7 +540,8 @@ hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, ui
   if (a.d <= 768) return launch_direct<64, 3, 1>(a, code, teams, st);
   if (a.d <= 1024) return launch_direct<64, 2, 2>(a, code, teams, st);
   if (a.d <= 1536) return launch_direct<64, 3, 2>(a, code, teams, st);
-  return launch_direct<64, 4, 2>(a, code, teams, st);
+  if (a.d <= 2048) return launch_direct<64, 4, 2>(a, code, teams, st);
+  return launch_direct<64, 0, 2>(a, code, teams, st);
 }
 
 }  // namespace qsgd

@@ -31,7 +31,7 @@ constexpr uint32_t kMaxTeams = 8192;       // most teams (regions) one encode us
 #ifndef QSGD_ENC_TEAMS
 #define QSGD_ENC_TEAMS 128u
 #endif
-// Direct encoder (Elias codes, d <= 2048): teams per compute unit, about what its registers let
+// Direct encoder (Elias codes): teams per compute unit, about what its registers let
 // be resident at once (25.6M values: 20 -> 53.7 us, 32 -> 53.2; 20M of d = 1500: 24 -> 48.9, 32 -> 45.9).
 #ifndef QSGD_DIRECT_TEAMS
 #define QSGD_DIRECT_TEAMS 32u
