@@ -362,9 +362,10 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // Which apply step the Elias decoder takes.  The share of nonzero levels of Q_s grows
   // like s / sqrt(d) (Lemma 3.1 (iii)); above 1/8 a string has more records per
   // 256-position window than the counting apply handles well, and Code'_s has a
-  // record for every coordinate.  (The counting apply keeps a bit per message in a 32-bit
+  // record for every coordinate; with the largest value as scale the share is larger still (14M
+  // values, d = 80, s = 1, K = 7: 323 us by the ring decoder, 91 by the tile decoder).  (The counting apply keeps a bit per message in a 32-bit
   // word: more than 32 messages go the other way whatever the data.)
-  a.kloop = (g.code == QSGD_CODE_DENSE || 64ull * g.s * g.s > g.d || K > 32) ? 1u : 0u;
+  a.kloop = (dense_strings(g) || K > 32) ? 1u : 0u;
 
   const uint32_t cus = (uint32_t)device_cus();
   if (g.n > 0 && g.code == QSGD_CODE_SPARSE && g.d > kEntryMinD && std::isfinite(c)) {
@@ -392,12 +393,15 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     if (launch_raw_apply(a, raw_args(g, L), st) != hipSuccess) return QSGD_ERR_HIP;
   }
   if (g.nb == 0) return QSGD_OK;
-  const bool bytes = g.code != QSGD_CODE_FIXED && g.d <= kMaxBucketFast && g.s <= 127;   // levels fit a byte
-  if (bytes && split_pays(g, K, a.kloop || g.d % 4)) {
+  // Levels fit a byte.  (The general path's reader, a thread per stretch or bucket and message after
+  // message, is left with the rest: 573 thousand values in one bucket, Code'_s, s = 127, K = 7:
+  // 17.6 ms there, 65 us in the split decoder.)
+  const bool bytes = g.code != QSGD_CODE_FIXED && g.s <= 127;
+  if (bytes && g.d <= kMaxBucketFast && split_pays(g, K, a.kloop || g.d % 4)) {
     ScopedTiming tm("decode_elias", st);
     return launch_decode_split(a, cus, string_words(g), st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
   }
-  if (bytes && (a.kloop || g.d % 4)) {
+  if (bytes && g.d <= kMaxBucketFast && (a.kloop || g.d % 4)) {
     // dense strings, and bucket sizes that the ring decoder's loads do not fit: the tile
     // decoder, one lane per string
     uint32_t gw = 1;  // buckets per wavefront: a power of two, gw * K lanes
@@ -423,6 +427,13 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
       return QSGD_OK;
     }
     float* acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes);
+    if (bytes && g.d > kEntryMinD && g.d * g.per_elem < 0xF0000000ull) {   // (bit positions in 32 bits)
+      a.acc = acc;
+      if (launch_decode_split(a, cus, string_words(g), st) != hipSuccess ||
+          launch_gen_apply(a, acc, blocks, st) != hipSuccess)
+        return QSGD_ERR_HIP;
+      return QSGD_OK;
+    }
     if (launch_gen_zero(acc, g.n, blocks, st) != hipSuccess ||
         launch_gen_parse(a, acc, g.d > kEntryMinD, st) != hipSuccess ||
         launch_gen_apply(a, acc, blocks, st) != hipSuccess)

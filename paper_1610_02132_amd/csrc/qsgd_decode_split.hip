@@ -16,6 +16,12 @@
 // brings into step by itself; the units of a string exchange their ends through LDS.  A workgroup
 // works on as many units at a time as it has room for, a bucket's strings one behind the other.
 //
+// Buckets above kEntryMinD carry a list of entry points, at most one per segment of kSeg positions: a
+// workgroup then takes a segment, reads the stretch between two entry points that it lies in
+// from every message, and checks that the stretch ends where the next one starts, at the
+// position the list names.  The sums go to an accumulator, which is applied to x only if all
+// strings were sound.
+//
 // A step of a walk looks up the next kBits bits in a table in LDS that holds up to two records;
 // longer records are read by arithmetic.  Levels must fit a signed byte (s <= 127).
 //
@@ -25,6 +31,8 @@
 //   20 thousand values, d = 8192, s = 40, K = 2     294 -> 42 us
 //   1M values, d = 2124, s = 23 (max scale), K = 2  273 -> 74 us
 //   2.1M values, d = 523, s = 3, K = 8              670 -> 35 us
+//   573 thousand values in one bucket, Code'_s, s = 127, K = 7   17.6 ms -> 65 us
+//   4M values, d = 100 thousand, s = 2, K = 16      1230 -> 291 us
 // Pieces of up to seven words a lane, a wavefront to a string, took 68, 118 and 54 us.
 #include <algorithm>
 #include <type_traits>
@@ -93,14 +101,27 @@ __device__ __forceinline__ int32_t field5(uint32_t e, uint32_t at) {   // signed
   return (int32_t)(e << (27u - at)) >> 27;
 }
 
-// LDS, in words: rows, then per message of a batch (scale, first word, end bit, first unit), a
-// total, per unit (end of the last lane, positions passed), and what the next turn goes on from.
-constexpr uint32_t kPerRow = 4, kPerUnit = 2, kMore = 4;
+// LDS, in words: rows, then per message of a batch (scale, first word, words, first and end bit,
+// position before, position behind, first unit), a total, per unit (end of the last lane,
+// positions passed), and what the next turn goes on from.
+constexpr uint32_t kPerRow = 8, kPerUnit = 2, kMore = 4;
+constexpr uint32_t kLast = 0xFFFFFFFFu;   // position behind: the string's end, wherever it is
+
+// The last of `ents` entry points (bit, position before it) at or before position P; 0: the
+// string's start.  (A damaged list gives some number in range, the same one for everybody.)
+__device__ __forceinline__ uint32_t entry_before(const uint32_t* list, uint32_t ents, uint32_t P) {
+  uint32_t lo = 0, hi = ents;
+  while (lo < hi) {
+    const uint32_t mid = lo + (hi - lo + 1u) / 2u;
+    if (list[2ull * mid - 1u] <= P) lo = mid; else hi = mid - 1u;
+  }
+  return lo;
+}
 
 }  // namespace
 
-// A workgroup per bucket at a time.
-template <int CODE, int NG>
+// A workgroup per bucket at a time; LONGB (buckets above kEntryMinD): per segment of kSeg positions.
+template <int CODE, int NG, bool LONGB>
 __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a) {
   if (*a.status != 0) return;
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
@@ -109,11 +130,15 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
   const uint32_t tid = threadIdx.x, lane = tid & 63u, threads = blockDim.x;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t K = a.K, s = a.s, rows = a.rows, lanes = a.lanes;
-  const uint32_t row_words = (a.d + 3u) / 4u;
+  const uint32_t row_words = LONGB ? kSeg / 4u : (a.d + 3u) / 4u;
   float* const scales = reinterpret_cast<float*>(smem + rows * row_words);
   uint32_t* const s_word = smem + rows * (row_words + 1u);
-  uint32_t* const s_end = s_word + rows;
-  uint32_t* const s_unit = s_end + rows;             // rows + 1 of them
+  uint32_t* const s_words = s_word + rows;
+  uint32_t* const s_begin = s_words + rows;
+  uint32_t* const s_end = s_begin + rows;
+  uint32_t* const s_prev = s_end + rows;
+  uint32_t* const s_next = s_prev + rows;
+  uint32_t* const s_unit = s_next + rows;            // rows + 1 of them
   const uint32_t slots = threads / lanes;            // units worked on at a time
   uint32_t* const carry = s_unit + rows + 1u;        // 2: entry and position of the next turn's first unit
   uint32_t* const u_exit = carry + 2;
@@ -132,17 +157,23 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
     for (uint32_t i = tid; i < rows * row_words; i += threads) smem[i] = 0;
   }
 
-  for (uint32_t b = blockIdx.x; b < a.nb; b += gridDim.x) {
+  const uint32_t segs = LONGB ? (a.d - 1u) / kSeg + 1u : 1u;   // (a.nb * segs < 2^32)
+  for (uint32_t task = blockIdx.x; task < a.nb * segs; task += gridDim.x) {
+    const uint32_t b = LONGB ? task / segs : task, P = LONGB ? (task - b * segs) * kSeg : 0u;
     uint64_t base;
-    uint32_t m;
-    bucket_extent(a, b, base, m);
-    float* const x = a.x + base;
+    uint32_t M;
+    bucket_extent(a, b, base, M);
+    if (LONGB && P >= M) continue;
+    const uint32_t m = LONGB ? min(kSeg, M - P) : M;   // positions P + 1 .. P + m of the bucket's M
+    base += P;
+    float* const x = (LONGB ? a.acc : a.x) + base;
     float4 xr[NG], sum[NG];
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       const uint32_t e = 4u * (tid + (uint32_t)i * threads);
       xr[i] = make_float4(0.f, 0.f, 0.f, 0.f);
       sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (LONGB) continue;
       if (e + 3 < m) {
         const v4f_any v = *reinterpret_cast<const v4f_any*>(x + e);
         xr[i] = make_float4(v.x, v.y, v.z, v.w);
@@ -162,24 +193,51 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
           const uint64_t msg_words = a.msg_words[k0 + lane];
           const uint32_t o0 = msg[H_WORDS + b], o1 = msg[H_WORDS + b + 1];
           bool open = o0 < o1 && pay + o1 <= msg_words;
-          uint32_t endbit = 0, first = 0;
+          uint32_t begin = 32, endbit = 0, first = 0, words = 0, prev = 0, next = kLast;
           if (open) {
             const uint32_t* const str = msg + (pay + o0);
             first = str[0];
-            endbit = (o1 - o0) * 32u;
+            words = o1 - o0;
+            uint32_t ents = 0;
+            if (LONGB) {
+              ents = str[words - 1u];
+              open = 2ull * ents + 1u < words;
+              words = open ? words - (2u * ents + 1u) : 1u;
+            }
+            endbit = words * 32u;
             if (kSparse) {
-              const uint32_t last = str[o1 - o0 - 1u];
+              const uint32_t last = str[words - 1u];
               endbit -= 1u + (uint32_t)(__ffs((int)last) - 1);
-              open = last != 0 && endbit >= 32u;
+              open = open && last != 0 && endbit >= 32u;
             } else {
-              open = endbit > 32u;
+              open = open && endbit > 32u;
+            }
+            if (LONGB && open) {
+              // the stretch between two entry points that this segment lies in; every stretch is
+              // somebody's if the first segment's is the first, the next segment's the same or
+              // the next, and the last segment's the last
+              const uint32_t* const list = str + words;
+              const uint32_t e = entry_before(list, ents, P);
+              const uint32_t e2 = P + m < M ? entry_before(list, ents, P + kSeg) : ents;
+              open = (P != 0 || e == 0) && (e2 == e || (e2 == e + 1u && P + m < M));
+              if (e) { begin = list[2u * e - 2u]; prev = list[2u * e - 1u]; }
+              uint32_t stop = endbit;
+              if (e < ents) { stop = list[2u * e]; next = list[2u * e + 1u]; }
+              open = open && begin >= 32u && begin <= stop && stop <= endbit && prev <= M && next != prev;
+              endbit = stop;
+              if (begin == endbit && (next != kLast || (!kSparse && prev < M))) open = false;
             }
           }
           if (!open) flag_corrupt(a.status);
           scales[lane] = open ? __uint_as_float(first) / (float)s : 0.f;
           s_word[lane] = o0;
+          s_words[lane] = words;
+          s_begin[lane] = begin;
           s_end[lane] = open ? endbit : 0u;
-          const uint32_t words = open ? (endbit - 32u + 31u) / 32u : 0u;   // (the first word is the scale)
+          s_prev[lane] = prev;
+          s_next[lane] = next;
+          // words that hold records (the first word of a string is the scale)
+          words = open && begin < endbit ? (endbit + 31u) / 32u - begin / 32u : 0u;
           units = (words + lanes - 1u) / lanes;
         }
         const uint32_t incl = wave_incl_scan_u32(units, (int)lane);
@@ -196,7 +254,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
         for (uint32_t step = 32; step; step >>= 1)
           if (r + step < kn && s_unit[r + step] <= u) r += step;
         const uint32_t ui = u - s_unit[r];                     // unit of the string
-        const uint32_t wi = 1u + ui * lanes + l;               // word of the string
+        const uint32_t begin = LONGB ? s_begin[r] : 32u;
+        const uint32_t wi = begin / 32u + ui * lanes + l;      // word of the string
         const uint32_t endbit = live ? s_end[r] : 0u;
         const uint32_t end = min(32u, endbit > 32u * wi ? endbit - 32u * wi : 0u);
         const bool idle = end == 0;                            // the string ends before this word
@@ -204,14 +263,15 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
         uint32_t w0 = 0, w1 = 0, w2 = 0;
         if (!idle) {
           const uint32_t* const str = a.msgs[k0 + r] + (pay + s_word[r]);
-          const uint32_t nwords = (endbit + 31u) / 32u + (kSparse && endbit % 32u == 0 ? 1u : 0u);
+          const uint32_t nwords = s_words[r];
           w0 = str[wi];
           w1 = wi + 1u < nwords ? str[wi + 1u] : 0u;
           w2 = wi + 2u < nwords ? str[wi + 2u] : 0u;
         }
         uint8_t* const row = reinterpret_cast<uint8_t*>(smem + r * row_words);
 
-        uint32_t entry = 0, exit = 0, adv = 0;
+        const uint32_t next = LONGB ? s_next[r] : kLast;
+        uint32_t entry = LONGB && l == 0 && ui == 0 ? begin & 31u : 0u, exit = 0, adv = 0;
         bool fail = false;
         const bool goes_on = ui != 0;                          // behind another unit of its string
         if (l == 0 && goes_on && slot == 0) entry = carry[0];  // (known from the turn before)
@@ -227,22 +287,26 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
               const bool two = o + len1 < end;
               const uint32_t p1 = p + ((e >> 8) & 15u), p2 = p + ((e >> 12) & 31u);
               if (W) {
-                if (p1 <= m) row[p1 - 1u] = (uint8_t)field5(e, 17);
-                if (two && p2 <= m) row[p2 - 1u] = (uint8_t)field5(e, 22);
+                if (p1 - 1u - P < m) row[p1 - 1u - P] = (uint8_t)field5(e, 17);
+                if (two && p2 - 1u - P < m) row[p2 - 1u - P] = (uint8_t)field5(e, 22);
               }
               o += two ? (e >> 4) & 15u : len1;
               p = two ? p2 : p1;
             } else {
               uint32_t gap = 1, ol = 0, ll;
               if (kSparse) gap = omega_peek3(v1, ol);
-              const uint32_t q = o + ol;                       // (below 64: the gap's code has 23 bits at most)
-              const uint64_t pair = q < 32u ? ((uint64_t)w0 << 32 | w1) : ((uint64_t)w1 << 32 | w2);
+              if (LONGB && kSparse && gap == 0)                // (2^16 and more: up to 43 bits)
+                gap = omega_loop(((uint64_t)w0 << 32 | w1) << o | ((uint64_t)w2 << o >> 32), ol);
+              const uint32_t q = o + ol;                       // (gap, sign and level end below bit 96)
+              const uint64_t pair = q < 32u ? ((uint64_t)w0 << 32 | w1)
+                                  : q < 64u ? ((uint64_t)w1 << 32 | w2) : (uint64_t)w2 << 32;
               const uint32_t v = (uint32_t)(pair << (q & 31u) >> 32);
               uint32_t lev = omega_peek3(v << 1, ll);
-              if (gap == 0 || lev == 0 || lev > (kSparse ? s : s + 1u)) { fail = true; break; }
+              if (gap == 0 || lev == 0 || lev > (kSparse ? s : s + 1u) || (LONGB && gap > M)) { fail = true; break; }
               if (!kSparse) lev -= 1u;
               p += gap;
-              if (W) { if (p <= m) row[p - 1u] = (uint8_t)((v >> 31) ? 0u - lev : lev); }
+              if (W && LONGB && kSparse && p > M) { fail = true; break; }
+              if (W) { if (p - 1u - P < m) row[p - 1u - P] = (uint8_t)((v >> 31) ? 0u - lev : lev); }
               o = q + 1u + ll;
             }
           }
@@ -280,16 +344,19 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
           for (uint32_t t = slot; t > slot - min(ui, slot); --t) start += u_adv[t - 1u];
           if (ui > slot) start += carry[1];
         }
+        if (LONGB && ui <= slot) start += s_prev[r];
         const uint32_t exit_was = exit;
         __syncthreads();                       // carry is read, and may be written now
         if (slot == slots - 1u && l == lanes - 1u) { carry[0] = exit - 32u; carry[1] = start + adv; }
         if (!idle) {
           walk(std::true_type{}, start);
           bool bad;
-          if (kSparse) bad = fail || (final_word && (exit_was != end || start + adv > m));
-          // (what stands behind the m-th record of Code'_s is padding)
-          else bad = (fail && start + adv < m) || (final_word && start + adv < m) ||
-                     (final_word && exit_was > end && adv && start + adv <= m);
+          if (kSparse || next != kLast)
+            bad = fail || (final_word && (exit_was != end || start + adv > M || (next != kLast && start + adv != next)));
+          // (what stands behind the bucket's last record of Code'_s is padding)
+          else
+            bad = (fail && start + adv < M) || (final_word && start + adv < M) ||
+                  (final_word && exit_was > end && adv && start + adv <= M);
           if (bad) flag_corrupt(a.status);
         }
         if (turn + slots < total) __syncthreads();   // carry, before it is read
@@ -297,7 +364,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
       __syncthreads();
       // ---- add up the rows in message order, and clear them -------------------------------------
       // (zeros are left out where no term belongs: it matters to a scale that is not finite)
-      const bool records_only = kSparse || a.d % 4u != 0;
+      const bool records_only = LONGB || kSparse || a.d % 4u != 0;
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
         const uint32_t g = tid + (uint32_t)i * threads;
@@ -323,7 +390,9 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
     for (int i = 0; i < NG; ++i) {
       const uint32_t e = 4u * (tid + (uint32_t)i * threads);
       float4 v = xr[i];
-      if (a.step) {
+      if (LONGB) {
+        v = sum[i];
+      } else if (a.step) {
         v.x = fmaf(-a.c, sum[i].x, v.x); v.y = fmaf(-a.c, sum[i].y, v.y);
         v.z = fmaf(-a.c, sum[i].z, v.z); v.w = fmaf(-a.c, sum[i].w, v.w);
       } else {
@@ -343,13 +412,13 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
 
 namespace {
 
-template <int CODE>
+template <int CODE, bool LONGB>
 hipError_t launch_split(const DecodeArgs& a, uint32_t blocks, uint32_t waves, uint32_t lds, hipStream_t st) {
   const dim3 grid(blocks), block(64 * waves);
-  const uint32_t ng = (a.d + 256u * waves - 1) / (256u * waves);
-  if (ng <= 1) hipLaunchKernelGGL((k_decode_split<CODE, 1>), grid, block, lds, st, a);
-  else if (ng <= 2) hipLaunchKernelGGL((k_decode_split<CODE, 2>), grid, block, lds, st, a);
-  else if (ng <= 4) hipLaunchKernelGGL((k_decode_split<CODE, 4>), grid, block, lds, st, a);
+  const uint32_t ng = ((LONGB ? kSeg : a.d) + 256u * waves - 1) / (256u * waves);
+  if (ng <= 1) hipLaunchKernelGGL((k_decode_split<CODE, 1, LONGB>), grid, block, lds, st, a);
+  else if (ng <= 2) hipLaunchKernelGGL((k_decode_split<CODE, 2, LONGB>), grid, block, lds, st, a);
+  else if (ng <= 4) hipLaunchKernelGGL((k_decode_split<CODE, 4, LONGB>), grid, block, lds, st, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -357,19 +426,26 @@ hipError_t launch_split(const DecodeArgs& a, uint32_t blocks, uint32_t waves, ui
 }  // namespace
 
 hipError_t launch_decode_split(DecodeArgs& a, uint32_t cus, uint32_t words, hipStream_t st) {
+  const bool lng = a.d > kEntryMinD;
+  const uint32_t span = lng ? kSeg : a.d;
+  // (a stretch between entry points has some kEntryBits at least)
+  if (lng) words = std::max((uint32_t)((uint64_t)words * kSeg / a.d), kEntryBits / 32u + 8u);
   a.lanes = words > 32 ? 64 : words > 16 ? 32 : 16;
-  const uint32_t row = (a.d + 3) / 4 * 4;
+  const uint32_t row = (span + 3) / 4 * 4;
   // rows of all messages at once if half of a compute unit's LDS holds them, else in batches
   a.rows = std::max(1u, std::min(a.K, 72u * 1024u / row));
   // a lane for every word of a batch, and at most 16 positions per thread in the sum
   const uint32_t units = a.rows * ((words + a.lanes - 1) / a.lanes);
   uint32_t waves = std::min(kSplitWaves, (units * a.lanes + 63) / 64);
-  waves = std::max(waves, (a.d + 1023) / 1024);
+  waves = std::max(waves, (span + 1023) / 1024);
   const uint32_t lds = 4 * (a.rows * (row / 4 + kPerRow) + kPerUnit * (64 * waves / a.lanes) + kMore);
   const uint32_t fit = std::max(1u, std::min(32u / waves, 156u * 1024u / (lds + 4 * kEntries)));
-  const uint32_t blocks = std::min(a.nb, cus * fit);
-  if (a.code == QSGD_CODE_SPARSE) return launch_split<QSGD_CODE_SPARSE>(a, blocks, waves, lds, st);
-  return launch_split<QSGD_CODE_DENSE>(a, blocks, waves, lds, st);
+  const uint32_t tasks = a.nb * ((a.d - 1) / span + 1);
+  const uint32_t blocks = std::min(tasks, cus * fit);
+  if (lng) return a.code == QSGD_CODE_SPARSE ? launch_split<QSGD_CODE_SPARSE, true>(a, blocks, waves, lds, st)
+                                             : launch_split<QSGD_CODE_DENSE, true>(a, blocks, waves, lds, st);
+  return a.code == QSGD_CODE_SPARSE ? launch_split<QSGD_CODE_SPARSE, false>(a, blocks, waves, lds, st)
+                                    : launch_split<QSGD_CODE_DENSE, false>(a, blocks, waves, lds, st);
 }
 
 }  // namespace qsgd

@@ -168,6 +168,20 @@ __device__ __forceinline__ uint32_t omega_peek3(uint32_t w, uint32_t& len) {
   return v;
 }
 
+// Decoder rule of the recursive Elias code (App. A.2) on a 64-bit window; values
+// below 2^32.  Returns 0 for malformed input; `len` = bits used.
+__device__ __forceinline__ uint32_t omega_loop(uint64_t w, uint32_t& len) {
+  uint32_t N = 1, used = 0;
+  for (;;) {
+    if ((w >> 63) == 0) { len = used + 1; return N; }
+    if (N > 31u || used + N + 2u > 64u) { len = 0; return 0; }
+    const uint32_t v = (uint32_t)(w >> (63u - N));
+    w <<= (N + 1u);
+    used += N + 1u;
+    N = v;
+  }
+}
+
 // ---- bit strings: stream bit j is bit 31-(j%32) of word j/32 --------------------
 // ORs the `len` (1..64) low bits of `code` into zero-initialised LDS words so that
 // the code's first bit lands on stream bit `bitoff`.

@@ -17,7 +17,7 @@
 // the order k = 0, 1, ...); a last kernel applies the accumulator to x.  Buckets
 // above 8192 values carry a list of entry points behind their string and are read
 // by a workgroup, a thread per stretch; shorter ones by a thread per bucket (levels
-// above 127 only: the tile and split decoders take any bucket size up to 8192).
+// above 127 only: the tile and split decoders take the others).
 #include <cmath>
 
 #include "qsgd_device.hpp"
@@ -498,20 +498,6 @@ __device__ __forceinline__ uint64_t peek64(const uint32_t* w, uint64_t nwords, u
   return off ? (hi << off) | (a2 >> (32u - off)) : hi;
 }
 
-// Decoder rule of the recursive Elias code (App. A.2) on a 64-bit window; values
-// below 2^32.  Returns 0 for malformed input; `len` = bits used.
-__device__ __forceinline__ uint32_t omega_loop(uint64_t w, uint32_t& len) {
-  uint32_t N = 1, used = 0;
-  for (;;) {
-    if ((w >> 63) == 0) { len = used + 1; return N; }
-    if (N > 31u || used + N + 2u > 64u) { len = 0; return 0; }
-    const uint32_t v = (uint32_t)(w >> (63u - N));
-    w <<= (N + 1u);
-    used += N + 1u;
-    N = v;
-  }
-}
-
 }  // namespace
 
 __global__ __launch_bounds__(256) void k_gen_zero(float* p, uint64_t n) {
@@ -735,7 +721,7 @@ __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* 
 //            messages in turns into a dense accumulator.
 // Bound by latency: the stretch's chain of records (about 46, an LDS round trip and some 40
 // instructions each) and four launches.  13M values, s = 1, K = 16: 180 us with a dense
-// accumulator (zeroed, counted, stored, resolved, applied: 24 us of it for x alone), FIGURE.
+// accumulator (zeroed, counted, stored, resolved, applied: 24 us of it for x alone), 48 this way.
 // Untouched coordinates: fma(-c, 0, x) is x for c >= 0; where it is not (accumulating, and
 // c < 0, turn -0 into +0) one more launch does that.
 

@@ -172,6 +172,7 @@ struct DecodeArgs {
   uint32_t q16;          // 1: 16-bit records (counting apply, s <= 4)
   // few strings: lanes that share a string, messages whose rows are in LDS at once
   uint32_t lanes, rows;
+  float* acc;            // buckets above kEntryMinD: where their sums go
   // fixed width
   uint32_t fixed_bits;
   uint32_t fixed_words_full;

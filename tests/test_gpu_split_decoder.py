@@ -73,3 +73,57 @@ def test_damaged_strings_are_flagged(code, d, n):
         q.qsgd_decode_accumulate(P, [msg], x[:n], ws)
         assert q.qsgd_workspace_status(ws) != 0
         assert not x[n:].any()
+
+
+@pytest.mark.parametrize("code", [q.CODE_SPARSE, q.CODE_DENSE])
+@pytest.mark.parametrize("d,s,K,n", [
+    (8193, 40, 3, 8193), (10_000, 127, 40, 25_001), (8200, 5, 64, 20_000), (37_906, 103, 2, 37_906),
+    (100_000, 2, 16, 350_003), (70_001, 30, 5, 140_002),
+])
+def test_segments_of_long_buckets(code, d, s, K, n):
+    P0 = q.Params(n=n, s=s, d=d, code=code, norm=q.NORM_MAX if K == 5 else q.NORM_L2, seed=5)
+    dev, host = messages(P0, n, K)
+    assert check_step(P0, dev, host, 0.1, np.linspace(-1, 1, n, dtype=np.float32), K) == 0
+
+
+def test_gaps_beyond_16_bits():
+    """Values at both ends of a long bucket only; too many records for the sparse path's estimate."""
+    n, K = 300_000, 16
+    dev, host = [], []
+    for k in range(K):
+        P = q.Params(n=n, s=4, d=n, code=q.CODE_SPARSE, seed=5, stream_id=k)
+        g = torch.zeros(n)
+        ends = torch.randn(400, generator=torch.Generator().manual_seed(k))
+        g[:200], g[-200:] = ends[:200], ends[200:]
+        g[140_000 + k] = 3.0
+        status, words, msg = Device(P).encode(g.cuda())
+        assert status == 0
+        assert compare_encode(P, g.numpy(), words) == 0
+        dev.append(msg)
+        host.append(words)
+    P0 = q.Params(n=n, s=4, d=n, code=q.CODE_SPARSE, seed=5)
+    assert check_step(P0, dev, host, 0.1, np.linspace(-1, 1, n, dtype=np.float32), K) == 0
+
+
+@pytest.mark.parametrize("code", [q.CODE_SPARSE, q.CODE_DENSE])
+def test_damaged_entry_lists_leave_x_alone(code):
+    n, K = 60_000, 8
+    P = q.Params(n=n, s=60, d=n, code=code, seed=5)
+    dev, host = messages(P, n, K)
+    nw, ents = host[0].size, int(host[0][-1])
+    assert ents >= 6
+    lst = nw - 1 - 2 * ents
+    ws = torch.zeros(q.qsgd_workspace_bytes(P, K) // 4, dtype=torch.int32, device="cuda")
+    x0 = torch.linspace(-1, 1, n).cuda()
+    for index, value in [
+            (nw - 1, ents + 1), (nw - 1, ents - 1), (nw - 1, nw), (lst, 31), (lst + 2, 32 * nw),
+            (lst + 4, int(host[0][lst + 4]) + 1), (lst + 5, int(host[0][lst + 5]) + 1),
+            (lst + 5, int(host[0][lst + 3])), (lst + 1, n), (lst + 2 * ents - 1, n + 5), (lst, int(host[0][lst + 2]))]:
+        if code == q.CODE_DENSE and (index, value) == (nw - 1, ents - 1):
+            continue   # a sound list without its first entry, whose words read as padding
+        bad = dev[0][:nw].clone()
+        bad[index] = value
+        x = x0.clone()
+        q.qsgd_sgd_step(P, [bad] + dev[1:], 0.1, x, ws)
+        assert q.qsgd_workspace_status(ws) == -3, (index - lst, value)
+        assert torch.equal(x, x0)
