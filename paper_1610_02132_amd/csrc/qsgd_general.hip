@@ -721,7 +721,8 @@ __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* 
 //            messages in turns into a dense accumulator.
 // Bound by latency: the stretch's chain of records (about 46, an LDS round trip and some 40
 // instructions each) and four launches.  13M values, s = 1, K = 16: 180 us with a dense
-// accumulator (zeroed, counted, stored, resolved, applied: 24 us of it for x alone), 48 this way.
+// accumulator (zeroed, counted, stored, resolved, applied: 24 us of it for x alone), 46 this way (49
+// with level and sign always read by a second round trip).
 // Untouched coordinates: fma(-c, 0, x) is x for c >= 0; where it is not (accumulating, and
 // c < 0, turn -0 into +0) one more launch does that.
 
@@ -850,10 +851,16 @@ __global__ __launch_bounds__(64) void k_sparse_list(DecodeArgs a, uint32_t* area
           uint32_t gl, ll;
           const uint32_t v = peek(at_bit);
           uint32_t gap = omega_peek3(v, gl);
-          if (gap == 0)                                        // 2^16 and more, or malformed
-            gap = omega_loop((uint64_t)v << 32 | peek(at_bit + 32u), gl);
-          const uint32_t w = peek(at_bit + gl);
-          const uint32_t lev = omega_peek3(w << 1, ll);
+          // the usual level, 1, is a zero behind the sign: both are among the 32 bits already
+          // there (the gap's code has 23 bits at most), and no lane looks further
+          uint32_t w = v << gl, lev = 1;
+          ll = 1;
+          if (__builtin_amdgcn_ballot_w64(gap == 0 || ((w >> 30) & 1u) != 0)) {
+            if (gap == 0)                                      // 2^16 and more, or malformed
+              gap = omega_loop((uint64_t)v << 32 | peek(at_bit + 32u), gl);
+            w = peek(at_bit + gl);
+            lev = omega_peek3(w << 1, ll);
+          }
           at_bit += gl + 1u + ll;
           at_pos += gap;
           const bool good = (gap != 0) & (lev != 0) & (lev <= a.s) & (at_pos <= m) & (gap <= m) &
