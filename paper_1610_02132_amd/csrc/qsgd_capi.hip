@@ -182,6 +182,22 @@ uint32_t string_words(const Geometry& g) {
   return 1 + (uint32_t)(bits / 32.0);
 }
 
+// About how many nonzero levels a bucket of Code_s has whose string takes `words` words: every one
+// costs a sign, a bit of level at least, and the code word of its gap.
+double records_of(const Geometry& g, double words) {
+  const double bits = 32.0 * words, d = (double)g.d;
+  double q = bits / 3.0;
+  for (int i = 0; i < 8 && q > 1.0; ++i) q = bits / (2.0 + omega_len_host((uint64_t)std::max(1.0, d / q)));
+  return std::min(q, d);
+}
+
+// Words a bucket's string has in the shortest of the messages, going by the readable bytes behind
+// it: what they were cut to, or else the size of a buffer.
+double shortest_string(const Geometry& g, const size_t* msg_bytes, uint32_t K) {
+  const double words = (double)(*std::min_element(msg_bytes, msg_bytes + K) / 4);
+  return std::max(1.0, (words - H_WORDS - (double)g.table_words) / (double)std::max<uint64_t>(g.nb, 1));
+}
+
 // Whether a lane for every word of the strings (split decoder) beats a lane for every string.
 // With few strings the latter takes as long as its longest string, 0.64 us per word (tile decoder) or
 // 1.7 us (ring decoder, sparse strings), measured from 5 to 470 words; the former takes some
@@ -372,7 +388,10 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     // Long buckets of Code_s: a message has at most q = s (s + sqrt(d)) nonzero levels in
     // expectation (Lemma 3.1 (iii)), so about K^2 q^2 / (2 d) coordinates are hit by two
     // messages.  Where that is a few hundred at most, only the touched coordinates are updated.
-    const double q = (double)g.s * ((double)g.s + std::sqrt((double)g.d));
+    // With the largest value as scale there is no such bound (4M normal values, s = 1: 630
+    // thousand nonzero levels), and the messages' lengths say how many there are.
+    const double q = g.norm == QSGD_NORM_MAX ? records_of(g, shortest_string(g, msg_bytes, K))
+                                             : (double)g.s * ((double)g.s + std::sqrt((double)g.d));
     if ((double)K * K * q * q <= 512.0 * (double)g.d) {
       uint8_t* const area = static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes;
       // wavefronts per string: a stretch is about 1024 bits, a record about Elias(d / q) + 3

@@ -716,9 +716,11 @@ __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* 
 //   apply    a record whose position is not in `multi` updates x (0 + v = v is the sum in
 //            message order), the others go to the bucket's collision list
 //   resolve  a coordinate on that list is summed from 0 in message order by the thread that
-//            holds its record of the lowest message.  Lists that overflowed (the messages
-//            collide, or are longer, than expected) make the bucket's workgroup read the
-//            messages in turns into a dense accumulator.
+//            holds its record of the lowest message.  Where the messages collide more often
+//            than that list has room for, every coordinate in `multi` gets an accumulator
+//            instead, and the messages' lists are gone through one after the other; where
+//            a message's own list overflowed, the bucket's workgroup reads the messages in
+//            turns into a dense accumulator.  Both are linear in the number of records.
 // Bound by latency: the stretch's chain of records (about 46, an LDS round trip and some 40
 // instructions each) and four launches.  13M values, s = 1, K = 16: 180 us with a dense
 // accumulator (zeroed, counted, stored, resolved, applied: 24 us of it for x alone), 46 this way (49
@@ -744,13 +746,15 @@ __device__ __forceinline__ CollideList collide_list(uint8_t* lists, uint64_t b) 
   return l;
 }
 
-// A bucket's share of the accumulator area, m words: two bitmaps, a counter per message, and the
-// messages' lists of records.  cap 0: too small a bucket for that.
+// A bucket's share of the accumulator area, m words: two bitmaps, a counter per message, the
+// messages' lists of records (two words each), and an accumulator for every coordinate that two
+// messages can name (half as many as there are records).  cap 0: too small a bucket for that.
 struct SparseArea {
   uint32_t *seen, *multi, *count;
   uint32_t fixed;   // words in front of the lists
   uint32_t cap;     // records per list
   uint32_t* lists;
+  float* sums;      // K * cap / 2
   __device__ uint32_t* pos(uint32_t k) const { return lists + 2ull * k * cap; }
   __device__ uint32_t* val(uint32_t k) const { return lists + (2ull * k + 1ull) * cap; }
 };
@@ -763,7 +767,8 @@ __device__ __forceinline__ SparseArea sparse_area(uint32_t* area, uint64_t base,
   s.count = s.multi + mw;
   s.fixed = 2u * mw + K;
   s.lists = s.seen + s.fixed;
-  s.cap = m > s.fixed ? (m - s.fixed) / (2u * K) : 0u;
+  s.cap = m > s.fixed ? (uint32_t)(2ull * (m - s.fixed) / (5u * K)) : 0u;
+  s.sums = reinterpret_cast<float*>(s.lists + 2ull * K * s.cap);
   return s;
 }
 
@@ -982,6 +987,7 @@ __global__ __launch_bounds__(1024) void k_sparse_resolve(DecodeArgs a, uint32_t*
   __shared__ uint8_t lk[kCollide];
   constexpr int kHashBits = 11;
   __shared__ uint32_t head[1 << kHashBits], next[kCollide];
+  __shared__ uint32_t wave_total[1024 / 64];
   const uint64_t b = blockIdx.x;
   const uint64_t base = b * (uint64_t)a.d;
   const uint32_t m = (uint32_t)min((uint64_t)a.d, a.n - base);
@@ -998,21 +1004,55 @@ __global__ __launch_bounds__(1024) void k_sparse_resolve(DecodeArgs a, uint32_t*
     if (threadIdx.x == 0) bad = 0;
     __syncthreads();
     if (!overflow) {
-      // the collision list alone was too short: the coordinates in `multi` remain
-      for (uint32_t p0 = 0; p0 < m; p0 += 32u * 1024u) {
-        const uint32_t w = p0 / 32u + threadIdx.x;
-        uint32_t bits = w < (m + 31u) / 32u ? s.multi[w] : 0u;
-        while (bits) {
+      // the collision list alone was too short: the coordinates in `multi` remain.  `seen` has
+      // done its work and takes the number of them before every word of the bitmap.
+      const uint32_t mw = (m + 31u) >> 5, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+      constexpr uint32_t kPer = 8;   // words per thread and trip
+      uint32_t before = 0;
+      for (uint32_t w0 = 0; w0 < mw; w0 += 1024u * kPer) {
+        const uint32_t at = w0 + threadIdx.x * kPer;
+        uint32_t cnt[kPer], mine = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; ++j) {
+          cnt[j] = at + j < mw ? (uint32_t)__popc(s.multi[at + j]) : 0u;
+          mine += cnt[j];
+        }
+        const uint32_t incl = wave_incl_scan_u32(mine, (int)lane);
+        if (lane == 63u) wave_total[wave] = incl;
+        __syncthreads();
+        uint32_t run = before + incl - mine;
+        for (uint32_t w = 0; w < 1024u / 64u; ++w) {
+          const uint32_t t = wave_total[w];
+          run += w < wave ? t : 0u;
+          before += t;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < kPer; ++j) {
+          if (at + j < mw) s.seen[at + j] = run;
+          run += cnt[j];
+        }
+        __syncthreads();
+      }
+      // (at most K * cap / 2: each of them has two records at least)
+      for (uint32_t i = threadIdx.x; i < before; i += blockDim.x) s.sums[i] = 0.f;
+      __syncthreads();
+      // a message names a coordinate at most once: no two threads add to the same sum
+      for (uint32_t k = 0; k < a.K; ++k) {
+        const uint32_t* const rp = s.pos(k);
+        const uint32_t* const rv = s.val(k);
+        const uint32_t n = s.count[k];
+#pragma unroll 4
+        for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+          const uint32_t p = rp[i], bits = s.multi[p >> 5], bit = 1u << (p & 31u);
+          if (bits & bit) s.sums[s.seen[p >> 5] + (uint32_t)__popc(bits & (bit - 1u))] += __uint_as_float(rv[i]);
+        }
+        __syncthreads();   // message k is in before message k + 1 adds to the same coordinates
+      }
+      for (uint32_t w = threadIdx.x; w < mw; w += blockDim.x) {
+        uint32_t bits = s.multi[w], at = bits ? s.seen[w] : 0u;
+        for (; bits; bits &= bits - 1u, ++at) {
           const uint32_t p = w * 32u + (uint32_t)__ffs((int)bits) - 1u;
-          bits &= bits - 1u;
-          float sum = 0.f;
-          for (uint32_t k = 0; k < a.K; ++k) {
-            const uint32_t* const q = s.pos(k);
-            const uint32_t n = s.count[k];
-            for (uint32_t i = 0; i < n; ++i)
-              if (q[i] == p) { sum += __uint_as_float(s.val(k)[i]); break; }
-          }
-          x[p] = updated(a, x[p], sum);
+          x[p] = updated(a, x[p], s.sums[at]);
         }
       }
       return;

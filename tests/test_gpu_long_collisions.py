@@ -1,0 +1,87 @@
+"""Long buckets of Code_s whose messages name the same coordinates more often than the decoder
+of sparse messages plans for: the list of shared coordinates overflows, a message's own list
+overflows, a last bucket too short for any list, and max-scaled messages, which have no bound on
+their records.  Bar: x bit-identical to the oracle's, both ways of applying the sum."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import paper_1610_02132_amd as q  # noqa: E402
+from gpu_harness import Device, check_step  # noqa: E402
+from oracle import qsgd_oracle as qo  # noqa: E402
+
+COLLIDE = 1024      # places for records at shared coordinates, per bucket
+H_NORM = 3
+
+
+def messages(n, d, share, K, as_l2):
+    """K messages with about share * n records.  Encoded with the largest value as scale, which
+    brings any number of them; as_l2: sent under the other norm's header (the strings are alike),
+    whose number of records the decoder believes to know."""
+    dev, host = [], []
+    for k in range(K):
+        gen = torch.Generator().manual_seed(1000 * k + n)
+        g = torch.where(torch.rand(n, generator=gen) < 0.5, -share, share)
+        g[::d] = 1.0
+        g *= 1.0 + 0.25 * k              # every peer has another scale
+        P = q.Params(n=n, s=1, d=d, code=q.CODE_SPARSE, norm=q.NORM_MAX, seed=3, stream_id=k)
+        status, words, msg = Device(P).encode(g.cuda())
+        assert status == 0
+        if as_l2:
+            words[H_NORM] = q.NORM_L2
+            msg[H_NORM] = q.NORM_L2
+        dev.append(msg[: words.size].clone())
+        host.append(words)
+    return dev, host
+
+
+def records(host, n, d):
+    """Per bucket: records per message, records at coordinates that several messages name."""
+    named = np.stack([qo.decode_tuple(w)["levels"] != 0 for w in host])
+    out = []
+    for b in range(0, n, d):
+        part = named[:, b:b + d]
+        terms = part.sum(axis=0)
+        out.append((part.sum(axis=1), int(terms[terms > 1].sum()), part.shape[1]))
+    return out
+
+
+def list_capacity(m, K):
+    fixed = 2 * ((m + 31) // 32) + K
+    return 2 * (m - fixed) // (5 * K) if m > fixed else 0
+
+
+@pytest.mark.parametrize("K,n,d,share", [(2, 60_001, 60_001, 0.13), (3, 60_001, 60_001, 0.11),
+                                         (3, 120_002 + 5_000, 60_001, 0.11)])
+def test_more_shared_coordinates_than_the_list_holds(K, n, d, share):
+    dev, host = messages(n, d, share, K, as_l2=True)
+    for counts, shared, m in records(host, n, d)[: n // d]:
+        assert shared > COLLIDE and counts.max() <= list_capacity(m, K)
+    P0 = q.Params(n=n, s=1, d=d, code=q.CODE_SPARSE, seed=3)
+    assert check_step(P0, dev, host, 0.1, np.linspace(-1, 1, n, dtype=np.float32), K) == 0
+
+
+@pytest.mark.parametrize("K,n,d,share", [(2, 20_001, 20_001, 0.3), (4, 2 * 20_001 + 40, 20_001, 0.3),
+                                         (16, 9_000 + 900, 9_000, 0.02)])
+def test_more_records_than_a_messages_list_holds(K, n, d, share):
+    """The last one: full buckets fit, the short last one does not."""
+    dev, host = messages(n, d, share, K, as_l2=True)
+    assert any(counts.max() > list_capacity(m, K) for counts, _, m in records(host, n, d))
+    P0 = q.Params(n=n, s=1, d=d, code=q.CODE_SPARSE, seed=3)
+    assert check_step(P0, dev, host, 0.1, np.linspace(-1, 1, n, dtype=np.float32), K) == 0
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 16])
+@pytest.mark.parametrize("d,share", [(20_011, 0.2), (20_011, 0.001), (9_001, 0.05)])
+@pytest.mark.parametrize("whole_buffers", [False, True])
+def test_max_scaled_long_buckets(K, d, share, whole_buffers):
+    """The messages' lengths, or buffers that hold any message, pick the decoder."""
+    n = 2 * d + 77
+    dev, host = messages(n, d, share, K, as_l2=False)
+    P0 = q.Params(n=n, s=1, d=d, code=q.CODE_SPARSE, norm=q.NORM_MAX, seed=3)
+    if whole_buffers:
+        room = q.qsgd_max_encoded_bytes(P0) // 4
+        dev = [torch.cat([m, m.new_zeros(room - m.numel())]) for m in dev]
+    assert check_step(P0, dev, host, 0.1, np.linspace(-1, 1, n, dtype=np.float32), K) == 0

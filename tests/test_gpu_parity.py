@@ -207,9 +207,9 @@ def test_survivor_list_overflow_takes_the_direct_coder():
 def test_long_sparse_buckets_read_all_messages_at_once(same_gradient, nb):
     """Long buckets (d > 8192), s = 1, K = 16: the decoder reads the K messages at the same
     time and sums coordinates that several messages hit from a list, in message order.
-    Spikes shared by all peers give coordinates with up to 16 terms; the same gradient for
-    every peer makes the messages collide so often that the list overflows and the
-    workgroup falls back to reading the messages in turns."""
+    Spikes shared by all peers give coordinates with up to 16 terms, the same gradient for
+    every peer some 80 to 100 of them.  (The list has room for all of these; messages that
+    collide more often are in test_gpu_long_collisions.py.)"""
     d, K = 150_001, 16
     n = nb * d - (7 if nb > 1 else 0)
     gen = torch.Generator().manual_seed(99)
