@@ -123,9 +123,9 @@ __device__ __forceinline__ uint32_t entry_before(const uint32_t* list, uint32_t 
 // A workgroup per bucket at a time; LONGB (buckets above kEntryMinD): per segment of kSeg positions.
 template <int CODE, int NG, bool LONGB>
 __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a) {
-  if (*a.status != 0) return;
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
-  __shared__ uint32_t table[kEntries];
+  __shared__ uint32_t table[kEntries], damaged;
+  const uint32_t status = *a.status;
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, threads = blockDim.x;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -155,7 +155,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
       table[i] = e;
     }
     for (uint32_t i = tid; i < rows * row_words; i += threads) smem[i] = 0;
+    if (tid == 0) damaged = status;
   }
+  // (other workgroups set the status word meanwhile: a workgroup's wavefronts leave together)
+  __syncthreads();
+  if (damaged) return;
 
   const uint32_t segs = LONGB ? (a.d - 1u) / kSeg + 1u : 1u;   // (a.nb * segs < 2^32)
   for (uint32_t task = blockIdx.x; task < a.nb * segs; task += gridDim.x) {

@@ -143,10 +143,11 @@ __device__ __forceinline__ void wave_fence() {
 // buckets, gw * K <= 64 (lane = (bucket g, message k)), until none is left.
 template <int CODE, int NP>
 __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a) {
-  if (*a.status != 0) return;
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
   constexpr uint32_t kEntries = tab_entries<CODE>();
   __shared__ uint4 table[kEntries / 2];
+  __shared__ uint32_t damaged;
+  const uint32_t status = *a.status;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // per wavefront: tile, string rings, scales
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
     }
   };
   uint32_t task = blockIdx.x * waves + wave;
-  request_task(task);
+  if (status == 0) request_task(task);
 
   {
     // two entries per load, eight loads in flight; a level above s is for the general reader
@@ -203,8 +204,14 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
       }
     }
     for (uint32_t j = lane; j < kTileBytes / 4u; j += kWave) *lds_at<uint32_t>(tile + 4u * j) = 0u;
+    if (tid == 0) damaged = status;
   }
+  // Other workgroups set the status word meanwhile: the wavefronts go by what the first one
+  // read, since a part of the table would be missing without one of them.  (A word set that
+  // late stems from this launch, and the headers are sound.)
   __syncthreads();
+  if (damaged) return;
+  if (status != 0) request_task(task);
 
   for (; task < tasks; task += gridDim.x * waves) {
     const uint32_t gcount = min(gw, a.nb - task * gw);

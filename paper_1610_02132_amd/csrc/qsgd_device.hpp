@@ -308,6 +308,16 @@ __device__ __forceinline__ uint32_t lane_bcast(uint32_t v, int src) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, src);
 }
 
+// Whether an earlier kernel found a message damaged, asked once for the whole workgroup: other
+// workgroups of the same launch set the word too (flag_corrupt), and wavefronts that read it one
+// by one could disagree and leave the others alone with barriers and half-filled LDS.
+__device__ __forceinline__ bool damaged_before(const uint32_t* status) {
+  __shared__ uint32_t word;
+  if (threadIdx.x == 0) word = *status;
+  __syncthreads();
+  return word != 0;
+}
+
 // Records "a message did not parse / did not match" in a status word.
 __device__ __forceinline__ void flag_corrupt(uint32_t* status) {
   atomicExch(status, 0xFFFFFFFDu);  // QSGD_ERR_CORRUPT (-3)

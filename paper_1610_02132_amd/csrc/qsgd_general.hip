@@ -692,7 +692,7 @@ __device__ __forceinline__ bool parse_in_turns(const DecodeArgs& a, const String
 // Long buckets (d > kEntryMinD): the string is followed by a list of entry points, so a
 // workgroup reads one bucket with a thread per stretch, message after message.
 __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* acc) {
-  if (*a.status != 0) return;
+  if (damaged_before(a.status)) return;
   __shared__ uint32_t bad;
   __shared__ StringRef refs[QSGD_MAX_PEERS];
   if (threadIdx.x == 0) bad = 0;
@@ -979,7 +979,7 @@ __global__ __launch_bounds__(256) void k_sparse_apply(DecodeArgs a, uint32_t* ar
 }
 
 __global__ __launch_bounds__(1024) void k_sparse_resolve(DecodeArgs a, uint32_t* area, uint8_t* lists) {
-  if (*a.status != 0) return;
+  if (damaged_before(a.status)) return;
   __shared__ uint32_t bad;
   __shared__ StringRef refs[QSGD_MAX_PEERS];
   __shared__ uint32_t lpos[kCollide];

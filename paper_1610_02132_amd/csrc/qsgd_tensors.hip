@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) void k_raw_pack(RawArgs a) {
 // Decode side: x_i <- x_i + sum_l raw_l[i]  or  x_i <- fma(-c, sum_l raw_l[i], x_i),
 // the sum over the messages in ascending order.
 __global__ __launch_bounds__(256) void k_raw_apply(DecodeArgs a, RawArgs r) {
-  if (*a.status != 0) return;
+  if (damaged_before(a.status)) return;
   __shared__ uint64_t base[QSGD_MAX_PEERS];   // word index of the raw section in message k
   __shared__ uint32_t bad;
   if (threadIdx.x == 0) bad = 0;
