@@ -175,23 +175,26 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
     // (CP = 0: one bucket at a time, its runs are read twice instead of kept in registers)
     const uint32_t runs = CP > 0 ? (uint32_t)CP : __builtin_amdgcn_readfirstlane((m + kStep - 1u) / kStep);
 
+    auto load_four = [&](uint32_t e0, bool full) -> float4 {
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (full || e0 + 3 < m) {
+        if constexpr (ODD) {
+          const v4f_any t = *reinterpret_cast<const v4f_any*>(gb + e0);
+          x = make_float4(t.x, t.y, t.z, t.w);
+        } else {
+          x = *reinterpret_cast<const float4*>(gb + e0);
+        }
+      } else {
+        if (e0 + 0 < m) x.x = gb[e0 + 0];
+        if (e0 + 1 < m) x.y = gb[e0 + 1];
+        if (e0 + 2 < m) x.z = gb[e0 + 2];
+      }
+      return x;
+    };
     auto load_run = [&](uint32_t at, bool full, float (&x8)[R]) {
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const uint32_t e0 = at + l * R + 4 * q;
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (full || e0 + 3 < m) {
-          if constexpr (ODD) {
-            const v4f_any t = *reinterpret_cast<const v4f_any*>(gb + e0);
-            x = make_float4(t.x, t.y, t.z, t.w);
-          } else {
-            x = *reinterpret_cast<const float4*>(gb + e0);
-          }
-        } else {
-          if (e0 + 0 < m) x.x = gb[e0 + 0];
-          if (e0 + 1 < m) x.y = gb[e0 + 1];
-          if (e0 + 2 < m) x.z = gb[e0 + 2];
-        }
+        const float4 x = load_four(at + l * R + 4 * q, full);
         x8[4 * q] = x.x; x8[4 * q + 1] = x.y; x8[4 * q + 2] = x.z; x8[4 * q + 3] = x.w;
       }
     };
@@ -202,35 +205,70 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
 
     // ---- scale of each bucket: reduction over its LPB lanes ------------------------------
     float scale;
+    // (a bucket's sum of squares is taken in one order, whichever shape the number of buckets
+    // picks: a slice has to get the whole vector's scales)
     if (a.norm_mode == 0) {
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;   // squares are exact in fp64
-      auto add_run = [&](const float (&x8)[R]) {
-#pragma unroll
-        for (int j = 0; j < R; j += 4) {
-          s0 = fma((double)x8[j], (double)x8[j], s0);
-          s1 = fma((double)x8[j + 1], (double)x8[j + 1], s1);
-          s2 = fma((double)x8[j + 2], (double)x8[j + 2], s2);
-          s3 = fma((double)x8[j + 3], (double)x8[j + 3], s3);
-        }
+      double ss;
+      auto square = [](float x, double sum) { return fma((double)x, (double)x, sum); };   // (exact in fp64)
+      auto group_sum = [](double v) {   // right in the last lane of each bucket
+        v += dpp_fetch_f64<kDppShr1, 0xf>(v);
+        v += dpp_fetch_f64<kDppShr2, 0xf>(v);
+        v += dpp_fetch_f64<kDppShr4, 0xf>(v);
+        v += dpp_fetch_f64<kDppShr8, 0xf>(v);
+        if (LPB >= 32) v += dpp_fetch_f64<kDppBcast15, 0xa>(v);
+        if (LPB >= 64) v += dpp_fetch_f64<kDppBcast31, 0xc>(v);
+        return v;
       };
-      if constexpr (CP > 0) {
+      if constexpr (CP == 1) {
+        // 64 < d <= 256: runs of four or eight.  Four values at a time, then pairwise by position:
+        // a run of eight is what the first step of the lanes' tree adds up of two runs of four.
+        double quad[Q];
 #pragma unroll
-        for (int c = 0; c < CP; ++c) add_run(v[c]);
+        for (int t = 0; t < Q; ++t)
+          quad[t] = square(v[0][4 * t + 1], square(v[0][4 * t], 0.0)) +
+                    square(v[0][4 * t + 3], square(v[0][4 * t + 2], 0.0));
+        ss = Q == 1 ? quad[0] : quad[0] + quad[Q - 1];
+        ss = group_sum(ss);
+      } else if constexpr (CP > 1) {   // (one shape per bucket size)
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+        for (int c = 0; c < CP; ++c) {
+#pragma unroll
+          for (int j = 0; j < R; j += 4) {
+            s0 = square(v[c][j], s0);
+            s1 = square(v[c][j + 1], s1);
+            s2 = square(v[c][j + 2], s2);
+            s3 = square(v[c][j + 3], s3);
+          }
+        }
+        ss = group_sum((s0 + s1) + (s2 + s3));
       } else {
-#pragma unroll 2
-        for (uint32_t c = 0; c < runs; ++c) {
-          float x8[R];
-          load_run(c * kStep, run_full(c), x8);
-          add_run(x8);
+        // d > 2048: in the order of the encoder with a team of wavefronts per bucket, 2048 values
+        // a wavefront, in chunks of 256
+        constexpr uint32_t kShare = 8 * kChunk;
+        ss = 0.0;
+#pragma unroll 1
+        for (uint32_t at = 0; at < m; at += kShare) {
+          double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+          auto add_four = [&](const float4& x) {
+            s0 = square(x.x, s0);
+            s1 = square(x.y, s1);
+            s2 = square(x.z, s2);
+            s3 = square(x.w, s3);
+          };
+          if (at + kShare <= m) {   // (all of it requested together)
+            float4 x[8];
+#pragma unroll
+            for (uint32_t c = 0; c < 8; ++c) x[c] = load_four(at + c * kChunk + 4u * l, true);
+#pragma unroll
+            for (uint32_t c = 0; c < 8; ++c) add_four(x[c]);
+          } else {
+#pragma unroll 4
+            for (uint32_t e = at; e < m; e += kChunk) add_four(load_four(e + 4u * l, false));
+          }
+          ss += group_sum((s0 + s1) + (s2 + s3));
         }
       }
-      double ss = (s0 + s1) + (s2 + s3);
-      ss += dpp_fetch_f64<kDppShr1, 0xf>(ss);
-      ss += dpp_fetch_f64<kDppShr2, 0xf>(ss);
-      ss += dpp_fetch_f64<kDppShr4, 0xf>(ss);
-      ss += dpp_fetch_f64<kDppShr8, 0xf>(ss);
-      if (LPB >= 32) ss += dpp_fetch_f64<kDppBcast15, 0xa>(ss);
-      if (LPB >= 64) ss += dpp_fetch_f64<kDppBcast31, 0xc>(ss);
       scale = (float)sqrt(ss);  // right in the last lane of each bucket
     } else {
       float mx = 0.f;
