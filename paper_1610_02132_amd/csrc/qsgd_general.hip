@@ -713,8 +713,8 @@ __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* 
 //   list     a wavefront per 64 stretches between entry points, a thread per stretch, string
 //            words staged in LDS: (position, value) into the message's list, the position's
 //            bit into `seen` and, if it was set already, into `multi`
-//   apply    a record whose position is not in `multi` updates x (0 + v = v is the sum in
-//            message order), the others go to the bucket's collision list
+//   apply    a record whose position is not in `multi` updates x (0 + v is the sum in message
+//            order), the others go to the bucket's collision list
 //   resolve  a coordinate on that list is summed from 0 in message order by the thread that
 //            holds its record of the lowest message.  Where the messages collide more often
 //            than that list has room for, every coordinate in `multi` gets an accumulator
@@ -969,7 +969,7 @@ __global__ __launch_bounds__(256) void k_sparse_apply(DecodeArgs a, uint32_t* ar
     for (uint32_t j = 0; j < kU; ++j) {
       if (i0 + j * step >= n) continue;
       if (((bits[j] >> (p[j] & 31u)) & 1u) == 0) {   // (only this record names the coordinate)
-        x[p[j]] = updated(a, old[j], v[j]);
+        x[p[j]] = updated(a, old[j], 0.f + v[j]);    // (a sum starts from +0: -0 does not stay)
       } else {
         const uint32_t idx = atomicAdd(cl.count, 1u);
         if (idx < kCollide) { cl.pos[idx] = p[j]; cl.val[idx] = v[j]; cl.msg[idx] = k; }

@@ -85,3 +85,28 @@ def test_max_scaled_long_buckets(K, d, share, whole_buffers):
         room = q.qsgd_max_encoded_bytes(P0) // 4
         dev = [torch.cat([m, m.new_zeros(room - m.numel())]) for m in dev]
     assert check_step(P0, dev, host, 0.1, np.linspace(-1, 1, n, dtype=np.float32), K) == 0
+
+
+@pytest.mark.parametrize("eta", [0.1, -0.1, 0.0])
+def test_values_that_underflow(eta):
+    """A scale so small that level / s times it is zero: a negative record adds -0 to a sum of +0,
+    which leaves a -0 in x what it is."""
+    n = 20_000
+    P = q.Params(n=n, s=2, d=n, code=q.CODE_SPARSE, seed=3)
+    g = torch.zeros(n)
+    g[7], g[100], g[19_000] = -1.0, -0.9, 1.1
+    status, words, msg = Device(P).encode(g.cuda())
+    assert status == 0 and (qo.decode_tuple(words)["levels"] != 0).sum() >= 2
+    at = int(qo.payload_offset_words(words))
+    words[at] = 1                                       # the smallest positive scale
+    msg[at] = 1
+    x0 = np.full(n, -0.0, dtype=np.float32)
+    ws = torch.zeros(q.qsgd_workspace_bytes(P, 1) // 4, dtype=torch.int32, device="cuda")
+    x = torch.from_numpy(x0.copy()).cuda()
+    q.qsgd_sgd_step(P, [msg], eta, x, ws)
+    want = qo.sgd_step([words], eta, x0)
+    assert np.array_equal(x.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    acc = torch.from_numpy(x0.copy()).cuda()
+    q.qsgd_decode_accumulate(P, [msg], acc, ws)
+    want = qo.decode_accumulate([words], x0)
+    assert np.array_equal(acc.cpu().numpy().view(np.uint32), want.view(np.uint32))
