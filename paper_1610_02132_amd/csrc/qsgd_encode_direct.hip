@@ -7,21 +7,24 @@
 // lane's first one?), one look-up per value in a table in LDS that holds the whole code word
 // of (gap, sign, level), the run's code words joined in a 64-bit register, a prefix sum of the
 // lengths, and two or three ORs into the bucket's string in LDS.  The gap in front of a run's
-// first nonzero level may be beyond the table and is then coded by arithmetic.  Levels of 32 to 63
+// first nonzero level may be beyond the table and is then coded by arithmetic.  Levels from 32 on
 // and runs of more than 64 bits look up gap and level one by one and go out four values at a
-// time (where levels are expected to be high: LONG); a level beyond that sends its wavefront
-// through a small general coder.  Above d = 2048
-// a bucket's runs do not fit the registers: they are read twice, the second time from the caches.
+// time, two with levels from 64 on (where such levels are possible: LONG).  Above d = 2048 a
+// bucket's runs do not fit the registers: they are read twice, the second time from the caches.
 //
 // Bound by instruction issue: about 45 vector instructions per value and lane (of those Philox 10,
 // rounding 8, code word 10), 78% of the issue slots.  25.6M values, s = 16, d = 512: 60 us through
 // the survivor ring (about 100 instructions), 42 directly; Code'_s of the same data 62 -> 36 us.
 // A copy of the bytes would take 19 us.  Per encode, before and after: 57M values, d = 2124,
 // s = 23 (max scale) 351 -> 187 us; 35M values, d = 4996, s = 11 153 -> 79 us.  (Kept in
-// registers, 4 to 16 runs: 57M of d = 2124 689 us, of which most was the general coder, but also
-// 30M of d = 8192, s = 40 177 instead of 89.)  Bucket sizes that are no multiple of 4 pay a Philox
+// registers, 4 to 16 runs: 30M of d = 8192, s = 40 177 us instead of 89.)  Levels from 64 on, 10M
+// values, largest value as scale, s = 255, d = 512 / 2048: Code_s 56 / 80 us through the survivor
+// ring, 105 / 158 one value at a time from memory, 44 / 54 two at a time; Code'_s 48 / 54, 85 /
+// 102, 35 / 43.  Bucket sizes that are no multiple of 4 pay a Philox
 // block per run and two selects per value: 20M values, d = 443, s = 11, 80 us, 261 on the general
 // path.
+#include <type_traits>
+
 #include "qsgd_device.hpp"
 #include "qsgd_encode_wave.hpp"
 #include "qsgd_kernels.hpp"
@@ -113,8 +116,9 @@ __device__ __forceinline__ uint32_t group_last(uint32_t v, int last_lane) {
 }  // namespace
 
 // ODD: bucket sizes that are no multiple of 4, whose buckets start anywhere in a Philox block.
-// LONG: with the coder of long code words, which costs 12 registers (and 25.6M values, s = 16,
-// d = 512 52.7 -> 58.7 us); without it they go through the general coder.
+// LONG: with the coder of long code words, which costs 25.6M values, s = 16, d = 512 50.1 -> 51.0
+// us and d = 2048 55.6 -> 62.6; without it the few runs of more than 64 bits are read again by a
+// small general coder.
 template <int LPB, int CP, int Q, int CODE, bool ODD, bool LONG>
 __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs a) {
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
@@ -385,49 +389,62 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
         const uint32_t incl = group_incl_sum<LPB>(len);
         if (len) lds_emit(dst, bits + incl - len, acc, len);
         bits += group_last<LPB>(incl, last_lane);
-      } else if (LONG && __builtin_amdgcn_ballot_w64(zmax > zlong) == 0) {
-        // long code words: gap and level looked up one by one, the first gap and every four
-        // values go out by themselves (at most 61 bits)
-        uint64_t gc = 0, part[Q];
-        uint32_t gl = 0, plen[Q], first = 0, tot = 0, prev = 0;
-        if constexpr (kSparse) {
+      } else if (LONG) {
+        // long code words: gap and level looked up one by one, the first gap and every V values go
+        // out by themselves: four values with levels up to zlong (at most 61 bits), else two (a
+        // level of 2^16 in Code'_s has 28 bits, so at most 58)
+        auto code_words = [&](auto values) {
+          constexpr int V = decltype(values)::value, kParts = R / V;
+          uint64_t gc = 0, part[kParts];
+          uint32_t gl = 0, plen[kParts], first = 0, tot = 0, prev = 0;
+          if constexpr (kSparse) {
 #pragma unroll
-          for (int j = R - 1; j >= 0; --j) first = z[j] ? (uint32_t)j + 1u : first;
-          if (first) omega_encode(e0 + first - prev0, gc, gl);
-          tot = gl;
-        }
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          part[q] = 0; plen[q] = 0;
-#pragma unroll
-          for (int j = 4 * q; j < 4 * q + 4; ++j) {
-            if (kSparse ? z[j] != 0 : full || e0 + (uint32_t)j < m) {
-              const uint32_t lw = omegas[kSparse ? z[j] : z[j] + 1u], ll = lw & 0xFFu;
-              if (kSparse && prev) {
-                const uint32_t gw = omegas[(uint32_t)j + 1u - prev];
-                part[q] = part[q] << (gw & 63u) | gw >> 8;
-                plen[q] += gw & 0xFFu;
-              }
-              part[q] = part[q] << (ll + 1u) | ((x8[j] < 0.f ? 1u : 0u) << ll | lw >> 8);
-              plen[q] += ll + 1u;
-              prev = (uint32_t)j + 1u;
-            }
+            for (int j = R - 1; j >= 0; --j) first = z[j] ? (uint32_t)j + 1u : first;
+            if (first) omega_encode(e0 + first - prev0, gc, gl);
+            tot = gl;
           }
-          tot += plen[q];
-        }
-        const uint32_t incl = group_incl_sum<LPB>(tot);
-        uint32_t at = bits + incl - tot;
-        if (gl) lds_emit(dst, at, gc, gl);
-        at += gl;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          if (plen[q]) lds_emit(dst, at, part[q], plen[q]);
-          at += plen[q];
-        }
-        bits += group_last<LPB>(incl, last_lane);
+          for (int q = 0; q < kParts; ++q) {
+            part[q] = 0; plen[q] = 0;
+#pragma unroll
+            for (int j = V * q; j < V * q + V; ++j) {
+              if (kSparse ? z[j] != 0 : full || e0 + (uint32_t)j < m) {
+                uint32_t k = (V == 4 ? z[j] : min(z[j], s)) + (kSparse ? 0u : 1u);
+                uint32_t lw = omegas[V == 4 || k < kOmegas ? k : 31u - (uint32_t)__clz((int)k)];
+                uint32_t code = lw >> 8, ll = lw & 0xFFu;
+                if (V != 4 && k >= kOmegas) {   // the code word of its length, open, then k itself
+                  const uint32_t nb = 32u - (uint32_t)__clz((int)k);
+                  code = code >> 1 << (nb + 1u) | k << 1;
+                  ll += nb;
+                }
+                if (kSparse && prev) {
+                  const uint32_t gw = omegas[(uint32_t)j + 1u - prev];
+                  part[q] = part[q] << (gw & 63u) | gw >> 8;
+                  plen[q] += gw & 0xFFu;
+                }
+                part[q] = part[q] << (ll + 1u) | ((x8[j] < 0.f ? 1u : 0u) << ll | code);
+                plen[q] += ll + 1u;
+                prev = (uint32_t)j + 1u;
+              }
+            }
+            tot += plen[q];
+          }
+          const uint32_t incl = group_incl_sum<LPB>(tot);
+          uint32_t at = bits + incl - tot;
+          if (gl) lds_emit(dst, at, gc, gl);
+          at += gl;
+#pragma unroll
+          for (int q = 0; q < kParts; ++q) {
+            if (plen[q]) lds_emit(dst, at, part[q], plen[q]);
+            at += plen[q];
+          }
+          bits += group_last<LPB>(incl, last_lane);
+        };
+        if (__builtin_amdgcn_ballot_w64(zmax > zlong) == 0) code_words(std::integral_constant<int, 4>());
+        else code_words(std::integral_constant<int, 2>());
       } else {
-        // the general coder, from memory (rare: kept small rather than fast, so that it costs
-        // the usual path no registers): lengths, prefix sum, then one code word at a time
+        // the general coder, from memory (rare with s < 32: kept small rather than fast, so that it
+        // costs the usual path no registers): lengths, prefix sum, then one code word at a time
         uint32_t off = 0, incl = 0;
 #pragma unroll 1
         for (int pass = 0; pass < 2; ++pass) {
@@ -526,9 +543,11 @@ hipError_t launch_code(const EncodeArgs& a, uint32_t code, uint32_t teams, hipSt
   return hipGetLastError();
 }
 
-// Mean level of normal values above one: with one or two bits of gap and sign, eight values are
-// then close to 64 bits.
+// Levels that the table of code words does not hold, which a single large value brings about
+// whatever the others are, or a mean level of normal values above one: with one or two bits of gap
+// and sign, eight values are then close to 64 bits.
 bool long_words(const EncodeArgs& a) {
+  if (a.s >= kMaxLev) return true;
   const float scale = a.norm_mode ? sqrtf(2.f * logf((float)a.d + 2.f)) : sqrtf((float)a.d);
   return 0.8f * (float)a.s > 1.2f * scale;
 }
