@@ -231,13 +231,21 @@ void plan_encode(const Geometry& g, uint64_t ws_avail, EncodePlan& pl) {
   // Above 2048 values a wavefront reads its bucket's runs twice, and one wavefront to a bucket
   // has to fill the machine; the other encoder has a team of wavefronts per bucket (30M values,
   // d = 8192, s = 40: 117 and 89 us, 1M 20 and 36; Code'_s, s = 80: 74 and 84; 4M of d = 3000: 35 and
-  // 22; 9M of d = 3232, Code'_s: 46 and 36).  Buckets that no vector load fits have no other
+  // 22; 9M of d = 3232, Code'_s: 46 and 36).  Only the team's work shrinks with the share of nonzero
+  // levels, which the largest value as scale leaves open (20M values of Code_s, max, team and direct:
+  // d = 4096, s = 1, normal 80 and 50, Student-t 31 and 50, outliers 43 and 50; s = 4 84 / 53, 73 /
+  // 52, 68 / 52), and at d = 8192 all four of its wavefronts have work (max, s = 1 77 / 57, 29 / 58,
+  // 32 / 57, s = 12 89 / 79, 73 / 73, 68 / 76; L2, s = 12 66 / 72, s = 24 75 / 72, s = 40 88 / 73;
+  // d = 6400, s = 12 80 / 64): over these distributions the geometric mean of team / direct is 0.78
+  // to 1.08 for d = 8192 up to s = 24, 1.0 for s = 1 from d = 4096 on (1.14 at 3000) and 1.1 to 1.9
+  // for the rest, L2 and max.  Buckets that no vector load fits have no other
   // encoder but the general path (20M values, d = 443: 261 and 80 us, d = 41: 2250 and 113).
   const bool sparse = g.code == QSGD_CODE_SPARSE;
   if (g.code == QSGD_CODE_FIXED) pl.direct = false;
   else if (g.d % 4 != 0) pl.direct = true;
   else if (g.d <= 2048) pl.direct = dense_strings(g) || g.d <= 512 || g.d > 1024;
   else pl.direct = dense_strings(g) && g.max_words(g.d) <= 4096 &&   // (LDS: eight wavefronts at least)
+                   (!sparse || (g.d <= 7168 ? g.s > 1 || g.d <= 3072 : 8ull * g.s * g.s > g.d)) &&
                    nb >= cus * (g.d <= 4096 ? (sparse ? 2u : 8u) : (sparse ? 4u : 24u));
   // direct: the teams a compute unit holds at once, whole passes each; else persistent teams
   // well above what is resident
@@ -379,7 +387,11 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // like s / sqrt(d) (Lemma 3.1 (iii)); above 1/8 a string has more records per
   // 256-position window than the counting apply handles well, and Code'_s has a
   // record for every coordinate; with the largest value as scale the share is larger still (14M
-  // values, d = 80, s = 1, K = 7: 323 us by the ring decoder, 91 by the tile decoder).  (The counting apply keeps a bit per message in a 32-bit
+  // values, d = 80, s = 1, K = 7: 323 us by the ring decoder, 91 by the tile decoder).  Heavy tails
+  // bring that share down, but not in every bucket, and the ring decoder waits for the longest
+  // string (8M values, K = 16, max, ring / tile: 0.1% of the values x100 d = 512, s = 4 292 / 106 us,
+  // d = 8192, s = 1 773 / 301; Student-t 222 / 95, 452 / 304; 1% x1000, all strings short, 192 / 88,
+  // 76 / 166).  (The counting apply keeps a bit per message in a 32-bit
   // word: more than 32 messages go the other way whatever the data.)
   a.kloop = (dense_strings(g) || K > 32) ? 1u : 0u;
 

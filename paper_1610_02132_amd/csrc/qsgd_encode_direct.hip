@@ -207,6 +207,21 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
 #pragma unroll
     for (int c = 0; c < CP; ++c) load_run((uint32_t)c * kStep, all_full, v[c]);
 
+    // values [at, at + kShare) of a bucket above d = 2048, four at a time
+    constexpr uint32_t kShare = 8 * kChunk;
+    auto read_share = [&](uint32_t at, auto&& take) {
+      if (at + kShare <= m) {   // (all of it requested together)
+        float4 x[8];
+#pragma unroll
+        for (uint32_t c = 0; c < 8; ++c) x[c] = load_four(at + c * kChunk + 4u * l, true);
+#pragma unroll
+        for (uint32_t c = 0; c < 8; ++c) take(x[c]);
+      } else {
+#pragma unroll 4
+        for (uint32_t e = at; e < m; e += kChunk) take(load_four(e + 4u * l, false));
+      }
+    };
+
     // ---- scale of each bucket: reduction over its LPB lanes ------------------------------
     float scale;
     // (a bucket's sum of squares is taken in one order, whichever shape the number of buckets
@@ -249,27 +264,16 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
       } else {
         // d > 2048: in the order of the encoder with a team of wavefronts per bucket, 2048 values
         // a wavefront, in chunks of 256
-        constexpr uint32_t kShare = 8 * kChunk;
         ss = 0.0;
 #pragma unroll 1
         for (uint32_t at = 0; at < m; at += kShare) {
           double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-          auto add_four = [&](const float4& x) {
+          read_share(at, [&](const float4& x) {
             s0 = square(x.x, s0);
             s1 = square(x.y, s1);
             s2 = square(x.z, s2);
             s3 = square(x.w, s3);
-          };
-          if (at + kShare <= m) {   // (all of it requested together)
-            float4 x[8];
-#pragma unroll
-            for (uint32_t c = 0; c < 8; ++c) x[c] = load_four(at + c * kChunk + 4u * l, true);
-#pragma unroll
-            for (uint32_t c = 0; c < 8; ++c) add_four(x[c]);
-          } else {
-#pragma unroll 4
-            for (uint32_t e = at; e < m; e += kChunk) add_four(load_four(e + 4u * l, false));
-          }
+          });
           ss += group_sum((s0 + s1) + (s2 + s3));
         }
       }
@@ -284,12 +288,11 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
 #pragma unroll
         for (int c = 0; c < CP; ++c) max_run(v[c]);
       } else {
-#pragma unroll 2
-        for (uint32_t c = 0; c < runs; ++c) {
-          float x8[R];
-          load_run(c * kStep, run_full(c), x8);
-          max_run(x8);
-        }
+#pragma unroll 1
+        for (uint32_t at = 0; at < m; at += kShare)
+          read_share(at, [&](const float4& x) {
+            mx = fmaxf(fmaxf(mx, fmaxf(fabsf(x.x), fabsf(x.y))), fmaxf(fabsf(x.z), fabsf(x.w)));
+          });
       }
       mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr1, 0xf>(__float_as_uint(mx))));
       mx = fmaxf(mx, __uint_as_float(dpp_fetch<kDppShr2, 0xf>(__float_as_uint(mx))));
