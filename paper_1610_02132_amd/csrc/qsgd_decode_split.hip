@@ -6,9 +6,9 @@
 // began there, and stops at the first record boundary behind them.  Then it compares where it
 // started with where the lane below stopped, and reads again from there if the two differ, until
 // no lane has to: the string's first lane starts at a true boundary, so by induction every lane
-// does then.  Prefix codes fall into step by themselves within a few records, so three to six
-// rounds are the rule; a damaged string takes at most one round per lane.  A prefix sum of the
-// positions passed gives every lane its place, and a last walk writes signed levels as bytes
+// does then.  Prefix codes fall into step by themselves within a few records, so three to five
+// rounds are the rule for strings of some 15 to 50 words and five to ten for 450 to 950; a
+// damaged string takes at most one round per lane.  A prefix sum of the positions passed gives every lane its place, and a last walk writes signed levels as bytes
 // into the message's row in LDS.  The rows of a bucket are then added up in message order in
 // registers, as in the tile decoder.
 //
@@ -47,19 +47,6 @@ namespace {
 constexpr uint32_t kBits = 10;
 constexpr uint32_t kEntries = 1u << kBits;
 
-struct Token { uint32_t value, len; };
-constexpr Token omega_of(uint32_t bits, uint32_t n) {   // code word at the top of n bits
-  uint32_t N = 1, used = 0;
-  for (;;) {
-    if (used >= n) return {0, 0};
-    if (((bits >> (n - 1 - used)) & 1u) == 0) return {N, used + 1};
-    if (used + N + 1 > n) return {0, 0};
-    const uint32_t v = (bits >> (n - used - (N + 1))) & ((1u << (N + 1)) - 1u);
-    used += N + 1;
-    N = v;
-  }
-}
-
 // Entry: bits of one / of two records (0, 4), positions passed (8, 12: 4 and 5 bits), their
 // signed levels (17, 22: 5 bits each).  A single record stands twice; length 0: none fits.
 constexpr uint32_t record_entry(bool sparse, uint32_t bits) {
@@ -94,8 +81,6 @@ struct alignas(16) Records {
 };
 __device__ const Records<QSGD_CODE_SPARSE> g_records_sparse;
 __device__ const Records<QSGD_CODE_DENSE> g_records_dense;
-
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ int32_t field5(uint32_t e, uint32_t at) {   // signed
   return (int32_t)(e << (27u - at)) >> 27;

@@ -32,7 +32,8 @@
 // Table of 2^9 / 2^10 / 2^11 entries with 3 / 3 / 2 look-ups: 111 / 110 / 142 us on the first
 // (2^11 leaves LDS for 11 wavefronts per compute unit instead of 13: its 6250 groups of
 // buckets then take three rounds instead of two).  Bytes and operations put the floor of the
-// first at 45 us (HBM); instruction issue bounds it.
+// first at 45 us (HBM); the chain of phase 1 bounds it (9.5 vector and 4.2 scalar instructions per
+// value and message, 0.48 vector instructions per SIMD and four clocks).
 #include "qsgd_device.hpp"
 #include "qsgd_kernels.hpp"
 
@@ -51,21 +52,6 @@ static_assert(kTabState >= 0x1000u && kTabState < 0x10000u, "state bit");
 
 struct TabEntry { uint32_t x, y; };
 template <int CODE> constexpr uint32_t tab_entries() { return CODE == QSGD_CODE_SPARSE ? 2 * kTabSize : kTabSize; }
-
-struct Token { uint32_t value, len; };   // len 0: the code word does not end inside the bits
-
-// Elias code word at the top of the n low bits of `bits`.
-constexpr Token omega_of(uint32_t bits, uint32_t n) {
-  uint32_t N = 1, used = 0;
-  for (;;) {
-    if (used >= n) return {0, 0};
-    if (((bits >> (n - 1 - used)) & 1u) == 0) return {N, used + 1};
-    if (used + N + 1 > n) return {0, 0};
-    const uint32_t v = (bits >> (n - used - (N + 1))) & ((1u << (N + 1)) - 1u);
-    used += N + 1;
-    N = v;
-  }
-}
 
 constexpr TabEntry tab_entry(int code, uint32_t state, uint32_t bits) {
   const bool sparse = code == QSGD_CODE_SPARSE;
@@ -125,7 +111,6 @@ constexpr uint32_t kDone = kDoneFlag / 2;      // cursors above: finished (a cur
 struct __attribute__((packed, aligned(4))) Words4 { uint32_t w[4]; };
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // LDS by its byte address: a cursor is one register then, without a base to add.
 #define QSGD_LDS __attribute__((address_space(3)))

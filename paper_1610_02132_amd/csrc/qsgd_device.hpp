@@ -168,6 +168,20 @@ __device__ __forceinline__ uint32_t omega_peek3(uint32_t w, uint32_t& len) {
   return v;
 }
 
+// Elias code word at the top of the n low bits of `bits`, for tables made by the compiler.
+struct Token { uint32_t value, len; };   // len 0: the code word does not end inside the bits
+constexpr Token omega_of(uint32_t bits, uint32_t n) {
+  uint32_t N = 1, used = 0;
+  for (;;) {
+    if (used >= n) return {0, 0};
+    if (((bits >> (n - 1 - used)) & 1u) == 0) return {N, used + 1};
+    if (used + N + 1 > n) return {0, 0};
+    const uint32_t v = (bits >> (n - used - (N + 1))) & ((1u << (N + 1)) - 1u);
+    used += N + 1;
+    N = v;
+  }
+}
+
 // Decoder rule of the recursive Elias code (App. A.2) on a 64-bit window; values
 // below 2^32.  Returns 0 for malformed input; `len` = bits used.
 __device__ __forceinline__ uint32_t omega_loop(uint64_t w, uint32_t& len) {
@@ -211,6 +225,7 @@ __device__ __forceinline__ void global_emit(uint32_t* words, uint64_t bitoff, ui
 // For data that is touched once (the gradient, x): the caches then keep what is
 // touched again, such as message strings read piece by piece.
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));   // any element's address
 __device__ __forceinline__ float4 load_stream(const float* p) {
   const v4f v = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
   return make_float4(v.x, v.y, v.z, v.w);

@@ -540,7 +540,8 @@ void k_encode_fixed_small(EncodeArgs a) {
 }
 
 // The K gradients of a double-buffered pass's chunk in one launch: a chunk of 16M values alone is
-// 16 thousand wavefronts, four rounds of what the machine holds, and ran at 3.7 TB/s; FIGURE.
+// 16 thousand wavefronts, four rounds of what the machine holds, and ran at 3.7 TB/s; eight of
+// them together (4 bits, d = 512) take 113 us, 5.2 TB/s.
 template <int LPB, int CP, int B>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(QSGD_FS_WAVES)))
 void k_encode_fixed_small_batch(EncodeArgs a, EncodeBatch batch) {

@@ -12,17 +12,19 @@
 // time, two with levels from 64 on (where such levels are possible: LONG).  Above d = 2048 a
 // bucket's runs do not fit the registers: they are read twice, the second time from the caches.
 //
-// Bound by instruction issue: about 45 vector instructions per value and lane (of those Philox 10,
-// rounding 8, code word 10), 78% of the issue slots.  25.6M values, s = 16, d = 512: 60 us through
-// the survivor ring (about 100 instructions), 42 directly; Code'_s of the same data 62 -> 36 us.
+// Bound by instruction issue: on 25.6M values, s = 16, d = 512, 51 vector instructions per value
+// and lane (of those Philox 10, rounding 8, code word 10) and 17 scalar ones, 0.8 vector
+// instructions per SIMD and four clocks.  The same data 60 us through the survivor ring, 42
+// directly; Code'_s 62 -> 36 us.
 // A copy of the bytes would take 19 us.  Per encode, before and after: 57M values, d = 2124,
 // s = 23 (max scale) 351 -> 187 us; 35M values, d = 4996, s = 11 153 -> 79 us.  (Kept in
 // registers, 4 to 16 runs: 30M of d = 8192, s = 40 177 us instead of 89.)  Levels from 64 on, 10M
 // values, largest value as scale, s = 255, d = 512 / 2048: Code_s 56 / 80 us through the survivor
 // ring, 105 / 158 one value at a time from memory, 44 / 54 two at a time; Code'_s 48 / 54, 85 /
 // 102, 35 / 43.  Bucket sizes that are no multiple of 4 pay a Philox
-// block per run and two selects per value: 20M values, d = 443, s = 11, 80 us, 261 on the general
-// path.
+// block per run and the move of its words by g0 % 4, which the compiler makes through scratch
+// memory (48 to 64 bytes per lane, a dozen stores and loads per run): 20M values, d = 443, s = 11,
+// 80 us, 261 on the general path.
 #include <type_traits>
 
 #include "qsgd_device.hpp"
@@ -32,8 +34,6 @@
 namespace qsgd {
 
 namespace {
-
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // Code word table: index gap * 64 + level * 2 + sign, entry (code << 8) | length; Code_s: gap 0
 // stands for sign and level alone, level 0 has length 0 (also at the kGuard gaps below 0, which
@@ -568,7 +568,9 @@ hipError_t launch_direct(const EncodeArgs& a, uint32_t code, uint32_t teams, hip
 // Lanes per bucket: one run of eight values (four up to d = 64) per lane up to d = 512, several
 // runs of all 64 lanes beyond.  (Two runs per lane and half the lanes per bucket at d = 512
 // share the work per bucket, but cost wavefronts: 53.7 us instead of 53.2 on 25.6M values,
-// 42.4 instead of 41.3 on 20M sparser ones.)  Few buckets: runs of four and twice the lanes
+// 42.4 instead of 41.3 on 20M sparser ones.)  Four runs of eight stay in registers for 1536 < d <=
+// 2048, although that leaves two to four wavefronts per SIMD: reading them twice instead takes 20M
+// values, s = 16, d = 1800 50.1 -> 58.7 us, Code'_s 46.5 -> 52.8, d = 2048 47.6 -> 49.5.  Few buckets: runs of four and twice the lanes
 // up to d = 256, for the shortest chain.
 static int lanes_per_bucket(uint32_t d, bool few) {
   if (d <= 64) return 16;

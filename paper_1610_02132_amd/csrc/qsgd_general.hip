@@ -1,4 +1,5 @@
-// General path: any bucket size d (d > 8192, d not a multiple of 4, d = n).
+// General path: any bucket size d (used for d > 8192, d = n among them, and for fixed width with d
+// not a multiple of 4).
 //
 // Encode.  A bucket no longer fits one workgroup's registers, so it is cut into
 // segments of 2048 values, one wavefront each, and the steps that the bucket path

@@ -46,7 +46,7 @@ def strings(P, g, base):
     (q.CODE_SPARSE, 128, 5, 4500, 4000), (q.CODE_DENSE, 100, 7, 4500, 900),
     (q.CODE_SPARSE, 256, 5, 4500, 4000), (q.CODE_DENSE, 132, 7, 4500, 4096),
     (q.CODE_SPARSE, 4096, 9, 600, 500), (q.CODE_SPARSE, 2500, 9, 600, 300),
-    (q.CODE_DENSE, 2052, 9, 2100, 700), (q.CODE_SPARSE, 8192, 12, 1100, 1000),
+    (q.CODE_DENSE, 2052, 9, 2100, 700), (q.CODE_SPARSE, 8192, 33, 1100, 1000),
     (q.CODE_SPARSE, 5000, 11, 1100, 550),
 ])
 def test_few_and_many_buckets_give_the_same_words(code, d, s, nb, few):
