@@ -239,7 +239,7 @@ void plan_encode(const Geometry& g, uint64_t ws_avail, EncodePlan& pl) {
   // d = 6400, s = 12 80 / 64): over these distributions the geometric mean of team / direct is 0.78
   // to 1.08 for d = 8192 up to s = 24, 1.0 for s = 1 from d = 4096 on (1.14 at 3000) and 1.1 to 1.9
   // for the rest, L2 and max.  Buckets that no vector load fits have no other
-  // encoder but the general path (20M values, d = 443: 261 and 80 us, d = 41: 2250 and 113).
+  // encoder but the general path (10M values, d = 443: 141 and 33 us, d = 41: 1150 and 55).
   const bool sparse = g.code == QSGD_CODE_SPARSE;
   if (g.code == QSGD_CODE_FIXED) pl.direct = false;
   else if (g.d % 4 != 0) pl.direct = true;

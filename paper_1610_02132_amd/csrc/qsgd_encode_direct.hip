@@ -22,9 +22,8 @@
 // values, largest value as scale, s = 255, d = 512 / 2048: Code_s 56 / 80 us through the survivor
 // ring, 105 / 158 one value at a time from memory, 44 / 54 two at a time; Code'_s 48 / 54, 85 /
 // 102, 35 / 43.  Bucket sizes that are no multiple of 4 pay a Philox
-// block per run and the move of its words by g0 % 4, which the compiler makes through scratch
-// memory (48 to 64 bytes per lane, a dozen stores and loads per run): 20M values, d = 443, s = 11,
-// 80 us, 261 on the general path.
+// block per run and two selects per draw word: 10M values, d = 443, s = 11, 33 us (47 with the words
+// in scratch memory, 141 on the general path), d = 41 55 (71, 1150).
 #include <type_traits>
 
 #include "qsgd_device.hpp"
@@ -327,10 +326,12 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs 
       }
       if constexpr (ODD) {   // the run's first value has word g0 % 4 of the first block
         const bool one = (g0 & 1u) != 0, two = (g0 & 2u) != 0;
+        // (values to choose from, not places: a choice of places keeps r in scratch memory)
+        auto choose = [](bool take, uint32_t then, uint32_t other) { return take ? then : other; };
 #pragma unroll
-        for (int j = 0; j < R + 2; ++j) r[j] = one ? r[j + 1] : r[j];
+        for (int j = 0; j < R + 2; ++j) r[j] = choose(one, r[j + 1], r[j]);
 #pragma unroll
-        for (int j = 0; j < R; ++j) r[j] = two ? r[j + 2] : r[j];
+        for (int j = 0; j < R; ++j) r[j] = choose(two, r[j + 2], r[j]);
       }
 #pragma unroll
       for (int j = 0; j < R; ++j) {
