@@ -118,8 +118,12 @@ __device__ __forceinline__ uint32_t group_last(uint32_t v, int last_lane) {
 // LONG: with the coder of long code words, which costs 25.6M values, s = 16, d = 512 50.1 -> 51.0
 // us and d = 2048 55.6 -> 62.6; without it the few runs of more than 64 bits are read again by a
 // small general coder.
+// (Above d = 2048 the loads of the first reading would cost the fifth wavefront per SIMD: 20M values,
+// s = 16, without / with the bound: d = 2052 60 / 55 us, 3000 53 / 54, 8192 72 / 73, Code'_s 53 / 49
+// and 48 / 47.)
 template <int LPB, int CP, int Q, int CODE, bool ODD, bool LONG>
-__global__ __launch_bounds__(64 * kDirectWaves) void k_encode_direct(EncodeArgs a) {
+__global__ __launch_bounds__(64 * kDirectWaves) __attribute__((amdgpu_waves_per_eu(CP == 0 ? 5 : 1)))
+void k_encode_direct(EncodeArgs a) {
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
   constexpr uint32_t NB = 64 / LPB;             // buckets per wavefront pass
   constexpr int R = 4 * Q;                      // values of a run
