@@ -88,7 +88,7 @@ __device__ __forceinline__ int32_t field5(uint32_t e, uint32_t at) {   // signed
 
 // LDS, in words: rows, then per message of a batch (scale, first word, words, first and end bit,
 // position before, position behind, first unit), a total, per unit (end of the last lane,
-// positions passed), and what the next turn goes on from.
+// positions passed), what the next turn goes on from, and the status word.
 constexpr uint32_t kPerRow = 8, kPerUnit = 2, kMore = 4;
 constexpr uint32_t kLast = 0xFFFFFFFFu;   // position behind: the string's end, wherever it is
 
@@ -109,7 +109,7 @@ __device__ __forceinline__ uint32_t entry_before(const uint32_t* list, uint32_t 
 template <int CODE, int NG, bool LONGB>
 __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a) {
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
-  __shared__ uint32_t table[kEntries], damaged;
+  __shared__ uint32_t table[kEntries];
   const uint32_t status = *a.status;
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, threads = blockDim.x;
@@ -128,6 +128,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
   uint32_t* const carry = s_unit + rows + 1u;        // 2: entry and position of the next turn's first unit
   uint32_t* const u_exit = carry + 2;
   uint32_t* const u_adv = u_exit + slots;
+  uint32_t* const damaged = u_adv + slots;
   const uint32_t slot = tid / lanes, l = lane & (lanes - 1u);
   const uint64_t pay = (uint64_t)H_WORDS + a.table_words;
 
@@ -140,11 +141,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
       table[i] = e;
     }
     for (uint32_t i = tid; i < rows * row_words; i += threads) smem[i] = 0;
-    if (tid == 0) damaged = status;
+    if (tid == 0) *damaged = status;
   }
   // (other workgroups set the status word meanwhile: a workgroup's wavefronts leave together)
   __syncthreads();
-  if (damaged) return;
+  if (*damaged) return;
 
   const uint32_t segs = LONGB ? (a.d - 1u) / kSeg + 1u : 1u;   // (a.nb * segs < 2^32)
   for (uint32_t task = blockIdx.x; task < a.nb * segs; task += gridDim.x) {

@@ -104,6 +104,7 @@ constexpr uint32_t kPiece = 4;                 // words fetched at a time
 constexpr uint32_t kRingSlots = kStrRing + 1;
 constexpr uint32_t kWaveBytes = kTileBytes + 4 * 64 * kRingSlots + 4 * 64;
 static_assert(kWaveBytes % 16 == 0 && kRowBytes % 4 == 0 && kTileBytes % 16 == 0, "alignment");
+constexpr uint32_t kFlagBytes = 16;            // behind the wavefronts' parts: one word for all of them
 constexpr uint32_t kSteps = 4;                 // steps between two top-ups of the string rings
 constexpr uint32_t kDoneFlag = 0x40000000u;    // added to a finished lane's cursor
 constexpr uint32_t kDone = kDoneFlag / 2;      // cursors above: finished (a cursor moves back by d at most)
@@ -131,14 +132,14 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
   constexpr uint32_t kEntries = tab_entries<CODE>();
   __shared__ uint4 table[kEntries / 2];
-  __shared__ uint32_t damaged;
   const uint32_t status = *a.status;
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // per wavefront: tile, string rings, scales
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // per wavefront: tile, string rings, scales; a word
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
   const uint32_t waves = blockDim.x >> 6;
   const uint32_t tab = lds_address(table);
   const uint32_t tile = lds_address(lds) + wave * kWaveBytes;
+  QSGD_LDS uint32_t* const damaged = lds_at<uint32_t>(lds_address(lds) + waves * kWaveBytes);
   const uint32_t scales = tile + kTileBytes + 4u * 64u * kRingSlots;
   const uint32_t K = a.K, gw = a.gw, s = a.s;
   const uint32_t K4 = K < 4u ? K : (K + 3u) & ~3u;   // stride of a bucket's scales
@@ -151,13 +152,14 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
   const uint32_t tasks = (a.nb + gw - 1) / gw;
   const uint32_t* const msg = a.msgs[g < gw ? k : 0u];
   const uint64_t msg_words = a.msg_words[g < gw ? k : 0u];
+  const bool has_table = msg_words >= pay;   // (whatever the header check found: asked before its word is known)
 
   // this lane's entry of the offset table and extent of its bucket, one group ahead
   uint32_t n_o0 = 0, n_o1 = 0, n_base = 0, n_m = 0;
   auto request_task = [&](uint32_t task) {
     n_o0 = n_o1 = n_base = n_m = 0;
     const uint32_t b = task * gw + g;
-    if (task < tasks && g < gw && b < a.nb) {
+    if (task < tasks && g < gw && b < a.nb && has_table) {
       uint64_t base;
       bucket_extent(a, b, base, n_m);
       n_base = (uint32_t)base;              // (n < 2^32)
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
     }
   };
   uint32_t task = blockIdx.x * waves + wave;
-  if (status == 0) request_task(task);
+  request_task(task);
 
   {
     // two entries per load, eight loads in flight; a level above s is for the general reader
@@ -189,14 +191,12 @@ __global__ __launch_bounds__(64 * kTileMaxWaves) void k_decode_tile(DecodeArgs a
       }
     }
     for (uint32_t j = lane; j < kTileBytes / 4u; j += kWave) *lds_at<uint32_t>(tile + 4u * j) = 0u;
-    if (tid == 0) damaged = status;
+    if (tid == 0) *damaged = status;
   }
   // Other workgroups set the status word meanwhile: the wavefronts go by what the first one
-  // read, since a part of the table would be missing without one of them.  (A word set that
-  // late stems from this launch, and the headers are sound.)
+  // read, since a part of the table would be missing without one of them.
   __syncthreads();
-  if (damaged) return;
-  if (status != 0) request_task(task);
+  if (*damaged) return;
 
   for (; task < tasks; task += gridDim.x * waves) {
     const uint32_t gcount = min(gw, a.nb - task * gw);
@@ -500,7 +500,7 @@ namespace {
 template <int CODE>
 hipError_t launch_tile(const DecodeArgs& a, uint32_t blocks, uint32_t waves, hipStream_t st) {
   const dim3 grid(blocks), block(64 * waves);
-  const size_t lds = waves * (size_t)kWaveBytes;
+  const size_t lds = waves * (size_t)kWaveBytes + kFlagBytes;
   if (a.gw <= 2) hipLaunchKernelGGL((k_decode_tile<CODE, 1>), grid, block, lds, st, a);
   else if (a.gw <= 4) hipLaunchKernelGGL((k_decode_tile<CODE, 2>), grid, block, lds, st, a);
   else hipLaunchKernelGGL((k_decode_tile<CODE, 4>), grid, block, lds, st, a);
@@ -512,7 +512,7 @@ hipError_t launch_tile(const DecodeArgs& a, uint32_t blocks, uint32_t waves, hip
 uint32_t tile_max_waves(uint32_t code) {
   const uint32_t table = 8u * (code == QSGD_CODE_SPARSE ? tab_entries<QSGD_CODE_SPARSE>()
                                                         : tab_entries<QSGD_CODE_DENSE>());
-  const uint32_t fit = (160u * 1024u - table) / kWaveBytes;
+  const uint32_t fit = (160u * 1024u - table - kFlagBytes) / kWaveBytes;
   return fit < kTileMaxWaves ? fit : kTileMaxWaves;
 }
 
