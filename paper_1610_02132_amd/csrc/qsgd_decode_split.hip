@@ -341,8 +341,9 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
         if (!idle) {
           walk(std::true_type{}, start);
           bool bad;
+          // (every lane asks: positions are counted in 32 bits and could come round by the last one)
           if (kSparse || next != kLast)
-            bad = fail || (final_word && (exit_was != end || start + adv > M || (next != kLast && start + adv != next)));
+            bad = fail || start + adv > M || (final_word && (exit_was != end || (next != kLast && start + adv != next)));
           // (what stands behind the bucket's last record of Code'_s is padding)
           else
             bad = (fail && start + adv < M) || (final_word && start + adv < M) ||
