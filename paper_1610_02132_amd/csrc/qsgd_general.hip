@@ -868,9 +868,10 @@ __global__ __launch_bounds__(64) void k_sparse_list(DecodeArgs a, uint32_t* area
             lev = omega_peek3(w << 1, ll);
           }
           at_bit += gl + 1u + ll;
-          at_pos += gap;
-          const bool good = (gap != 0) & (lev != 0) & (lev <= a.s) & (at_pos <= m) & (gap <= m) &
+          // (not the new position <= m: it is counted in 32 bits and could come round)
+          const bool good = (gap != 0) & (lev != 0) & (lev <= a.s) & (gap <= m - at_pos) &
                             (at_bit <= stop_bit);
+          at_pos += gap;
           const float mag = sr.scale * (float)lev;
           rpos[cnt * 64 + lane] = at_pos - 1u;
           rval[cnt * 64 + lane] = (w >> 31) ? -mag : mag;
@@ -885,8 +886,8 @@ __global__ __launch_bounds__(64) void k_sparse_list(DecodeArgs a, uint32_t* area
           const uint32_t w = (uint32_t)(peek64(sr.str, sr.nwords, bitpos + gl) >> 32);
           const uint32_t lev = omega_peek3(w << 1, ll);
           bitpos += gl + 1u + ll;
+          ok = gap != 0 && lev != 0 && lev <= a.s && gap <= m - at_pos && bitpos <= stop;
           at_pos += gap;
-          ok = gap != 0 && lev != 0 && lev <= a.s && gap <= m && at_pos <= m && bitpos <= stop;
           if (ok) {
             const float mag = sr.scale * (float)lev;
             rpos[cnt * 64 + lane] = at_pos - 1u;

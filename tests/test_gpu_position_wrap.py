@@ -56,3 +56,14 @@ def test_short_bucket(d):
     status, x = step(P, msg)
     assert status == 0 and x.nonzero().flatten().tolist() == [4, 104]
 
+
+def test_long_bucket_of_more_than_2_31_values():
+    n = (1 << 31) + 2000
+    P, msg = message(n, n, [(1 << 31) + 1000, 1 << 31], entries=())
+    status, x = step(P, msg)
+    assert status == -3
+    assert not bool(x[:4096].any()) and not bool(x[1 << 31:].any())
+    P, msg = message(n, n, [7, (1 << 31) + 1000], entries=())
+    status, x = step(P, msg)
+    assert status == 0
+    assert float(x[6]) == 1.0 and float(x[(1 << 31) + 1006]) == 1.0 and int(x[:1 << 20].count_nonzero()) == 1
