@@ -1059,13 +1059,14 @@ __global__ __launch_bounds__(1024) void k_sparse_resolve(DecodeArgs a, uint32_t*
       }
       return;
     }
-    for (uint32_t p = threadIdx.x; p < m; p += blockDim.x) acc[p] = 0.f;
+    // (64 bits: a bucket may have 2^32 - 1 values, and the step past its end would come round)
+    for (uint64_t p = threadIdx.x; p < m; p += blockDim.x) acc[p] = 0.f;
     __syncthreads();
     if (!open_strings(a, b, refs, &bad) || !parse_in_turns(a, refs, m, acc, &bad)) {
       if (threadIdx.x == 0) flag_corrupt(a.status);
       return;
     }
-    for (uint32_t p = threadIdx.x; p < m; p += blockDim.x) x[p] = updated(a, x[p], acc[p]);
+    for (uint64_t p = threadIdx.x; p < m; p += blockDim.x) x[p] = updated(a, x[p], acc[p]);
     return;
   }
   for (uint32_t e = threadIdx.x; e < L; e += blockDim.x) {

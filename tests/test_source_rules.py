@@ -50,3 +50,12 @@ def test_wavefronts_of_a_workgroup_leave_together():
             assert not alone, f"{file}: {name} leaves wavefront by wavefront"
     for name in ("k_decode_split", "k_decode_tile", "k_sparse_resolve", "k_gen_parse_entries", "k_raw_apply"):
         assert name in seen
+
+
+def test_loops_over_a_long_buckets_values_count_in_64_bits():
+    """A bucket of the general path has up to 2^32 - 1 values: an index of 32 bits that a stride takes
+    past such an end starts over, and the loop does not end."""
+    text = re.sub(r"//[^\n]*", "", open(os.path.join(CSRC, "qsgd_general.hip")).read())
+    loops = re.findall(r"for \((\w+) (\w+) = [^;]*threadIdx\.x[^;]*; \2 < (?:m|a\.n); \2 \+= ", text)
+    assert len(loops) >= 3
+    assert all(kind == "uint64_t" for kind, _ in loops), loops
