@@ -750,6 +750,7 @@ __device__ __forceinline__ CollideList collide_list(uint8_t* lists, uint64_t b) 
 // A bucket's share of the accumulator area, m words: two bitmaps, a counter per message, the
 // messages' lists of records (two words each), and an accumulator for every coordinate that two
 // messages can name (half as many as there are records).  cap 0: too small a bucket for that.
+__host__ __device__ constexpr uint32_t bitmap_words(uint32_t m) { return (m >> 5) + (m % 32u ? 1u : 0u); }   // (m + 31 can overflow)
 struct SparseArea {
   uint32_t *seen, *multi, *count;
   uint32_t fixed;   // words in front of the lists
@@ -762,7 +763,7 @@ struct SparseArea {
 __device__ __forceinline__ SparseArea sparse_area(uint32_t* area, uint64_t base, uint32_t m,
                                                   uint32_t K) {
   SparseArea s;
-  const uint32_t mw = (m + 31u) >> 5;
+  const uint32_t mw = bitmap_words(m);
   s.seen = area + base;
   s.multi = s.seen + mw;
   s.count = s.multi + mw;
@@ -775,7 +776,7 @@ __device__ __forceinline__ SparseArea sparse_area(uint32_t* area, uint64_t base,
 
 __global__ __launch_bounds__(256) void k_sparse_clear(DecodeArgs a, uint32_t* area, uint8_t* lists) {
   if (blockIdx.x == 0) check_headers(a);
-  const uint32_t per = 2u * ((a.d + 31u) >> 5) + a.K;   // words of a full bucket
+  const uint32_t per = 2u * bitmap_words(a.d) + a.K;   // words of a full bucket
   const uint64_t total = (uint64_t)a.nb * per;
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total;
        i += (uint64_t)gridDim.x * 256) {
@@ -1008,7 +1009,7 @@ __global__ __launch_bounds__(1024) void k_sparse_resolve(DecodeArgs a, uint32_t*
     if (!overflow) {
       // the collision list alone was too short: the coordinates in `multi` remain.  `seen` has
       // done its work and takes the number of them before every word of the bitmap.
-      const uint32_t mw = (m + 31u) >> 5, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+      const uint32_t mw = bitmap_words(m), lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
       constexpr uint32_t kPer = 8;   // words per thread and trip
       uint32_t before = 0;
       for (uint32_t w0 = 0; w0 < mw; w0 += 1024u * kPer) {
@@ -1188,7 +1189,7 @@ hipError_t launch_gen_parse(const DecodeArgs& a, float* acc, bool entries, hipSt
 // area: n words; lists: a.nb x kCollideBytes behind it; chunks: wavefronts per string.
 hipError_t launch_sparse_long(const DecodeArgs& a, uint32_t* area, uint8_t* lists, uint32_t cus,
                               uint32_t chunks, hipStream_t st) {
-  const uint64_t clear = (uint64_t)a.nb * (2u * ((a.d + 31u) >> 5) + a.K);
+  const uint64_t clear = (uint64_t)a.nb * (2u * bitmap_words(a.d) + a.K);
   const uint64_t most = (uint64_t)cus * 32;
   const uint32_t blocks = (uint32_t)((clear + 255) / 256 < most ? (clear + 255) / 256 : most);
   hipLaunchKernelGGL(k_sparse_clear, dim3(blocks), dim3(256), 0, st, a, area, lists);

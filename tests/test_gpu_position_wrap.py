@@ -67,3 +67,14 @@ def test_long_bucket_of_more_than_2_31_values():
     status, x = step(P, msg)
     assert status == 0
     assert float(x[6]) == 1.0 and float(x[(1 << 31) + 1006]) == 1.0 and int(x[:1 << 20].count_nonzero()) == 1
+
+
+@pytest.mark.parametrize("n", [(1 << 32) - 1, (1 << 32) - 31])
+def test_the_longest_buckets(n):
+    """Buckets whose length plus 31 does not fit 32 bits: bitmaps, lists and x keep apart."""
+    at = [3, 41, 42, 300, 70_000, (1 << 31) + 5, n]
+    P, msg = message(n, n, [b - a for a, b in zip([0] + at, at)], entries=())
+    status, x = step(P, msg)
+    assert status == 0
+    assert [float(x[i - 1]) for i in at] == [1.0] * len(at)
+    assert int(x[:1 << 20].count_nonzero()) == 5 and int(x[-(1 << 20):].count_nonzero()) == 1
