@@ -198,18 +198,17 @@ double shortest_string(const Geometry& g, const size_t* msg_bytes, uint32_t K) {
   return std::max(1.0, (words - H_WORDS - (double)g.table_words) / (double)std::max<uint64_t>(g.nb, 1));
 }
 
-// Whether a lane for every word of the strings (split decoder) beats a lane for every string.
-// With few strings the latter takes as long as its longest string, 0.64 us per word (tile decoder) or
-// 1.7 us (ring decoder, sparse strings), measured from 5 to 470 words; the former takes some
-// 12 us more than a launch does and works off about 10 thousand words per us (6 thousand of
-// sparse strings, whose records need the general reader).  Step, us, lane per string / split:
-//   d = 512, s = 16 (37 words): 78 strings 33 / 18, 4096 strings 32 / 24, 16384 strings 34 / 62
+// About how long the decoders with a lane for every string take (us): as long as the longest string,
+// 1.7 us per word (ring decoder, sparse strings), or at least the windows of a bucket (tile decoder:
+// 0.64 us per word, 0.042 per value, whichever is more, and 2.2 values per ns where the machine is full).
+// The split decoder's plan has its own estimate.  Step, us, lane per string / split:
+//   d = 512, s = 16 (37 words): 48 strings 34 / 17, 3128 strings 33 / 23, 16384 strings 34 / 62
 //   d = 8192, s = 40 (466 words): 4 strings 294 / 42, 4096 strings 347 / 192, 8192 strings 342 / 382
 //   d = 8192, s = 4 (102 words, ring): 4 strings 170 / 30, 8192 strings 347 / 170
-bool split_pays(const Geometry& g, uint32_t K, bool tile) {
-  const double words = string_words(g), strings = (double)g.nb * K;
-  if (tile) return 12.0 + strings * words / 10000.0 < 5.0 + 0.64 * words;
-  return 17.0 + strings * words / 6000.0 < 3.0 + 1.7 * words;
+float per_string_us(const Geometry& g, uint32_t K, bool tile) {
+  const float words = (float)string_words(g), d = (float)g.d;
+  if (tile) return std::max(5.f + 0.64f * words, 7.f + 0.042f * d) + (float)g.nb * (float)K * d / 2.2e6f;
+  return 3.f + 1.7f * words;
 }
 
 // Dense strings: the share of nonzero levels grows like s / sqrt(d) (Lemma 3.1 (iii)); with the
@@ -428,9 +427,12 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // message, is left with the rest: 573 thousand values in one bucket, Code'_s, s = 127, K = 7:
   // 17.6 ms there, 65 us in the split decoder.)
   const bool bytes = g.code != QSGD_CODE_FIXED && g.s <= 127;
-  if (bytes && g.d <= kMaxBucketFast && split_pays(g, K, a.kloop || g.d % 4)) {
-    ScopedTiming tm("decode_elias", st);
-    return launch_decode_split(a, cus, string_words(g), st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
+  if (bytes && g.d <= kMaxBucketFast) {
+    const SplitPlan p = plan_decode_split(a, cus, string_words(g));
+    if (p.us < per_string_us(g, K, a.kloop || g.d % 4)) {
+      ScopedTiming tm("decode_elias", st);
+      return launch_decode_split(a, p, st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
+    }
   }
   if (bytes && g.d <= kMaxBucketFast && (a.kloop || g.d % 4)) {
     // dense strings, and bucket sizes that the ring decoder's loads do not fit: the tile
@@ -460,7 +462,7 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     float* acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes);
     if (bytes && g.d > kEntryMinD && g.d * g.per_elem < 0xF0000000ull) {   // (bit positions in 32 bits)
       a.acc = acc;
-      if (launch_decode_split(a, cus, string_words(g), st) != hipSuccess ||
+      if (launch_decode_split(a, plan_decode_split(a, cus, string_words(g)), st) != hipSuccess ||
           launch_gen_apply(a, acc, blocks, st) != hipSuccess)
         return QSGD_ERR_HIP;
       return QSGD_OK;

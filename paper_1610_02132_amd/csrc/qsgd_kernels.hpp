@@ -170,8 +170,9 @@ struct DecodeArgs {
   uint32_t rec;          // record slots per string (message-by-message apply)
   uint32_t kloop;        // 1: records are applied message by message (dense messages)
   uint32_t q16;          // 1: 16-bit records (counting apply, s <= 4)
-  // few strings: lanes that share a string, messages whose rows are in LDS at once
-  uint32_t lanes, rows;
+  // few strings: lanes that share a string, messages whose rows are in LDS at once, words of
+  // theirs that are worked on at a time
+  uint32_t lanes, rows, turn_words;
   float* acc;            // buckets above kEntryMinD: where their sums go
   // fixed width
   uint32_t fixed_bits;
@@ -286,8 +287,15 @@ hipError_t launch_decode_fixed(const DecodeArgs& a, uint32_t blocks, hipStream_t
 hipError_t launch_decode_elias(const DecodeArgs& a, uint32_t blocks, size_t lds, hipStream_t st);
 hipError_t launch_decode_tile(const DecodeArgs& a, uint32_t blocks, uint32_t waves, hipStream_t st);
 constexpr uint32_t kSplitWaves = 16;         // most wavefronts of the split decoder's workgroup
+struct SplitPlan {
+  bool bits;                          // a lane for every bit of the strings, else for every word
+  uint32_t lanes, rows, turn_words;   // (see DecodeArgs)
+  uint32_t waves, blocks, lds;
+  float us;                           // about how long it takes
+};
 // `words`: about how long a string is
-hipError_t launch_decode_split(DecodeArgs& a, uint32_t cus, uint32_t words, hipStream_t st);
+SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words);
+hipError_t launch_decode_split(DecodeArgs& a, const SplitPlan& p, hipStream_t st);
 constexpr uint32_t kTileMaxWaves = 13;       // wavefronts of the tile decoder's largest workgroup
 uint32_t tile_max_waves(uint32_t code);      // ... and what LDS holds of them
 
