@@ -677,6 +677,7 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
     a.header = header; a.table = table; a.payload = payload;
     a.cap_words = cap_words; a.table_words = g.table_words;
     a.partial = reinterpret_cast<double*>(wsb + gp.off_partial);
+    a.words = reinterpret_cast<uint32_t*>(wsb + gp.off_partial);
     a.scale = reinterpret_cast<float*>(wsb + gp.off_scale);
     a.seginfo = reinterpret_cast<uint32_t*>(wsb + gp.off_seginfo);
     a.segstart = reinterpret_cast<uint64_t*>(wsb + gp.off_segstart);
@@ -684,21 +685,16 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
     a.segrank = reinterpret_cast<uint32_t*>(wsb + gp.off_segrank);
     a.segprev = reinterpret_cast<uint32_t*>(wsb + gp.off_segprev);
     a.bents = reinterpret_cast<uint32_t*>(wsb + gp.off_bents);
-    a.entries = (g.code != QSGD_CODE_FIXED && g.d > kEntryMinD) ? 1u : 0u;
     a.slots = reinterpret_cast<uint32_t*>(wsb + gp.off_slots);
     a.fixed_bits = g.fixed_bits;
     a.fixed_words_full = g.max_words(g.d);
     a.fixed_payload_words = g.code == QSGD_CODE_FIXED ? g.max_payload_words() : 0;
     const bool aligned = g.d % 4 == 0;
     ScopedTiming tm("encode_general", st);
-    if (launch_gen_partial(a, st) != hipSuccess) return QSGD_ERR_HIP;
     if (launch_gen_scale(a, st) != hipSuccess) return QSGD_ERR_HIP;
     if (launch_gen_encode(a, aligned, st) != hipSuccess) return QSGD_ERR_HIP;
     if (g.code != QSGD_CODE_FIXED) {
-      if (launch_gen_scan(a, st) != hipSuccess) return QSGD_ERR_HIP;
-      const uint32_t fill_blocks =
-          (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, (cap_words + 2047) / 2048), 4096);
-      if (launch_gen_fill(a, fill_blocks, st) != hipSuccess) return QSGD_ERR_HIP;
+      if (launch_gen_scan(a, (uint32_t)device_cus(), st) != hipSuccess) return QSGD_ERR_HIP;
       if (launch_gen_place(a, st) != hipSuccess) return QSGD_ERR_HIP;
     }
     return QSGD_OK;

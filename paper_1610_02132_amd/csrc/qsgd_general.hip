@@ -4,15 +4,16 @@
 // Encode.  A bucket no longer fits one workgroup's registers, so it is cut into
 // segments of 2048 values, one wavefront each, and the steps that the bucket path
 // does inside a workgroup become kernels:
-//   partial  per-segment sum of squares (fp64) or max            -> workspace
-//   scale    per-bucket reduction of the partials, s/scale
+//   partial  sum of squares (fp64) or max of every group of up to sixteen segments -> workspace
+//   scale    (buckets of several groups) their sum
 //   encode   per-segment sub-stream (same wavefront code as the bucket path, with
-//            code words wide enough for 32-bit gaps)              -> workspace slot
-//   scan     one workgroup walks the segments in order: which nonzero precedes a
-//            segment's first one (max-scan), the bit offset of every segment in
-//            its bucket string (sum-scan), the word offset of every bucket
-//   fill     zeroes the payload
-//   place    per segment: ORs gap code, sub-stream and stop bit into the payload
+//            code words wide enough for 32-bit gaps) -> workspace slot
+//   scan     a workgroup per bucket walks its segments in order: which nonzero precedes a
+//            segment's first one (max-scan), the bit offset of every segment in the
+//            bucket string (sum-scan), the entry points
+//   table    (several buckets) the word offset of every bucket; it, or `scan`, clears the
+//            words that segments share
+//   place    per segment: gap code, sub-stream and stop bit into the payload, shared words by OR
 // Decode.  Records are added to a dense fp32 accumulator in the workspace, bucket by
 // bucket and inside a bucket message after message (so every coordinate's sum has
 // the order k = 0, 1, ...); a last kernel applies the accumulator to x.  Buckets
@@ -69,69 +70,26 @@ __device__ __forceinline__ float4 load_quad_any(const float* __restrict__ g, uin
   return v;
 }
 
-// Inclusive scans over a 1024-thread workgroup (16 wavefronts).
-// 64-bit value of the lane a DPP control names (0 where there is none).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ unsigned long long dpp_fetch_u64(unsigned long long v) {
-  const uint32_t lo = dpp_fetch<CTRL, ROW_MASK>((uint32_t)v);
-  const uint32_t hi = dpp_fetch<CTRL, ROW_MASK>((uint32_t)(v >> 32));
-  return ((unsigned long long)hi << 32) | lo;
-}
-
-// (the operations used here have 0 as their identity: sums and maxima of unsigned values)
-template <typename T, typename Op>
-__device__ __forceinline__ T block_incl_scan(T v, T identity, T* wave_tot, Op op) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  v = op(v, dpp_fetch_u64<kDppShr1, 0xf>(v));
-  v = op(v, dpp_fetch_u64<kDppShr2, 0xf>(v));
-  v = op(v, dpp_fetch_u64<kDppShr4, 0xf>(v));
-  v = op(v, dpp_fetch_u64<kDppShr8, 0xf>(v));
-  v = op(v, dpp_fetch_u64<kDppBcast15, 0xa>(v));
-  v = op(v, dpp_fetch_u64<kDppBcast31, 0xc>(v));
-  // (wave_tot is free here: every call ends with a barrier after its reads)
-  if (lane == 63) wave_tot[wave] = v;
-  __syncthreads();
-  T pre = identity;
-  for (int w = 0; w < wave; ++w) pre = op(pre, wave_tot[w]);
-  __syncthreads();
-  return op(pre, v);
-}
-
-struct OpSum { __device__ unsigned long long operator()(unsigned long long a, unsigned long long b) const { return a + b; } };
-struct OpMax { __device__ unsigned long long operator()(unsigned long long a, unsigned long long b) const { return a > b ? a : b; } };
-
 }  // namespace
 
 // ---- encode --------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256) void k_gen_partial(GenArgs a) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t seg = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (seg >= a.nseg) return;
-  const SegRef r = seg_ref(a, seg);
-  double ss = 0.0;
-  float mx = 0.f;
-  for (int c = 0; c < kSegChunks; ++c) {
-    const uint32_t e = (uint32_t)c * kChunk + lane * 4;
-    if ((uint32_t)c * kChunk >= r.len) break;
-    const float4 v = load_quad_any(a.g, r.gidx0, e, r.len);
-    if (a.norm_mode == 0) {
-      ss = fma((double)v.x, (double)v.x, ss);
-      ss = fma((double)v.y, (double)v.y, ss);
-      ss = fma((double)v.z, (double)v.z, ss);
-      ss = fma((double)v.w, (double)v.w, ss);
-    } else {
-      mx = fmaxf(fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
-    }
-  }
-  if (a.norm_mode == 0) ss = wave_sum_f64(ss);
-  else ss = (double)wave_max_f32(mx);
-  if (lane == 0) a.partial[seg] = ss;
-}
+namespace {
 
-__global__ __launch_bounds__(256) void k_gen_scale(GenArgs a) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t b = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+// Segments of a bucket are added up in groups of G = 1, 2, 4, 8 or 16 (what a bucket has, or
+// sixteen), a wavefront each; the groups of a bucket follow each other in `partial`.
+constexpr uint32_t kPartialWaves = 16;
+__host__ __device__ inline uint32_t group_size(uint64_t spb) { return spb >= 9 ? 16u : spb >= 5 ? 8u : spb >= 3 ? 4u : (uint32_t)spb; }
+__host__ __device__ inline uint64_t groups_of(uint64_t spb) { const uint32_t G = group_size(spb); return (spb + G - 1) / G; }
+
+}  // namespace
+
+// Also writes the header and, fixed width, "no escape" into every bucket's string.  (13M values: 10 us,
+// the bytes alone take 8 at the rate the card reads.)
+__global__ __launch_bounds__(64 * kPartialWaves) void k_gen_partial(GenArgs a) {
+  __shared__ double sums[kPartialWaves];
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     uint32_t* h = a.header;
     h[H_MAGIC] = kMagic; h[H_VERSION] = 1; h[H_CODE] = a.code; h[H_NORM] = a.norm_mode;
@@ -143,44 +101,76 @@ __global__ __launch_bounds__(256) void k_gen_scale(GenArgs a) {
     h[H_PW_HI] = (uint32_t)(a.fixed_payload_words >> 32);
     h[H_STATUS] = 0; h[H_ITER] = a.iteration;
   }
-  if (b >= a.nb) return;
-  // sixteen independent chains per lane, their loads in flight together: with thousands of
-  // segments in one bucket the memory latency of each trip sets the pace
-  constexpr int kChains = 16;
-  double accs[kChains];
+  const uint32_t G = group_size(a.spb);
+  const uint64_t gpb = groups_of(a.spb);
+  const uint64_t group = (uint64_t)blockIdx.x * (kPartialWaves / G) + wave / G;
+  const uint64_t b = group / gpb;
+  const uint64_t j = (group - b * gpb) * G + wave % G;
+  double ss = 0.0;
+  if (b < a.nb && j < a.spb) {
+    const SegRef r = seg_ref(a, b * a.spb + j);
+    const float* const g = a.g + r.gidx0;
+    float4 v[kSegChunks];
+    if (r.len == kSeg) {
 #pragma unroll
-  for (int t = 0; t < kChains; ++t) accs[t] = 0.0;
-  uint64_t j = lane;
-  for (; j + (kChains - 1) * kWave < a.spb; j += kChains * kWave) {
-    double p[kChains];
+      for (int c = 0; c < kSegChunks; ++c) {
+        const v4f_any x = *reinterpret_cast<const v4f_any*>(g + (uint32_t)c * kChunk + lane * 4u);
+        v[c] = make_float4(x.x, x.y, x.z, x.w);
+      }
+    } else {
 #pragma unroll
-    for (int t = 0; t < kChains; ++t) p[t] = a.partial[b * a.spb + j + (uint64_t)t * kWave];
-#pragma unroll
-    for (int t = 0; t < kChains; ++t)
-      accs[t] = a.norm_mode == 0 ? accs[t] + p[t] : fmax(accs[t], p[t]);
-  }
-  for (; j < a.spb; j += kWave) {
-    const double p = a.partial[b * a.spb + j];
-    accs[0] = a.norm_mode == 0 ? accs[0] + p : fmax(accs[0], p);
-  }
-#pragma unroll
-  for (int w = kChains / 2; w >= 1; w /= 2) {
-#pragma unroll
-    for (int t = 0; t < w; ++t)
-      accs[t] = a.norm_mode == 0 ? accs[t] + accs[t + w] : fmax(accs[t], accs[t + w]);
-  }
-  const double acc = accs[0];
-  float scale;
-  if (a.norm_mode == 0) scale = (float)sqrt(wave_sum_f64(acc));
-  else scale = wave_max_f32((float)acc);
-  if (lane == 0) {
-    a.scale[b] = scale;
-    if (a.code == QSGD_CODE_FIXED) {
-      uint32_t* str = a.payload + b * a.fixed_words_full;
-      str[0] = __float_as_uint(scale);
-      str[1] = 0xFFFFFFFFu;
+      for (int c = 0; c < kSegChunks; ++c)
+        v[c] = load_quad_any(a.g, r.gidx0, (uint32_t)c * kChunk + lane * 4u, r.len);
     }
+    if (a.norm_mode == 0) {
+      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+      for (int c = 0; c < kSegChunks; ++c) {
+        s0 = fma((double)v[c].x, (double)v[c].x, s0);
+        s1 = fma((double)v[c].y, (double)v[c].y, s1);
+        s2 = fma((double)v[c].z, (double)v[c].z, s2);
+        s3 = fma((double)v[c].w, (double)v[c].w, s3);
+      }
+      ss = wave_sum_f64((s0 + s1) + (s2 + s3));
+    } else {
+      float mx = 0.f;
+#pragma unroll
+      for (int c = 0; c < kSegChunks; ++c)
+        mx = fmaxf(fmaxf(mx, fmaxf(fabsf(v[c].x), fabsf(v[c].y))), fmaxf(fabsf(v[c].z), fabsf(v[c].w)));
+      ss = (double)wave_max_f32(mx);
+    }
+    if (j == 0 && a.code == QSGD_CODE_FIXED && lane == 0) a.payload[b * a.fixed_words_full + 1u] = 0xFFFFFFFFu;
   }
+  if (lane == 0) sums[wave] = ss;
+  __syncthreads();
+  if (wave % G == 0 && lane == 0 && b < a.nb) {
+    double t = sums[wave];
+    for (uint32_t w = 1; w < G; ++w) t = a.norm_mode == 0 ? t + sums[wave + w] : fmax(t, sums[wave + w]);
+    if (gpb == 1) a.scale[b] = a.norm_mode == 0 ? (float)sqrt(t) : (float)t;
+    else a.partial[group] = t;
+  }
+}
+
+// A workgroup per bucket adds up its groups.  (One wavefront took 7.6 us over the 6348 segments of 13M
+// values.)
+__global__ __launch_bounds__(256) void k_gen_scale(GenArgs a) {
+  __shared__ double sums[4];
+  const uint64_t b = blockIdx.x, n = groups_of(a.spb);
+  const double* const p = a.partial + b * n;
+  double acc = 0.0;   // (squares and magnitudes: 0 is below all of them)
+  for (uint64_t g0 = threadIdx.x; g0 < n; g0 += 8 * 256) {
+    double v[8];
+#pragma unroll
+    for (uint32_t t = 0; t < 8; ++t) v[t] = g0 + t * 256 < n ? p[g0 + t * 256] : 0.0;
+#pragma unroll
+    for (uint32_t t = 0; t < 8; ++t) acc = a.norm_mode == 0 ? acc + v[t] : fmax(acc, v[t]);
+  }
+  acc = a.norm_mode == 0 ? wave_sum_f64(acc) : (double)wave_max_f32((float)acc);
+  if ((threadIdx.x & 63u) == 0) sums[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    a.scale[b] = a.norm_mode == 0 ? (float)sqrt((sums[0] + sums[1]) + (sums[2] + sums[3]))
+                                  : (float)fmax(fmax(sums[0], sums[1]), fmax(sums[2], sums[3]));
 }
 
 template <int CODE, bool ALIGNED>
@@ -206,6 +196,7 @@ __global__ __launch_bounds__(64) void k_gen_encode(GenArgs a) {
         v[c] = load_quad_any(a.g, r.gidx0, (uint32_t)c * kChunk + lane * 4, r.len);
     }
     const float scale = a.scale[r.b];
+    if (CODE == QSGD_CODE_FIXED && r.j == 0 && lane == 0) a.payload[r.b * a.fixed_words_full] = __float_as_uint(scale);
     QuantCtx qc;
     qc.s_f = (float)a.s;
     qc.inv = (scale > 0.f) ? qc.s_f / scale : 0.f;
@@ -265,222 +256,318 @@ __global__ __launch_bounds__(64) void k_gen_encode(GenArgs a) {
   if (CODE == QSGD_CODE_FIXED) return;
   __syncthreads();
   if (lane == 0) {
-    a.seginfo[3 * seg + 0] = wo.first_pos;
-    a.seginfo[3 * seg + 1] = wo.last_pos;
-    a.seginfo[3 * seg + 2] = wo.bits;
+    a.seginfo[seg] = wo.first_pos;
+    a.seginfo[a.nseg + seg] = wo.last_pos;
+    a.seginfo[2 * a.nseg + seg] = wo.bits;
   }
   uint32_t* slot = a.slots + seg * a.sub_words;
   const uint32_t nw = (wo.bits + 31u) >> 5;
   for (uint32_t j = lane; j < nw; j += kWave) slot[j] = sub[j];
 }
 
-// One workgroup of 1024 threads walks all segments in order, kScanPer consecutive segments
-// per thread and trip: a thread scans its own segments one after the other and the
-// workgroup scans the threads' totals.
+// A workgroup walks a bucket's segments in order, kScanPer consecutive ones per thread and trip: a
+// thread scans its own segments one after the other and the workgroup scans the threads' totals.
+//
+// Words of the payload that hold bits of two segments hold the first bit of one of them and the
+// last bit of another: they are cleared (here if there is one bucket, else by `table`), and `place`
+// ORs into them.  All other words have one writer.
+//
+// One bucket: latency and instruction issue of one compute unit.  6348 segments (13M values): 21.8 us
+// with all buckets in one workgroup and 64-bit arithmetic throughout, and 4.7 for a launch that
+// cleared the payload; 10 this way (eight segments per thread, one trip instead of two, or the second
+// trip's loads ahead of the first: the same).
 constexpr int kScanPer = 4;
-constexpr uint32_t kScanTrip = 1024 * kScanPer;
-__global__ __launch_bounds__(1024) void k_gen_scan(GenArgs a) {
-  __shared__ unsigned long long wave_tot[16];
-  __shared__ unsigned long long tmp[kScanTrip];   // one value per segment of the trip
-  __shared__ unsigned long long tot[1024];        // one value per thread
-  __shared__ unsigned long long carry[5];  // max global position, bits in open bucket, words,
-                                           // bits of the last segment, entries in open bucket
-  const int i = threadIdx.x;
-  if (i == 0) {
-    carry[0] = 0; carry[1] = 0; carry[2] = 0; carry[3] = 0; carry[4] = 0;
-    a.table[0] = 0;
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4)));
+
+namespace {
+
+// Bits of the recursive Elias code of k >= 1: groups of 1, 2, 3, 5, 9 and 17 bits or more.
+__device__ __forceinline__ uint32_t omega_bits(uint32_t k) {
+  const uint32_t n = 32u - (uint32_t)__clz((int)k);
+  return n + (n > 1u ? 1u : 0u) + (n > 2u ? 2u : 0u) + (n > 4u ? 3u : 0u) + (n > 8u ? 1u : 0u) + (n > 16u ? 4u : 0u);
+}
+
+// Words [at, at + kScanPer) of an array of n (zeros past its end).
+__device__ __forceinline__ void load_words(const uint32_t* p, uint64_t at, uint64_t n, uint32_t (&v)[kScanPer]) {
+  if (at + kScanPer <= n) {
+#pragma unroll
+    for (int t = 0; t < kScanPer; t += 4) {
+      const v4u_any x = *reinterpret_cast<const v4u_any*>(p + at + t);
+      v[t] = x.x; v[t + 1] = x.y; v[t + 2] = x.z; v[t + 3] = x.w;
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < kScanPer; ++t) v[t] = at + t < n ? p[at + t] : 0u;
   }
+}
+__device__ __forceinline__ void store_words(uint32_t* p, uint64_t at, uint64_t n, const uint32_t (&v)[kScanPer]) {
+  if (at + kScanPer <= n) {
+#pragma unroll
+    for (int t = 0; t < kScanPer; t += 4) {
+      v4u_any x; x.x = v[t]; x.y = v[t + 1]; x.z = v[t + 2]; x.w = v[t + 3];
+      *reinterpret_cast<v4u_any*>(p + at + t) = x;
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < kScanPer; ++t) if (at + t < n) p[at + t] = v[t];
+  }
+}
+
+// Inclusive scan over a workgroup of up to 16 wavefronts; `total`: of all of it.  The caller alternates
+// between two buffers of wave totals: a barrier then lies between a buffer's reads and its next use.
+template <bool MAX>
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* wave_tot, uint32_t& total) {
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  v = MAX ? wave_incl_max_u32(v) : wave_incl_scan_u32(v, (int)lane);
+  if (lane == 63u) wave_tot[wave] = v;
   __syncthreads();
+  uint32_t pre = 0;
+  total = 0;
+  for (uint32_t w = 0; w < waves; ++w) {
+    const uint32_t t = wave_tot[w];
+    if (w == wave) pre = total;
+    total = MAX ? max(total, t) : total + t;
+  }
+  return MAX ? max(pre, v) : pre + v;
+}
+
+// Clears the word of a bucket's string (at word `str` of the payload) in which a segment's bits end
+// and others' may go on.  (The first segment with any starts on a word; the others start where one ends.)
+__device__ __forceinline__ void clear_shared(const GenArgs& a, uint64_t str, uint64_t end, bool any) {
+  if (any && (end & 31u) && str + (end >> 5) < a.cap_words) a.payload[str + (end >> 5)] = 0;
+}
+
+// Length and status of the message, and the table's padding.
+__device__ __forceinline__ void close_message(const GenArgs& a, uint64_t total) {
+  a.header[H_PW_LO] = (uint32_t)total;
+  a.header[H_PW_HI] = (uint32_t)(total >> 32);
+  for (uint64_t t = a.nb + 1; t < a.table_words; ++t) a.table[t] = 0;
+  if (total > a.cap_words || total > 0xFFFFFFFFull) a.header[H_STATUS] = (uint32_t)QSGD_ERR_CAPACITY;
+}
+
+}  // namespace
+
+__global__ __launch_bounds__(1024) void k_gen_scan(GenArgs a) {
+  __shared__ uint32_t wave_tot[2][16], below[1024];
+  const uint32_t tid = threadIdx.x, spb = (uint32_t)a.spb;
+  const uint64_t b = blockIdx.x, base = b * a.spb;
+  const uint64_t m = min(a.d, a.n - b * a.d);
+  const uint32_t segs = (uint32_t)((m + kSeg - 1) / kSeg);   // (of spb: the last bucket has fewer)
   const bool sparse = a.code == QSGD_CODE_SPARSE;
-  for (uint64_t c0 = 0; c0 < a.nseg; c0 += kScanTrip) {
-    uint64_t seg[kScanPer], b[kScanPer];
-    uint32_t idx[kScanPer], j[kScanPer], first[kScanPer], last[kScanPer], bits[kScanPer];
-    bool live[kScanPer];
-    unsigned long long base[kScanPer];
-#pragma unroll
-    for (int t = 0; t < kScanPer; ++t) {
-      idx[t] = (uint32_t)i * kScanPer + t;
-      seg[t] = c0 + idx[t];
-      live[t] = seg[t] < a.nseg;
-      b[t] = 0; j[t] = 0; first[t] = 0; last[t] = 0; bits[t] = 0;
-      if (live[t]) {
-        b[t] = seg[t] / a.spb; j[t] = (uint32_t)(seg[t] - b[t] * a.spb);
-        first[t] = a.seginfo[3 * seg[t]]; last[t] = a.seginfo[3 * seg[t] + 1];
-        bits[t] = a.seginfo[3 * seg[t] + 2];
-      }
-      base[t] = b[t] * a.d;
-    }
-    const unsigned long long c_max = carry[0], c_bits = carry[1], c_words = carry[2];
-    const unsigned long long c_tb = carry[3], c_ents = carry[4];
+  // of the trips before: last position, bits, entries, bits of the last segment
+  uint32_t c_last = 0, c_ents = 0, c_tb = 0;
+  uint64_t c_bits = 32;
+  for (uint32_t s0 = 0; s0 < spb; s0 += kScanPer * blockDim.x) {
+    const uint32_t j0 = s0 + tid * kScanPer;
+    uint32_t first[kScanPer], last[kScanPer], bits[kScanPer];
+    load_words(a.seginfo + base, j0, spb, first);
+    load_words(a.seginfo + a.nseg + base, j0, spb, last);
+    load_words(a.seginfo + 2 * a.nseg + base, j0, spb, bits);
     // which nonzero precedes each segment's first one: prefix maximum of the last positions
-    unsigned long long m_loc[kScanPer];
+    uint32_t most = 0, total;
 #pragma unroll
-    for (int t = 0; t < kScanPer; ++t) {
-      const unsigned long long lastg = (live[t] && first[t]) ? base[t] + last[t] : 0ull;
-      m_loc[t] = t ? (m_loc[t - 1] > lastg ? m_loc[t - 1] : lastg) : lastg;
+    for (int t = 0; t < kScanPer; ++t) most = first[t] ? last[t] : most;   // (they ascend)
+    const uint32_t m_incl = block_scan<true>(most, wave_tot[0], total);
+    const uint32_t m_below = dpp_fetch<kDppWaveShr1, 0xf>(m_incl);
+    uint32_t prev[kScanPer], gap[kScanPer], tb[kScanPer];
+    // (the thread below: of the same wavefront, or by way of LDS)
+    uint32_t before = m_below;
+    if ((tid & 63u) == 0) {
+      before = 0;
+      for (uint32_t w = 0; w < (tid >> 6); ++w) before = max(before, wave_tot[0][w]);
     }
-    tot[i] = block_incl_scan<unsigned long long>(m_loc[kScanPer - 1], 0ull, wave_tot, OpMax());
-    __syncthreads();
-    const unsigned long long m_before = i ? tot[i - 1] : 0ull;   // threads before this one
-    const unsigned long long chunk_max = tot[1023];
-    uint32_t prev_in_bucket[kScanPer], gap[kScanPer];
-    unsigned long long tb[kScanPer], s_loc[kScanPer];
+    before = max(before, c_last);
+    c_last = max(c_last, total);
+    uint32_t sum = 0;
 #pragma unroll
     for (int t = 0; t < kScanPer; ++t) {
-      unsigned long long prevg = t ? (m_before > m_loc[t - 1] ? m_before : m_loc[t - 1]) : m_before;
-      prevg = prevg > c_max ? prevg : c_max;
-      prev_in_bucket[t] = prevg > base[t] ? (uint32_t)(prevg - base[t]) : 0u;
-      gap[t] = (live[t] && first[t] && sparse) ? first[t] - prev_in_bucket[t] : 0u;
-      const uint32_t glen = gap[t] ? omega_length(gap[t]) : 0u;
-      tb[t] = (unsigned long long)glen + bits[t];
-      s_loc[t] = (t ? s_loc[t - 1] : 0ull) + tb[t];
+      prev[t] = before;
+      gap[t] = sparse && first[t] ? first[t] - before : 0u;
+      before = first[t] ? last[t] : before;
+      tb[t] = (gap[t] ? omega_bits(gap[t]) : 0u) + bits[t];   // (some 10^5 bits at most)
+      sum += tb[t];
     }
     // bit offset of each segment inside its bucket string
-    const unsigned long long s_tot =
-        block_incl_scan<unsigned long long>(s_loc[kScanPer - 1], 0ull, wave_tot, OpSum());
-    unsigned long long s_excl[kScanPer];
-#pragma unroll
-    for (int t = 0; t < kScanPer; ++t) {
-      s_excl[t] = s_tot - s_loc[kScanPer - 1] + s_loc[t] - tb[t];
-      tmp[idx[t]] = s_excl[t];
-    }
-    tot[i] = tb[kScanPer - 1];   // (tot was last read before the scan's barriers)
+    const uint32_t s_incl = block_scan<false>(sum, wave_tot[1], total);
+    uint64_t start = c_bits + (s_incl - sum);
+    c_bits += total;
+    below[tid] = tb[kScanPer - 1];
     __syncthreads();
-    unsigned long long before[kScanPer], tb_prev[kScanPer];
-#pragma unroll
-    for (int t = 0; t < kScanPer; ++t) {
-      // bits of this bucket's records before this segment
-      if (j[t] <= idx[t]) before[t] = s_excl[t] - tmp[idx[t] - j[t]];
-      else before[t] = c_bits + s_excl[t];
-      tb_prev[t] = t ? tb[t - 1] : (i ? tot[i - 1] : c_tb);
-    }
-    __syncthreads();
-    // entry list of long buckets: segment j >= 1 is listed iff its bit offset lies in a
+    const uint32_t tb_prev = tid ? below[tid - 1] : c_tb;
+    // entry list: segment j >= 1 is listed iff its bit offset lies in a
     // later block of kEntryBits bits than the offset of segment j - 1
-    bool listed[kScanPer];
-    unsigned long long e_loc[kScanPer];
+    static_assert(kEntryBits == 1024, "shift");
+    uint32_t listed = 0;   // a bit per segment
+    uint64_t at = start;
+    uint32_t block = (uint32_t)((j0 ? start - tb_prev : start) >> 10);
 #pragma unroll
     for (int t = 0; t < kScanPer; ++t) {
-      const unsigned long long start = 32ull + before[t];
-      const unsigned long long m_b = live[t] ? min((unsigned long long)a.d, a.n - base[t]) : 0ull;
-      listed[t] = a.entries && live[t] && j[t] >= 1 && (unsigned long long)j[t] * kSeg < m_b &&
-                  (start / kEntryBits) > ((start - tb_prev[t]) / kEntryBits) &&
-                  start < (1ull << 32);
-      e_loc[t] = (t ? e_loc[t - 1] : 0ull) + (listed[t] ? 1ull : 0ull);
+      const uint32_t now = (uint32_t)(at >> 10);
+      listed |= now != block && j0 + t < segs && (at >> 32) == 0 ? 1u << t : 0u;
+      block = now;
+      at += tb[t];
     }
-    const unsigned long long e_tot =
-        block_incl_scan<unsigned long long>(e_loc[kScanPer - 1], 0ull, wave_tot, OpSum());
-    unsigned long long e_excl[kScanPer];
+    c_tb = below[blockDim.x - 1];
+    const uint32_t e_incl = block_scan<false>((uint32_t)__popc(listed), wave_tot[0], total);
+    uint32_t rank = c_ents + e_incl - (uint32_t)__popc(listed);
+    c_ents += total;
+    uint32_t ranks[kScanPer];
 #pragma unroll
     for (int t = 0; t < kScanPer; ++t) {
-      e_excl[t] = e_tot - e_loc[kScanPer - 1] + e_loc[t] - (listed[t] ? 1ull : 0ull);
-      tmp[idx[t]] = e_excl[t];
+      ranks[t] = (listed >> t) & 1u ? rank : 0xFFFFFFFFu;
+      rank += (listed >> t) & 1u;
+      prev[t] = sparse ? prev[t] : (j0 + t) * kSeg;
     }
-    __syncthreads();
-    unsigned long long rank[kScanPer], ents[kScanPer], w_loc[kScanPer];
-    bool is_end[kScanPer];
+    at = start;
+    if (j0 + kScanPer <= spb) {
+      uint64_t* const out = a.segstart + base + j0;
 #pragma unroll
-    for (int t = 0; t < kScanPer; ++t) {
-      // listed segments of this bucket before this one
-      if (j[t] <= idx[t]) rank[t] = e_excl[t] - tmp[idx[t] - j[t]];
-      else rank[t] = c_ents + e_excl[t];
-      is_end[t] = live[t] && j[t] == a.spb - 1;
-      ents[t] = rank[t] + (listed[t] ? 1ull : 0ull);  // at the end: of the bucket
-      unsigned long long words = 0;
-      if (is_end[t]) {
-        words = (32ull + before[t] + tb[t] + (sparse ? 1ull : 0ull) + 31ull) >> 5;
-        if (a.entries) words += 2ull * ents[t] + 1ull;
+      for (int t = 0; t < kScanPer; t += 2) {
+        const uint64_t a1 = at + tb[t];
+        v4u_any x; x.x = (uint32_t)at; x.y = (uint32_t)(at >> 32); x.z = (uint32_t)a1; x.w = (uint32_t)(a1 >> 32);
+        *reinterpret_cast<v4u_any*>(out + t) = x;
+        at = a1 + tb[t + 1];
       }
-      w_loc[t] = (t ? w_loc[t - 1] : 0ull) + words;
+    } else {
+#pragma unroll
+      for (int t = 0; t < kScanPer; ++t) {
+        if (j0 + t < spb) a.segstart[base + j0 + t] = at;
+        at += tb[t];
+      }
     }
-    const unsigned long long w_tot =
-        block_incl_scan<unsigned long long>(w_loc[kScanPer - 1], 0ull, wave_tot, OpSum());
+    store_words(a.seggap + base, j0, spb, gap);
+    store_words(a.segrank + base, j0, spb, ranks);
+    store_words(a.segprev + base, j0, spb, prev);
+    if (a.nb == 1) {
+      at = start;
+      if ((start + sum) >> 5 < a.cap_words) {
 #pragma unroll
-    for (int t = 0; t < kScanPer; ++t) {
-      if (!live[t]) continue;
-      const unsigned long long w_incl = w_tot - w_loc[kScanPer - 1] + w_loc[t];
-      a.segstart[seg[t]] = 32ull + before[t];
-      a.seggap[seg[t]] = gap[t];
-      if (a.entries) {
-        a.segrank[seg[t]] = listed[t] ? (uint32_t)rank[t] : 0xFFFFFFFFu;
-        a.segprev[seg[t]] = sparse ? prev_in_bucket[t] : j[t] * kSeg;
-        if (is_end[t]) a.bents[b[t]] = (uint32_t)ents[t];
-      }
-      if (is_end[t]) {
-        const unsigned long long off = c_words + w_incl;
-        a.table[b[t] + 1] = off > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)off;
-      }
-      // (the carries were read at the top of this trip, several barriers ago)
-      if (idx[t] == kScanTrip - 1 || seg[t] == a.nseg - 1) {
-        carry[0] = chunk_max > c_max ? chunk_max : c_max;
-        carry[1] = is_end[t] ? 0ull : before[t] + tb[t];
-        carry[2] = c_words + w_incl;
-        carry[3] = tb[t];
-        carry[4] = is_end[t] ? 0ull : ents[t];
+        for (int t = 0; t < kScanPer; ++t) {
+          at += tb[t];
+          if (tb[t] && ((uint32_t)at & 31u)) a.payload[at >> 5] = 0;
+        }
+      } else {
+#pragma unroll 1
+        for (int t = 0; t < kScanPer; ++t) {
+          at += tb[t];
+          clear_shared(a, 0, at, tb[t] != 0);
+        }
       }
     }
     __syncthreads();
   }
-  if (i == 0) {
-    const unsigned long long total = carry[2];
-    a.header[H_PW_LO] = (uint32_t)total;
-    a.header[H_PW_HI] = (uint32_t)(total >> 32);
-    for (uint64_t t = a.nb + 1; t < a.table_words; ++t) a.table[t] = 0;
-    if (total > a.cap_words || total > 0xFFFFFFFFull)
-      a.header[H_STATUS] = (uint32_t)QSGD_ERR_CAPACITY;
+  if (tid == 0) {
+    const uint64_t words = ((c_bits + (sparse ? 1u : 0u) + 31u) >> 5) + 2ull * c_ents + 1u;
+    a.bents[b] = c_ents;
+    if (a.nb == 1) {
+      a.table[0] = 0;
+      a.table[1] = (uint32_t)min(words, (uint64_t)0xFFFFFFFFull);
+      close_message(a, words);
+    } else {
+      a.words[b] = (uint32_t)min(words, (uint64_t)0xFFFFFFFFull);
+    }
   }
 }
 
-__global__ __launch_bounds__(256) void k_gen_fill(GenArgs a) {
-  const uint64_t total = a.header[H_PW_LO] | ((uint64_t)a.header[H_PW_HI] << 32);
-  const uint64_t lim = min(total, a.cap_words);
-  for (uint64_t w = (uint64_t)blockIdx.x * 256 + threadIdx.x; w < lim; w += (uint64_t)gridDim.x * 256)
-    a.payload[w] = 0;
+// Several buckets: their word offsets, and the words that their segments share.  A workgroup takes a
+// run of buckets and adds up the words of those before by itself.
+__global__ __launch_bounds__(256) void k_gen_table(GenArgs a, uint32_t per) {
+  __shared__ uint64_t part[4], str[256];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint64_t b_begin = (uint64_t)blockIdx.x * per, b_end = min(b_begin + per, a.nb);
+  uint64_t base = 0;
+#pragma unroll 8
+  for (uint64_t b = tid; b < b_begin; b += 256) base += a.words[b];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) base += __shfl_xor(base, o, kWave);
+  if (lane == 0) part[wave] = base;
+  __syncthreads();
+  base = (part[0] + part[1]) + (part[2] + part[3]);
+  if (blockIdx.x == 0 && tid == 0) a.table[0] = 0;
+  const uint32_t spb = (uint32_t)a.spb;
+  for (uint64_t b0 = b_begin; b0 < b_end; b0 += 256) {
+    const uint64_t b = b0 + tid;
+    const uint64_t mine = b < b_end ? a.words[b] : 0u;
+    uint64_t incl = mine;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint64_t up = __shfl_up(incl, o, kWave);
+      if (lane >= (uint32_t)o) incl += up;
+    }
+    __syncthreads();
+    if (lane == 63u) part[wave] = incl;
+    __syncthreads();
+    uint64_t all = 0;
+    for (uint32_t w = 0; w < 4; ++w) {
+      if (w < wave) incl += part[w];
+      all += part[w];
+    }
+    str[tid] = base + incl - mine;
+    if (b < b_end) a.table[b + 1] = (uint32_t)min(base + incl, (uint64_t)0xFFFFFFFFull);
+    __syncthreads();
+    const uint32_t here = (uint32_t)min(b_end - b0, (uint64_t)256);
+    for (uint32_t i = tid; i < here * spb; i += 256) {   // (spb is below 2^21: few buckets then)
+      const uint64_t seg = b0 * spb + i;
+      const uint32_t gap = a.seggap[seg];
+      const uint32_t tb = (gap ? omega_bits(gap) : 0u) + a.seginfo[2 * a.nseg + seg];
+      clear_shared(a, str[i / spb], a.segstart[seg] + tb, tb != 0);
+    }
+    base += all;
+  }
+  if (b_end == a.nb && tid == 0) close_message(a, base);
 }
 
-__global__ __launch_bounds__(64) void k_gen_place(GenArgs a) {
+__global__ __launch_bounds__(256) void k_gen_place(GenArgs a) {
   if (a.header[H_STATUS] != 0) return;  // does not fit: nothing is written
-  const int lane = threadIdx.x;
-  const uint64_t seg = blockIdx.x;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint64_t seg = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (seg >= a.nseg) return;
+  const uint32_t bits = a.seginfo[2 * a.nseg + seg];
+  const uint32_t gap = a.seggap[seg];
+  const uint64_t start = a.segstart[seg];
+  const uint32_t r = a.segrank[seg];
   const uint64_t b = seg / a.spb;
   const uint32_t j = (uint32_t)(seg - b * a.spb);
   uint32_t* const str = a.payload + a.table[b];
-  const uint32_t bits = a.seginfo[3 * seg + 2];
-  const uint32_t gap = a.seggap[seg];
-  const uint64_t start = a.segstart[seg];
+  uint64_t gc = 0;
   uint32_t glen = 0;
+  if (gap) omega_encode(gap, gc, glen);
+  const uint64_t end = start + glen + bits;
   if (lane == 0) {
     if (j == 0) str[0] = __float_as_uint(a.scale[b]);
-    if (gap) {
-      uint64_t gc;
-      omega_encode(gap, gc, glen);
-      global_emit(str, start, gc, glen);
+    if (j == a.spb - 1 && a.code == QSGD_CODE_SPARSE) {   // the stop bit
+      if (end & 31u) atomicOr(&str[end >> 5], 0x80000000u >> (end & 31u));
+      else str[end >> 5] = 0x80000000u;
     }
-    if (j == a.spb - 1 && a.code == QSGD_CODE_SPARSE) global_emit(str, start + glen + bits, 1ull, 1u);
-  }
-  if (a.entries && lane == 0) {
     // the entry list sits behind the string's last word: pairs, then their count
     const uint32_t ents = a.bents[b];
     uint32_t* const list = a.payload + a.table[b + 1] - (2u * ents + 1u);
-    const uint32_t r = a.segrank[seg];
     if (r != 0xFFFFFFFFu) {
       list[2u * r] = (uint32_t)start;
       list[2u * r + 1u] = a.segprev[seg];
     }
     if (j == a.spb - 1) list[2u * ents] = ents;
   }
-  glen = lane_bcast(glen, 0);
-  const uint64_t o = start + glen;
-  const uint64_t w0 = o >> 5;
-  const uint32_t sh = (uint32_t)(o & 31u);
-  const uint32_t* slot = a.slots + seg * a.sub_words;
+  if (end == start) return;
+  // word i of the segment's words: the gap's code word (at the top of `top`), then the slot's bits
+  const uint64_t top = glen ? gc << (64u - glen) : 0ull;
+  const uint32_t sh = (uint32_t)(start & 31u), off = sh + glen;
+  uint32_t* const out = str + (start >> 5);
+  const uint32_t words = (uint32_t)(((end + 31u) >> 5) - (start >> 5));
+  const uint32_t* const slot = a.slots + seg * a.sub_words;
   const uint32_t nw = (bits + 31u) >> 5;
-  for (uint32_t t = lane; t < nw; t += kWave) {
-    const uint32_t x = slot[t];
-    if (x) {
-      atomicOr(&str[w0 + t], x >> sh);
-      if (sh && (x << (32u - sh))) atomicOr(&str[w0 + t + 1], x << (32u - sh));
-    }
+  for (uint32_t i = lane; i < words; i += kWave) {
+    uint32_t x = i == 0 ? (uint32_t)(top >> 32 >> sh)
+               : i == 1 ? (uint32_t)(top >> sh)
+               : i == 2 && sh ? (uint32_t)top << (32u - sh) : 0u;
+    const int32_t rel = (int32_t)(32u * i - off);   // slot bit at the word's first bit
+    const int32_t q = rel >> 5;
+    const uint32_t lo = q >= 0 && (uint32_t)q < nw ? slot[q] : 0u;
+    const uint32_t hi = q + 1 >= 0 && (uint32_t)(q + 1) < nw ? slot[q + 1] : 0u;
+    x |= (uint32_t)(((uint64_t)lo << 32 | hi) << (rel & 31) >> 32);
+    const bool shared = (i == 0 && sh) || (i == words - 1u && (end & 31u));
+    if (shared) atomicOr(&out[i], x);
+    else out[i] = x;
   }
 }
 
@@ -1142,12 +1229,10 @@ __global__ __launch_bounds__(256) void k_gen_decode_fixed(DecodeArgs a) {
 
 // ---- launchers -------------------------------------------------------------------------
 
-hipError_t launch_gen_partial(const GenArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_gen_partial, dim3((uint32_t)((a.nseg + 3) / 4)), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
 hipError_t launch_gen_scale(const GenArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_gen_scale, dim3((uint32_t)((a.nb + 3) / 4)), dim3(256), 0, st, a);
+  const uint64_t per = kPartialWaves / group_size(a.spb), groups = a.nb * groups_of(a.spb);
+  hipLaunchKernelGGL(k_gen_partial, dim3((uint32_t)((groups + per - 1) / per)), dim3(64 * kPartialWaves), 0, st, a);
+  if (groups > a.nb) hipLaunchKernelGGL(k_gen_scale, dim3((uint32_t)a.nb), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 hipError_t launch_gen_encode(const GenArgs& a, bool aligned, hipStream_t st) {
@@ -1162,16 +1247,17 @@ hipError_t launch_gen_encode(const GenArgs& a, bool aligned, hipStream_t st) {
 #undef QSGD_GEN
   return hipGetLastError();
 }
-hipError_t launch_gen_scan(const GenArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_gen_scan, dim3(1), dim3(1024), 0, st, a);
-  return hipGetLastError();
-}
-hipError_t launch_gen_fill(const GenArgs& a, uint32_t blocks, hipStream_t st) {
-  hipLaunchKernelGGL(k_gen_fill, dim3(blocks), dim3(256), 0, st, a);
+hipError_t launch_gen_scan(const GenArgs& a, uint32_t cus, hipStream_t st) {
+  const uint32_t threads = a.spb <= 64 * kScanPer ? 64 : a.spb <= 256 * kScanPer ? 256 : 1024;
+  hipLaunchKernelGGL(k_gen_scan, dim3((uint32_t)a.nb), dim3(threads), 0, st, a);
+  if (a.nb > 1) {
+    const uint32_t per = (uint32_t)((a.nb + cus - 1) / cus);
+    hipLaunchKernelGGL(k_gen_table, dim3((uint32_t)((a.nb + per - 1) / per)), dim3(256), 0, st, a, per);
+  }
   return hipGetLastError();
 }
 hipError_t launch_gen_place(const GenArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_gen_place, dim3((uint32_t)a.nseg), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(k_gen_place, dim3((uint32_t)((a.nseg + 3) / 4)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 hipError_t launch_gen_zero(float* p, uint64_t n, uint32_t blocks, hipStream_t st) {

@@ -241,15 +241,15 @@ struct GenArgs {
   uint64_t cap_words;
   uint64_t table_words;
   // workspace
-  double* partial;     // nseg: sum of squares (or max) of each segment
+  double* partial;     // sum of squares (or max) of each group of segments, at most nseg of them
+  uint32_t* words;     // nb: words of every bucket's string (where `partial` was)
   float* scale;        // nb
-  uint32_t* seginfo;   // 3 * nseg: first position, last position, bits
+  uint32_t* seginfo;   // first positions, last positions, bits: nseg of each
   uint64_t* segstart;  // nseg: bit offset of the segment's gap code in its bucket string
   uint32_t* seggap;    // nseg: gap in front of the segment's first record (0: none)
   uint32_t* segrank;   // nseg: index of the segment in its bucket's entry list, or ~0
   uint32_t* segprev;   // nseg: position of the last coded coordinate before the segment
   uint32_t* bents;     // nb: entries listed by the bucket
-  uint32_t entries;    // 1: strings are followed by an entry list (d > kEntryMinD)
   uint32_t* slots;     // nseg * sub_words
   // fixed width
   uint32_t fixed_bits;
@@ -305,11 +305,9 @@ hipError_t launch_write_layout_header(uint32_t* header, uint32_t* table, uint32_
                                       hipStream_t st);
 hipError_t launch_raw_pack(const RawArgs& a, hipStream_t st);
 hipError_t launch_raw_apply(const DecodeArgs& a, const RawArgs& r, hipStream_t st);
-hipError_t launch_gen_partial(const GenArgs& a, hipStream_t st);
 hipError_t launch_gen_scale(const GenArgs& a, hipStream_t st);
 hipError_t launch_gen_encode(const GenArgs& a, bool aligned, hipStream_t st);
-hipError_t launch_gen_scan(const GenArgs& a, hipStream_t st);
-hipError_t launch_gen_fill(const GenArgs& a, uint32_t blocks, hipStream_t st);
+hipError_t launch_gen_scan(const GenArgs& a, uint32_t cus, hipStream_t st);
 hipError_t launch_gen_place(const GenArgs& a, hipStream_t st);
 hipError_t launch_gen_zero(float* p, uint64_t n, uint32_t blocks, hipStream_t st);
 hipError_t launch_gen_parse(const DecodeArgs& a, float* acc, bool entries, hipStream_t st);
