@@ -81,6 +81,8 @@ struct Geometry {
   // Elias buckets of a size that no vector load fits: coded like those of the bucket path, in a
   // workspace as large as the general path asks for
   bool odd_bucket() const { return n > 0 && d % 4 != 0 && d <= kMaxBucketFast && code != QSGD_CODE_FIXED; }
+  // ... and short ones of fixed width
+  bool odd_fixed() const { return n > 0 && d % 4 != 0 && d <= 1024 && code == QSGD_CODE_FIXED; }
 };
 
 // General path (any d): segments of kSeg values, workspace layout.
@@ -654,7 +656,7 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
       return QSGD_ERR_HIP;
     return QSGD_OK;
   }
-  if (g.odd_bucket()) {
+  if (g.odd_bucket() || g.odd_fixed()) {
     GenPlan gp;
     plan_general(g, gp);
     if (gp.nseg > 0x7FFFFFFFull) return QSGD_ERR_UNSUPPORTED;

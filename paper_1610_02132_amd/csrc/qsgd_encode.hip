@@ -357,7 +357,7 @@ __global__ __launch_bounds__(64 * TW)
 // form, so the wavefront reads its buckets once and writes their strings in place;
 // the per-bucket work (scale reduction, square root, divide) is shared by the
 // buckets that ride in one wavefront.
-template <int LPB, int CP, int B>
+template <int LPB, int CP, int B, bool ODD>
 __device__ __forceinline__ void encode_fixed_small(const EncodeArgs& a) {
   constexpr int NB = 64 / LPB;             // buckets per wavefront pass
   constexpr uint32_t kStep = LPB * 4;      // values one pass of the bucket's lanes covers
@@ -400,12 +400,20 @@ __device__ __forceinline__ void encode_fixed_small(const EncodeArgs& a) {
 #pragma unroll
     for (int c = 0; c < CP; ++c) {
       const uint32_t e0 = (uint32_t)c * kStep + l * 4;
+      auto quad = [&]() {
+        if constexpr (ODD) {
+          const v4f_any t = *reinterpret_cast<const v4f_any*>(gb + e0);
+          return make_float4(t.x, t.y, t.z, t.w);
+        } else {
+          return *reinterpret_cast<const float4*>(gb + e0);
+        }
+      };
       if (all_full) {
-        v[c] = *reinterpret_cast<const float4*>(gb + e0);
+        v[c] = quad();
       } else {
         v[c] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (e0 + 3 < m) {
-          v[c] = *reinterpret_cast<const float4*>(gb + e0);
+          v[c] = quad();
         } else {
           if (e0 + 0 < m) v[c].x = gb[e0 + 0];
           if (e0 + 1 < m) v[c].y = gb[e0 + 1];
@@ -416,7 +424,10 @@ __device__ __forceinline__ void encode_fixed_small(const EncodeArgs& a) {
     {
       const uint64_t g0 = a.index_base + base + l * 4;
       uint32_t hi;
-      if (QSGD_UHI && uniform_counter_hi(g0, g0 + (uint64_t)(CP - 1) * kStep, hi)) {
+      if constexpr (ODD) {
+#pragma unroll
+        for (int c = 0; c < CP; ++c) draw4<false>(g0 + (uint64_t)c * kStep, qc, r[c]);
+      } else if (QSGD_UHI && uniform_counter_hi(g0, g0 + (uint64_t)(CP - 1) * kStep, hi)) {
 #pragma unroll
         for (int c = 0; c < CP; ++c) draw4_uniform_hi(g0 + (uint64_t)c * kStep, hi, qc, r[c]);
       } else {
@@ -533,10 +544,10 @@ __device__ __forceinline__ void encode_fixed_small(const EncodeArgs& a) {
   }
 }
 
-template <int LPB, int CP, int B>
+template <int LPB, int CP, int B, bool ODD>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(QSGD_FS_WAVES)))
 void k_encode_fixed_small(EncodeArgs a) {
-  encode_fixed_small<LPB, CP, B>(a);
+  encode_fixed_small<LPB, CP, B, ODD>(a);
 }
 
 // The K gradients of a double-buffered pass's chunk in one launch: a chunk of 16M values alone is
@@ -550,7 +561,7 @@ void k_encode_fixed_small_batch(EncodeArgs a, EncodeBatch batch) {
   a.header = batch.msg[k];
   a.payload = batch.msg[k] + H_WORDS;
   a.stream_id += k;
-  encode_fixed_small<LPB, CP, B>(a);
+  encode_fixed_small<LPB, CP, B, false>(a);
 }
 
 // Moves each team's region to its place in the message: base_j = words of the teams
@@ -687,12 +698,15 @@ static void fixed_small_shape(int lpb, int cp, uint32_t bits, F&& f) {
   else field(integral_constant<int, 64>(), integral_constant<int, 4>());
 }
 
-// d <= 1024, d % 4 == 0; a.bper counts groups of 64/lpb buckets per team.
+// d <= 1024; a.bper counts groups of 64/lpb buckets per team.  (Bucket sizes off 4 take unaligned loads
+// and two Philox blocks per quad; 10M values on the general path, a wavefront or more per bucket, and
+// here: d = 443, s = 255 64 and 18 us, d = 41, s = 15 467 and 26.)
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,
                                      hipStream_t st) {
   fixed_small_shape(lpb, cp, a.fixed_bits, [&](auto l, auto c, auto b) {
-    hipLaunchKernelGGL((k_encode_fixed_small<decltype(l)::value, decltype(c)::value, decltype(b)::value>),
-                       dim3(teams), dim3(64), 0, st, a);
+    constexpr int L = decltype(l)::value, C = decltype(c)::value, B = decltype(b)::value;
+    if (a.d % 4) hipLaunchKernelGGL((k_encode_fixed_small<L, C, B, true>), dim3(teams), dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((k_encode_fixed_small<L, C, B, false>), dim3(teams), dim3(64), 0, st, a);
   });
   return hipGetLastError();
 }
