@@ -458,7 +458,7 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     const uint32_t blocks = (uint32_t)std::min<uint64_t>((g.n + 255) / 256, (uint64_t)cus * 32);
     ScopedTiming tm("decode_general", st);
     if (g.code == QSGD_CODE_FIXED) {
-      if (launch_gen_decode_fixed(a, blocks, st) != hipSuccess) return QSGD_ERR_HIP;
+      if (launch_gen_decode_fixed(a, cus, st) != hipSuccess) return QSGD_ERR_HIP;
       return QSGD_OK;
     }
     float* acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes);

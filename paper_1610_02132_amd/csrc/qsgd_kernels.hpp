@@ -319,6 +319,6 @@ constexpr uint32_t kCollideBytes = 256 + 12 * kCollide;
 hipError_t launch_sparse_long(const DecodeArgs& a, uint32_t* area, uint8_t* lists, uint32_t cus,
                               uint32_t chunks, hipStream_t st);
 hipError_t launch_gen_apply(const DecodeArgs& a, const float* acc, uint32_t blocks, hipStream_t st);
-hipError_t launch_gen_decode_fixed(const DecodeArgs& a, uint32_t blocks, hipStream_t st);
+hipError_t launch_gen_decode_fixed(const DecodeArgs& a, uint32_t cus, hipStream_t st);
 
 }  // namespace qsgd
