@@ -172,14 +172,18 @@ struct EncodePlan {
   uint64_t ws_bytes;
 };
 
-// About how many words a full bucket's string has: the levels of normal values, mean
-// magnitude 0.8 of their rms (Elias codes).
-uint32_t string_words(const Geometry& g) {
+// Mean level of normal values, whose mean magnitude is 0.8 of their rms.
+double mean_level(const Geometry& g) {
   const double d = (double)g.d;
-  const double t = 0.8 * g.s / (g.norm == QSGD_NORM_MAX ? std::sqrt(2.0 * std::log(d + 2.0)) : std::sqrt(d));
+  return 0.8 * g.s / (g.norm == QSGD_NORM_MAX ? std::sqrt(2.0 * std::log(d + 2.0)) : std::sqrt(d));
+}
+
+// About how many words a full bucket's string then has (Elias codes).
+uint32_t string_words(const Geometry& g) {
+  const double d = (double)g.d, t = mean_level(g);
   const double level = omega_len_host((uint64_t)t + 1), share = 1.0 - std::exp(-t);
   const double bits = g.code == QSGD_CODE_DENSE
-                          ? d * (1.0 + level)
+                          ? d * (1.0 + (1.0 - share) + share * omega_len_host((uint64_t)std::max(2.0, t / share + 1.5)))
                           : d * share * (1.0 + level + omega_len_host((uint64_t)(1.0 / share)));
   return 1 + (uint32_t)(bits / 32.0);
 }
@@ -200,21 +204,45 @@ double shortest_string(const Geometry& g, const size_t* msg_bytes, uint32_t K) {
   return std::max(1.0, (words - H_WORDS - (double)g.table_words) / (double)std::max<uint64_t>(g.nb, 1));
 }
 
-// About how long the decoders with a lane for every string take (us): as long as the longest string,
-// 1.7 us per word (ring decoder, sparse strings), or at least the windows of a bucket (tile decoder:
-// 0.64 us per word, 0.042 per value, whichever is more, and 2.2 values per ns where the machine is full).
-// The split decoder's plan has its own estimate.  Step, us, lane per string / split:
-//   d = 512, s = 16 (37 words): 48 strings 34 / 17, 3128 strings 33 / 23, 16384 strings 34 / 62
-//   d = 8192, s = 40 (466 words): 4 strings 294 / 42, 4096 strings 347 / 192, 8192 strings 342 / 382
-//   d = 8192, s = 4 (102 words, ring): 4 strings 170 / 30, 8192 strings 347 / 170
-float per_string_us(const Geometry& g, uint32_t K, bool tile) {
-  const float words = (float)string_words(g), d = (float)g.d;
-  if (tile) return std::max(5.f + 0.64f * words, 7.f + 0.042f * d) + (float)g.nb * (float)K * d / 2.2e6f;
-  return 3.f + 1.7f * words;
+// ... and no more than the K messages have room for, on the average: they may be cut to their length.
+uint32_t string_words(const Geometry& g, const size_t* msg_bytes, uint32_t K, uint64_t raw_words) {
+  const double fixed = (double)(H_WORDS + g.table_words + raw_words);
+  double words = 0.0;
+  for (uint32_t k = 0; k < K; ++k) words += std::max(0.0, (double)(msg_bytes[k] / 4) - fixed);
+  words = words / ((double)std::max<uint64_t>(g.nb, 1) * K) + 1.0;
+  const uint32_t guess = string_words(g);
+  return words < (double)guess ? (uint32_t)words : guess;
+}
+
+// About how long the decoders with a lane for every string take (us): the windows of a bucket and the
+// records of a string one after the other, or all of them at the rate of a machine that is full, and x
+// read and written.  Levels that the tile decoder's table does not hold cost it twice; a record of the
+// ring decoder costs the more the more of them fall in a window.  Fitted to 286 steps (d = 96 .. 8192, s = 3
+// .. 100% of sqrt(d), L2 and max, both codes, K = 1 .. 24, 20 thousand to 60M values and c5), 12% off on
+// the average (tile) and 30% (ring); the choice by these two and the split decoder's estimate is 1% behind
+// the best of the three on them, 28% where the ring decoder had all of 64 s^2 <= d.
+// Ring / tile / split, us:
+//   16M values, K = 4:  d = 512, s = 2 101 / 52 / 185   d = 4096, s = 2 202 / 126 / 122
+//                       d = 4096, s = 8 633 / 178 / 217  d = 8192, s = 7 544 / 285 / 245
+//   60M values, K = 16: d = 1024, s = 1 168 / 278 / 1217   d = 4096, s = 2 195 / 366 / 1596
+//                       d = 4096, s = 5 659 / 441 / 3570   d = 8192, s = 5 721 / 411 / 2484
+//   1e9 values, d = 8192, s = 4, outliers, K = 16: 1780 / 3678 / 21400
+//   Code'_s, K = 9: 2M values, d = 1024, s = 32 - / 70 / 288   d = 8192, s = 30 - / 379 / 91
+float both(float latency, float rate) { return std::sqrt(latency * latency + rate * rate); }
+float tile_us(const Geometry& g, uint32_t K, float words) {
+  const float d = (float)g.d, strings = (float)g.nb * (float)K;
+  const float beyond = std::min(1.f, std::max(0.f, ((float)mean_level(g) - 4.f) / 6.f));
+  return 8.3f + both(0.0247f * d + 0.329f * words * (1.f + 2.58f * beyond),
+                     strings * (1.5e-7f * d + 6.03e-6f * words) + 1.4e-6f * (float)g.nb * d);
+}
+float ring_us(const Geometry& g, uint32_t K, float words) {
+  const float d = (float)g.d, dense = words * words / d, strings = (float)g.nb * (float)K;
+  return 32.f + both(106.f * dense + 0.01f * d, strings * 8.58e-4f * dense + 1.4e-6f * (float)g.nb * d);
 }
 
 // Dense strings: the share of nonzero levels grows like s / sqrt(d) (Lemma 3.1 (iii)); with the
-// largest value as scale it is larger still, and Code'_s codes every coordinate.
+// largest value as scale it is larger still, and Code'_s codes every coordinate.  (What the encoder
+// goes by; the decoder's choice has its own estimates.)
 bool dense_strings(const Geometry& g) {
   return g.code == QSGD_CODE_DENSE || 64ull * g.s * g.s > g.d || g.norm == QSGD_NORM_MAX;
 }
@@ -384,17 +412,18 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   a.status = static_cast<uint32_t*>(ws);
   a.fixed_bits = g.fixed_bits;
   a.fixed_words_full = (uint32_t)g.max_words(g.d);
-  // Which apply step the Elias decoder takes.  The share of nonzero levels of Q_s grows
-  // like s / sqrt(d) (Lemma 3.1 (iii)); above 1/8 a string has more records per
-  // 256-position window than the counting apply handles well, and Code'_s has a
-  // record for every coordinate; with the largest value as scale the share is larger still (14M
-  // values, d = 80, s = 1, K = 7: 323 us by the ring decoder, 91 by the tile decoder).  Heavy tails
-  // bring that share down, but not in every bucket, and the ring decoder waits for the longest
-  // string (8M values, K = 16, max, ring / tile: 0.1% of the values x100 d = 512, s = 4 292 / 106 us,
-  // d = 8192, s = 1 773 / 301; Student-t 222 / 95, 452 / 304; 1% x1000, all strings short, 192 / 88,
-  // 76 / 166).  (The counting apply keeps a bit per message in a 32-bit
-  // word: more than 32 messages go the other way whatever the data.)
-  a.kloop = (dense_strings(g) || K > 32) ? 1u : 0u;
+  // Which decoder, and which apply step, Elias strings of buckets up to 8192 values take: the ring
+  // decoder with the counting apply, which keeps a bit per message in a 32-bit word (more than 32
+  // messages go the other way whatever the data), or the tile decoder.  Code'_s has a record for
+  // every coordinate, and with the largest value as scale the share of nonzero levels depends on the
+  // data: heavy tails bring it down, but not in every bucket, and the ring decoder waits for the
+  // longest string (8M values, K = 16, max, ring / tile: 0.1% of the values x100 d = 512, s = 4 292 /
+  // 106 us, d = 8192, s = 1 773 / 301; Student-t 222 / 95, 452 / 304; 1% x1000, all strings short, 192 /
+  // 88, 76 / 166).
+  const uint32_t words = string_words(g, msg_bytes, K, a.raw_words);
+  const bool elias = g.code != QSGD_CODE_FIXED && g.n > 0;
+  a.kloop = (g.code != QSGD_CODE_SPARSE || g.norm == QSGD_NORM_MAX || K > 32 || g.s > 127 ||
+             (elias && tile_us(g, K, (float)words) < ring_us(g, K, (float)words))) ? 1u : 0u;
 
   const uint32_t cus = (uint32_t)device_cus();
   if (g.n > 0 && g.code == QSGD_CODE_SPARSE && g.d > kEntryMinD && std::isfinite(c)) {
@@ -430,8 +459,8 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // 17.6 ms there, 65 us in the split decoder.)
   const bool bytes = g.code != QSGD_CODE_FIXED && g.s <= 127;
   if (bytes && g.d <= kMaxBucketFast) {
-    const SplitPlan p = plan_decode_split(a, cus, string_words(g));
-    if (p.us < per_string_us(g, K, a.kloop || g.d % 4)) {
+    const SplitPlan p = plan_decode_split(a, cus, words);
+    if (p.us < (a.kloop || g.d % 4 ? tile_us(g, K, (float)words) : ring_us(g, K, (float)words))) {
       ScopedTiming tm("decode_elias", st);
       return launch_decode_split(a, p, st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
     }
@@ -464,7 +493,7 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     float* acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes);
     if (bytes && g.d > kEntryMinD && g.d * g.per_elem < 0xF0000000ull) {   // (bit positions in 32 bits)
       a.acc = acc;
-      if (launch_decode_split(a, plan_decode_split(a, cus, string_words(g)), st) != hipSuccess ||
+      if (launch_decode_split(a, plan_decode_split(a, cus, words), st) != hipSuccess ||
           launch_gen_apply(a, acc, blocks, st) != hipSuccess)
         return QSGD_ERR_HIP;
       return QSGD_OK;

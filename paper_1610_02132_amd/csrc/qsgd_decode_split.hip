@@ -659,10 +659,28 @@ SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words) {
   if (p.bits) {
     p.us = 8.f + 0.025f * (float)cu_words + 1.1f * (float)(per_cu - 1);
   } else {
-    const bool rare = sparse && 24u * words <= span;
-    const float once = (rare ? 17.f : sparse ? 12.f : 11.f) + (sparse ? 0.06f : 0.02f) * (float)words;
-    const float slots = (float)tasks * (float)a.K * (float)((words + p.lanes - 1) / p.lanes * p.lanes);
-    p.us = 2.f + std::max(once, 0.6f * once + slots / (rare ? 13e3f : sparse ? 17e3f : 22e3f));
+    // The turns of a workgroup one after the other, or all words at the rate of a machine that is full; a
+    // second unit of a string costs both.  Fitted like the other decoders' estimates, where the choice
+    // is made (18 to 26% off on the average).
+    const uint32_t batches = (a.K + p.rows - 1) / p.rows;
+    const float turns = (float)(batches * ((word_waves + p.waves - 1) / p.waves)) * (float)((tasks - 1) / p.blocks + 1);
+    const float strings = (float)tasks * (float)a.K, values = strings * (float)span, several = words > 64 ? 1.f : 0.f;
+    const float slots = strings * (float)((words + p.lanes - 1) / p.lanes * p.lanes);
+    float fixed, turn, rate;
+    if (!sparse) {
+      fixed = 0.5f;
+      turn = 12.4f * turns * (1.f + 0.52f * several);
+      rate = slots * 4.3e-5f * (1.f + 0.7f * several);
+    } else if (24u * words <= span) {
+      fixed = 6.1f;
+      turn = 17.2f * turns * (1.f + 0.6f * several);
+      rate = slots * 2.9e-5f * (1.f + several) + values * 1.35e-6f;
+    } else {
+      fixed = 5.4f;
+      turn = 13.7f * turns * (1.f + 0.54f * several);
+      rate = slots * 5.7e-5f * (1.f + 0.75f * several) + values * 7.1e-7f;
+    }
+    p.us = fixed + std::sqrt(turn * turn + rate * rate);
   }
   return p;
 }
