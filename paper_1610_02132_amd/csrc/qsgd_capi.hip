@@ -436,12 +436,13 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
                                              : (double)g.s * ((double)g.s + std::sqrt((double)g.d));
     if ((double)K * K * q * q <= 512.0 * (double)g.d) {
       uint8_t* const area = static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes;
-      // wavefronts per string: a stretch is about 1024 bits, a record about Elias(d / q) + 3
+      // a stretch is about 1024 bits, a record about Elias(d / q) + 3
       const double bits = q * (omega_len_host((uint64_t)((double)g.d / q) + 1) + 3.0);
-      const uint32_t chunks = (uint32_t)std::min(64.0, bits / (64.0 * kEntryBits) + 1.0);
+      const uint32_t stretches = (uint32_t)std::min(4096.0, bits / kEntryBits + 1.0);
+      const uint32_t chunks = (uint32_t)std::min(256.0, q / 512.0 + 1.0);
       ScopedTiming tm("decode_general", st);
       return launch_sparse_long(a, reinterpret_cast<uint32_t*>(area), area + align_up(4 * g.n, 256),
-                                cus, chunks, st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
+                                cus, stretches, chunks, st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
     }
   }
   {

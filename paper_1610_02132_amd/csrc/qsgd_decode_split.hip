@@ -73,20 +73,6 @@ constexpr uint32_t last_group(uint32_t bits) {
   }
   return more;
 }
-// Where they start: one behind the leading 1.
-__device__ __forceinline__ uint32_t last_group_at(uint32_t more) {
-  return ((more < 8u ? 0x66663310u : 0x77777777u) >> (4u * more & 31u)) & 15u;
-}
-
-// The code word at the top of v, by its last group: a 0 has to follow it, or else (open) the code
-// word has a group more, its value being 2^16 at least.
-__device__ __forceinline__ uint32_t by_last_group(uint32_t v, uint32_t more, uint32_t& len, uint32_t& open) {
-  const uint32_t at = last_group_at(more) + more;
-  len = at + 1u;
-  open = __builtin_amdgcn_ubfe(v, 31u - at, 1u);
-  return 1u << more | __builtin_amdgcn_ubfe(v, 32u - at, more);
-}
-
 // Entry: bits of one / of two records (0, 4), positions passed (8, 12: 4 and 5 bits), their
 // signed levels (17, 22: 5 bits each).  A single record stands twice; length 0: none fits.  And
 // last_group of the first code word (28; behind the sign in Code'_s, of the level).

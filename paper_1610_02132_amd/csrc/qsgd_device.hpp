@@ -182,6 +182,29 @@ constexpr Token omega_of(uint32_t bits, uint32_t n) {
   }
 }
 
+// An Elias code word by its LAST group: how many bits that has after its leading 1 (`more`) is known
+// from the first seven bits of the code word at the top of v, if it has three groups at most.
+__device__ __forceinline__ uint32_t last_group_bits(uint32_t v) {
+  const uint32_t n = 3u + __builtin_amdgcn_ubfe(v, 30u, 1u);   // bits of the second group, if there is one
+  const uint32_t second = __builtin_amdgcn_ubfe(v, 30u - n, n), third = __builtin_amdgcn_ubfe(v, 29u - n, 1u);
+  uint32_t more = third ? second : n - 1u;
+  more = (v >> 29) & 1u ? more : 1u;
+  return v >> 31 ? more : 0u;
+}
+// Where they start: one behind the leading 1.
+__device__ __forceinline__ uint32_t last_group_at(uint32_t more) {
+  return ((more < 8u ? 0x66663310u : 0x77777777u) >> (4u * more & 31u)) & 15u;
+}
+
+// The code word at the top of v, by its last group: a 0 has to follow it, or else (open) the code
+// word has a group more, its value being 2^16 at least.
+__device__ __forceinline__ uint32_t by_last_group(uint32_t v, uint32_t more, uint32_t& len, uint32_t& open) {
+  const uint32_t at = last_group_at(more) + more;
+  len = at + 1u;
+  open = __builtin_amdgcn_ubfe(v, 31u - at, 1u);
+  return 1u << more | __builtin_amdgcn_ubfe(v, 32u - at, more);
+}
+
 // Decoder rule of the recursive Elias code (App. A.2) on a 64-bit window; values
 // below 2^32.  Returns 0 for malformed input; `len` = bits used.
 __device__ __forceinline__ uint32_t omega_loop(uint64_t w, uint32_t& len) {

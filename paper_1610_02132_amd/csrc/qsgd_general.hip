@@ -573,21 +573,6 @@ __global__ __launch_bounds__(256) void k_gen_place(GenArgs a) {
 
 // ---- decode --------------------------------------------------------------------------
 
-namespace {
-
-// 64 stream bits starting at bit `bitpos` of a string of nwords words (zeros past the end).
-__device__ __forceinline__ uint64_t peek64(const uint32_t* w, uint64_t nwords, uint64_t bitpos) {
-  const uint64_t wi = bitpos >> 5;
-  const uint32_t off = (uint32_t)(bitpos & 31u);
-  const uint64_t a0 = wi < nwords ? w[wi] : 0u;
-  const uint64_t a1 = wi + 1 < nwords ? w[wi + 1] : 0u;
-  const uint64_t a2 = wi + 2 < nwords ? w[wi + 2] : 0u;
-  const uint64_t hi = (a0 << 32) | a1;
-  return off ? (hi << off) | (a2 >> (32u - off)) : hi;
-}
-
-}  // namespace
-
 __global__ __launch_bounds__(256) void k_gen_zero(float* p, uint64_t n) {
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256)
     p[i] = 0.f;
@@ -798,9 +783,8 @@ __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* 
 // is, so no dense accumulator is made: the records of all K messages are listed first (a
 // damaged message must leave x alone), then each updates its own coordinate.  Four launches:
 //   clear    checks the headers, clears the bucket's bitmaps and counters
-//   list     a wavefront per 64 stretches between entry points, a thread per stretch, string
-//            words staged in LDS: (position, value) into the message's list, the position's
-//            bit into `seen` and, if it was set already, into `multi`
+//   list     a workgroup per stretch between entry points: (position, value) into the message's
+//            list, the position's bit into `seen` and, if it was set already, into `multi`
 //   apply    a record whose position is not in `multi` updates x (0 + v is the sum in message
 //            order), the others go to the bucket's collision list
 //   resolve  a coordinate on that list is summed from 0 in message order by the thread that
@@ -809,10 +793,12 @@ __global__ __launch_bounds__(256) void k_gen_parse_entries(DecodeArgs a, float* 
 //            instead, and the messages' lists are gone through one after the other; where
 //            a message's own list overflowed, the bucket's workgroup reads the messages in
 //            turns into a dense accumulator.  Both are linear in the number of records.
-// Bound by latency: the stretch's chain of records (about 46, an LDS round trip and some 40
-// instructions each) and four launches.  13M values, s = 1, K = 16: 180 us with a dense
-// accumulator (zeroed, counted, stored, resolved, applied: 24 us of it for x alone), 46 this way (49
-// with level and sign always read by a second round trip).
+// Bound by latency and four launches.  13M values, s = 1, K = 16: 180 us with a dense accumulator (zeroed,
+// counted, stored, resolved, applied: 24 us of it for x alone), 46 with a thread per stretch, record
+// after record (46 of them, 0.65 us each), 30 with a lane per bit (of the list's 15: 2 to open the
+// string, 5 for the bits, 1 for a dozen rounds, 4 for the atomics); 13M values, d = 9000, s = 2, K = 8,
+// where a wavefront had two stretches, 640 and 190.  Workgroups of two or eight wavefronts: list 17
+// and 16 instead of 15 us, 124 and 234 instead of 124.
 // Untouched coordinates: fma(-c, 0, x) is x for c >= 0; where it is not (accumulating, and
 // c < 0, turn -0 into +0) one more launch does that.
 
@@ -880,20 +866,23 @@ __global__ __launch_bounds__(256) void k_sparse_clear(DecodeArgs a, uint32_t* ar
   }
 }
 
-constexpr uint32_t kStage = 4096;   // words of a string a wavefront stages
-constexpr uint32_t kPad = 8;        // zeros behind them: a damaged record may reach past its stretch
-constexpr uint32_t kSlots = 32;     // records a thread reads between two deliveries
-__global__ __launch_bounds__(64) void k_sparse_list(DecodeArgs a, uint32_t* area, uint8_t* lists) {
-  if (*a.status != 0) return;
-  __shared__ uint32_t words[kStage];
-  __shared__ uint32_t rpos[64 * kSlots];
-  __shared__ float rval[64 * kSlots];
-  const int lane = threadIdx.x;
+// A workgroup per stretch, kListWords words of it at a time.  Nobody reads record after record: a lane
+// for every BIT reads the record that would begin there (all of them side by side), four rounds of
+// "where does the record at my end lead" give every word a table of where one leaves it from each of
+// its bits, and a lane per word follows those tables from the stretch's start, which is known, until
+// no word's entry changes any more.
+constexpr uint32_t kListWords = 64, kListThreads = 256;
+__global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_sparse_list(DecodeArgs a, uint32_t* area, uint8_t* lists) {
+  if (damaged_before(a.status)) return;
+  __shared__ uint32_t words[kListWords + 4], what[kListWords * 32], gaps[kListWords * 32], carry[2];
+  __shared__ uint8_t leaves[kListWords * 32];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t b = blockIdx.x;
   const uint32_t k = blockIdx.y;
   StringRef sr;
   if (!open_string(a, k, b, true, sr)) {   // (the same in every lane)
-    if (lane == 0) flag_corrupt(a.status);
+    if (tid == 0) flag_corrupt(a.status);
     return;
   }
   const uint64_t base = b * (uint64_t)a.d;
@@ -903,125 +892,137 @@ __global__ __launch_bounds__(64) void k_sparse_list(DecodeArgs a, uint32_t* area
   uint32_t* const lval = s.val(k);
   uint32_t* const overflow = collide_list(lists, b).overflow;
 
-  for (uint64_t r0 = (uint64_t)blockIdx.z * 64; r0 <= sr.ents; r0 += 64ull * gridDim.z) {
-    const uint64_t r = r0 + lane;
-    const bool mine = r <= sr.ents, last_stretch = r == sr.ents;
-    uint64_t bitpos = 0, stop = 0, pos = 0, pos_end = 0;
-    bool ok = true;
-    if (mine) {
-      bitpos = r ? sr.list[2 * (r - 1)] : 32;
-      pos = r ? sr.list[2 * (r - 1) + 1] : 0;
-      stop = last_stretch ? sr.endbit : sr.list[2 * r];
-      pos_end = last_stretch ? 0 : sr.list[2 * r + 1];
-      ok = bitpos >= 32 && bitpos <= stop && stop <= sr.endbit && pos <= m;
-      if (!ok) stop = bitpos = 0;
+  for (uint64_t r = blockIdx.z; r <= sr.ents; r += gridDim.z) {
+    const bool last_stretch = r == sr.ents;
+    const uint64_t bitpos = r ? sr.list[2 * (r - 1)] : 32;
+    const uint64_t stop = last_stretch ? sr.endbit : sr.list[2 * r];
+    const uint32_t pos_end = last_stretch ? 0u : sr.list[2 * r + 1];
+    uint32_t at_pos = r ? sr.list[2 * (r - 1) + 1] : 0u;
+    if (!(bitpos >= 32 && bitpos <= stop && stop <= sr.endbit && at_pos <= m) ||
+        (bitpos == stop && !last_stretch && at_pos != pos_end)) {
+      if (tid == 0) flag_corrupt(a.status);
+      continue;
     }
-    // the wavefront's stretches lie side by side: their words, read together
-    const uint32_t w_first = wave_min_u32(mine && ok ? (uint32_t)(bitpos >> 5) : 0xFFFFFFFFu);
-    const uint32_t w_end = wave_max_u32(mine && ok ? (uint32_t)((stop + 31) >> 5) : 0u);
-    const uint32_t span = w_end > w_first ? w_end - w_first : 0u;
-    const bool staged = span <= kStage - kPad;
-    if (staged) {
-#pragma unroll 8
-      for (uint32_t i = lane; i < span; i += 64) words[1 + i] = sr.str[w_first + i];
-      if (lane == 0) words[0] = 0;
-      if (lane < (int)kPad - 1) words[1 + span + lane] = 0;
-    }
-    __syncthreads();
-    // positions fit 32 bits, bit offsets are counted from the first staged word on
-    const uint64_t bit0 = staged ? (uint64_t)w_first * 32u : 0u;
-    uint32_t at_bit = (uint32_t)(bitpos - bit0), at_pos = (uint32_t)pos;
-    const uint32_t stop_bit = (uint32_t)(stop - bit0);
-    bool more = mine && ok && bitpos < stop;
-    while (__builtin_amdgcn_ballot_w64(more)) {
-      uint32_t cnt = 0;
-      if (staged) {
-        // 32 stream bits from bit `at` on: two words of LDS, aligned (p = at - 1: no shift by 32)
-        auto peek = [&](uint32_t at) -> uint32_t {
-          const uint32_t p = at - 1u + 32u;                  // (one word of padding in front)
-          return __builtin_amdgcn_alignbit(words[p >> 5], words[(p >> 5) + 1u], ~p);
+    uint32_t entry0 = (uint32_t)(bitpos & 31u);
+    for (uint64_t w0 = bitpos >> 5; w0 * 32u < stop; w0 += kListWords) {
+      const uint32_t here = (uint32_t)min((uint64_t)kListWords, ((stop + 31u) >> 5) - w0);
+      if (tid < here + 4u) words[tid] = w0 + tid < sr.nwords ? sr.str[w0 + tid] : 0u;
+      __syncthreads();
+      for (uint32_t t0 = 2u * wave; t0 < here; t0 += kListThreads / 32u) {
+        const uint32_t t = t0 + (lane >> 5), o = lane & 31u;   // (t may be `here`: nobody asks for it)
+        const uint32_t x0 = words[t], x1 = words[t + 1u], x2 = words[t + 2u], x3 = words[t + 3u];
+        const uint32_t h0 = x0 >> 1, h1 = __builtin_amdgcn_alignbit(x0, x1, 1);
+        const uint32_t h2 = __builtin_amdgcn_alignbit(x1, x2, 1), h3 = __builtin_amdgcn_alignbit(x2, x3, 1);
+        // 32 bits from bit q on, q < 96
+        auto peek = [&](uint32_t q) {
+          const bool one = q >= 32u, two = q >= 64u;
+          uint32_t hi = one ? h1 : h0, lo = one ? h2 : h1;
+          hi = two ? h2 : hi;
+          lo = two ? h3 : lo;
+          return __builtin_amdgcn_alignbit(hi, lo, ~q);
         };
-        while (more && cnt < kSlots) {
-          uint32_t gl, ll;
-          const uint32_t v = peek(at_bit);
-          uint32_t gap = omega_peek3(v, gl);
-          // the usual level, 1, is a zero behind the sign: both are among the 32 bits already
-          // there (the gap's code has 23 bits at most), and no lane looks further
-          uint32_t w = v << gl, lev = 1;
-          ll = 1;
-          if (__builtin_amdgcn_ballot_w64(gap == 0 || ((w >> 30) & 1u) != 0)) {
-            if (gap == 0)                                      // 2^16 and more, or malformed
-              gap = omega_loop((uint64_t)v << 32 | peek(at_bit + 32u), gl);
-            w = peek(at_bit + gl);
-            lev = omega_peek3(w << 1, ll);
-          }
-          at_bit += gl + 1u + ll;
-          // (not the new position <= m: it is counted in 32 bits and could come round)
-          const bool good = (gap != 0) & (lev != 0) & (lev <= a.s) & (gap <= m - at_pos) &
-                            (at_bit <= stop_bit);
-          at_pos += gap;
-          const float mag = sr.scale * (float)lev;
-          rpos[cnt * 64 + lane] = at_pos - 1u;
-          rval[cnt * 64 + lane] = (w >> 31) ? -mag : mag;
-          cnt += good ? 1u : 0u;
-          ok = good;
-          more = good & (at_bit < stop_bit);
+        uint32_t gl, ll, open, more;
+        const uint32_t v = peek(o);
+        uint32_t gap = by_last_group(v, last_group_bits(v), gl, open);
+        if (open) {
+          // four groups, of 2, 3, 5 and gap + 1 bits (2^16 to 2^32 - 1), or malformed
+          more = gap;
+          const bool four = more >= 16u && more <= 31u && peek(o + 11u + (more & 31u)) >> 31 == 0;
+          gap = four ? peek(o + 10u) >> (31u - (more & 31u)) : 0u;
+          gl = (more & 31u) + 12u;                             // (43 at most)
         }
-      } else {                                                 // stretches too long to stage
-        while (more && cnt < kSlots) {
-          uint32_t gl, ll;
-          const uint32_t gap = omega_loop(peek64(sr.str, sr.nwords, bitpos), gl);
-          const uint32_t w = (uint32_t)(peek64(sr.str, sr.nwords, bitpos + gl) >> 32);
-          const uint32_t lev = omega_peek3(w << 1, ll);
-          bitpos += gl + 1u + ll;
-          ok = gap != 0 && lev != 0 && lev <= a.s && gap <= m - at_pos && bitpos <= stop;
-          at_pos += gap;
-          if (ok) {
-            const float mag = sr.scale * (float)lev;
-            rpos[cnt * 64 + lane] = at_pos - 1u;
-            rval[cnt * 64 + lane] = (w >> 31) ? -mag : mag;
-            ++cnt;
-          }
-          more = ok && bitpos < stop;
-        }
-      }
-      // deliver: a place in the message's list for every record, and its bit
-      const uint32_t incl = wave_incl_scan_u32(cnt, lane);
-      const uint32_t total = lane_bcast(incl, 63);
-      uint32_t at = 0;
-      if (s.cap && lane == 0) at = atomicAdd(&s.count[k], total);
-      at = lane_bcast(at, 0);
-      if (at + total > s.cap) {
-        if (lane == 0) *overflow = 1;
-      } else {
-        at += incl - cnt;
-        constexpr uint32_t kFly = 16;
-        for (uint32_t i0 = 0; i0 < cnt; i0 += kFly) {
-          uint32_t p[kFly], old[kFly];
+        const uint32_t w = peek(o + gl);
+        const uint32_t lev = by_last_group(w << 1, last_group_bits(w << 1), ll, open);
+        const bool good = gap != 0 && gap <= m && !open && lev <= a.s;
+        const uint32_t len = gl + 1u + ll;                     // (67 at most)
+        uint32_t to = good ? o + len : 32u;
+        what[t * 32u + o] = good ? len | (w >> 31) << 7 | lev << 8 : 0u;   // length, sign, level
+        gaps[t * 32u + o] = gap;
 #pragma unroll
-          for (uint32_t j = 0; j < kFly; ++j) {
-            old[j] = 0;
-            if (i0 + j < cnt) {
-              p[j] = rpos[(i0 + j) * 64 + lane];
-              old[j] = atomicOr(&s.seen[p[j] >> 5], 1u << (p[j] & 31u));
-              lpos[at + i0 + j] = p[j];
-              lval[at + i0 + j] = __float_as_uint(rval[(i0 + j) * 64 + lane]);
+        for (int i = 0; i < 4; ++i) {                          // (eleven records at most in a word)
+          const uint32_t on = (uint32_t)__shfl((int)to, (int)((lane & 32u) | (to & 31u)), kWave);
+          to = to < 32u ? on : to;
+        }
+        leaves[t * 32u + o] = (uint8_t)to;
+      }
+      __syncthreads();
+      if (wave == 0) {
+        const uint64_t word_bit = (w0 + lane) * 32u;
+        const uint32_t end = lane < here && word_bit < stop ? (uint32_t)min((uint64_t)32, stop - word_bit) : 0u;
+        const bool idle = end == 0;
+        uint32_t entry = lane == 0 ? entry0 : 0u, exit = 0;
+        bool again = !idle;
+        for (uint32_t round = 0; round <= kListWords; ++round) {
+          if (again) exit = entry < 32u ? leaves[lane * 32u + entry] : entry;
+          const uint32_t below = (uint32_t)__shfl_up((int)exit, 1, kWave) - 32u;
+          const uint32_t now = lane == 0 || idle ? entry : below;
+          again = now != entry;
+          entry = now;
+          if (__builtin_amdgcn_ballot_w64(again) == 0) break;
+        }
+        // the word's records
+        constexpr int kMost = 11;
+        uint32_t rec[kMost], gap[kMost], o = entry, adv = 0;
+        bool ok = true;
+#pragma unroll
+        for (int i = 0; i < kMost; ++i) {
+          rec[i] = gap[i] = 0;
+          if (o < end && ok) {
+            rec[i] = what[lane * 32u + o];
+            gap[i] = gaps[lane * 32u + o];
+            ok = rec[i] != 0;
+            if (ok) { adv += gap[i]; o += rec[i] & 127u; }
+          }
+        }
+        const uint32_t p_incl = wave_incl_scan_u32(adv, (int)lane);
+        uint32_t p = at_pos + p_incl - adv;
+        // (not the new position <= m: it is counted in 32 bits and could come round)
+        uint32_t sound = 0;
+#pragma unroll
+        for (int i = 0; i < kMost; ++i) {
+          if (rec[i]) {
+            ok = ok && p <= m && gap[i] <= m - p;
+            p += gap[i];
+            gap[i] = p - 1u;                                   // (the record's place from here on)
+            sound += ok ? 1u : 0u;
+          }
+        }
+        // the stretch ends where the next one starts, at the position the list names
+        const bool final_word = !idle && word_bit + 32u >= stop;
+        if (!idle && (!ok || (final_word && (o != end || (!last_stretch && p != pos_end))))) flag_corrupt(a.status);
+        // deliver: a place in the message's list for every record, and its bit
+        const uint32_t incl = wave_incl_scan_u32(sound, (int)lane);
+        const uint32_t total = lane_bcast(incl, 63);
+        uint32_t at = 0;
+        if (s.cap && lane == 0 && total) at = atomicAdd(&s.count[k], total);
+        at = lane_bcast(at, 0);
+        if (at + total > s.cap) {
+          if (lane == 0) *overflow = 1;
+        } else {
+          at += incl - sound;
+          uint32_t old[kMost];
+#pragma unroll
+          for (int i = 0; i < kMost; ++i) {
+            old[i] = 0;
+            if ((uint32_t)i < sound) {
+              const float mag = sr.scale * (float)(rec[i] >> 8);
+              old[i] = atomicOr(&s.seen[gap[i] >> 5], 1u << (gap[i] & 31u));
+              lpos[at + i] = gap[i];
+              lval[at + i] = __float_as_uint((rec[i] >> 7) & 1u ? -mag : mag);
             }
           }
 #pragma unroll
-          for (uint32_t j = 0; j < kFly; ++j) {
-            if (i0 + j < cnt && (old[j] >> (p[j] & 31u)) & 1u)
-              atomicOr(&s.multi[p[j] >> 5], 1u << (p[j] & 31u));
+          for (int i = 0; i < kMost; ++i) {
+            if ((uint32_t)i < sound && (old[i] >> (gap[i] & 31u)) & 1u)
+              atomicOr(&s.multi[gap[i] >> 5], 1u << (gap[i] & 31u));
           }
         }
+        // what the next words go on from
+        if (lane == kListWords - 1u) { carry[0] = exit - 32u; carry[1] = at_pos + p_incl; }
       }
       __syncthreads();
+      if (here == kListWords) { entry0 = carry[0]; at_pos = carry[1]; }
     }
-    // the stretch ends where the next one starts, at the position the list names
-    if (staged) bitpos = bit0 + at_bit;
-    if (mine && ok && !last_stretch) ok = bitpos == stop && at_pos == pos_end;
-    if (!ok) flag_corrupt(a.status);
-    __syncthreads();
   }
 }
 
@@ -1336,17 +1337,18 @@ hipError_t launch_gen_parse(const DecodeArgs& a, float* acc, bool entries, hipSt
   }
   return hipGetLastError();
 }
-// area: n words; lists: a.nb x kCollideBytes behind it; chunks: wavefronts per string.
+// area: n words; lists: a.nb x kCollideBytes behind it; stretches: about how many a string has; chunks:
+// workgroups per list in `apply`.
 hipError_t launch_sparse_long(const DecodeArgs& a, uint32_t* area, uint8_t* lists, uint32_t cus,
-                              uint32_t chunks, hipStream_t st) {
+                              uint32_t stretches, uint32_t chunks, hipStream_t st) {
   const uint64_t clear = (uint64_t)a.nb * (2u * bitmap_words(a.d) + a.K);
   const uint64_t most = (uint64_t)cus * 32;
   const uint32_t blocks = (uint32_t)((clear + 255) / 256 < most ? (clear + 255) / 256 : most);
   hipLaunchKernelGGL(k_sparse_clear, dim3(blocks), dim3(256), 0, st, a, area, lists);
-  hipLaunchKernelGGL(k_sparse_list, dim3(a.nb, a.K, chunks), dim3(64), 0, st, a, area, lists);
+  hipLaunchKernelGGL(k_sparse_list, dim3(a.nb, a.K, stretches), dim3(kListThreads), 0, st, a, area, lists);
   if (!a.step || std::signbit(a.c))
     hipLaunchKernelGGL(k_plus_zero, dim3(cus * 32), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_sparse_apply, dim3(a.nb, a.K, 4 * chunks), dim3(256), 0, st, a, area, lists);
+  hipLaunchKernelGGL(k_sparse_apply, dim3(a.nb, a.K, chunks), dim3(256), 0, st, a, area, lists);
   hipLaunchKernelGGL(k_sparse_resolve, dim3(a.nb), dim3(1024), 0, st, a, area, lists);
   return hipGetLastError();
 }

@@ -317,7 +317,7 @@ hipError_t launch_gen_parse(const DecodeArgs& a, float* acc, bool entries, hipSt
 constexpr uint32_t kCollide = 1024;
 constexpr uint32_t kCollideBytes = 256 + 12 * kCollide;
 hipError_t launch_sparse_long(const DecodeArgs& a, uint32_t* area, uint8_t* lists, uint32_t cus,
-                              uint32_t chunks, hipStream_t st);
+                              uint32_t stretches, uint32_t chunks, hipStream_t st);
 hipError_t launch_gen_apply(const DecodeArgs& a, const float* acc, uint32_t blocks, hipStream_t st);
 hipError_t launch_gen_decode_fixed(const DecodeArgs& a, uint32_t cus, hipStream_t st);
 
