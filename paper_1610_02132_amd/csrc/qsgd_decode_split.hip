@@ -637,6 +637,11 @@ SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words) {
            (uint64_t)per_cu * (lds_bytes(true) + 4 * kEntries) <= 156u * 1024u;
   p.waves = p.bits ? std::max(word_waves, std::min(std::min(kSplitWaves, 24u / per_cu), (a.K * words + 1) / 2))
                    : std::min(kSplitWaves, word_waves);
+  // Segments: the more of them, the smaller the workgroups, which wait for each other less (16M values,
+  // d = 9770, Code'_s, s = 85, K = 4, 16 / 8 / 4 / 2 wavefronts: 693 / 625 / 593 / 491 us; 13M, one bucket, s = 4,
+  // K = 8 349 / 349 / 321 / 368; 4M, d = 100 thousand, K = 16 321 / 254 / 277 / 442; 1M, d = 10 thousand, K = 8,
+  // 16 / 12 / 8 84 / 65 / 72).
+  if (lng && !p.bits) p.waves = std::min(p.waves, per_cu >= 16 ? std::max(2u, std::min(4u, a.K / 2)) : per_cu >= 4 ? 8u : 12u);
   p.waves = std::max(p.waves, (span + 1023) / 1024);
   if (!p.bits) p.turn_words = 64 * p.waves;
   p.lds = lds_bytes(p.bits);
