@@ -129,7 +129,8 @@ void k_encode_direct(EncodeArgs a) {
   constexpr int R = 4 * Q;                      // values of a run
   constexpr uint32_t kStep = LPB * R;           // values one run of the bucket's lanes covers
   constexpr uint32_t kTab = code_entries<kSparse>();
-  __shared__ uint32_t codes[kTab], omegas[LONG ? kOmegas : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t codes[kTab];
+  __shared__ uint32_t omegas[LONG ? kOmegas : 1];
   extern __shared__ uint32_t smem[];            // per wavefront: NB bucket strings of dst_words
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
@@ -141,9 +142,19 @@ void k_encode_direct(EncodeArgs a) {
     const uint32_t *src, *om;
     if constexpr (kSparse) { src = g_codes_sparse.e; om = g_codes_sparse.omega; }
     else { src = g_codes_dense.e; om = g_codes_dense.omega; }
-    for (uint32_t i = tid; i < kTab; i += blockDim.x) codes[i] = src[i];
+    // (16 bytes a load, all of them in flight)
+    constexpr uint32_t kQuads = kTab / 4, kLoads = (kQuads + 64 * kDirectWaves - 1) / (64 * kDirectWaves);
+    uint4 t[kLoads];
+#pragma unroll
+    for (uint32_t j = 0; j < kLoads; ++j)
+      t[j] = reinterpret_cast<const uint4*>(src)[min((uint32_t)tid + j * 64u * kDirectWaves, kQuads - 1u)];
     if (LONG && tid < (int)kOmegas) omegas[tid] = om[tid];
     for (uint32_t j = l; j < a.dst_words; j += LPB) dst[j] = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kLoads; ++j) {
+      const uint32_t i = (uint32_t)tid + j * 64u * kDirectWaves;
+      if (i < kQuads) reinterpret_cast<uint4*>(codes)[i] = t[j];
+    }
   }
   if (blockIdx.x == 0 && tid == 0) {  // header; length and status are completed later
     uint32_t* h = a.header;
