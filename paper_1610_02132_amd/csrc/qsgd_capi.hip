@@ -445,16 +445,14 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
                                 cus, stretches, chunks, st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
     }
   }
-  {
+  if (L && L->R) {   // the headers, and the small tensors: raw values behind the strings
+    ScopedTiming tm("decode_raw", st);
+    if (launch_raw_apply(a, raw_args(g, L), st) != hipSuccess) return QSGD_ERR_HIP;
+  } else {
     ScopedTiming tm("decode_check", st);
     if (launch_decode_check(a, st) != hipSuccess) return QSGD_ERR_HIP;
   }
-  if (g.n == 0) return QSGD_OK;
-  if (L && L->R) {   // the small tensors: raw values behind the strings
-    ScopedTiming tm("decode_raw", st);
-    if (launch_raw_apply(a, raw_args(g, L), st) != hipSuccess) return QSGD_ERR_HIP;
-  }
-  if (g.nb == 0) return QSGD_OK;
+  if (g.n == 0 || g.nb == 0) return QSGD_OK;
   // Levels fit a byte.  (The general path's reader, a thread per stretch or bucket and message after
   // message, is left with the rest: 573 thousand values in one bucket, Code'_s, s = 127, K = 7:
   // 17.6 ms there, 65 us in the split decoder.)
@@ -824,9 +822,8 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
     const uint32_t wgs = 4 * (uint32_t)device_cus();
     c.tpb = std::min<uint32_t>(kWave, std::max<uint32_t>(4, (pl.teams + wgs - 1) / wgs));
     ScopedTiming tm("encode_compact", st);
-    if (launch_encode_compact(c, st) != hipSuccess) return QSGD_ERR_HIP;
-  }
-  if (L && L->R) {
+    if (launch_encode_compact(c, L ? &ra : nullptr, st) != hipSuccess) return QSGD_ERR_HIP;
+  } else if (L && L->R) {
     ScopedTiming tm("encode_raw", st);
     if (launch_raw_pack(ra, st) != hipSuccess) return QSGD_ERR_HIP;
   }

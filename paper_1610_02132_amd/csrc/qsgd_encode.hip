@@ -573,11 +573,17 @@ void k_encode_fixed_small_batch(EncodeArgs a, EncodeBatch batch) {
 // are added up, and the next team's before this one is stored, 7.2 at 7143.
 constexpr uint32_t kCompactWaves = 4;
 typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4)));
-__global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactArgs a) {
+//
+// RAW: the workgroups behind the teams' copy the small tensors of a tensor-aware message, a piece of
+// kRawPiece values each, behind all strings.  (A launch of their own took 4.7 us.)
+template <bool RAW>
+__global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactArgs a, RawArgs r) {
   __shared__ unsigned long long part[kCompactWaves];
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
-  const uint32_t t_begin = blockIdx.x * a.tpb;
+  const uint32_t groups = (a.teams + a.tpb - 1) / a.tpb;
+  const bool raw = RAW && blockIdx.x >= groups;
+  const uint32_t t_begin = raw ? a.teams : blockIdx.x * a.tpb;
   const uint32_t t_end = min(t_begin + a.tpb, a.teams);
 
   // (tpb <= 64: lane l keeps the total of the workgroup's team l)
@@ -617,6 +623,24 @@ __global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactAr
   unsigned long long base = 0;
 #pragma unroll
   for (uint32_t w = 0; w < kCompactWaves; ++w) base += part[w];
+
+  if constexpr (RAW) {
+    if (raw) {
+      // (where a string did not fit the message is void, whatever stands in it)
+      if (base + r.raw_words > a.cap_words) return;
+      const uint4 e = r.rtab[blockIdx.x - groups];
+      const float* __restrict__ src = r.g + (uint64_t)e.x * 4u;
+      uint32_t* __restrict__ dst = a.payload + base + e.z;
+      const uint32_t i = (uint32_t)tid * 4u;
+      if (i + 3u < e.y) {
+        const v4u_any v = *reinterpret_cast<const v4u_any*>(src + i);   // tensors start at 16-byte multiples
+        *reinterpret_cast<v4u_any*>(dst + i) = v;
+      } else {
+        for (uint32_t j = i; j < e.y; ++j) dst[j] = __float_as_uint(src[j]);
+      }
+      return;
+    }
+  }
 
   bool all_fit = true;
   for (uint32_t j = t_begin; j < t_end; ++j) {
@@ -754,9 +778,12 @@ hipError_t launch_encode_fixed_small_batch(const EncodeArgs& a, const EncodeBatc
   return hipGetLastError();
 }
 
-hipError_t launch_encode_compact(const CompactArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_encode_compact, dim3((a.teams + a.tpb - 1) / a.tpb),
-                     dim3(64 * kCompactWaves), 0, st, a);
+static_assert(kRawPiece == 4 * 64 * kCompactWaves, "a piece per workgroup, four values per thread");
+hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, hipStream_t st) {
+  const uint32_t groups = (a.teams + a.tpb - 1) / a.tpb;
+  const dim3 block(64 * kCompactWaves);
+  if (raw && raw->R) hipLaunchKernelGGL(k_encode_compact<true>, dim3(groups + raw->R), block, 0, st, a, *raw);
+  else hipLaunchKernelGGL(k_encode_compact<false>, dim3(groups), block, 0, st, a, RawArgs());
   return hipGetLastError();
 }
 

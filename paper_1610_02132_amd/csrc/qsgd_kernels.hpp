@@ -179,13 +179,8 @@ struct DecodeArgs {
   uint32_t fixed_words_full;
 };
 
-// One thread per message (the first workgroup of a launch, at least K threads): resets the
-// status word; the header must describe the same code as the call.
-__device__ __forceinline__ void check_headers(const DecodeArgs& a) {
-  const uint32_t k = threadIdx.x;
-  if (k == 0) *a.status = 0;
-  __syncthreads();
-  if (k >= a.K) return;
+// Whether the header of message k describes the same code as the call.
+__device__ __forceinline__ bool header_sound(const DecodeArgs& a, uint32_t k) {
   bool ok = a.msg_words[k] >= (uint64_t)H_WORDS + a.table_words;
   if (ok) {
     const uint32_t* h = a.msgs[k];
@@ -201,7 +196,16 @@ __device__ __forceinline__ void check_headers(const DecodeArgs& a) {
       ok = strings + a.raw_words == pw;
     }
   }
-  if (!ok) flag_corrupt(a.status);
+  return ok;
+}
+
+// One thread per message (the first workgroup of a launch, at least K threads): resets the
+// status word, and reports headers that do not fit the call.
+__device__ __forceinline__ void check_headers(const DecodeArgs& a) {
+  const uint32_t k = threadIdx.x;
+  if (k == 0) *a.status = 0;
+  __syncthreads();
+  if (k < a.K && !header_sound(a, k)) flag_corrupt(a.status);
 }
 
 // Raw section of tensor-aware messages: the small tensors in pieces of kRawPiece values.
@@ -273,7 +277,9 @@ hipError_t launch_encode_bucket(const EncodeArgs& a, uint32_t code, int tw, int 
 constexpr uint32_t kDirectWaves = 4;   // wavefronts (teams) that share a code word table
 uint32_t direct_buckets_per_pass(uint32_t d, bool few);
 hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, uint32_t teams, hipStream_t st);
-hipError_t launch_encode_compact(const CompactArgs& a, hipStream_t st);
+struct RawArgs;
+// raw: the small tensors of a tensor-aware message, or null
+hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, hipStream_t st);
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,
                                      hipStream_t st);
 hipError_t launch_encode_fixed_small_batch(const EncodeArgs& a, const EncodeBatch& batch, uint32_t K,
@@ -304,6 +310,7 @@ hipError_t launch_write_layout_header(uint32_t* header, uint32_t* table, uint32_
                                       uint64_t raw_words, uint32_t stream_id, uint32_t iteration,
                                       hipStream_t st);
 hipError_t launch_raw_pack(const RawArgs& a, hipStream_t st);
+// (the header check included)
 hipError_t launch_raw_apply(const DecodeArgs& a, const RawArgs& r, hipStream_t st);
 hipError_t launch_gen_scale(const GenArgs& a, hipStream_t st);
 hipError_t launch_gen_encode(const GenArgs& a, bool aligned, hipStream_t st);
