@@ -270,10 +270,22 @@ void plan_encode(const Geometry& g, uint64_t ws_avail, EncodePlan& pl) {
   // for the rest, L2 and max.  Buckets that no vector load fits have no other
   // encoder but the general path (10M values, d = 443: 141 and 33 us, d = 41: 1150 and 55).
   const bool sparse = g.code == QSGD_CODE_SPARSE;
+  // Code_s where several wavefronts share a bucket: the survivors of all of a wavefront's
+  // chunks are listed before they are coded when the list is expected to be at most half
+  // full, the share of nonzero levels being at most s (s + sqrt(d)) / d (Lemma 3.1 (iii));
+  // a wavefront whose list overflows after all starts over with the direct coder.  Sparse strings
+  // that are too dense for it are coded chunk by chunk, which the direct encoder does better up to
+  // d = 7168 (30M values, team / direct: d = 2500, s = 4 118 / 63 us, d = 4096, s = 4 91 / 66, s = 8 94 /
+  // 64, d = 6000, s = 5 113 / 73, d = 8192, s = 8 87 / 85; with the list d = 2500, s = 2 58 / 65, d = 4096, s = 3
+  // 42 / 64; 3M values, d = 4096, s = 4 18 / 20).
+  const uint32_t list = qsgd::list_records(pl.cpw);
+  const bool listed = sparse && pl.tw >= 2 &&
+                      2.0 * g.s * (g.s + std::sqrt((double)g.d)) * (pl.cpw * kChunk) <= (double)g.d * list;
   if (g.code == QSGD_CODE_FIXED) pl.direct = false;
   else if (g.d % 4 != 0) pl.direct = true;
   else if (g.d <= 2048) pl.direct = dense_strings(g) || g.d <= 512 || g.d > 1024;
-  else pl.direct = dense_strings(g) && g.max_words(g.d) <= 4096 &&   // (LDS: eight wavefronts at least)
+  else pl.direct = (dense_strings(g) || (sparse && !listed && g.d <= 7168 && nb >= cus * 4u)) &&
+                   g.max_words(g.d) <= 4096 &&   // (LDS: eight wavefronts at least)
                    (!sparse || (g.d <= 7168 ? g.s > 1 || g.d <= 3072 : 8ull * g.s * g.s > g.d)) &&
                    nb >= cus * (g.d <= 4096 ? (sparse ? 2u : 8u) : (sparse ? 4u : 24u));
   // direct: the teams a compute unit holds at once, whole passes each; else persistent teams
@@ -299,15 +311,7 @@ void plan_encode(const Geometry& g, uint64_t ws_avail, EncodePlan& pl) {
     }
     pl.ws_bytes = kTotalsBytes + (uint64_t)pl.teams * pl.region_words * 4;
   }
-  // Code_s where several wavefronts share a bucket: the survivors of all of a wavefront's
-  // chunks are listed before they are coded when the list is expected to be at most half
-  // full, the share of nonzero levels being at most s (s + sqrt(d)) / d (Lemma 3.1 (iii));
-  // a wavefront whose list overflows after all starts over with the direct coder.
-  pl.ring = 0;
-  const uint32_t list = qsgd::list_records(pl.cpw);
-  if (g.code == QSGD_CODE_SPARSE && pl.tw >= 2 &&
-      2.0 * g.s * (g.s + std::sqrt((double)g.d)) * (pl.cpw * kChunk) <= (double)g.d * list)
-    pl.ring = list;
+  pl.ring = listed ? list : 0;
   const size_t ring_words =
       g.code == QSGD_CODE_SPARSE ? qsgd::ring_words(pl.ring ? pl.ring : qsgd::kRing) : 0;
   pl.lds = 4 * ((size_t)pl.dst_words + (size_t)pl.tw * (pl.sub_words + ring_words)) + 8 * pl.tw +
