@@ -143,9 +143,8 @@ size_t qsgd_static_scratch_bytes(void);
  *                  with the same n, d, s, code, norm as *p), 1 <= K <= QSGD_MAX_PEERS
  *   msg_bytes      host array of K sizes: readable bytes behind each pointer (the
  *                  kernels never read past them, whatever a header claims)
- *                  Pass a message's own length where it is known: it tells how dense
- *                  max-scaled Code_s messages of buckets above 8192 values are, which
- *                  picks the decoder (the results are the same)
+ *                  Pass a message's own length where it is known: it tells how long
+ *                  the strings are, which picks the decoder (the results are the same)
  *   acc_dev        in/out: n floats, device, 16-byte aligned
  *   workspace_dev  >= qsgd_workspace_bytes(p, K); word 0 receives the status
  * Errors: INVALID_ARG, CAPACITY, HIP, UNSUPPORTED on the host; a header that does

@@ -219,8 +219,9 @@ uint32_t string_words(const Geometry& g, const size_t* msg_bytes, uint32_t K, ui
 // read and written.  Levels that the tile decoder's table does not hold cost it twice; a record of the
 // ring decoder costs the more the more of them fall in a window.  Fitted to 286 steps (d = 96 .. 8192, s = 3
 // .. 100% of sqrt(d), L2 and max, both codes, K = 1 .. 24, 20 thousand to 60M values and c5), 12% off on
-// the average (tile) and 30% (ring); the choice by these two and the split decoder's estimate is 1% behind
-// the best of the three on them, 28% where the ring decoder had all of 64 s^2 <= d.
+// the average (tile) and 30% (ring); the choice by these two and the split decoder's estimate is about 1%
+// behind the best on the steps of the fit, and was 28% on the 126 of them with Code_s and L2 where the ring
+// decoder had all of 64 s^2 <= d.
 // Ring / tile / split, us:
 //   16M values, K = 4:  d = 512, s = 2 101 / 52 / 185   d = 4096, s = 2 202 / 126 / 122
 //                       d = 4096, s = 8 633 / 178 / 217  d = 8192, s = 7 544 / 285 / 245
