@@ -140,7 +140,7 @@ __device__ __forceinline__ uint32_t entry_before(const uint32_t* list, uint32_t 
 template <int CODE, int NG, bool LONGB, bool BITS>
 __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a) {
   constexpr bool kSparse = CODE == QSGD_CODE_SPARSE;
-  __shared__ uint32_t table[kEntries];
+  __shared__ __attribute__((aligned(16))) uint32_t table[kEntries];   // (filled 16 bytes at a time)
   const uint32_t status = *a.status;
   extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   const uint32_t thread = threadIdx.x, threads = blockDim.x;

@@ -59,3 +59,15 @@ def test_loops_over_a_long_buckets_values_count_in_64_bits():
     loops = re.findall(r"for \((\w+) (\w+) = [^;]*threadIdx\.x[^;]*; \2 < (?:m|a\.n); \2 \+= ", text)
     assert len(loops) >= 3
     assert all(kind == "uint64_t" for kind, _ in loops), loops
+
+
+def test_arrays_stored_16_bytes_at_a_time_say_so():
+    """An array of words in LDS is aligned to 4 bytes unless it says otherwise."""
+    seen = []
+    for file, name, _, block, _ in kernels():
+        for array in set(re.findall(r"reinterpret_cast<uint4\s*\*>\((\w+)\)\[", block)):
+            decl = re.search(r"[^;{}]*__shared__[^;]*\b%s\[" % array, block)
+            if decl:
+                seen.append((file, array))
+                assert "aligned(16)" in decl.group(0), f"{file}: {name}: {array}"
+    assert len(seen) >= 2
