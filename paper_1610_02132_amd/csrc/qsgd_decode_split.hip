@@ -418,7 +418,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
             if (LONGB && gap > 0xFFFFu) gap = 0;               // (read again where it is used)
           }
           recs[t * 32u + o] = len ? len | (lev & 0xFFu) << 8 | gap << 16 : 0u;
-          // two records at least, then four, eight, sixteen: all of a word's
+          // Eight of these jumps leave the word from wherever they begin.  A jump of two records passes 6
+          // bits at least.  One of a single record may pass 3, but then the record behind does not fit
+          // in the rest of the kBits bits: these two jumps pass kBits + 1 = 11 at least.  (Where the
+          // entry was dropped for a level above s, the record with that level ends the chain: `to` = 32.)
 #pragma unroll
           for (int i = 0; i < 3; ++i) {
             const uint32_t on = (uint32_t)__shfl((int)to, (int)((lane & 32u) | (to & 31u)), kWave);
