@@ -383,7 +383,6 @@ RawArgs raw_args(const Geometry& g, const qsgd_layout* L) {
   std::memset(&r, 0, sizeof r);
   r.rtab = L->rtab; r.R = L->R; r.raw_words = L->raw;
   r.fixed_strings = g.code == QSGD_CODE_FIXED ? g.nb * g.max_words(g.d) : 0;
-  r.nb = (uint32_t)g.nb;
   return r;
 }
 
@@ -738,8 +737,7 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
   if (L && g.nb == 0) {   // every tensor travels raw: header (and an empty table) only
     if (cap_words < raw_words) return QSGD_ERR_CAPACITY;
     RawArgs ra = raw_args(g, L);
-    ra.g = g_dev; ra.header = header; ra.table = table; ra.payload = payload;
-    ra.cap_words = cap_words;
+    ra.g = g_dev; ra.payload = payload; ra.cap_words = cap_words;
     ScopedTiming tm("encode_raw", st);
     if (launch_write_layout_header(header, table, g.code, g.norm, g.s, g.d, g.n, raw_words,
                                    p->stream_id, p->iteration, st) != hipSuccess)
@@ -783,8 +781,7 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
   RawArgs ra;
   if (L) {
     ra = raw_args(g, L);
-    ra.g = g_dev; ra.header = header; ra.table = table; ra.payload = payload;
-    ra.cap_words = cap_words;
+    ra.g = g_dev; ra.payload = payload; ra.cap_words = cap_words;
   }
   if (g.code == QSGD_CODE_FIXED && g.d <= 1024) {
     // small buckets: several ride in one wavefront

@@ -232,18 +232,6 @@ __device__ __forceinline__ void lds_emit(uint32_t* words, uint32_t bitoff, uint6
   if (sh + len > 64u) atomicOr(&words[w + 2], (uint32_t)top << (32u - sh));
 }
 
-// Same on global memory (words zero-initialised, shared by several writers).
-__device__ __forceinline__ void global_emit(uint32_t* words, uint64_t bitoff, uint64_t code,
-                                            uint32_t len) {
-  const uint64_t top = code << (64u - len);
-  const uint64_t w = bitoff >> 5;
-  const uint32_t sh = (uint32_t)(bitoff & 31u);
-  const uint64_t a = top >> sh;
-  atomicOr(&words[w], (uint32_t)(a >> 32));
-  if (sh + len > 32u) atomicOr(&words[w + 1], (uint32_t)a);
-  if (sh + len > 64u) atomicOr(&words[w + 2], (uint32_t)top << (32u - sh));
-}
-
 // ---- streaming accesses ----------------------------------------------------------
 // For data that is touched once (the gradient, x): the caches then keep what is
 // touched again, such as message strings read piece by piece.
@@ -317,17 +305,6 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
   v = min(v, dpp_fetch_or<kDppShr8, 0xf>(0xFFFFFFFFu, v));
   v = min(v, dpp_fetch_or<kDppBcast15, 0xa>(0xFFFFFFFFu, v));
   v = min(v, dpp_fetch_or<kDppBcast31, 0xc>(0xFFFFFFFFu, v));
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// Max over the 64 lanes, returned to every lane.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  v = max(v, dpp_fetch<kDppShr1, 0xf>(v));
-  v = max(v, dpp_fetch<kDppShr2, 0xf>(v));
-  v = max(v, dpp_fetch<kDppShr4, 0xf>(v));
-  v = max(v, dpp_fetch<kDppShr8, 0xf>(v));
-  v = max(v, dpp_fetch<kDppBcast15, 0xa>(v));
-  v = max(v, dpp_fetch<kDppBcast31, 0xc>(v));
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 

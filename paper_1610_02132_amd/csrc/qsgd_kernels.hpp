@@ -214,14 +214,11 @@ struct RawArgs {
   const uint4* rtab;         // per piece: (start / 4, length, offset in the raw section, 0)
   uint32_t R;
   uint64_t raw_words;        // all raw values of a message
-  uint64_t fixed_strings;    // fixed width: words of all bucket strings; else 0 (read the table)
+  uint64_t fixed_strings;    // words of all bucket strings where the host knows them (fixed width), else 0
   // encode
   const float* g;
-  uint32_t* header;
-  const uint32_t* table;
   uint32_t* payload;
   uint64_t cap_words;
-  uint32_t nb;
 };
 
 constexpr uint32_t kSeg = 2048;  // values per segment on the general path
@@ -277,7 +274,6 @@ hipError_t launch_encode_bucket(const EncodeArgs& a, uint32_t code, int tw, int 
 constexpr uint32_t kDirectWaves = 4;   // wavefronts (teams) that share a code word table
 uint32_t direct_buckets_per_pass(uint32_t d, bool few);
 hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, uint32_t teams, hipStream_t st);
-struct RawArgs;
 // raw: the small tensors of a tensor-aware message, or null
 hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, hipStream_t st);
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,

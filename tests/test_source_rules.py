@@ -71,3 +71,11 @@ def test_arrays_stored_16_bytes_at_a_time_say_so():
                 seen.append((file, array))
                 assert "aligned(16)" in decl.group(0), f"{file}: {name}: {array}"
     assert len(seen) >= 2
+
+
+def test_every_device_function_has_a_caller():
+    text = "".join(re.sub(r"//[^\n]*", "", open(os.path.join(CSRC, n)).read()) for n in sorted(os.listdir(CSRC)))
+    names = set(re.findall(r"__device__\b[^;{}()]*?\b(\w+)\([^;{]*\)\s*\{", text))
+    assert len(names) >= 40
+    alone = [n for n in sorted(names) if len(re.findall(r"\b%s\b" % n, text)) < 2]
+    assert not alone, alone
