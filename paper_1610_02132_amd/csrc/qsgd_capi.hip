@@ -204,46 +204,8 @@ double shortest_string(const Geometry& g, const size_t* msg_bytes, uint32_t K) {
   return std::max(1.0, (words - H_WORDS - (double)g.table_words) / (double)std::max<uint64_t>(g.nb, 1));
 }
 
-// ... and no more than the K messages have room for, on the average: they may be cut to their length.
-uint32_t string_words(const Geometry& g, const size_t* msg_bytes, uint32_t K, uint64_t raw_words) {
-  const double fixed = (double)(H_WORDS + g.table_words + raw_words);
-  double words = 0.0;
-  for (uint32_t k = 0; k < K; ++k) words += std::max(0.0, (double)(msg_bytes[k] / 4) - fixed);
-  words = words / ((double)std::max<uint64_t>(g.nb, 1) * K) + 1.0;
-  const uint32_t guess = string_words(g);
-  return words < (double)guess ? (uint32_t)words : guess;
-}
-
-// About how long the decoders with a lane for every string take (us): the windows of a bucket and the
-// records of a string one after the other, or all of them at the rate of a machine that is full, and x
-// read and written.  Levels that the tile decoder's table does not hold cost it twice; a record of the
-// ring decoder costs the more the more of them fall in a window.  Fitted to 286 steps (d = 96 .. 8192, s = 3
-// .. 100% of sqrt(d), L2 and max, both codes, K = 1 .. 24, 20 thousand to 60M values and c5), 12% off on
-// the average (tile) and 30% (ring); the choice by these two and the split decoder's estimate is about 1%
-// behind the best on the steps of the fit, and was 28% on the 126 of them with Code_s and L2 where the ring
-// decoder had all of 64 s^2 <= d.
-// Ring / tile / split, us:
-//   16M values, K = 4:  d = 512, s = 2 101 / 52 / 185   d = 4096, s = 2 202 / 126 / 122
-//                       d = 4096, s = 8 633 / 178 / 217  d = 8192, s = 7 544 / 285 / 245
-//   60M values, K = 16: d = 1024, s = 1 168 / 278 / 1217   d = 4096, s = 2 195 / 366 / 1596
-//                       d = 4096, s = 5 659 / 441 / 3570   d = 8192, s = 5 721 / 411 / 2484
-//   1e9 values, d = 8192, s = 4, outliers, K = 16: 1780 / 3678 / 21400
-//   Code'_s, K = 9: 2M values, d = 1024, s = 32 - / 70 / 288   d = 8192, s = 30 - / 379 / 91
-float both(float latency, float rate) { return std::sqrt(latency * latency + rate * rate); }
-float tile_us(const Geometry& g, uint32_t K, float words) {
-  const float d = (float)g.d, strings = (float)g.nb * (float)K;
-  const float beyond = std::min(1.f, std::max(0.f, ((float)mean_level(g) - 4.f) / 6.f));
-  return 8.3f + both(0.0247f * d + 0.329f * words * (1.f + 2.58f * beyond),
-                     strings * (1.5e-7f * d + 6.03e-6f * words) + 1.4e-6f * (float)g.nb * d);
-}
-float ring_us(const Geometry& g, uint32_t K, float words) {
-  const float d = (float)g.d, dense = words * words / d, strings = (float)g.nb * (float)K;
-  return 32.f + both(106.f * dense + 0.01f * d, strings * 8.58e-4f * dense + 1.4e-6f * (float)g.nb * d);
-}
-
 // Dense strings: the share of nonzero levels grows like s / sqrt(d) (Lemma 3.1 (iii)); with the
-// largest value as scale it is larger still, and Code'_s codes every coordinate.  (What the encoder
-// goes by; the decoder's choice has its own estimates.)
+// largest value as scale it is larger still, and Code'_s codes every coordinate.
 bool dense_strings(const Geometry& g) {
   return g.code == QSGD_CODE_DENSE || 64ull * g.s * g.s > g.d || g.norm == QSGD_NORM_MAX;
 }
@@ -386,6 +348,114 @@ RawArgs raw_args(const Geometry& g, const qsgd_layout* L) {
   return r;
 }
 
+// How long the strings of a step are, in words: `words` on the average over the messages that were cut
+// to their length (a message has the guess where a whole buffer stands behind it, whatever the others
+// say, and is taken for two guesses at most), and the guess itself, that of normal values.
+struct StringLength { double words, guess; };
+StringLength string_length(const Geometry& g, const qsgd_layout* L, const size_t* msg_bytes, uint32_t K) {
+  const double nb = (double)std::max<uint64_t>(g.nb, 1), guess = string_words(g);
+  const double fixed = (double)(H_WORDS + g.table_words + (L ? L->raw : 0));
+  const uint64_t full = g.nb - (L ? L->short_buckets : 0);   // the worst case, at least
+  const double whole = L ? (double)full * (double)g.max_words(g.d) : (double)g.max_payload_words();
+  double sum = 0.0;
+  for (uint32_t k = 0; k < K; ++k) {
+    const double room = std::max(0.0, (double)(msg_bytes[k] / 4) - fixed);
+    sum += room < whole ? std::min(room / nb + 0.5, 2.0 * guess) : guess;
+  }
+  return {sum / K, guess};
+}
+
+// A lane for every string: buckets per wavefront (a power of two, gw * K lanes) and how the wavefronts
+// share the machine.
+struct TilePlan { uint32_t gw, per_cu, rounds, waves, blocks; };
+TilePlan plan_tile(const Geometry& g, uint32_t K, uint32_t cus) {
+  TilePlan p;
+  p.gw = 1;
+  while (p.gw * 2 * K <= 64) p.gw *= 2;
+  while (p.gw > 1 && (g.nb + p.gw - 1) / p.gw < (uint64_t)cus * 4) p.gw /= 2;
+  const uint32_t tasks = (uint32_t)((g.nb + p.gw - 1) / p.gw);
+  // as many wavefronts per compute unit as give every one of them the same number of
+  // groups; at least four, one per SIMD, share the work of loading the table
+  const uint32_t most = tile_max_waves(g.code);
+  p.per_cu = (uint32_t)(((uint64_t)tasks + cus - 1) / cus);
+  p.rounds = (p.per_cu + most - 1) / most;
+  p.waves = std::max(4u, (p.per_cu + p.rounds - 1) / p.rounds);
+  p.blocks = std::min(cus, (tasks + p.waves - 1) / p.waves);
+  return p;
+}
+uint32_t ring_buckets(const Geometry& g, uint32_t K, uint32_t cus) {   // per wavefront
+  uint32_t gw = 1;
+  while (gw * 2 * K <= 64 && gw * 2 <= 16) gw *= 2;
+  while (gw > 1 && (g.nb + gw - 1) / gw < (uint64_t)cus * 8) gw /= 2;
+  return gw;
+}
+
+// Which decoder reads the Elias strings of buckets up to 8192 values, by about how long (us) each of them
+// takes.  The tile decoder and the ring decoder have a lane for every string and wait for the longest
+// one, which is the nearer to the guess the shorter the strings are on the average (buckets with and
+// without an outlier); where the machine is full their wavefronts take turns.  The split decoder has a
+// lane for every word or bit (plan_decode_split).
+//
+// Fitted to 6716 steps drawn over d = 64 .. 8192 and off 4, s up to 64 (Code'_s 127), L2 and max, K = 1 ..
+// 32, 4 thousand to 100M values of five distributions, messages cut to their length; tile 14%, split 20%
+// and ring 21% off on 6716 others.  The estimates have to be a tenth apart before they overrule the
+// plainer rule: the ring decoder for 64 s^2 <= d (Code_s, L2), else the tile decoder, and the split
+// decoder for few strings.  On those others, chosen time over that of the best decoder, on the geometric
+// average, and share of steps slower than by the plainer rule by over 3%:  the plainer rule 1.105, -;  the
+// estimates alone 1.009, 2.4%;  this way 1.009, 1.5%, and with all messages in whole buffers 1.020, 1.6%.
+// Ring / tile / split, us:
+//   16M values, K = 4:  d = 512, s = 2 101 / 52 / 185   d = 4096, s = 2 202 / 126 / 122
+//                       d = 4096, s = 8 633 / 178 / 217  d = 8192, s = 7 544 / 285 / 245
+//   60M values, K = 16: d = 1024, s = 1 168 / 278 / 1217   d = 4096, s = 2 195 / 366 / 1596
+//                       d = 4096, s = 5 659 / 441 / 3570   d = 8192, s = 5 721 / 411 / 2484
+//   1e9 values, d = 8192, s = 4, outliers, K = 16: 1780 / 3678 / 21400
+//   Code'_s, K = 9: 2M values, d = 1024, s = 32 - / 70 / 288   d = 8192, s = 30 - / 379 / 91
+//   75 thousand values, Code'_s, d = 280, s = 10, outliers, K = 30 - / 25 / 39
+//   92 thousand values, d = 2564, s = 41, Student-t, K = 28 - / 145 / 125
+double tile_us(const Geometry& g, const TilePlan& p, const StringLength& w) {
+  const bool sparse = g.code == QSGD_CODE_SPARSE;
+  const double d = sparse ? (double)g.d : 0.0;   // (Code'_s: its records pay for the windows)
+  const double longest = w.words + 0.755 * std::max(0.0, w.guess - w.words);
+  // levels that the tile decoder's table does not hold cost it twice
+  const double far = 1.0 + std::min(1.0, std::max(0.0, (mean_level(g) - 4.0) / 6.0));
+  const double chain = 0.0235 * d + (sparse ? 0.438 : 0.588) * longest * far;
+  const double full = (double)p.per_cu / p.rounds * (0.00264 * d + 0.0596 * w.words * far);
+  return 10.6 + p.rounds * std::max(chain, full) + 1.94e-6 * (double)g.nb * (double)g.d;
+}
+double ring_us(const Geometry& g, uint32_t gw, const StringLength& w, uint32_t cus) {
+  const double longest = w.words + 0.6 * std::max(0.0, w.guess - w.words);
+  const double chain = 2.04 * longest + 16.8 * longest * longest / (double)g.d;   // (records that share a window)
+  const double tasks = (double)((g.nb + gw - 1) / gw);
+  return 7.0 + chain * std::max(1.0, 0.14 * tasks / cus) + 1.4e-6 * (double)g.nb * (double)g.d;
+}
+
+enum class Decoder { ring, tile, split };
+struct DecoderChoice { Decoder which; TilePlan tile; SplitPlan split; };
+DecoderChoice choose_decoder(const Geometry& g, const DecodeArgs& a, const StringLength& w, uint32_t cus) {
+  DecoderChoice c;
+  const uint32_t K = a.K;
+  c.tile = plan_tile(g, K, cus);
+  c.split = plan_decode_split(a, cus, (uint32_t)(w.words + 0.5));
+  // The counting apply of the ring decoder keeps a bit per message in a 32-bit word, and its loads
+  // are of four values.  With the largest value as scale the share of nonzero levels
+  // depends on the data: heavy tails bring it down, but not in every bucket, and the ring decoder
+  // waits for the longest string (8M values, K = 16, max, ring / tile: 0.1% of the values x100 d = 512,
+  // s = 4 292 / 106 us, d = 8192, s = 1 773 / 301; Student-t 222 / 95, 452 / 304; 1% x1000, all
+  // strings short, 192 / 88, 76 / 166).
+  const bool ring = g.code == QSGD_CODE_SPARSE && g.norm == QSGD_NORM_L2 && K <= 32 && g.d % 4 == 0;
+  const double tile = tile_us(g, c.tile, w), split = c.split.us;
+  const double ringed = ring ? ring_us(g, ring_buckets(g, K, cus), w, cus) : HUGE_VAL;
+  const double strings = (double)g.nb * K;
+  const bool tiled = !ring || dense_strings(g);
+  const bool few = tiled ? 12.0 + strings * w.guess / 10000.0 < 5.0 + 0.64 * w.guess
+                         : 17.0 + strings * w.guess / 6000.0 < 3.0 + 1.7 * w.guess;
+  c.which = few ? Decoder::split : tiled ? Decoder::tile : Decoder::ring;
+  const double plain = few ? split : tiled ? tile : ringed;
+  const double best = std::min(std::min(tile, ringed), split);
+  if (1.1 * best < plain) c.which = best == tile ? Decoder::tile : best == split ? Decoder::split : Decoder::ring;
+  return c;
+}
+
 int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* msgs_dev,
                const size_t* msg_bytes, uint32_t K, float c, uint32_t step, float* x_dev,
                void* ws, size_t ws_bytes, void* hip_stream) {
@@ -416,19 +486,6 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   a.status = static_cast<uint32_t*>(ws);
   a.fixed_bits = g.fixed_bits;
   a.fixed_words_full = (uint32_t)g.max_words(g.d);
-  // Which decoder, and which apply step, Elias strings of buckets up to 8192 values take: the ring
-  // decoder with the counting apply, which keeps a bit per message in a 32-bit word (more than 32
-  // messages go the other way whatever the data), or the tile decoder.  Code'_s has a record for
-  // every coordinate, and with the largest value as scale the share of nonzero levels depends on the
-  // data: heavy tails bring it down, but not in every bucket, and the ring decoder waits for the
-  // longest string (8M values, K = 16, max, ring / tile: 0.1% of the values x100 d = 512, s = 4 292 /
-  // 106 us, d = 8192, s = 1 773 / 301; Student-t 222 / 95, 452 / 304; 1% x1000, all strings short, 192 /
-  // 88, 76 / 166).
-  const uint32_t words = string_words(g, msg_bytes, K, a.raw_words);
-  const bool elias = g.code != QSGD_CODE_FIXED && g.n > 0;
-  a.kloop = (g.code != QSGD_CODE_SPARSE || g.norm == QSGD_NORM_MAX || K > 32 || g.s > 127 ||
-             (elias && tile_us(g, K, (float)words) < ring_us(g, K, (float)words))) ? 1u : 0u;
-
   const uint32_t cus = (uint32_t)device_cus();
   if (g.n > 0 && g.code == QSGD_CODE_SPARSE && g.d > kEntryMinD && std::isfinite(c)) {
     // Long buckets of Code_s: a message has at most q = s (s + sqrt(d)) nonzero levels in
@@ -461,30 +518,17 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // message, is left with the rest: 573 thousand values in one bucket, Code'_s, s = 127, K = 7:
   // 17.6 ms there, 65 us in the split decoder.)
   const bool bytes = g.code != QSGD_CODE_FIXED && g.s <= 127;
+  const StringLength length = bytes ? string_length(g, L, msg_bytes, K) : StringLength{0.0, 0.0};
   if (bytes && g.d <= kMaxBucketFast) {
-    const SplitPlan p = plan_decode_split(a, cus, words);
-    if (p.us < (a.kloop || g.d % 4 ? tile_us(g, K, (float)words) : ring_us(g, K, (float)words))) {
+    const DecoderChoice choice = choose_decoder(g, a, length, cus);
+    if (choice.which != Decoder::ring) {
+      a.gw = choice.tile.gw;
       ScopedTiming tm("decode_elias", st);
-      return launch_decode_split(a, p, st) == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
+      const hipError_t err = choice.which == Decoder::split
+                                 ? launch_decode_split(a, choice.split, st)
+                                 : launch_decode_tile(a, choice.tile.blocks, choice.tile.waves, st);
+      return err == hipSuccess ? QSGD_OK : QSGD_ERR_HIP;
     }
-  }
-  if (bytes && g.d <= kMaxBucketFast && (a.kloop || g.d % 4)) {
-    // dense strings, and bucket sizes that the ring decoder's loads do not fit: the tile
-    // decoder, one lane per string
-    uint32_t gw = 1;  // buckets per wavefront: a power of two, gw * K lanes
-    while (gw * 2 * K <= 64) gw *= 2;
-    while (gw > 1 && (g.nb + gw - 1) / gw < (uint64_t)cus * 4) gw /= 2;
-    a.gw = gw;
-    const uint32_t tasks = (uint32_t)((g.nb + gw - 1) / gw);
-    // as many wavefronts per compute unit as give every one of them the same number of
-    // groups; at least four, one per SIMD, share the work of loading the table
-    const uint32_t per_cu = (tasks + cus - 1) / cus, most = tile_max_waves(g.code);
-    const uint32_t rounds = (per_cu + most - 1) / most;
-    const uint32_t waves = std::max(4u, (per_cu + rounds - 1) / rounds);
-    const uint32_t blocks = std::min(cus, (tasks + waves - 1) / waves);
-    ScopedTiming tm("decode_elias", st);
-    if (launch_decode_tile(a, blocks, waves, st) != hipSuccess) return QSGD_ERR_HIP;
-    return QSGD_OK;
   }
   if (!g.bucket_path()) {
     const uint32_t blocks = (uint32_t)std::min<uint64_t>((g.n + 255) / 256, (uint64_t)cus * 32);
@@ -496,7 +540,7 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     float* acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes);
     if (bytes && g.d > kEntryMinD && g.d * g.per_elem < 0xF0000000ull) {   // (bit positions in 32 bits)
       a.acc = acc;
-      if (launch_decode_split(a, plan_decode_split(a, cus, words), st) != hipSuccess ||
+      if (launch_decode_split(a, plan_decode_split(a, cus, (uint32_t)(length.words + 0.5)), st) != hipSuccess ||
           launch_gen_apply(a, acc, blocks, st) != hipSuccess)
         return QSGD_ERR_HIP;
       return QSGD_OK;
@@ -517,9 +561,8 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
   // Elias codes: one lane per string.
   const uint32_t win = (uint32_t)std::min<uint64_t>((g.d + 3) & ~(uint64_t)3, 256);
   const uint32_t winp = (win + kChunk - 1) / kChunk * kChunk;
-  uint32_t gw = 1;  // buckets per wavefront: a power of two, gw * K lanes, gw * winp floats
-  while (gw * 2 * K <= 64 && gw * 2 <= 16) gw *= 2;
-  while (gw > 1 && (g.nb + gw - 1) / gw < (uint64_t)cus * 8) gw /= 2;
+  const uint32_t gw = ring_buckets(g, K, cus);  // a power of two: gw * K lanes, gw * winp floats
+  a.kloop = g.s > 127 ? 1u : 0u;                // (levels of a byte take the counting apply, or another decoder)
   a.win = win; a.winp = winp; a.gw = gw; a.rec = std::min(16u, 64u / gw);
   // LDS: accumulator, record rings, string word rings, Elias table, dump words; the message-by-message
   // apply also keeps 3 x 64 words of ring state (the counting apply does not pay for them)

@@ -621,7 +621,7 @@ SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words) {
   const uint32_t most = words + words / 5 + 2;
   p.lanes = most > 32 ? 64 : most > 16 ? 32 : 16;
   const uint32_t row = (span + 3) / 4 * 4;
-  const uint32_t tasks = a.nb * ((a.d - 1) / span + 1), per_cu = (tasks + cus - 1) / cus;
+  const uint32_t tasks = a.nb * ((a.d - 1) / span + 1), per_cu = (uint32_t)(((uint64_t)tasks + cus - 1) / cus);
   // rows of all messages at once if half of a compute unit's LDS holds them, else in batches
   p.rows = std::max(1u, std::min(a.K, 72u * 1024u / row));
   // a lane for every word of a batch, and at most 16 positions per thread in the sum
@@ -650,31 +650,19 @@ SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words) {
   p.lds = lds_bytes(p.bits);
   const uint32_t fit = std::max(1u, std::min(32u / p.waves, 156u * 1024u / (p.lds + 4 * kEntries)));
   p.blocks = std::min(tasks, cus * fit);
+  // (the whole step, header check and all; fitted like the other decoders' estimates, where the choice is made)
   if (p.bits) {
-    p.us = 8.f + 0.025f * (float)cu_words + 1.1f * (float)(per_cu - 1);
+    p.us = 13.2 + 0.0372 * (double)cu_words;
   } else {
-    // The turns of a workgroup one after the other, or all words at the rate of a machine that is full; a
-    // second unit of a string costs both.  Fitted like the other decoders' estimates, where the choice
-    // is made (18 to 26% off on the average).
-    const uint32_t batches = (a.K + p.rows - 1) / p.rows;
-    const float turns = (float)(batches * ((word_waves + p.waves - 1) / p.waves)) * (float)((tasks - 1) / p.blocks + 1);
-    const float strings = (float)tasks * (float)a.K, values = strings * (float)span, several = words > 64 ? 1.f : 0.f;
-    const float slots = strings * (float)((words + p.lanes - 1) / p.lanes * p.lanes);
-    float fixed, turn, rate;
-    if (!sparse) {
-      fixed = 0.5f;
-      turn = 12.4f * turns * (1.f + 0.52f * several);
-      rate = slots * 4.3e-5f * (1.f + 0.7f * several);
-    } else if (24u * words <= span) {
-      fixed = 6.1f;
-      turn = 17.2f * turns * (1.f + 0.6f * several);
-      rate = slots * 2.9e-5f * (1.f + several) + values * 1.35e-6f;
-    } else {
-      fixed = 5.4f;
-      turn = 13.7f * turns * (1.f + 0.54f * several);
-      rate = slots * 5.7e-5f * (1.f + 0.75f * several) + values * 7.1e-7f;
-    }
-    p.us = fixed + std::sqrt(turn * turn + rate * rate);
+    // the turns of a workgroup one after the other, and the words of a compute unit's buckets; a second
+    // unit of a string costs both
+    const uint32_t ups = (words + p.lanes - 1) / p.lanes;   // units per string
+    auto turns = [&](uint32_t n) { return (n * ups * p.lanes + 64 * p.waves - 1) / (64 * p.waves); };
+    const double serial = (double)((tasks - 1) / p.blocks + 1) * (double)(a.K / p.rows * turns(p.rows) + turns(a.K % p.rows));
+    const double work = (double)per_cu * a.K, values = (double)span;
+    p.us = 11.9 + serial * (sparse ? 6.96 : 6.57) * (ups > 1 ? 1.21 : 1.0) +
+           work * ((double)(ups * p.lanes) * (sparse ? 0.0061 : 0.0053) * (ups > 1 ? 1.93 : 1.0) + 3.8e-4 * values) +
+           1.4e-6 * (double)tasks * values;
   }
   return p;
 }

@@ -168,7 +168,7 @@ struct DecodeArgs {
   uint32_t win;          // window (positions per bucket per pass), multiple of 4
   uint32_t winp;         // accumulator stride per bucket: win rounded up to 256
   uint32_t rec;          // record slots per string (message-by-message apply)
-  uint32_t kloop;        // 1: records are applied message by message (dense messages)
+  uint32_t kloop;        // 1: records are applied message by message (levels above 127)
   uint32_t q16;          // 1: 16-bit records (counting apply, s <= 4)
   // few strings: lanes that share a string, messages whose rows are in LDS at once, words of
   // theirs that are worked on at a time
@@ -293,7 +293,7 @@ struct SplitPlan {
   bool bits;                          // a lane for every bit of the strings, else for every word
   uint32_t lanes, rows, turn_words;   // (see DecodeArgs)
   uint32_t waves, blocks, lds;
-  float us;                           // about how long it takes
+  double us;                          // about how long a step takes
 };
 // `words`: about how long a string is
 SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words);
