@@ -158,8 +158,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
   uint32_t* const s_prev = s_end + rows;
   uint32_t* const s_next = s_prev + rows;
   uint32_t* const s_unit = s_next + rows;            // rows + 1 of them
-  const uint32_t turn_words = a.turn_words;          // words worked on at a time, and units
-  const uint32_t slots = turn_words / lanes;
+  // words worked on at a time, and units (`lanes` is 16, 32 or 64: a division by it in every turn took
+  // 3% of a step of Code'_s)
+  const uint32_t turn_words = BITS ? a.turn_words : threads;
+  const uint32_t lane_bits = 31u - (uint32_t)__builtin_clz(lanes);
+  const uint32_t slots = turn_words >> lane_bits;
   uint32_t* const s_several = s_unit + rows + 1u;
   uint32_t* const carry = s_several + 1;             // 2: entry and position of the next turn's first unit
   uint32_t* const u_exit = carry + 2;
@@ -297,9 +300,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
       const uint32_t total = s_unit[kn];
       for (uint32_t turn = 0; turn < total; turn += slots) {
         const uint32_t tid = afresh(thread), lane = tid & 63u;
-        const uint32_t slot = tid / lanes, l = lane & (lanes - 1u);
+        const uint32_t slot = tid >> lane_bits, l = lane & (lanes - 1u);
         const uint32_t u = turn + slot;
-        const bool live = tid < turn_words && u < total;
+        const bool here = !BITS || tid < turn_words;
+        const bool live = here && u < total;
         // the string this unit belongs to: the last one that starts at or before it
         uint32_t r = 0;
         for (uint32_t step = 32; step; step >>= 1)
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
               o += two ? (e >> 4) & 15u : len1;
               p = two ? p2 : p1;
             } else {
-              uint32_t gap = 1, gl = 0, ll, open = 0, v = v1, more = e >> 28;
+              uint32_t gap = 1, gl = 0, ll, lev, open = 0, v = v1, more = e >> 28;
               if (kSparse) {
                 gap = by_last_group(v1, more, gl, open);
                 if (open) gap = LONGB ? omega_loop(((uint64_t)w0 << 32 | w1) << o | ((uint64_t)w2 << o >> 32), gl) : 0u;
@@ -358,7 +362,14 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
                 v = __builtin_amdgcn_alignbit(hi, lo, ~q);
                 more = table[v << 1 >> (32u - kBits)] >> 28;
               }
-              uint32_t lev = by_last_group(v << 1, more, ll, open);
+              if (kSparse || LONGB) {
+                lev = by_last_group(v << 1, more, ll, open);
+              } else {
+                // (group by group: 17 thousand values, d = 3376, s = 39, K = 5 47.4 us, by the last one 48.4; segments
+                // the other way round: 5M values, s = 127, max, K = 3 340 and 327)
+                lev = omega_peek3(v << 1, ll);
+                open = lev == 0 ? 1u : 0u;
+              }
               if (gap == 0 || open || lev > (kSparse ? s : s + 1u) || (LONGB && gap > M)) { fail = true; break; }
               if (!kSparse) lev -= 1u;
               p += gap;
@@ -376,12 +387,12 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
             w_words[turn_words + tid] = w1;
             w_words[2u * turn_words + tid] = w2;
           }
-          if (tid < turn_words && l == 0) u_exit[slot] = idle ? 0u : (endbit + 31u) / 32u - wi;   // words from here on
+          if (here && l == 0) u_exit[slot] = idle ? 0u : (endbit + 31u) / 32u - wi;   // words from here on
           __syncthreads();
         }
         // ---- a lane for every bit: the record that would begin there ----------------------------
         if (BITS) for (uint32_t t0 = wave * 2u; t0 < turn_words; t0 += threads / 32u) {
-          if ((t0 & (lanes - 1u)) >= __builtin_amdgcn_readfirstlane(u_exit[t0 / lanes])) continue;
+          if ((t0 & (lanes - 1u)) >= __builtin_amdgcn_readfirstlane(u_exit[t0 >> lane_bits])) continue;
           const uint32_t t = t0 + (lane >> 5), o = lane & 31u;
           const uint32_t w0 = w_words[t], w1 = w_words[turn_words + t], w2 = w_words[2u * turn_words + t];
           // the 32 bits from bit o on are alignbit(h0, h1, ~o)
@@ -446,7 +457,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
             if (__builtin_amdgcn_ballot_w64(again) == 0) break;
           }
           if (!several) break;
-          if (tid < turn_words && l == lanes - 1u) u_exit[slot] = exit - 32u;
+          if (here && l == lanes - 1u) u_exit[slot] = exit - 32u;
           __syncthreads();
           if (l == 0 && live && goes_on && slot != 0) {
             const uint32_t now = u_exit[slot - 1u];
@@ -486,7 +497,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(DecodeArgs a)
           if (l >= t) incl += up;
         }
         if (several) {
-          if (tid < turn_words && l == lanes - 1u) u_adv[slot] = incl;
+          if (here && l == lanes - 1u) u_adv[slot] = incl;
           __syncthreads();
         }
         uint32_t start = incl - adv;
