@@ -651,11 +651,21 @@ SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words) {
            (uint64_t)per_cu * (lds_bytes(true) + 4 * kEntries) <= 156u * 1024u;
   p.waves = p.bits ? std::max(word_waves, std::min(std::min(kSplitWaves, 24u / per_cu), (a.K * words + 1) / 2))
                    : std::min(kSplitWaves, word_waves);
-  // Segments: the more of them, the smaller the workgroups, which wait for each other less (16M values,
-  // d = 9770, Code'_s, s = 85, K = 4, 16 / 8 / 4 / 2 wavefronts: 693 / 625 / 593 / 491 us; 13M, one bucket, s = 4,
-  // K = 8 349 / 349 / 321 / 368; 4M, d = 100 thousand, K = 16 321 / 254 / 277 / 442; 1M, d = 10 thousand, K = 8,
-  // 16 / 12 / 8 84 / 65 / 72).
-  if (lng && !p.bits) p.waves = std::min(p.waves, per_cu >= 16 ? std::max(2u, std::min(4u, a.K / 2)) : per_cu >= 4 ? 8u : 12u);
+  // Segments: the more of them, the smaller the workgroups, which wait for each other less; where a
+  // compute unit has a single one, it gets all the wavefronts it can use.  479 steps over 20 thousand to 10M
+  // values, both codes, K = 1 .. 16; time over that of the best of 16, 12, 8, 4 and 2 wavefronts, by
+  // segments per compute unit:
+  //            16     12     8      4                  16     12     8      4
+  //   1        1.00   1.06   1.18   1.54     8 .. 15   1.18   1.09   1.08   1.01
+  //   2, 3     1.11   1.01   1.05   1.28     16 ..     1.24   1.11   1.14   1.05
+  //   4, 5     1.09   1.02   1.03   1.07
+  //   6, 7     1.14   1.05   1.03   1.03
+  // (16M values, d = 9770, Code'_s, s = 85, K = 4, 62 per compute unit: 16 / 8 / 4 / 2 693 / 625 / 593 / 491 us; 13M,
+  // one bucket, s = 4, K = 8 349 / 349 / 321 / 368; many messages have the units for eight where there are eight
+  // segments: 4M, d = 100 thousand, s = 2, K = 16 321 / 254 / 277 / 442.)
+  if (lng && !p.bits)
+    p.waves = std::min(p.waves, per_cu >= 16 ? std::max(2u, std::min(4u, a.K / 2)) : per_cu >= 8 ? (a.K >= 12 ? 8u : 4u)
+                                : per_cu >= 6 ? 8u : per_cu >= 2 ? 12u : 16u);
   p.waves = std::max(p.waves, (span + 1023) / 1024);
   if (!p.bits) p.turn_words = 64 * p.waves;
   p.lds = lds_bytes(p.bits);

@@ -32,7 +32,9 @@ int main() {   // n d s code norm K, words of a string, messages in whole buffer
       bytes[k] = k < whole ? qsgd_max_encoded_bytes(&p)
                            : 4 * (size_t)(H_WORDS + g.table_words + words * (double)g.nb);
     const StringLength w = string_length(g, nullptr, bytes, K);
-    std::printf("%d %.3f %.3f\n", (int)choose_decoder(g, a, w, 256).which, w.words, w.guess);
+    const SplitPlan split = plan_decode_split(a, 256, (uint32_t)(w.words + 0.5));
+    std::printf("%d %.3f %.3f %d\n", g.d > kEntryMinD ? 2 : (int)choose_decoder(g, a, w, 256).which, w.words,
+                w.guess, split.bits ? 0 : (int)split.waves);
   }
 }
 """
@@ -79,12 +81,12 @@ def ask(tmp_path_factory):
     def answers(rows):
         text = "".join(" ".join(map(str, r)) + "\n" for r in rows)
         out = subprocess.run([str(path / "ask")], input=text, capture_output=True, text=True, check=True).stdout
-        return [(int(a), float(b), float(c)) for a, b, c in (line.split() for line in out.splitlines())]
+        return [(int(a), float(b), float(c), int(d)) for a, b, c, d in (line.split() for line in out.splitlines())]
     return answers
 
 
 def test_the_fastest_decoder_or_nearly(ask):
-    for step, (which, _, _) in zip(STEPS, ask([s[:7] + (0,) for s in STEPS])):
+    for step, (which, _, _, _) in zip(STEPS, ask([s[:7] + (0,) for s in STEPS])):
         times = step[7]
         assert times[which] is not None and times[which] <= 1.1 * min(t for t in times if t), (step, which)
 
@@ -106,3 +108,14 @@ def test_strings_longer_than_the_guess_count(ask):
     guess = ask([shape + (1.0, 4)])[0][2]
     assert abs(ask([shape + (1.5 * guess, 0)])[0][1] - (1.5 * guess + 0.5)) < 0.05
     assert ask([shape + (3.0 * guess, 0)])[0][1] == 2.0 * guess
+
+
+@pytest.mark.parametrize("n,d,s,K,waves", [
+    (43_649, 15_102, 58, 16, 16), (20_162, 20_162, 122, 8, 16), (520_000, 520_000, 80, 8, 16),   # one for a compute unit
+    (530_000, 530_000, 80, 4, 12), (3_400_000, 3_400_000, 80, 6, 8), (4_000_000, 100_000, 80, 16, 8),
+    (4_000_000, 100_000, 80, 8, 4), (16_000_000, 9770, 85, 4, 2),
+    (16_000_000, 9770, 85, 16, 4), (9_000, 9_000, 80, 1, 3),                                       # (no more words than that)
+])
+def test_wavefronts_of_a_segment(ask, n, d, s, K, waves):
+    """The fewer segments a compute unit has, the more wavefronts share one."""
+    assert ask([(n, d, s, DENSE, L2, K, 0, K)])[0][3] == waves
