@@ -1,5 +1,6 @@
-// General path: any bucket size d (used for d > 8192, d = n among them, and for fixed width with d
-// not a multiple of 4).
+// General path: any bucket size d (used for d > 8192, d = n among them, and for fixed width with d not a
+// multiple of 4: decode of every such size, encode of those above 1024; the encoder of small buckets takes
+// the others).
 //
 // Encode.  A bucket no longer fits one workgroup's registers, so it is cut into
 // segments of 2048 values, one wavefront each, and the steps that the bucket path
@@ -1202,92 +1203,80 @@ __global__ __launch_bounds__(256) void k_gen_apply(DecodeArgs a, const float* ac
     a.x[i] = a.step ? fmaf(-a.c, acc[i], a.x[i]) : a.x[i] + acc[i];
 }
 
-// Fixed width, any bucket size: a thread has eight consecutive values of a bucket, the words of four
-// messages requested together, peers summed in order.  (A value per thread, 64-bit divisions and five
-// loads of its own for each, and this way: 20M values in one bucket, s = 256, K = 4 145 and 55 us,
-// 10M of d = 443 78 and 37, 20M of d = 60 thousand, 4 bits, K = 16 573 and 134.)
+// Fixed width, any bucket size: a thread has consecutive values of a bucket, eight of up to four bits and
+// four wider ones, and takes the messages one after the other.  (The words of four messages
+// requested together, eight values of any width: 28 thousand values, 16 bits, K = 14 19.0 us and 14.9 this way, as
+// with a value per thread; 10M of d = 443, 8 bits, K = 4 35.9 and 31.2; 20M in one bucket, 8 bits, K = 4 56.0
+// and 51.1, with a value per thread and 64-bit divisions 145; 20M of d = 60 thousand, 4 bits, K = 16 133 and 120.)
+__host__ __device__ constexpr int fixed_values(int bits) { return bits <= 4 ? 8 : 4; }
 template <int B>
 __global__ __launch_bounds__(256) void k_gen_decode_fixed(DecodeArgs a) {
   if (*a.status != 0) return;
   constexpr uint32_t fmask = (1u << B) - 1u;
-  constexpr int LW = B == 2 ? 1 : B / 4;   // level words of eight values (2 bits: half a word)
-  constexpr int KG = 4;
+  constexpr int V = fixed_values(B), LW = V * B < 32 ? 1 : V * B / 32;   // level words of a thread's values
   const float s_f = (float)a.s;
-  const uint32_t gpb = (a.d >> 3) + (a.d & 7u ? 1u : 0u);   // groups of eight in a bucket
+  const uint32_t gpb = a.d / V + (a.d % V ? 1u : 0u);   // threads for a bucket
   const uint64_t total = (uint64_t)a.nb * gpb;
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (uint64_t)gridDim.x * 256) {
     const uint64_t b = total >> 32 ? i / gpb : (uint32_t)i / gpb;
-    const uint32_t e = (uint32_t)(i - b * gpb) * 8u;
+    const uint32_t e = (uint32_t)(i - b * gpb) * V;
     const uint64_t base = b * (uint64_t)a.d;
     const uint64_t m = min((uint64_t)a.d, a.n - base);
     if (e >= m) continue;
-    const uint32_t here = (uint32_t)min(m - e, (uint64_t)8);
+    const uint32_t here = (uint32_t)min(m - e, (uint64_t)V);
     const uint64_t lw = (m * B + 31) >> 5, sw = (m + 31) >> 5;
     const uint64_t off = (uint64_t)H_WORDS + b * (uint64_t)a.fixed_words_full;
     const uint64_t wi = ((uint64_t)e * B) >> 5;
     float* const x = a.x + base + e;
-    float xv[8], sum[8];
-    if (here == 8) {
-      const v4f_any p = *reinterpret_cast<const v4f_any*>(x), q = *reinterpret_cast<const v4f_any*>(x + 4);
-      xv[0] = p.x; xv[1] = p.y; xv[2] = p.z; xv[3] = p.w;
-      xv[4] = q.x; xv[5] = q.y; xv[6] = q.z; xv[7] = q.w;
+    float xv[V], sum[V];
+    if (here == V) {
+#pragma unroll
+      for (int j = 0; j < V; j += 4) {
+        const v4f_any p = *reinterpret_cast<const v4f_any*>(x + j);
+        xv[j] = p.x; xv[j + 1] = p.y; xv[j + 2] = p.z; xv[j + 3] = p.w;
+      }
     } else {
 #pragma unroll
-      for (uint32_t j = 0; j < 8; ++j) xv[j] = j < here ? x[j] : 0.f;
+      for (uint32_t j = 0; j < V; ++j) xv[j] = j < here ? x[j] : 0.f;
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) sum[j] = 0.f;
-    for (uint32_t k0 = 0; k0 < a.K; k0 += KG) {
-      uint32_t head[KG][2], lev[KG][LW], sign[KG];
-      bool have[KG];
+    for (int j = 0; j < V; ++j) sum[j] = 0.f;
+    for (uint32_t k = 0; k < a.K; ++k) {
+      if (off + 2 + lw + sw > a.msg_words[k]) { flag_corrupt(a.status); continue; }
+      const uint32_t* const str = a.msgs[k] + off;
+      uint32_t lev[LW];
+      if (wi + LW <= lw) {
 #pragma unroll
-      for (int t = 0; t < KG; ++t) {
-        const uint32_t k = min(k0 + (uint32_t)t, a.K - 1u);
-        const uint32_t* const str = a.msgs[k] + off;
-        have[t] = off + 2 + lw + sw <= a.msg_words[k];
-        head[t][0] = head[t][1] = sign[t] = 0;
+        for (int w = 0; w < LW; ++w) lev[w] = str[2 + wi + w];
+      } else {
 #pragma unroll
-        for (int w = 0; w < LW; ++w) lev[t][w] = 0;
-        if (have[t]) {
-          head[t][0] = str[0]; head[t][1] = str[1];
-          if (wi + LW <= lw) {
-#pragma unroll
-            for (int w = 0; w < LW; ++w) lev[t][w] = str[2 + wi + w];
-          } else {
-#pragma unroll
-            for (int w = 0; w < LW; ++w) if (wi + w < lw) lev[t][w] = str[2 + wi + w];
-          }
-          sign[t] = str[2 + lw + (e >> 5)] >> (e & 31u);
-        }
+        for (int w = 0; w < LW; ++w) lev[w] = wi + w < lw ? str[2 + wi + w] : 0u;
       }
+      const uint32_t sign = str[2 + lw + (e >> 5)] >> (e & 31u);
+      const float sc = __uint_as_float(str[0]) / s_f;
+      const uint32_t esc = str[1] - e;              // (below V: one of these values)
+      if (V * B < 32) lev[0] >>= (e * B) & 31u;
 #pragma unroll
-      for (int t = 0; t < KG; ++t) {
-        if (k0 + t >= a.K) break;
-        if (!have[t]) { flag_corrupt(a.status); continue; }
-        const float sc = __uint_as_float(head[t][0]) / s_f;
-        const uint32_t esc = head[t][1] - e;          // (below 8: one of these values)
-        if (B == 2) lev[t][0] >>= (e & 8u) * 2u;
-#pragma unroll
-        for (uint32_t j = 0; j < 8; ++j) {
-          uint32_t z = (lev[t][j * B / 32] >> (j * B % 32)) & fmask;
-          z = esc == j ? a.s : z;
-          if (z > a.s && j < here) { flag_corrupt(a.status); z = 0; }
-          const float mag = sc * (float)z;
-          sum[j] += z && ((sign[t] >> j) & 1u) ? -mag : mag;
-        }
+      for (uint32_t j = 0; j < V; ++j) {
+        uint32_t z = (lev[j * B / 32] >> (j * B % 32)) & fmask;
+        z = esc == j ? a.s : z;
+        if (z > a.s && j < here) { flag_corrupt(a.status); z = 0; }
+        const float mag = sc * (float)z;
+        sum[j] += z && ((sign >> j) & 1u) ? -mag : mag;
       }
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) xv[j] = a.step ? fmaf(-a.c, sum[j], xv[j]) : xv[j] + sum[j];
-    if (here == 8) {
-      v4f_any p, q;
-      p.x = xv[0]; p.y = xv[1]; p.z = xv[2]; p.w = xv[3];
-      q.x = xv[4]; q.y = xv[5]; q.z = xv[6]; q.w = xv[7];
-      *reinterpret_cast<v4f_any*>(x) = p;
-      *reinterpret_cast<v4f_any*>(x + 4) = q;
+    for (int j = 0; j < V; ++j) xv[j] = a.step ? fmaf(-a.c, sum[j], xv[j]) : xv[j] + sum[j];
+    if (here == V) {
+#pragma unroll
+      for (int j = 0; j < V; j += 4) {
+        v4f_any p;
+        p.x = xv[j]; p.y = xv[j + 1]; p.z = xv[j + 2]; p.w = xv[j + 3];
+        *reinterpret_cast<v4f_any*>(x + j) = p;
+      }
     } else {
 #pragma unroll
-      for (uint32_t j = 0; j < 8; ++j) if (j < here) x[j] = xv[j];
+      for (uint32_t j = 0; j < V; ++j) if (j < here) x[j] = xv[j];
     }
   }
 }
@@ -1357,8 +1346,9 @@ hipError_t launch_gen_apply(const DecodeArgs& a, const float* acc, uint32_t bloc
   return hipGetLastError();
 }
 hipError_t launch_gen_decode_fixed(const DecodeArgs& a, uint32_t cus, hipStream_t st) {
-  const uint64_t groups = (uint64_t)a.nb * ((a.d >> 3) + (a.d & 7u ? 1u : 0u)), most = (uint64_t)cus * 1024;
-  const dim3 grid((uint32_t)((groups + 255) / 256 < most ? (groups + 255) / 256 : most)), block(256);
+  const uint32_t V = fixed_values((int)a.fixed_bits);
+  const uint64_t threads = (uint64_t)a.nb * (a.d / V + (a.d % V ? 1u : 0u)), most = (uint64_t)cus * 1024;
+  const dim3 grid((uint32_t)((threads + 255) / 256 < most ? (threads + 255) / 256 : most)), block(256);
   switch (a.fixed_bits) {
     case 2: hipLaunchKernelGGL(k_gen_decode_fixed<2>, grid, block, 0, st, a); break;
     case 4: hipLaunchKernelGGL(k_gen_decode_fixed<4>, grid, block, 0, st, a); break;
