@@ -569,14 +569,18 @@ void k_encode_fixed_small_batch(EncodeArgs a, EncodeBatch batch) {
 // it adds up the totals before its first team itself (at most kMaxTeams words, 16 bytes a
 // load, from the L2) instead of reading prefix sums that a launch of its own would have to
 // make first.  Bound by latency: with that launch and its gap 5.2 us at 40 teams and 15.4
-// at 7143 (25.6M values), without it 2.6 and 9.8; with a team's words requested before the totals
-// are added up, and the next team's before this one is stored, 7.2 at 7143.
+// at 7143 (25.6M values), without it 2.6 and 9.8.
 constexpr uint32_t kCompactWaves = 4;
 typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4)));
 //
+// AHEAD (wavefronts with several teams): a team's words are requested before its place is known, those
+// of the first one before the totals are added up, those of the next one when this one is stored: 9.8 -> 7.2
+// us at 7143 teams.  A wavefront with a single team gains nothing by it and has more to issue
+// (20 thousand values 3.36 and 3.64 us, 1M 3.9 and 4.2, 4M 5.7 and 6.0).
+//
 // RAW: the workgroups behind the teams' copy the small tensors of a tensor-aware message, a piece of
 // kRawPiece values each, behind all strings.  (A launch of their own took 4.7 us.)
-template <bool RAW>
+template <bool RAW, bool AHEAD>
 __global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactArgs a, RawArgs r) {
   __shared__ unsigned long long part[kCompactWaves];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -588,13 +592,12 @@ __global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactAr
 
   // (tpb <= 64: lane l keeps the total of the workgroup's team l)
   const uint32_t own = t_begin + (uint32_t)lane < t_end ? a.totals[t_begin + lane] : 0u;
-  // The wavefront's next team, in registers as far as it goes: nothing of it depends on where it is to
-  // be stored, so it is under way while the totals are added up and while the team before is stored.
+  // AHEAD: the wavefront's next team, in registers as far as it goes
   constexpr uint32_t kQuads = 4;
   uint4 next[kQuads];
   uint32_t next_off = 0;
   auto request = [&](uint32_t i) {   // team t_begin + i
-    if (t_begin + i >= t_end) return;
+    if (!AHEAD || t_begin + i >= t_end) return;
     const uint32_t mine = lane_bcast(own, (int)i), j = t_begin + i;
     if (mine <= a.region_words) {   // (regions start on 16 bytes and hold whole quads)
       const uint4* const src = reinterpret_cast<const uint4*>(a.staging + (uint64_t)j * a.region_words);
@@ -654,7 +657,7 @@ __global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactAr
         const uint32_t* __restrict__ src = a.staging + (uint64_t)j * a.region_words;
         uint32_t* __restrict__ dstp = a.payload + base;
 #pragma unroll
-        for (uint32_t u = 0; u < kQuads; ++u) {
+        for (uint32_t u = 0; u < (AHEAD ? kQuads : 0u); ++u) {
           const uint32_t i = 4u * (u * kWave + lane);
           if (i + 4u <= mine) {
             v4u_any x; x.x = next[u].x; x.y = next[u].y; x.z = next[u].z; x.w = next[u].w;
@@ -666,12 +669,12 @@ __global__ __launch_bounds__(64 * kCompactWaves) void k_encode_compact(CompactAr
           }
         }
 #pragma unroll 4
-        for (uint32_t i = 4u * kQuads * kWave + lane; i < mine; i += kWave) dstp[i] = src[i];
+        for (uint32_t i = (AHEAD ? 4u * kQuads * kWave : 0u) + lane; i < mine; i += kWave) dstp[i] = src[i];
       }
       const uint32_t b_begin = j * a.bper;
       const uint32_t b_end = min(b_begin + a.bper, a.nb);
-      if (b_begin + lane < b_end) a.table[b_begin + lane] = (uint32_t)min(base + next_off, 0xFFFFFFFFull);
-      for (uint32_t b = b_begin + kWave + lane; b < b_end; b += kWave)
+      if (AHEAD && b_begin + lane < b_end) a.table[b_begin + lane] = (uint32_t)min(base + next_off, 0xFFFFFFFFull);
+      for (uint32_t b = b_begin + (AHEAD ? kWave : 0u) + lane; b < b_end; b += kWave)
         a.table[b] = (uint32_t)min(base + a.table[b], 0xFFFFFFFFull);
       request(j - t_begin + kCompactWaves);
     }
@@ -782,8 +785,16 @@ static_assert(kRawPiece == 4 * 64 * kCompactWaves, "a piece per workgroup, four 
 hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, hipStream_t st) {
   const uint32_t groups = (a.teams + a.tpb - 1) / a.tpb;
   const dim3 block(64 * kCompactWaves);
-  if (raw && raw->R) hipLaunchKernelGGL(k_encode_compact<true>, dim3(groups + raw->R), block, 0, st, a, *raw);
-  else hipLaunchKernelGGL(k_encode_compact<false>, dim3(groups), block, 0, st, a, RawArgs());
+  const bool with_raw = raw && raw->R;
+  const RawArgs r = with_raw ? *raw : RawArgs();
+  const dim3 grid(groups + (with_raw ? raw->R : 0));
+  if (a.tpb > kCompactWaves) {
+    if (with_raw) hipLaunchKernelGGL((k_encode_compact<true, true>), grid, block, 0, st, a, r);
+    else hipLaunchKernelGGL((k_encode_compact<false, true>), grid, block, 0, st, a, r);
+  } else {
+    if (with_raw) hipLaunchKernelGGL((k_encode_compact<true, false>), grid, block, 0, st, a, r);
+    else hipLaunchKernelGGL((k_encode_compact<false, false>), grid, block, 0, st, a, r);
+  }
   return hipGetLastError();
 }
 
