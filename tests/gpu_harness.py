@@ -51,7 +51,8 @@ def compare_encode(P: q.Params, g_host: np.ndarray, gpu_words: np.ndarray):
 
 
 def check_step(P: q.Params, msgs_dev, msgs_host, eta, x_host: np.ndarray, K: int):
-    """GPU fused step and accumulate vs the oracle on the same messages."""
+    """GPU fused step and accumulate vs the oracle on the same messages.  Returns how many values of
+    the two results differ in their bits, the sign of a zero among them."""
     ws = torch.zeros(max(q.qsgd_workspace_bytes(P, K), 256) // 4, dtype=torch.int32,
                      device="cuda")
     x = torch.from_numpy(x_host.copy()).cuda()
@@ -64,8 +65,10 @@ def check_step(P: q.Params, msgs_dev, msgs_host, eta, x_host: np.ndarray, K: int
     q.qsgd_decode_accumulate(P, msgs_dev, acc, ws)
     assert q.qsgd_workspace_status(ws) == 0
     want_acc = qo.decode_accumulate(msgs_host, x_host)
-    assert_close(acc.cpu().numpy(), want_acc, x_host)
-    return int(np.count_nonzero(got.view(np.uint32) != want.view(np.uint32)))
+    got_acc = acc.cpu().numpy()
+    assert_close(got_acc, want_acc, x_host)
+    return sum(int(np.count_nonzero(a.view(np.uint32) != b.view(np.uint32)))
+               for a, b in ((got, want), (got_acc, want_acc)))
 
 
 def assert_close(got, want, x0):
