@@ -866,8 +866,15 @@ static int encode_impl(const qsgd_params* p, const qsgd_layout* L, uint64_t inde
     c.teams = pl.teams;
     const uint32_t wgs = 4 * (uint32_t)device_cus();
     c.tpb = std::min<uint32_t>(kWave, std::max<uint32_t>(4, (pl.teams + wgs - 1) / wgs));
+    // A team's words ahead of its place: from some 64 words a team on where wavefronts have several teams, from
+    // 160 on everywhere.  Encode, us, without / with: d = 512, s = 16 (35 words a string), 3.5M values 14.0 / 14.4, 7M
+    // (two strings a team) 20.2 / 19.9, 25M (six) 48.3 / 45.4; d = 512, s = 2 (10 words), 15M (four) 33.7 / 33.9; d = 1024,
+    // Code'_s, s = 30 (95 words), 2M 10.3 / 10.6, 7M 19.0 / 18.9, 10M (two) 25.7 / 23.3; d = 4096, s = 30 (230 words), 3.5M
+    // 21.0 / 20.1.
+    const double team_words = (double)pl.bper * string_words(g);
+    const bool ahead = team_words >= 160.0 || (team_words >= 64.0 && c.tpb > 4);
     ScopedTiming tm("encode_compact", st);
-    if (launch_encode_compact(c, L ? &ra : nullptr, st) != hipSuccess) return QSGD_ERR_HIP;
+    if (launch_encode_compact(c, L ? &ra : nullptr, ahead, st) != hipSuccess) return QSGD_ERR_HIP;
   } else if (L && L->R) {
     ScopedTiming tm("encode_raw", st);
     if (launch_raw_pack(ra, st) != hipSuccess) return QSGD_ERR_HIP;

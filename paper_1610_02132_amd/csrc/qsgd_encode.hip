@@ -573,10 +573,9 @@ void k_encode_fixed_small_batch(EncodeArgs a, EncodeBatch batch) {
 constexpr uint32_t kCompactWaves = 4;
 typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4)));
 //
-// AHEAD (wavefronts with several teams): a team's words are requested before its place is known, those
-// of the first one before the totals are added up, those of the next one when this one is stored: 9.8 -> 7.2
-// us at 7143 teams.  A wavefront with a single team gains nothing by it and has more to issue
-// (20 thousand values 3.36 and 3.64 us, 1M 3.9 and 4.2, 4M 5.7 and 6.0).
+// AHEAD: a team's words are requested before its place is known, those of a wavefront's first team before the
+// totals are added up, those of its next one when this one is stored (25.6M values, 7143 teams: 9.8 -> 7.2 us).
+// Where a team has few words there is little to wait for and more to issue (20 thousand values: 3.36 and 3.68).
 //
 // RAW: the workgroups behind the teams' copy the small tensors of a tensor-aware message, a piece of
 // kRawPiece values each, behind all strings.  (A launch of their own took 4.7 us.)
@@ -782,13 +781,13 @@ hipError_t launch_encode_fixed_small_batch(const EncodeArgs& a, const EncodeBatc
 }
 
 static_assert(kRawPiece == 4 * 64 * kCompactWaves, "a piece per workgroup, four values per thread");
-hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, hipStream_t st) {
+hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, bool ahead, hipStream_t st) {
   const uint32_t groups = (a.teams + a.tpb - 1) / a.tpb;
   const dim3 block(64 * kCompactWaves);
   const bool with_raw = raw && raw->R;
   const RawArgs r = with_raw ? *raw : RawArgs();
   const dim3 grid(groups + (with_raw ? raw->R : 0));
-  if (a.tpb > kCompactWaves) {
+  if (ahead) {
     if (with_raw) hipLaunchKernelGGL((k_encode_compact<true, true>), grid, block, 0, st, a, r);
     else hipLaunchKernelGGL((k_encode_compact<false, true>), grid, block, 0, st, a, r);
   } else {

@@ -275,7 +275,8 @@ constexpr uint32_t kDirectWaves = 4;   // wavefronts (teams) that share a code w
 uint32_t direct_buckets_per_pass(uint32_t d, bool few);
 hipError_t launch_encode_direct(const EncodeArgs& a, uint32_t code, bool few, uint32_t teams, hipStream_t st);
 // raw: the small tensors of a tensor-aware message, or null
-hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, hipStream_t st);
+// ahead: ask for a team's words before its place is known
+hipError_t launch_encode_compact(const CompactArgs& a, const RawArgs* raw, bool ahead, hipStream_t st);
 hipError_t launch_encode_fixed_small(const EncodeArgs& a, int lpb, int cp, uint32_t teams,
                                      hipStream_t st);
 hipError_t launch_encode_fixed_small_batch(const EncodeArgs& a, const EncodeBatch& batch, uint32_t K,
