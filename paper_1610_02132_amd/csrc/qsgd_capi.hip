@@ -179,13 +179,13 @@ double mean_level(const Geometry& g) {
 }
 
 // About how many words a full bucket's string then has (Elias codes).
-uint32_t string_words(const Geometry& g) {
+double string_words(const Geometry& g) {
   const double d = (double)g.d, t = mean_level(g);
   const double level = omega_len_host((uint64_t)t + 1), share = 1.0 - std::exp(-t);
   const double bits = g.code == QSGD_CODE_DENSE
                           ? d * (1.0 + (1.0 - share) + share * omega_len_host((uint64_t)std::max(2.0, t / share + 1.5)))
                           : d * share * (1.0 + level + omega_len_host((uint64_t)(1.0 / share)));
-  return 1 + (uint32_t)(bits / 32.0);
+  return 1.5 + bits / 32.0;
 }
 
 // About how many nonzero levels a bucket of Code_s has whose string takes `words` words: every one
@@ -351,7 +351,10 @@ RawArgs raw_args(const Geometry& g, const qsgd_layout* L) {
 // How long the strings of a step are, in words: `words` on the average over the messages that were cut
 // to their length (a message has the guess where a whole buffer stands behind it, whatever the others
 // say, and is taken for two guesses at most), and the guess itself, that of normal values.
-struct StringLength { double words, guess; };
+struct StringLength {
+  double words, guess;
+  uint32_t planned() const { return (uint32_t)std::min(words + 0.5, guess - 0.5); }
+};
 StringLength string_length(const Geometry& g, const qsgd_layout* L, const size_t* msg_bytes, uint32_t K) {
   const double nb = (double)std::max<uint64_t>(g.nb, 1), guess = string_words(g);
   const double fixed = (double)(H_WORDS + g.table_words + (L ? L->raw : 0));
@@ -397,17 +400,19 @@ uint32_t ring_buckets(const Geometry& g, uint32_t K, uint32_t cus) {   // per wa
 // lane for every word or bit (plan_decode_split).
 //
 // Fitted to 6716 steps drawn over d = 64 .. 8192 and off 4, s up to 64 (Code'_s 127), L2 and max, K = 1 ..
-// 32, 4 thousand to 100M values of five distributions, messages cut to their length; tile 14%, split 20%
-// and ring 21% off on 6716 others.  The estimates have to be a tenth apart before they overrule the
-// plainer rule: the ring decoder for 64 s^2 <= d (Code_s, L2), else the tile decoder, and the split
-// decoder for few strings.  On those others, chosen time over that of the best decoder, on the geometric
-// average, and share of steps slower than by the plainer rule by over 3%:  the plainer rule 1.105, -;  the
-// estimates alone 1.009, 2.4%;  this way 1.009, 1.5%, and with all messages in whole buffers 1.020, 1.6%.
+// 32, 4 thousand to 100M values of five distributions, messages cut to their length, and the ring decoder's
+// to 48 of 67M and 268M values, K = 16, too (where the choice is 0.6% behind the best); tile 14%, split 20% and
+// ring 20% off on 6716 others.  Where the plainer rule (the ring decoder for 64 s^2 <= d, Code_s, L2, else the
+// tile decoder, and the split decoder for few strings) does not say the ring decoder, the estimates have to
+// be a tenth apart to overrule it.  On those others, chosen time over that of the best decoder, on the
+// geometric average, and share of steps slower than by the plainer rule by over 3%:  the plainer rule
+// 1.105, -;  this way 1.007, 1.6%, and with all messages in whole buffers 1.014, 1.6%.
 // Ring / tile / split, us:
 //   16M values, K = 4:  d = 512, s = 2 101 / 52 / 185   d = 4096, s = 2 202 / 126 / 122
 //                       d = 4096, s = 8 633 / 178 / 217  d = 8192, s = 7 544 / 285 / 245
 //   60M values, K = 16: d = 1024, s = 1 168 / 278 / 1217   d = 4096, s = 2 195 / 366 / 1596
 //                       d = 4096, s = 5 659 / 441 / 3570   d = 8192, s = 5 721 / 411 / 2484
+//   268M values, K = 16: d = 8192, s = 4 1061 / 1299 / -  s = 7 2194 / 1447 / -  d = 1024, s = 1 639 / 1197 / -
 //   1e9 values, d = 8192, s = 4, outliers, K = 16: 1780 / 3678 / 21400
 //   Code'_s, K = 9: 2M values, d = 1024, s = 32 - / 70 / 288   d = 8192, s = 30 - / 379 / 91
 //   75 thousand values, Code'_s, d = 280, s = 10, outliers, K = 30 - / 25 / 39
@@ -423,10 +428,11 @@ double tile_us(const Geometry& g, const TilePlan& p, const StringLength& w) {
   return 10.6 + p.rounds * std::max(chain, full) + 1.94e-6 * (double)g.nb * (double)g.d;
 }
 double ring_us(const Geometry& g, uint32_t gw, const StringLength& w, uint32_t cus) {
-  const double longest = w.words + 0.6 * std::max(0.0, w.guess - w.words);
-  const double chain = 2.04 * longest + 16.8 * longest * longest / (double)g.d;   // (records that share a window)
+  auto chain = [&](double words) { return 2.35 * words + 33.9 * words * words / (double)g.d; };   // (records that share a window)
+  const double longest = w.words + 0.755 * std::max(0.0, w.guess - w.words);
   const double tasks = (double)((g.nb + gw - 1) / gw);
-  return 7.0 + chain * std::max(1.0, 0.14 * tasks / cus) + 1.4e-6 * (double)g.nb * (double)g.d;
+  const double full = 0.0615 * tasks / cus * std::pow((double)gw, 0.366) * chain(w.words) + 2.7e-7 * (double)g.nb * (double)g.d;
+  return 2.5 + std::sqrt(chain(longest) * chain(longest) + full * full);
 }
 
 enum class Decoder { ring, tile, split };
@@ -435,7 +441,7 @@ DecoderChoice choose_decoder(const Geometry& g, const DecodeArgs& a, const Strin
   DecoderChoice c;
   const uint32_t K = a.K;
   c.tile = plan_tile(g, K, cus);
-  c.split = plan_decode_split(a, cus, (uint32_t)(w.words + 0.5));
+  c.split = plan_decode_split(a, cus, w.planned(), (uint32_t)(w.words + 0.5));
   // The counting apply of the ring decoder keeps a bit per message in a 32-bit word, and its loads
   // are of four values.  With the largest value as scale the share of nonzero levels
   // depends on the data: heavy tails bring it down, but not in every bucket, and the ring decoder
@@ -452,7 +458,8 @@ DecoderChoice choose_decoder(const Geometry& g, const DecodeArgs& a, const Strin
   c.which = few ? Decoder::split : tiled ? Decoder::tile : Decoder::ring;
   const double plain = few ? split : tiled ? tile : ringed;
   const double best = std::min(std::min(tile, ringed), split);
-  if (1.1 * best < plain) c.which = best == tile ? Decoder::tile : best == split ? Decoder::split : Decoder::ring;
+  const double sure = c.which == Decoder::ring ? 1.0 : 1.1;
+  if (sure * best < plain) c.which = best == tile ? Decoder::tile : best == split ? Decoder::split : Decoder::ring;
   return c;
 }
 
@@ -540,7 +547,7 @@ int run_decode(const qsgd_params* p, const qsgd_layout* L, const void* const* ms
     float* acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kStatusBytes + kTotalsBytes);
     if (bytes && g.d > kEntryMinD && g.d * g.per_elem < 0xF0000000ull) {   // (bit positions in 32 bits)
       a.acc = acc;
-      if (launch_decode_split(a, plan_decode_split(a, cus, (uint32_t)(length.words + 0.5)), st) != hipSuccess ||
+      if (launch_decode_split(a, plan_decode_split(a, cus, length.planned(), 0), st) != hipSuccess ||
           launch_gen_apply(a, acc, blocks, st) != hipSuccess)
         return QSGD_ERR_HIP;
       return QSGD_OK;

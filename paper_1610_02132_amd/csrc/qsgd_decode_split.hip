@@ -622,7 +622,7 @@ hipError_t launch_split(const DecodeArgs& a, const SplitPlan& p, hipStream_t st)
 //   Code_s, 45 words, 2344 strings          23 / 25 / 45      80 strings      13 / 20 / 46
 //   Code_s, 5 words, 6250 strings            - / 19 / 12      418 strings     10 / 13 / 11
 //   Code'_s, 50 words, 4688 strings          - / 16 / 29      160 strings      - / 12 / 32
-SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words) {
+SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words, uint32_t expected) {
   SplitPlan p;
   const bool lng = a.d > kEntryMinD, sparse = a.code == QSGD_CODE_SPARSE;
   const uint32_t span = lng ? kSeg : a.d;
@@ -673,11 +673,11 @@ SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words) {
   p.blocks = std::min(tasks, cus * fit);
   // (the whole step, header check and all; fitted like the other decoders' estimates, where the choice is made)
   if (p.bits) {
-    p.us = 13.2 + 0.0372 * (double)cu_words;
+    p.us = 13.2 + 0.0372 * (double)per_cu * a.K * expected;
   } else {
     // the turns of a workgroup one after the other, and the words of a compute unit's buckets; a second
     // unit of a string costs both
-    const uint32_t ups = (words + p.lanes - 1) / p.lanes;   // units per string
+    const uint32_t ups = (expected + p.lanes - 1) / p.lanes;   // units per string
     auto turns = [&](uint32_t n) { return (n * ups * p.lanes + 64 * p.waves - 1) / (64 * p.waves); };
     const double serial = (double)((tasks - 1) / p.blocks + 1) * (double)(a.K / p.rows * turns(p.rows) + turns(a.K % p.rows));
     const double work = (double)per_cu * a.K, values = (double)span;

@@ -296,8 +296,9 @@ struct SplitPlan {
   uint32_t waves, blocks, lds;
   double us;                          // about how long a step takes
 };
-// `words`: about how long a string is
-SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words);
+// `words`: how long a string is planned for (longer ones take more turns); `expected`: what its time is estimated
+// by (buckets up to kEntryMinD)
+SplitPlan plan_decode_split(const DecodeArgs& a, uint32_t cus, uint32_t words, uint32_t expected);
 hipError_t launch_decode_split(DecodeArgs& a, const SplitPlan& p, hipStream_t st);
 constexpr uint32_t kTileMaxWaves = 13;       // wavefronts of the tile decoder's largest workgroup
 uint32_t tile_max_waves(uint32_t code);      // ... and what LDS holds of them

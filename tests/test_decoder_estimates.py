@@ -32,7 +32,7 @@ int main() {   // n d s code norm K, words of a string, messages in whole buffer
       bytes[k] = k < whole ? qsgd_max_encoded_bytes(&p)
                            : 4 * (size_t)(H_WORDS + g.table_words + words * (double)g.nb);
     const StringLength w = string_length(g, nullptr, bytes, K);
-    const SplitPlan split = plan_decode_split(a, 256, (uint32_t)(w.words + 0.5));
+    const SplitPlan split = plan_decode_split(a, 256, w.planned(), 0);
     std::printf("%d %.3f %.3f %d\n", g.d > kEntryMinD ? 2 : (int)choose_decoder(g, a, w, 256).which, w.words,
                 w.guess, split.bits ? 0 : (int)split.waves);
   }
@@ -67,6 +67,13 @@ STEPS = [
     (356618, 231, 10, DENSE, L2, 5, 21.7, (None, 21, 30)),
     (141298, 176, 1, SPARSE, L2, 9, 4.4, (22, 17, 25)),
     (27777, 304, 12, DENSE, L2, 30, 28.1, (None, 27, 51)),
+    (67_000_000, 8192, 4, SPARSE, L2, 16, 102.4, (583, 394, None)),
+    (67_000_000, 4096, 3, SPARSE, L2, 16, 27.0, (206, 362, None)),
+    (67_000_000, 2048, 2, SPARSE, L2, 16, 26.7, (285, 349, None)),
+    (268_000_000, 8192, 7, SPARSE, L2, 16, 154.5, (2194, 1447, None)),
+    (268_000_000, 8192, 4, SPARSE, L2, 16, 102.4, (1061, 1299, None)),
+    (268_000_000, 1024, 1, SPARSE, L2, 16, 11.0, (639, 1197, None)),
+    (1_000_000_000, 8192, 4, SPARSE, L2, 16, 46.0, (1780, 3678, 21400)),
 ]
 
 
@@ -98,7 +105,7 @@ def test_a_whole_buffer_does_not_hide_the_others(ask):
     assert words < 0.5 * guess
     assert abs(cut[1] - (words + 0.5)) < 0.01
     assert abs(one[1] - ((K - 1) * (words + 0.5) + guess) / K) < 0.01
-    assert all_[1] == guess
+    assert abs(all_[1] - guess) < 0.01
     assert one[0] == cut[0] != all_[0]
 
 
@@ -107,7 +114,7 @@ def test_strings_longer_than_the_guess_count(ask):
     shape = (1_000_000, 512, 4, SPARSE, L2, 4)
     guess = ask([shape + (1.0, 4)])[0][2]
     assert abs(ask([shape + (1.5 * guess, 0)])[0][1] - (1.5 * guess + 0.5)) < 0.05
-    assert ask([shape + (3.0 * guess, 0)])[0][1] == 2.0 * guess
+    assert ask([shape + (3.0 * guess, 0)])[0][1] == pytest.approx(2.0 * guess, abs=0.01)
 
 
 @pytest.mark.parametrize("n,d,s,K,waves", [
