@@ -443,12 +443,12 @@ DecoderChoice choose_decoder(const Geometry& g, const DecodeArgs& a, const Strin
   c.tile = plan_tile(g, K, cus);
   c.split = plan_decode_split(a, cus, w.planned(), (uint32_t)(w.words + 0.5));
   // The counting apply of the ring decoder keeps a bit per message in a 32-bit word, and its loads
-  // are of four values.  With the largest value as scale the share of nonzero levels
+  // are of four values; the estimates know nothing of its shortest buckets.  With the largest value as scale the share of nonzero levels
   // depends on the data: heavy tails bring it down, but not in every bucket, and the ring decoder
   // waits for the longest string (8M values, K = 16, max, ring / tile: 0.1% of the values x100 d = 512,
   // s = 4 292 / 106 us, d = 8192, s = 1 773 / 301; Student-t 222 / 95, 452 / 304; 1% x1000, all
   // strings short, 192 / 88, 76 / 166).
-  const bool ring = g.code == QSGD_CODE_SPARSE && g.norm == QSGD_NORM_L2 && K <= 32 && g.d % 4 == 0;
+  const bool ring = g.code == QSGD_CODE_SPARSE && g.norm == QSGD_NORM_L2 && K <= 32 && g.d % 4 == 0 && g.d >= 64;
   const double tile = tile_us(g, c.tile, w), split = c.split.us;
   const double ringed = ring ? ring_us(g, ring_buckets(g, K, cus), w, cus) : HUGE_VAL;
   const double strings = (double)g.nb * K;

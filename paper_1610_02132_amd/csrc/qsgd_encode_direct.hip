@@ -12,7 +12,7 @@
 // time, two with levels from 64 on (where such levels are possible: LONG).  Above d = 2048 a
 // bucket's runs do not fit the registers: they are read twice, the second time from the caches.
 //
-// Bound by instruction issue: on 25.6M values, s = 16, d = 512, 51 vector instructions per value
+// Bound by instruction issue: on 25.6M values, s = 16, d = 512, 50 vector instructions per value
 // and lane (of those Philox 10, rounding 8, code word 10) and 17 scalar ones, 0.8 vector
 // instructions per SIMD and four clocks.  The same data 60 us through the survivor ring, 42
 // directly; Code'_s 62 -> 36 us.

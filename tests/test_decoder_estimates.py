@@ -126,3 +126,15 @@ def test_strings_longer_than_the_guess_count(ask):
 def test_wavefronts_of_a_segment(ask, n, d, s, K, waves):
     """The fewer segments a compute unit has, the more wavefronts share one."""
     assert ask([(n, d, s, DENSE, L2, K, 0, K)])[0][3] == waves
+
+
+def test_the_ring_decoder_is_kept_to_what_it_reads(ask):
+    """Code_s under the L2 scale, 32 messages at most (a bit each in a word), loads of four values, and no
+    shorter buckets than it was ever taken for."""
+    rows = [(n, d, s, code, norm, K, w, 0)
+            for n in (4_000, 500_000, 60_000_000) for d in (4, 20, 60, 64, 254, 1024, 8190, 8192) for s in (1, 3, 40)
+            for code in (SPARSE, DENSE) for norm in (L2, MAX) for K in (1, 8, 33, 64) for w in (1.2, 9.0, 200.0)]
+    chosen = [r for r, a in zip(rows, ask(rows)) if a[0] == RING]
+    assert chosen
+    for n, d, s, code, norm, K, _, _ in chosen:
+        assert code == SPARSE and norm == L2 and K <= 32 and d % 4 == 0 and d >= 64
